@@ -1,0 +1,252 @@
+"""What a program that uses this library has it do, as cases that can be timed.
+
+Four kinds of work, all through paper_2503_01330_amd.binding.Cache:
+
+  decode   one generated token through a stack of layers, each layer a cache that is already full
+           (the steady state of a long generation): one Cache.step per layer;
+  prompt   the next prompt into a handle that a server keeps: the cache is emptied (Cache.load of an
+           empty state), the prompt goes in at once (Cache.prefill), the first token is decoded;
+  session  the same with a handle of its own: created, filled, a few tokens decoded, closed;
+  resume   a checkpoint of a full cache (Cache.state) loaded into another handle (Cache.load), and
+           the first step from there.
+
+Shapes are those of the library's own configurations (paper_2503_01330_amd/synth.py: a
+Llama-2-7B-style stack of 32 layers x 32 heads x 128) and generic ones between them.  Queries and
+values are normal, keys are of low rank, as in synth.py; everything is drawn on the GPU from the seed.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2503_01330_amd import binding as wkv
+from paper_2503_01330_amd import synth
+
+TORCH = {"fp32": torch.float32, "fp16": torch.float16, "bf16": torch.bfloat16}
+RING = 32           # tokens of decode input a program has staged; passes take them in turn
+SESSION_STEPS = 8   # tokens a session decodes after its prompt
+
+
+def _decode(name, batch, heads, head_dim, dtype, budget, recent, layers, **kw):
+    return dict(name=name, kind="decode", batch=batch, heads=heads, head_dim=head_dim, dtype=dtype, budget=budget,
+                recent=recent, layers=layers, tokens=0, **{**_PLAIN, **kw})
+
+
+def _prompt(name, kind, batch, heads, head_dim, dtype, budget, recent, tokens, **kw):
+    return dict(name=name, kind=kind, batch=batch, heads=heads, head_dim=head_dim, dtype=dtype, budget=budget,
+                recent=recent, layers=1, tokens=tokens, **{**_PLAIN, **kw})
+
+
+# sink: protected first tokens; rank: of the keys; sink_gain: norm of the first four keys;
+# gains: per-head key norms min(Zipf(1.1), 8); evict: drop values instead of merging them
+_PLAIN = dict(sink=0, rank=16, sink_gain=1.0, gains=False, evict=False)
+
+
+def listed():
+    return [
+        # the smallest call: one tiny fp32 layer, where only latency counts
+        _decode("decode tiny fp32", 1, 4, 64, "fp32", 64, 16, 1, rank=8),
+        # one user talking to the model: a single sequence, a fifth of a 4096-token context kept
+        _decode("decode one sequence", 1, 32, 128, "fp16", 819, 64, 32),
+        # the headline: 32 layers, batch 8, a tenth of the context kept
+        _decode("decode stack batch 8", 8, 32, 128, "fp16", 410, 32, 32),
+        # a long context with attention sinks: few units with long score rows
+        _decode("decode long rows", 4, 32, 128, "fp16", 2048, 128, 1, sink_gain=8.0),
+        # a full serving batch in bf16
+        _decode("decode batch 64 bf16", 64, 32, 128, "bf16", 512, 32, 1, gains=True),
+        # a small model with narrow heads, sizes that are no multiple of anything, protected first tokens
+        _decode("decode ragged narrow", 5, 12, 64, "bf16", 333, 17, 12, sink=4),
+        # a short question: fits the budget, nothing is evicted
+        _prompt("prompt 77", "prompt", 1, 32, 128, "fp16", 819, 64, 77),
+        # a document of odd length for the small model
+        _prompt("prompt 1237 narrow bf16", "prompt", 2, 12, 64, "bf16", 333, 17, 1237, sink=4),
+        # the prompt of a bf16 serving batch
+        _prompt("prompt 2048 bf16", "prompt", 4, 32, 128, "bf16", 512, 32, 2048, gains=True),
+        # the largest: eight prompts as long as the model's context
+        _prompt("prompt 4096 batch 8", "prompt", 8, 32, 128, "fp16", 410, 32, 4096),
+        # a conversation with a handle of its own
+        _prompt("session 300", "session", 1, 32, 128, "fp16", 256, 32, 300),
+        # checkpoint and resume of a full cache with wide heads
+        dict(_decode("resume wide heads", 2, 8, 256, "fp16", 700, 50, 1), kind="resume"),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["decode", "decode", "decode", "prompt", "prompt", "prompt", "session", "resume"])
+    prompt = kind in ("prompt", "session")
+    dtype = rng.choice(["fp16", "bf16"] if prompt else ["fp16", "bf16", "fp16", "bf16", "fp32"])
+    head_dim = rng.choice([64, 128, 128] if prompt or dtype == "fp32" else [64, 128, 128, 256])
+    evict = rng.random() < 0.15
+    c = dict(kind=kind, head_dim=head_dim, dtype=dtype, heads=rng.choice([4, 8, 12, 20, 32, 32]), layers=1, tokens=0,
+             **dict(_PLAIN, evict=evict, sink=rng.choice([0, 0, 4]), gains=rng.random() < 0.25,
+                    sink_gain=rng.choice([1.0, 1.0, 8.0])))
+    c["budget"] = _log(rng, 48, 1024 if prompt else 2048)
+    c["recent"] = max(1, int(c["budget"] * rng.uniform(0.03, 0.3)))
+    row = 2 * head_dim * synth.DTYPE_BYTES[dtype]
+    if kind == "decode":
+        c["batch"] = _log(rng, 1, 64)
+        c["layers"] = rng.choice([1, 2, 6, 12, 24, 32])
+        # at most what the batch-8 stack of 32 layers keeps
+        while c["batch"] > 1 and c["batch"] * c["heads"] * c["layers"] * c["budget"] * row > 1700e6:
+            c["batch"] //= 2
+        while c["layers"] > 1 and c["batch"] * c["heads"] * c["layers"] * c["budget"] * row > 1700e6:
+            c["layers"] //= 2
+    elif kind == "resume":
+        c["batch"] = _log(rng, 1, 8)
+        while c["batch"] > 1 and c["batch"] * c["heads"] * c["budget"] * row > 60e6:
+            c["batch"] //= 2
+    else:
+        c["tokens"] = _log(rng, 16, 4096 if kind == "prompt" else 1024)
+        c["batch"] = _log(rng, 1, 16 if kind == "prompt" else 2)
+        while c["batch"] > 1 and c["batch"] * c["heads"] * c["tokens"] ** 2 * head_dim > 256 * 4096 ** 2 * 128:
+            c["batch"] //= 2
+    return c
+
+
+class _Inputs:
+    """q, k, v of a layer, token after token: q and v normal, k of low rank (a mixing matrix per head)."""
+
+    def __init__(self, case, seed):
+        self.case = case
+        self.gen = torch.Generator(device="cuda")
+        self.gen.manual_seed(seed)
+        self.mix = self._normal(case["heads"], case["rank"], case["head_dim"])
+        if case["gains"]:
+            z = np.random.Generator(np.random.Philox(seed)).zipf(1.1, size=case["heads"])
+            self.mix *= torch.from_numpy(np.minimum(z, 8.0).astype(np.float32)).cuda()[:, None, None]
+        self.made = 0
+
+    def _normal(self, *shape):
+        return torch.randn(*shape, generator=self.gen, device="cuda")
+
+    def tokens(self, n):
+        c = self.case
+        shape = (n, c["batch"], c["heads"], c["head_dim"])
+        q, v = self._normal(*shape), self._normal(*shape)
+        z = self._normal(c["heads"], n * c["batch"], c["rank"])
+        k = torch.matmul(z, self.mix) / math.sqrt(c["rank"])
+        k = k.reshape(c["heads"], n, c["batch"], c["head_dim"]).permute(1, 2, 0, 3).contiguous()
+        if self.made < 4:
+            k[: 4 - self.made] *= c["sink_gain"]
+        self.made += n
+        t = TORCH[c["dtype"]]
+        return q.to(t), k.to(t), v.to(t)
+
+
+def _cache(case, **kw):
+    return wkv.Cache(case["batch"], case["heads"], case["head_dim"], case["budget"], case["recent"],
+                     synth.DTYPE_CODE[case["dtype"]], n_sink=min(case["sink"], case["budget"] - case["recent"]),
+                     merge_mode=wkv.WKV_MERGE_NONE if case["evict"] else wkv.WKV_MERGE_CONVEX, **kw)
+
+
+def _full_cache(case, inputs):
+    """A cache that has been streamed full, and a few tokens beyond."""
+    cache = _cache(case)
+    n = case["budget"] + 4
+    scratch = None
+    for lo in range(0, n, 256):
+        q, k, v = inputs.tokens(min(256, n - lo))
+        scratch = torch.empty_like(q[0]) if scratch is None else scratch
+        for t in range(q.shape[0]):
+            cache.step(q[t], k[t], v[t], scratch)
+    return cache
+
+
+def prepare(case, seed):
+    shape = (case["batch"], case["heads"], case["head_dim"])
+    dtype = TORCH[case["dtype"]]
+    state = {"case": case, "at": 0}
+    if case["kind"] == "decode":
+        state["caches"], state["in"] = [], []
+        for layer in range(case["layers"]):
+            inputs = _Inputs(case, seed * 1000 + layer)
+            state["caches"].append(_full_cache(case, inputs))
+            state["in"].append(inputs.tokens(RING))
+        state["out"] = torch.empty(case["layers"], *shape, dtype=dtype, device="cuda")
+    elif case["kind"] == "resume":
+        inputs = _Inputs(case, seed)
+        state["full"], state["other"] = _full_cache(case, inputs), _cache(case)
+        state["in"] = inputs.tokens(1)
+        state["out"] = torch.empty(shape, dtype=dtype, device="cuda")
+    else:
+        inputs = _Inputs(case, seed)
+        state["prompt"] = inputs.tokens(case["tokens"])
+        state["in"] = inputs.tokens(SESSION_STEPS if case["kind"] == "session" else 1)
+        state["out"] = torch.empty_like(state["prompt"][0])
+        state["next"] = torch.empty_like(state["in"][0])
+        if case["kind"] == "prompt":
+            units = case["batch"] * case["heads"]
+            state["cache"] = _cache(case, max_prompt=case["tokens"])
+            rows = np.empty((units, 0, case["head_dim"]), np.float16)
+            state["empty"] = (rows, rows, np.empty((units, 0), np.float64), np.empty((units, 0), np.int32))
+    torch.cuda.synchronize()
+    return state
+
+
+def run(state):
+    case = state["case"]
+    if case["kind"] == "decode":
+        at = state["at"]
+        state["at"] = (at + 1) % RING
+        out = state["out"]
+        for layer, cache in enumerate(state["caches"]):
+            q, k, v = state["in"][layer]
+            cache.step(q[at], k[at], v[at], out[layer])
+        return out
+    if case["kind"] == "resume":
+        full, other = state["full"], state["other"]
+        K, V = full.state(wkv.WKV_K), full.state(wkv.WKV_V)
+        sums, pos = full.state(wkv.WKV_SCORE_SUM), full.state(wkv.WKV_POS)
+        other.load(full.tokens, K, V, sums, pos)
+        q, k, v = state["in"]
+        other.step(q[0], k[0], v[0], state["out"])
+        return {"K": K, "V": V, "sums": sums, "pos": pos, "out": state["out"]}
+    if case["kind"] == "prompt":
+        cache = state["cache"]
+        cache.load(0, *state["empty"])
+    else:
+        cache = _cache(case)
+    cache.prefill(*state["prompt"], state["out"])
+    q, k, v = state["in"]
+    for t in range(q.shape[0]):
+        cache.step(q[t], k[t], v[t], state["next"][t])
+    if case["kind"] == "session":
+        cache.close()
+    return {"prompt": state["out"], "next": state["next"]}
+
+
+def work(case):
+    units, d, m = case["batch"] * case["heads"], case["head_dim"], case["budget"]
+    eb = synth.DTYPE_BYTES[case["dtype"]]
+
+    def step(length):
+        # per attended entry a K and a V row and the score sum (read and written) and the token index; per unit q,
+        # k, v in, the output, the new rows and the merged row
+        return units * ((length + 1) * (2 * d * eb + 20) + 7 * d * eb), units * (length + 1) * (4 * d + 10)
+
+    if case["kind"] == "decode":
+        b, f = step(m)
+        return {"bytes": case["layers"] * b, "flops": case["layers"] * f}
+    if case["kind"] == "resume":
+        b, f = step(m)
+        state = units * m * (2 * d * eb + 12)
+        return {"bytes": b + 4 * state, "flops": f}        # out of one cache, into the host's arrays, and back into the other
+    P = case["tokens"]
+    L = min(P, m)
+    # q, k, v in, the output, the cache that is left; q.K and P.V over the causal half
+    b = units * (4 * P * d * eb + L * (2 * d * eb + 12))
+    f = units * 2 * d * P * (P + 1)
+    sb, sf = step(L)
+    n = SESSION_STEPS if case["kind"] == "session" else 1
+    return {"bytes": b + n * sb, "flops": f + n * sf}
+
+
+def tolerance(case):
+    # Outputs are rounded to the storage type once.  Measured against attention in 64 bits over the same rows (prompt outputs,
+    # and one step of a full cache), rel / max: fp32 2.5e-8 / 5.7e-8, fp16 2.1e-4 / 4.9e-4, bf16 1.6e-3 / 3.9e-3; four times that.
+    return {"fp32": {"rel": 1e-7, "max": 2.4e-7}, "fp16": {"rel": 8e-4, "max": 2e-3},
+            "bf16": {"rel": 6.5e-3, "max": 1.6e-2}}[case["dtype"]]
