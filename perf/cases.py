@@ -250,3 +250,125 @@ def tolerance(case):
     # and one step of a full cache), rel / max: fp32 2.5e-8 / 5.7e-8, fp16 2.1e-4 / 4.9e-4, bf16 1.6e-3 / 3.9e-3; four times that.
     return {"fp32": {"rel": 1e-7, "max": 2.4e-7}, "fp16": {"rel": 8e-4, "max": 2e-3},
             "bf16": {"rel": 6.5e-3, "max": 1.6e-2}}[case["dtype"]]
+
+
+# ---------------------------------------------------------------- the same in 64 bits, in plain torch
+_ROOM = 2 << 30      # bytes of one block of logits
+
+
+class _Plain:
+    """A cache of all units in fp64: K, V [units, entries, d]; score sums and token indices [units, entries].
+
+    Rows of attention, the running score sums, and the removal of the entry with the lowest average (its value
+    folded into its right neighbour's with the averages as weights), as wkv.h states them.  Merged values are
+    rounded to the cache's format when they are stored."""
+
+    def __init__(self, case):
+        self.case, self.t = case, 0
+        self.budget, self.recent = case["budget"], case["recent"]
+        self.sink = min(case["sink"], case["budget"] - case["recent"])
+
+    def _stored(self, x):
+        return x.to(TORCH[self.case["dtype"]]).double()
+
+    def fill(self, q, k, v):
+        """A prompt [tokens, batch, heads, d] into the empty cache; the attention rows, laid out like q."""
+        n, d = q.shape[0], q.shape[-1]
+        q, k, v = (x.double().reshape(n, -1, d).transpose(0, 1).contiguous() for x in (q, k, v))
+        units = q.shape[0]
+        out, sums = torch.empty_like(q), torch.empty(units, n, dtype=torch.float64, device="cuda")
+        ahead = torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1)
+        block = max(1, _ROOM // (8 * n * n))
+        for lo in range(0, units, block):
+            s = slice(lo, min(lo + block, units))
+            w = torch.bmm(q[s], k[s].transpose(1, 2).contiguous()).mul_(1 / math.sqrt(d))
+            w = torch.softmax(w.masked_fill_(ahead, -math.inf), dim=-1)
+            out[s] = torch.bmm(w, v[s])
+            sums[s] = w.sum(dim=1)
+        self.t, self.pos = n, torch.arange(n, device="cuda").repeat(units, 1)
+        self.K, self.V, self.sums = k, v, sums
+        if n > self.budget:
+            self._compress(n)
+        return out.transpose(0, 1)
+
+    def _compress(self, n):
+        units, m = self.K.shape[0], self.budget
+        score = self.sums / (n - self.pos)
+        score[:, : self.sink] = math.inf
+        score[:, n - self.recent:] = math.inf
+        order = torch.argsort(score, dim=1, stable=True)
+        score = self.sums / (n - self.pos)
+        at = torch.arange(units, device="cuda")
+        after, before = self.pos + 1, self.pos - 1      # neighbours still there; before token 0: a place of its own
+        after = torch.cat([after, torch.zeros_like(after[:, :1])], 1)
+        gone = order[:, : n - m].t().contiguous()
+        for j in gone:
+            r, p = after[at, j], before[at, j]
+            if not self.case["evict"]:
+                sj, sr = score[at, j], score[at, r]
+                self.V[at, r] = (sj[:, None] * self.V[at, j] + sr[:, None] * self.V[at, r]) / (sj + sr)[:, None]
+            after[at, p] = r                            # (p = -1 is the last place, which is no token's)
+            before[at, r] = p
+        keep = order[:, n - m:].sort(dim=1).values
+        wide = keep[:, :, None].expand(-1, -1, self.K.shape[2])
+        self.K, self.V = self.K.gather(1, wide), self._stored(self.V.gather(1, wide))
+        self.sums, self.pos = self.sums.gather(1, keep), keep
+
+    def step(self, q, k, v):
+        d, t = q.shape[-1], self.t
+        qu, ku, vu = (x.double().reshape(-1, 1, d) for x in (q, k, v))
+        at = torch.arange(qu.shape[0], device="cuda")
+        K, V = torch.cat([self.K, ku], 1), torch.cat([self.V, vu], 1)
+        w = torch.softmax((K * qu).sum(-1) / math.sqrt(d), dim=-1)
+        out = (w[:, :, None] * V).sum(1).reshape(q.shape)
+        sums = torch.cat([self.sums, torch.zeros_like(w[:, :1])], 1) + w
+        pos = torch.cat([self.pos, torch.full_like(self.pos[:, :1], t)], 1)
+        if K.shape[1] > self.budget:
+            score = sums / (t - pos + 1)
+            free = (pos >= self.sink) & (pos <= t - self.recent)
+            j = score.masked_fill(~free, math.inf).argmin(1)
+            if not self.case["evict"]:
+                r = pos.masked_fill(pos <= pos[at, j][:, None], t + 1).argmin(1)
+                sj, sr = score[at, j], score[at, r]
+                V[at, r] = self._stored((sj[:, None] * V[at, j] + sr[:, None] * V[at, r]) / (sj + sr)[:, None])
+            for x in (K, V, sums, pos):
+                x[at, j] = x[:, -1].clone()
+            K, V, sums, pos = K[:, :-1], V[:, :-1], sums[:, :-1], pos[:, :-1]
+        self.K, self.V, self.sums, self.pos, self.t = K, V, sums, pos, t + 1
+        return out
+
+
+def _plain_full(case, inputs):
+    cache, m, n = _Plain(case), case["budget"], case["budget"] + 4
+    parts = [inputs.tokens(min(256, n - lo)) for lo in range(0, n, 256)]
+    q, k, v = (torch.cat(x) for x in zip(*parts))
+    cache.fill(q[:m], k[:m], v[:m])
+    for t in range(m, n):
+        cache.step(q[t], k[t], v[t])
+    return cache
+
+
+def exact(case, seed):
+    if case["kind"] == "decode":
+        out = []
+        for layer in range(case["layers"]):
+            inputs = _Inputs(case, seed * 1000 + layer)
+            cache = _plain_full(case, inputs)
+            q, k, v = inputs.tokens(RING)
+            out.append(cache.step(q[0], k[0], v[0]))
+        return torch.stack(out)
+    inputs = _Inputs(case, seed)
+    if case["kind"] == "resume":
+        cache = _plain_full(case, inputs)
+        order = cache.pos.argsort(1)
+        wide = order[:, :, None].expand(-1, -1, case["head_dim"])
+        bits = case["dtype"] == "bf16"                  # Cache.state gives these as bit patterns
+        K, V = (None, None) if bits else (cache.K.gather(1, wide), cache.V.gather(1, wide))
+        sums = cache.sums.gather(1, order)
+        q, k, v = inputs.tokens(1)
+        return {"K": K, "V": V, "sums": sums, "pos": None, "out": cache.step(q[0], k[0], v[0])}
+    cache = _Plain(case)
+    prompt = cache.fill(*inputs.tokens(case["tokens"]))
+    prompt = prompt.reshape(case["tokens"], case["batch"], case["heads"], case["head_dim"])
+    q, k, v = inputs.tokens(SESSION_STEPS if case["kind"] == "session" else 1)
+    return {"prompt": prompt, "next": torch.stack([cache.step(q[t], k[t], v[t]) for t in range(q.shape[0])])}
