@@ -11,15 +11,16 @@
 //
 // Three kernels:
 //   1. wkv_prefill_rows: causal attention, one wave per tile of 16 queries, keys in tiles of 16.
-//      The logits are a dense contraction: v_mfma_f64_16x16x4_f64, fp16/bf16 inputs converted to
-//      fp64 (products and sums then reproduce an fp64 reference to ~1e-16, which is what makes
-//      the later selection reproduce it exactly, as in the decode kernels).  Online softmax in
+//      The logits are a dense contraction of 16-bit numbers, formed exactly: every row becomes 8-bit
+//      digits (once per workgroup, in LDS), the digits go through the int8 matrix instruction, the
+//      integer sums are put together in fp64 (what makes the later selection reproduce an fp64
+//      reference exactly, as in the decode kernels).  Online softmax in
 //      fp64; P.V with v_mfma_f32_16x16x16_f16 / _bf16 (fp32 accumulation): the weights go in as
 //      hi + lo 16-bit pairs straight from the registers the logits arrive in, the values as the raw
 //      cache words.  Writes o_t and the log-sum-exp of every row.
 //   2. wkv_prefill_scores: the column sums a_i = sum_{t >= i} exp(s_ti - lse_t): one wave per
-//      tile of 16 keys, looping over the query tiles below the diagonal, the same fp64 MFMA
-//      contraction again (recomputing the logits costs less than storing P^2/2 of them);
+//      tile of 16 keys, looping over the query tiles below the diagonal, the same contraction
+//      again (recomputing the logits costs less than storing P^2/2 of them);
 //      sums stay in registers, no atomics, fixed order.
 //   3. wkv_prefill_compress: one workgroup per unit: rank of every candidate by (score, token),
 //      the P - m lowest are removed; survivors are laid out in token order in the cache; every
@@ -29,11 +30,11 @@
 // MFMA operand layouts (one wave; g = lane / 16, x = lane % 16), as measured on gfx950:
 //   both: A operand = A[row x][k = g], B operand = B[k = g][column x];
 //   f64 16x16x4: result register r holds D[row g + 4r][column x];
-//   f32 16x16x4: result register r holds D[row 4g + r][column x];
 //   f32 16x16x16 (16-bit inputs): A operand = A[row x][k = 4g .. 4g+3], B operand = B[k = 4g .. 4g+3][column x],
-//   result as f32 16x16x4.
+//   result register r holds D[row 4g + r][column x];
+//   i32 16x16x64 (8-bit inputs): A[row x][k = 16g .. 16g+15], B[k = 16g .. 16g+15][column x], result as f32.
 // The reduction index of a contraction may be permuted at will as long as A and B agree, so a lane
-// simply takes a contiguous quarter of its row: MFMA step kk uses element g*(D/4) + kk of both.
+// simply takes a contiguous quarter of its row (or of 64 elements of it).
 #include "../../include/wkv.h"
 #include "wkv_internal.h"
 #include <mutex>
@@ -133,126 +134,301 @@ __device__ __forceinline__ void exp_table_init(double* tab) {
     if (threadIdx.x < 64) tab[threadIdx.x] = exp2((double)threadIdx.x * (1.0 / 64.0));
     __syncthreads();
 }
-__device__ __forceinline__ double exp_nonpos(double x, const double* tab) {
-    const double xc = (x < -750.0) ? -750.0 : x;                         // exp(-750) = 0 in fp64; keeps n in range; NaN stays NaN
-    const double kd = __builtin_rint(xc * 92.332482616893656877);        // 64 / ln 2
-    const double r = fma(kd, -0.010830424696249145, xc);                 // ln 2 / 64
+// ------------------------------------------------------------------ logits from 8-bit digits
+// A row of 16-bit numbers is, up to a power of two, a row of integers: n = x * 2^s with the row's own s,
+// chosen so that its largest magnitude lies in [2^26, 2^27).  n is written in four balanced base-256
+// digits (d0..d2 in [-128, 127], d3 in [-8, 8]), and q.k becomes sixteen dot products of digits,
+// which v_mfma_i32_16x16x64_i8 forms without any rounding: seven sums S_w over the pairs of weight
+// w = i + j, then A = S0 + 2^8 S1, B = S2 + 2^8 S3, C = S4 + 2^8 S5 + 2^16 S6, each below 2^31 for 128
+// elements (S1 <= 2^22, S3 <= 2^22 + 2^18, S6 <= 2^13), and q.k = (A + 2^16 B + 2^32 C) 2^-(s_q + s_k) with the
+// rounding of two fp64 additions: closer to the exact logit than a chain of D fp64 additions.
+// Why: the fp64 matrix instruction takes 64 cycles for 16x16x4 on this part and shares its pipe
+// with the fp64 vector instructions of the softmax; the sixteen digit products take 512 cycles per
+// 16x16x128 tile against 2048, and run beside them.
+// Measured (256 units, 4096 tokens, d 128, fp16): rows 13.1 -> 8.3 ms, scores 10.5 -> 5.65 ms; the int8
+// instructions then fill a third of the time and vector instructions (289 a tile in scores, a
+// third of them slicing) the rest.
+// A row whose elements are not all integers at its scale (an element more than 2^-26 below the
+// largest that uses its last bits; possible for bf16, and for fp16 rows that reach 8) or that holds
+// an infinity or a NaN is marked, and a tile that touches a marked row takes the fp64 instruction.
+constexpr int DIGITS = 4;
+
+typedef int int4v_t __attribute__((ext_vector_type(4)));
+
+// Logits are kept in units of ln 2 / 64: the exponential below then starts with a rounding, not a product.
+constexpr double LOGIT_UNIT = 92.332482616893656877;                       // 64 / ln 2
+template <int D> __device__ __forceinline__ double logit_scale() { return LOGIT_UNIT / sqrt((double)D); }
+
+// exp(x ln 2 / 64), see exp_nonpos below for the method; x <= 0, -inf or NaN
+__device__ __forceinline__ double exp_units(double x, const double* tab) {
+    const double xc = (x < -69250.0) ? -69250.0 : x;
+    const double kd = __builtin_rint(xc);
+    const double r = xc - kd;
     const int k = (int)kd;
     const double tj = tab[k & 63];
-    double p = fma(r, 1.0 / 24.0, 1.0 / 6.0);
-    p = fma(p, r, 0.5);
-    p = fma(p, r, 1.0);
+    // ln2/64 = c: c, c^2/2, c^3/6, c^4/24
+    double p = fma(r, 5.732851688640402e-10, 2.1173137155464776e-07);
+    p = fma(p, r, 5.86490495505617e-05);
+    p = fma(p, r, 0.010830424696249145);
     p = fma(p, r, 1.0);
     return ldexp(tj * p, k >> 6);
 }
 
-// S^T tile: rows = 16 keys, columns = 16 queries; register r of lane (g, x) = key g + 4r, query x.
-// Both operands are the exact storage values; the softmax scale is applied to the four results.
-template <class TT, int D>
-__device__ __forceinline__ double4_t logits_tile(const uint32_t (&kfrag)[D / 8], const double (&qd)[D / 4]) {
-    // two accumulators: an MFMA that continues the chain of the one before it waits for that
-    // one's result; alternating chains keeps the matrix unit issuing back to back
-    double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int kk = 0; kk < D / 4; kk += 2) {
-        s0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)frag_elem<TT>(kfrag, kk), qd[kk], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)frag_elem<TT>(kfrag, kk + 1), qd[kk + 1], s1, 0, 0, 0);
-    }
-    const double scale = 1.0 / sqrt((double)D);
-    return (s0 + s1) * scale;
+// The scale s of a row from the bits of its largest |x| (as fp32); bad: the row must not be sliced.
+__device__ __forceinline__ int digit_shift(uint32_t maxbits, bool& bad) {
+    const int e = (int)(maxbits >> 23);                                    // biased exponent of the largest element
+    bad = e == 255 || (e < 32 && maxbits != 0u);
+    return (maxbits == 0u || bad) ? 0 : 26 + 127 - e;
 }
 
-// The same tile with both operands already in fp64: for a loop in which one operand never changes
-// (its conversions are then paid once, not once per tile).
-template <int D>
-__device__ __forceinline__ double4_t logits_tile(const double (&kd)[D / 4], const double (&qd)[D / 4]) {
-    double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
+// Four elements -> the words of the four digit planes (byte i of plane b = digit b of element i);
+// frac collects what did not fit an integer.
+__device__ __forceinline__ void digits4(const float (&x)[4], int s, uint32_t (&w)[DIGITS], float& frac) {
+    uint32_t t[4];
 #pragma unroll
-    for (int kk = 0; kk < D / 4; kk += 2) {
-        s0 = __builtin_amdgcn_mfma_f64_16x16x4f64(kd[kk], qd[kk], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f64_16x16x4f64(kd[kk + 1], qd[kk + 1], s1, 0, 0, 0);
+    for (int i = 0; i < 4; ++i) {
+        const float f = ldexpf(x[i], s);
+        frac = fmaxf(frac, __builtin_amdgcn_fractf(f));
+        t[i] = ((uint32_t)(int)f + 0x00808080u) ^ 0x00808080u;             // bytes become balanced digits
     }
-    const double scale = 1.0 / sqrt((double)D);
-    return (s0 + s1) * scale;
+    const uint32_t l01 = __builtin_amdgcn_perm(t[1], t[0], 0x05010400u), h01 = __builtin_amdgcn_perm(t[1], t[0], 0x07030602u);
+    const uint32_t l23 = __builtin_amdgcn_perm(t[3], t[2], 0x05010400u), h23 = __builtin_amdgcn_perm(t[3], t[2], 0x07030602u);
+    w[0] = __builtin_amdgcn_perm(l23, l01, 0x05040100u);
+    w[1] = __builtin_amdgcn_perm(l23, l01, 0x07060302u);
+    w[2] = __builtin_amdgcn_perm(h23, h01, 0x05040100u);
+    w[3] = __builtin_amdgcn_perm(h23, h01, 0x07060302u);
+}
+
+template <class TT> __device__ __forceinline__ uint32_t abs_bits(float x) { return __builtin_bit_cast(uint32_t, x) & 0x7FFFFFFFu; }
+
+// Operands of one wave's own 16 rows, in registers: lane (g, x) holds elements 64 c + 16 g .. + 15 of row x.
+// scale: unit * 2^-s of row x.  Returns whether a row is marked (uniform).
+template <class TT, int D>
+__device__ __forceinline__ bool own_digits(const char* base, int row0, int P, size_t tok, int g, int x,
+                                           int4v_t (&dg)[D / 64][DIGITS], double& scale, double unit)
+{
+    constexpr int KS = D / 64;
+    const char* src = base + (size_t)min(row0 + x, P - 1) * tok;
+    uint32_t w[KS][8];
+    uint32_t mb = 0;
+#pragma unroll
+    for (int c = 0; c < KS; ++c) {
+        load_words<8>(src + (64 * c + 16 * g) * TT::BYTES, w[c]);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) mb = max(mb, abs_bits<TT>(frag_elem<TT>(w[c], e)));
+    }
+    mb = max(mb, (uint32_t)__shfl_xor((int)mb, 16));
+    mb = max(mb, (uint32_t)__shfl_xor((int)mb, 32));
+    bool bad;
+    const int s = digit_shift(mb, bad);
+    float frac = 0.f;
+#pragma unroll
+    for (int c = 0; c < KS; ++c)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+            float f[4];
+            uint32_t pl[DIGITS];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) f[i] = frag_elem<TT>(w[c], 4 * e4 + i);
+            digits4(f, s, pl, frac);
+#pragma unroll
+            for (int b = 0; b < DIGITS; ++b) dg[c][b][e4] = (int)pl[b];
+        }
+    scale = ldexp(unit, -s);
+    return __any(bad || frac != 0.f);
+}
+
+// Operands of the rows that a workgroup's waves share, in LDS: CHUNK rows (two tiles, or what the
+// workgroup's threads slice in one round if that is more), double-buffered.
+// A digit plane of 64 elements of 16 rows: block g (elements 16 g .. + 15) holds 16 bytes of each
+// row; blocks are 320 bytes apart, so that the sixteen threads that write one row (eight bytes each)
+// and the rows of a wave fall into different banks.
+constexpr int PLANE = 4 * 320;
+template <int D, int NW> constexpr int chunk_tiles() { return (64 * NW) / (D / 8) > 2 * TILE ? (64 * NW) / (D / 8) / TILE : 2; }
+template <int D, int CTILES> struct SharedRows {
+    static constexpr int CHUNK = CTILES * TILE;
+    unsigned char dg[2][CTILES][D / 64][DIGITS][PLANE];
+    double scale[2][CHUNK];
+    double lse[2][CHUNK];
+    int marked[2][CHUNK];
+};
+
+// One round of a workgroup's NT threads: a thread takes eight elements of a row; D / 8 threads a row.
+template <class TT, int D, int NT, int CTILES> struct ChunkLoad {
+    static constexpr int CHUNK = CTILES * TILE, TPR = D / 8, ROWS = NT / TPR, ROUNDS = CHUNK / ROWS;
+    static_assert(CHUNK % ROWS == 0 && ROUNDS >= 1, "a chunk is a whole number of rounds");
+    uint32_t w[ROUNDS][4];
+    double lse[ROUNDS];
+    __device__ __forceinline__ void request(const char* base, const double* lsep, int row0, int P, size_t tok) {
+        const int j = threadIdx.x % TPR, r = threadIdx.x / TPR;
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) {
+            const int row = min(row0 + i * ROWS + r, P - 1);
+            load_words<4>(base + (size_t)row * tok + j * 8 * TT::BYTES, w[i]);
+            if (lsep != nullptr && j == 0) lse[i] = lsep[row];
+        }
+    }
+    __device__ __forceinline__ void store(SharedRows<D, CTILES>& sh, int buf, bool with_lse, double unit) const {
+        const int j = threadIdx.x % TPR, r = threadIdx.x / TPR;
+#pragma unroll
+        for (int i = 0; i < ROUNDS; ++i) {
+            float f[8];
+            uint32_t mb = 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { f[e] = frag_elem<TT>(w[i], e); mb = max(mb, abs_bits<TT>(f[e])); }
+#pragma unroll
+            for (int off = 1; off < TPR; off <<= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, off));
+            bool bad;
+            const int s = digit_shift(mb, bad);
+            float frac = 0.f;
+            uint32_t p0[DIGITS], p1[DIGITS];
+            const float fa[4] = { f[0], f[1], f[2], f[3] }, fb[4] = { f[4], f[5], f[6], f[7] };
+            digits4(fa, s, p0, frac);
+            digits4(fb, s, p1, frac);
+            const int row = i * ROWS + r, t = row / TILE, x = row % TILE;
+            const int c = j >> 3, g = (j >> 1) & 3, half = j & 1;
+#pragma unroll
+            for (int b = 0; b < DIGITS; ++b)
+                *reinterpret_cast<uint2_t*>(&sh.dg[buf][t][c][b][g * 320 + x * 16 + half * 8]) = uint2_t{ p0[b], p1[b] };
+            const unsigned long long fm = __ballot(bad || frac != 0.f);
+            if (j == 0) {
+                const int lane = threadIdx.x & 63;
+                sh.scale[buf][row] = ldexp(unit, -s);
+                sh.marked[buf][row] = ((fm >> lane) & ((1ull << TPR) - 1)) != 0;
+                if (with_lse) sh.lse[buf][row] = lse[i];
+            }
+        }
+    }
+};
+
+// Unscaled S^T tile (rows = keys, columns = queries): register r of lane (g, x) = key 4g + r, query x.
+// SHARED_KEYS: the shared rows are the keys and the own rows the queries, or the other way round.
+template <int D, bool SHARED_KEYS>
+__device__ __forceinline__ void digit_tile(const unsigned char (&pl)[D / 64][DIGITS][PLANE], const int4v_t (&own)[D / 64][DIGITS],
+                                           int g, int x, double (&s)[4])
+{
+    int4v_t S[2 * DIGITS - 1];
+#pragma unroll
+    for (int w = 0; w < 2 * DIGITS - 1; ++w) S[w] = int4v_t{0, 0, 0, 0};
+#pragma unroll
+    for (int c = 0; c < D / 64; ++c)
+#pragma unroll
+        for (int i = 0; i < DIGITS; ++i) {
+            const int4v_t a = *reinterpret_cast<const int4v_t*>(&pl[c][i][g * 320 + x * 16]);
+#pragma unroll
+            for (int j = 0; j < DIGITS; ++j)
+                S[i + j] = SHARED_KEYS ? __builtin_amdgcn_mfma_i32_16x16x64_i8(a, own[c][j], S[i + j], 0, 0, 0)
+                                       : __builtin_amdgcn_mfma_i32_16x16x64_i8(own[c][j], a, S[i + j], 0, 0, 0);
+        }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int A = S[0][r] + (S[1][r] << 8), B = S[2][r] + (S[3][r] << 8), C = S[4][r] + (S[5][r] << 8) + (S[6][r] << 16);
+        s[r] = fma(fma((double)C, 65536.0, (double)B), 65536.0, (double)A);
+    }
+}
+
+// The same tile, scaled, with the fp64 matrix instruction, for tiles that touch a marked row.  Its result
+// register r of lane (g, x) is row g + 4r: row i is given key 4 (i % 4) + i / 4, so that the layout is digit_tile's.
+template <class TT, int D>
+__device__ __forceinline__ void exact_tile(const char* kb, const char* qb, int key0, int q0, int P, size_t tok, int g, int x, double (&s)[4])
+{
+    const char* kr = kb + (size_t)min(key0 + 4 * (x & 3) + (x >> 2), P - 1) * tok + g * (D / 4) * TT::BYTES;
+    const char* qr = qb + (size_t)min(q0 + x, P - 1) * tok + g * (D / 4) * TT::BYTES;
+    double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int e0 = 0; e0 < D / 4; e0 += 8) {
+        uint32_t kw[4], qw[4];
+        load_words<4>(kr + e0 * TT::BYTES, kw);
+        load_words<4>(qr + e0 * TT::BYTES, qw);
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            s0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)frag_elem<TT>(kw, e), (double)frag_elem<TT>(qw, e), s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)frag_elem<TT>(kw, e + 1), (double)frag_elem<TT>(qw, e + 1), s1, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s[r] = (s0[r] + s1[r]) * logit_scale<D>();
 }
 
 // ------------------------------------------------------------------ 1. rows
 // q, k, v, out: [P][units][D] (token-major, as a decode step sees them one token at a time).
-// lse: [units][P].  One workgroup = 4 waves = 4 consecutive query tiles of one unit.
-template <class TT, int D>
-__global__ __launch_bounds__(256, 2)
+// lse: [units][P], in units of ln 2 / 64.  One workgroup = NW waves = NW consecutive query tiles of one unit;
+// the keys are sliced into digits once per workgroup and read by every wave from LDS.
+template <class TT, int D, int NW>
+__global__ __launch_bounds__(64 * NW, 2)
 void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, const void* __restrict__ v_,
                       void* __restrict__ out_, double* __restrict__ lse, int P, int units)
 {
-    constexpr int CH = D / 4;                 // elements of a row per lane group
-    constexpr int ROWB = D * TT::BYTES;
+    constexpr int ROWB = D * TT::BYTES, CTILES = chunk_tiles<D, NW>();
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int g = lane >> 4, x = lane & 15;
     const int ntiles = (P + TILE - 1) / TILE;
-    const int groups = (ntiles + 3) / 4;
+    const int groups = (ntiles + NW - 1) / NW;
     const int u = xcd_unit(blockIdx.x, groups);
-    const int qt = (groups - 1 - (int)((blockIdx.x >> 3) % groups)) * 4 + wid;   // long rows are scheduled first
+    const int qt0 = (groups - 1 - (int)((blockIdx.x >> 3) % groups)) * NW;       // long rows are scheduled first
+    if (u >= units) return;                                                      // the whole workgroup
+    const int qt = qt0 + wid;
+    const bool active = qt < ntiles;                                             // an idle wave still slices keys
+    const int last = min(qt0 + NW - 1, ntiles - 1);                              // the workgroup's last key tile
     __shared__ double etab[64];
-    exp_table_init(etab);                     // every wave of the workgroup: ahead of the early exit
-    if (u >= units || qt >= ntiles) return;
+    __shared__ SharedRows<D, CTILES> sh;
+    exp_table_init(etab);
     const size_t tok = (size_t)units * ROWB;                              // bytes from one token to the next
     const char* qb = reinterpret_cast<const char*>(q_) + (size_t)u * ROWB;
     const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;
     const char* vb = reinterpret_cast<const char*>(v_) + (size_t)u * ROWB;
 
-    // the query fragment: row 16 qt + x (clamped), elements g*CH .. g*CH+CH-1, scaled, fp64
-    double qd[CH];
-    {
-        const int tq = min(qt * TILE + x, P - 1);
-        uint32_t w[CH / 2];
-        load_words<CH / 2>(qb + (size_t)tq * tok + g * CH * TT::BYTES, w);
-#pragma unroll
-        for (int e = 0; e < CH; ++e) qd[e] = (double)frag_elem<TT>(w, e);
-    }
-    double mrow = -INFINITY, lrow = 0.0;      // running maximum and sum of query x (same in the 4 lanes x, x+16, ...)
+    ChunkLoad<TT, D, 64 * NW, CTILES> next;
+    next.request(kb, nullptr, 0, P, tok);
+    int4v_t qdg[D / 64][DIGITS];
+    double qscale;
+    const bool qmarked = own_digits<TT, D>(qb, qt * TILE, P, tok, g, x, qdg, qscale, 1.0);
+    next.store(sh, 0, false, logit_scale<D>());
+
+    double mrow = -INFINITY, lrow = 0.0;      // running maximum of query x (same in the 4 lanes x, x+16, ...); this lane's share of the sum
     constexpr int NE = D / 16;                // output column sets: lane (g, x) owns columns NE*x .. NE*x+NE-1
     float4_t o[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) o[e] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-    // K fragment of a key tile: key 16 kt + x, the same quarter of the row as the query fragment.
-    // V fragments: keys 16 kt + g + 4r, columns NE*x .. NE*x+NE-1.  Two sets of fragment registers
-    // take turns: the next tile is requested into one set before the current tile is worked on
-    // from the other, so no fragment is ever copied.  A lane's byte offsets inside a tile never
-    // change; the tile's base address is uniform (scalar arithmetic), so a request costs one vector
-    // add per load.  Only a tile that reaches past the end of the prompt clamps its rows.
-    const size_t koff = (size_t)x * tok + g * CH * TT::BYTES;
     size_t voff[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) voff[r] = (size_t)(g + 4 * r) * tok + x * NE * TT::BYTES;
-    auto request = [&](int kt, uint32_t (&kf)[CH / 2], uint32_t (&vf)[4][NE / 2]) __attribute__((always_inline)) {
+    for (int r = 0; r < 4; ++r) voff[r] = (size_t)(4 * g + r) * tok + x * NE * TT::BYTES;
+    auto tile = [&](int kt, int buf) __attribute__((always_inline)) {
+        // V fragments: keys 16 kt + 4g + r, columns NE*x .. NE*x+NE-1; requested here, used after the softmax
+        // (a lane's offsets in a tile never change; only a tile that reaches past the prompt clamps its rows)
+        uint32_t vfrag[4][NE / 2];
         if (kt * TILE + TILE <= P) {                          // uniform
-            const size_t base = (size_t)kt * TILE * tok;
-            load_words<CH / 2>(kb + base + koff, kf);
+            const char* vt = vb + (size_t)(kt * TILE) * tok;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) load_words<NE / 2>(vb + base + voff[r], vf[r]);
+            for (int r = 0; r < 4; ++r) load_words<NE / 2>(vt + voff[r], vfrag[r]);
         } else {
-            load_words<CH / 2>(kb + (size_t)min(kt * TILE + x, P - 1) * tok + g * CH * TT::BYTES, kf);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                load_words<NE / 2>(vb + (size_t)min(kt * TILE + g + 4 * r, P - 1) * tok + x * NE * TT::BYTES, vf[r]);
+                load_words<NE / 2>(vb + (size_t)min(kt * TILE + 4 * g + r, P - 1) * tok + x * NE * TT::BYTES, vfrag[r]);
         }
-    };
-    auto tile = [&](int kt, const uint32_t (&kfrag)[CH / 2], const uint32_t (&vfrag)[4][NE / 2]) __attribute__((always_inline)) {
-        double4_t s = logits_tile<TT, D>(kfrag, qd);
-        if (kt == qt) {                       // the diagonal tile: key g + 4r may be attended by query x only if <= x
+        const int t = kt % CTILES;
+        double s[4];
+        if (__any(sh.marked[buf][t * TILE + x]) || qmarked) {
+            exact_tile<TT, D>(kb, qb, kt * TILE, qt * TILE, P, tok, g, x, s);
+        } else {
+            digit_tile<D, true>(sh.dg[buf][t], qdg, g, x, s);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) if (g + 4 * r > x) s[r] = -INFINITY;
+            for (int r = 0; r < 4; ++r) s[r] *= sh.scale[buf][t * TILE + 4 * g + r] * qscale;
+        }
+        if (kt == qt) {                       // the diagonal tile: key 4g + r may be attended by query x only if <= x
+#pragma unroll
+            for (int r = 0; r < 4; ++r) if (4 * g + r > x) s[r] = -INFINITY;
         }
         double tmax = fmax(fmax(s[0], s[1]), fmax(s[2], s[3]));
-        tmax = pair_max<32>(pair_max<16>(tmax));               // over the four lane groups: all 16 keys of the tile
-        const double mnew = fmax(mrow, tmax);                 // finite: key 16 kt + 0 <= every query of a later tile,
-                                                              // and on the diagonal key x is attended by query x
         // A running maximum that has not moved needs no rescaling, and after the first few key
-        // tiles of a row it rarely moves: the rescaling (an exp, the running sum and all output
-        // accumulators of the wave) is skipped unless some query of the tile needs it.
-        if (__any(mnew > mrow)) {
-            const double resc = exp_nonpos(mrow - mnew, etab);             // 0 on the first tile (mrow = -inf), 1 where nothing moved
+        // tiles of a row it rarely moves: the maximum over the four lane groups and the rescaling (an exp,
+        // the running sum and all output accumulators of the wave) are skipped unless some query needs them.
+        if (__any(tmax > mrow)) {
+            tmax = pair_max<32>(pair_max<16>(tmax));           // all 16 keys of the tile
+            const double mnew = fmax(mrow, tmax);             // finite: key 16 kt + 0 <= every query of a later tile,
+                                                              // and on the diagonal key x is attended by query x
+            const double resc = exp_units(mrow - mnew, etab);              // 0 on the first tile (mrow = -inf), 1 where nothing moved
             lrow *= resc;
             mrow = mnew;
             const float rf = (float)resc;                     // the output rows this lane holds (queries 4g + r') by their own factor
@@ -264,37 +440,37 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
             }
         }
         float p[4];
-        double psum = 0.0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) { const double e = exp_nonpos(s[r] - mrow, etab); psum += e; p[r] = (float)e; }
-        psum = rows_sum(psum);
-        lrow += psum;
+        for (int r = 0; r < 4; ++r) { const double e = exp_units(s[r] - mrow, etab); lrow += e; p[r] = (float)e; }
         // O[query][column] += sum over keys P[query][key] V[key][column] with the 16-bit matrix
-        // instruction (k = 16 keys at once): lane (g, x) supplies k-slots 4g + r, which stand for the
-        // keys g + 4r it already holds -- as A operand P[query x][key g + 4r], as B operand
-        // V[key g + 4r][column NE*x + e], the raw cache values.  P goes in as a sum of 16-bit parts.
+        // instruction (k = 16 keys at once): lane (g, x) supplies k-slots 4g + r: as A operand
+        // P[query x][key 4g + r], as B operand V[key 4g + r][column NE*x + e], the raw cache values.
+        // P goes in as a sum of 16-bit parts.
         uint2_t pa[weight_parts<TT>()];
         split16x4<TT>(p, pa);
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
             const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;      // high / low halves of two words
-            const uint2_t vb = { __builtin_amdgcn_perm(vfrag[1][e >> 1], vfrag[0][e >> 1], sel),
-                                 __builtin_amdgcn_perm(vfrag[3][e >> 1], vfrag[2][e >> 1], sel) };
+            const uint2_t vb2 = { __builtin_amdgcn_perm(vfrag[1][e >> 1], vfrag[0][e >> 1], sel),
+                                  __builtin_amdgcn_perm(vfrag[3][e >> 1], vfrag[2][e >> 1], sel) };
 #pragma unroll
-            for (int w = 0; w < weight_parts<TT>(); ++w) o[e] = mfma16<TT>(pa[w], vb, o[e]);
+            for (int w = 0; w < weight_parts<TT>(); ++w) o[e] = mfma16<TT>(pa[w], vb2, o[e]);
         }
     };
-    uint32_t kf0[CH / 2], vf0[4][NE / 2], kf1[CH / 2], vf1[4][NE / 2];
-    request(0, kf0, vf0);
-    for (int kt = 0; kt <= qt; kt += 2) {
-        request(min(kt + 1, qt), kf1, vf1);                   // past the last tile: a repeat, unused
-        tile(kt, kf0, vf0);
-        if (kt + 1 > qt) break;
-        request(min(kt + 2, qt), kf0, vf0);
-        tile(kt + 1, kf1, vf1);
+    // A chunk is worked on from one buffer while the next one is on its way from memory; it is sliced into
+    // the other buffer at the end of the round, which every wave left before the barrier at its start.
+    for (int kt = 0, buf = 0; kt <= last; kt += CTILES, buf ^= 1) {
+        __syncthreads();
+        const bool more = kt + CTILES <= last;
+        if (more) next.request(kb, nullptr, (kt + CTILES) * TILE, P, tok);
+        if (active)
+            for (int t = 0; t < CTILES && kt + t <= qt; ++t) tile(kt + t, buf);
+        if (more) next.store(sh, buf ^ 1, false, logit_scale<D>());
     }
+    if (!active) return;
 
     // o_t = O / l, log-sum-exp = m + log l
+    lrow = rows_sum(lrow);
     const float linv = (float)(1.0 / lrow);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -306,93 +482,81 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
             for (int e = 0; e < NE; ++e) store_elem<TT>(dst, e, o[e][r] * f);
         }
     }
-    if (g == 0 && qt * TILE + x < P) lse[(size_t)u * P + qt * TILE + x] = mrow + log(lrow);
+    if (g == 0 && qt * TILE + x < P) lse[(size_t)u * P + qt * TILE + x] = mrow + log(lrow) * LOGIT_UNIT;
 }
 
 // ------------------------------------------------------------------ 2. scores
-// a[u][i] = sum over rows t >= i of exp(s_ti - lse_t).  One wave per key tile.
-template <class TT, int D>
-__global__ __launch_bounds__(256)
+// a[u][i] = sum over rows t >= i of exp(s_ti - lse_t).  One wave per key tile, NW of them a workgroup, which
+// shares the sliced queries.
+template <class TT, int D, int NW>
+__global__ __launch_bounds__(64 * NW, 2)
 void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_, const double* __restrict__ lse,
                         double* __restrict__ a, int P, int units)
 {
-    constexpr int CH = D / 4;
-    constexpr int ROWB = D * TT::BYTES;
+    constexpr int ROWB = D * TT::BYTES, CTILES = chunk_tiles<D, NW>();
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int g = lane >> 4, x = lane & 15;
     const int ntiles = (P + TILE - 1) / TILE;
-    const int groups = (ntiles + 3) / 4;
+    const int groups = (ntiles + NW - 1) / NW;
     const int u = xcd_unit(blockIdx.x, groups);
-    const int kt = (int)((blockIdx.x >> 3) % groups) * 4 + wid;           // low key tiles have the most rows: first
+    const int kt0 = (int)((blockIdx.x >> 3) % groups) * NW;               // low key tiles have the most rows: first
+    if (u >= units) return;                                               // the whole workgroup
+    const int kt = kt0 + wid;
+    const bool active = kt < ntiles;
     __shared__ double etab[64];
-    exp_table_init(etab);                     // every wave of the workgroup: ahead of the early exit
-    if (u >= units || kt >= ntiles) return;
+    __shared__ SharedRows<D, CTILES> sh;
+    exp_table_init(etab);
     const size_t tok = (size_t)units * ROWB;
     const char* qb = reinterpret_cast<const char*>(q_) + (size_t)u * ROWB;
     const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;
+    const double* lseu = lse + (size_t)u * P;
 
-    // the wave's key fragment never changes: converted to fp64 once (64 registers), not once per query tile
-    double kd[CH];
-    {
-        uint32_t kfrag[CH / 2];
-        load_words<CH / 2>(kb + (size_t)min(kt * TILE + x, P - 1) * tok + g * CH * TT::BYTES, kfrag);
+    ChunkLoad<TT, D, 64 * NW, CTILES> next;
+    next.request(qb, lseu, kt0 * TILE, P, tok);
+    int4v_t kdg[D / 64][DIGITS];
+    double kx;
+    const bool kmarked = own_digits<TT, D>(kb, kt * TILE, P, tok, g, x, kdg, kx, logit_scale<D>());
+    double kscale[4], acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int e = 0; e < CH; ++e) kd[e] = (double)frag_elem<TT>(kfrag, e);
+    for (int r = 0; r < 4; ++r) kscale[r] = __shfl(kx, 4 * g + r);
+    next.store(sh, 0, true, 1.0);
+
+    for (int q0 = kt0, buf = 0; q0 < ntiles; q0 += CTILES, buf ^= 1) {
+        __syncthreads();
+        const bool more = q0 + CTILES < ntiles;
+        if (more) next.request(qb, lseu, (q0 + CTILES) * TILE, P, tok);
+        if (active)
+            for (int qt = max(q0, kt); qt < min(q0 + CTILES, ntiles); ++qt) {
+                const int t = qt % CTILES;
+                const double l = sh.lse[buf][t * TILE + x];
+                double s[4];
+                if (__any(sh.marked[buf][t * TILE + x]) || kmarked) {
+                    exact_tile<TT, D>(kb, qb, kt * TILE, qt * TILE, P, tok, g, x, s);
+                } else {
+                    digit_tile<D, false>(sh.dg[buf][t], kdg, g, x, s);
+                    const double qs = sh.scale[buf][t * TILE + x];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) s[r] *= kscale[r] * qs;
+                }
+                if (qt == kt || qt == ntiles - 1) {                        // causal, and inside the prompt
+                    const int tq = qt * TILE + x;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const bool on = tq < P && kt * TILE + 4 * g + r <= tq;
+                        acc[r] += exp_units(on ? s[r] - l : -INFINITY, etab);      // exp(-inf) = 0; no branch
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[r] += exp_units(s[r] - l, etab);
+                }
+            }
+        if (more) next.store(sh, buf ^ 1, true, 1.0);
     }
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    uint32_t wnext[CH / 2];
-    double lnext;
-    auto request = [&](int qt) {
-        const int tqc = min(qt * TILE + x, P - 1);
-        load_words<CH / 2>(qb + (size_t)tqc * tok + g * CH * TT::BYTES, wnext);
-        lnext = lse[(size_t)u * P + tqc];
-    };
-    // Software pipeline: the MFMA chain of the next query tile is issued in the same stretch of
-    // straight-line code as the exponentials of the current one, so the matrix unit and the
-    // vector unit of a SIMD work at the same time.  (Waves left to themselves run in lockstep --
-    // all in their MFMA chain, then all in their exponentials -- and the two units take turns.)
-    request(kt);
-    double4_t s_cur;
-    double l_cur = lnext;
-    {
-        double qd[CH];
-#pragma unroll
-        for (int e = 0; e < CH; ++e) qd[e] = (double)frag_elem<TT>(wnext, e);
-        request(min(kt + 1, ntiles - 1));
-        s_cur = logits_tile<D>(kd, qd);
-    }
-    for (int qt = kt; qt < ntiles; ++qt) {
-        const int tq = qt * TILE + x;
-        double qd[CH];
-#pragma unroll
-        for (int e = 0; e < CH; ++e) qd[e] = (double)frag_elem<TT>(wnext, e);
-        const double l_next = lnext;
-        request(min(qt + 2, ntiles - 1));
-        __builtin_amdgcn_sched_barrier(0);                                 // the requests are issued here, not later
-        double4_t s_next = logits_tile<D>(kd, qd);                 // tile qt + 1 (a repeat on the last round)
-        // The fragment just requested may be touched only once this chain has been issued: without
-        // these opaque uses the compiler converts it right behind its request, i.e. every round
-        // waits for the loads it has just issued.
-        {
-            double pin = s_next[0];
-#pragma unroll
-            for (int w = 0; w < CH / 2; ++w) asm volatile("" : "+v"(pin), "+v"(wnext[w]));
-            asm volatile("" : "+v"(pin), "+v"(lnext));
-            s_next[0] = pin;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int key = kt * TILE + g + 4 * r;
-            const bool on = tq < P && key <= tq;                           // causal, and inside the prompt
-            acc[r] += exp_nonpos(on ? s_cur[r] - l_cur : -INFINITY, etab);  // exp(-inf) = 0; no branch
-        }
-        s_cur = s_next;
-        l_cur = l_next;
-    }
+    if (!active) return;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const double c = row_allsum(acc[r]);                               // over the 16 queries x
-        const int key = kt * TILE + g + 4 * r;
+        const int key = kt * TILE + 4 * g + r;
         if (x == 0 && key < P) a[(size_t)u * P + key] = c;
     }
 }
@@ -745,9 +909,10 @@ template <class TT, int D>
 hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, void* out,
                double* lse, double* a, int P, hipStream_t stream)
 {
-    const int ntiles = (P + TILE - 1) / TILE, groups = (ntiles + 3) / 4;
-    hipLaunchKernelGGL((wkv_prefill_rows<TT, D>), dim3(xcd_grid(c.units, groups)), dim3(256), 0, stream, q, k, v, out, lse, P, c.units);
-    hipLaunchKernelGGL((wkv_prefill_scores<TT, D>), dim3(xcd_grid(c.units, groups)), dim3(256), 0, stream, q, k, lse, a, P, c.units);
+    constexpr int NW = 4;
+    const int ntiles = (P + TILE - 1) / TILE, groups = (ntiles + NW - 1) / NW;
+    hipLaunchKernelGGL((wkv_prefill_rows<TT, D, NW>), dim3(xcd_grid(c.units, groups)), dim3(64 * NW), 0, stream, q, k, v, out, lse, P, c.units);
+    hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NW>), dim3(xcd_grid(c.units, groups)), dim3(64 * NW), 0, stream, q, k, lse, a, P, c.units);
     const size_t lds = wkv_prefill_lds_bytes(P);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wkv_prefill_compress<TT, D>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

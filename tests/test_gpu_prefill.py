@@ -245,3 +245,35 @@ def test_llama_shaped_prompt_sampled_units():
     sel = np.sort(np.random.default_rng(11).choice(cfg.units, 3, replace=False))
     stats = _run(cfg, 4096, decode_steps=64, units_sel=sel)
     assert stats["min_gap"] >= 0
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("where", ["queries", "keys", "one row"])
+def test_rows_that_span_more_than_the_digits(dtype, d, where):
+    """Logits are formed from 8-bit digits of rows brought to integers below 2^27; a row with elements
+    that are no integers at its scale must take the fp64 instruction.  Such a row here: one large
+    element (times zero on the other side) and small ones below the last digit, which meet large
+    elements, so that dropping what does not fit would move a logit by more than 1e-5 (score sums are held to
+    1e-9).  Also a row of zeros and one of the smallest numbers.  130 tokens: a ragged last tile and
+    several workgroups a unit."""
+    P, m, R, U = 130, 48, 6, 3
+    cfg = synth.StreamConfig("pre-span", 8700, 1, U, d, dtype, P + 12, m, R)
+    g = np.random.default_rng(8700)
+    q, k, v = (g.standard_normal((cfg.steps, U, d)).astype(np.float32) for _ in range(3))
+    big, tiny = (60.0, 2.0 ** -13) if dtype == "fp16" else (2.0 ** 10, 2.0 ** -18)
+    rows = [97] if where == "one row" else [0, 1, 15, 16, 40, 63, 64, 100, 127, 129]
+    side, other = (q, k) if where == "queries" else (k, q)
+    side[rows] *= tiny
+    other *= 20.0       # (small logits everywhere would make every output the mean of a hundred values, which cancels: the
+                        # share of bit-exact bf16 outputs then falls with fp32 error / result, to 0.9989 at 130 tokens)
+    side[:, :, 0] = other[:, :, 0] = 0.0
+    side[rows, :, 0] = big
+    other[3] = 0.0
+    other[5] *= 2.0 ** -20 if dtype == "fp16" else 2.0 ** -120
+    got = parity.gpu_prefill(cfg, P, arrays=(q, k, v))
+    try:
+        stats = parity.compare_prefill(cfg, got, decode_steps=8)
+    finally:
+        got["cache"].close()
+    print(f"\n  {where}: {stats}", flush=True)
