@@ -9,7 +9,7 @@
 // by token; beyond that it is a different function (streamed tokens attend to an already
 // compressed cache).
 //
-// Three kernels:
+// Four kernels:
 //   1. wkv_prefill_rows: causal attention, one wave per tile of 16 queries, keys in tiles of 16.
 //      The logits are a dense contraction of 16-bit numbers, formed exactly: every row becomes 8-bit
 //      digits (once per workgroup, in LDS), the digits go through the int8 matrix instruction, the
@@ -23,9 +23,9 @@
 //      again (recomputing the logits costs less than storing P^2/2 of them);
 //      sums stay in registers, no atomics, fixed order.
 //   3. wkv_prefill_compress: one workgroup per unit: rank of every candidate by (score, token),
-//      the P - m lowest are removed; survivors are laid out in token order in the cache; every
-//      run of removed tokens is folded into the survivor on its right with the weights that the
-//      sequence of pairwise merges in ascending score order gives each raw row.
+//      the P - m lowest are removed; survivors get slots in token order; the weight with which every raw row
+//      enters the survivor on its right, as the sequence of pairwise merges in ascending score order gives it.
+//   4. wkv_prefill_fold: 16 survivors a workgroup: key rows copied, value rows summed with those weights.
 //
 // MFMA operand layouts (one wave; g = lane / 16, x = lane % 16), as measured on gfx950:
 //   both: A operand = A[row x][k = g], B operand = B[k = g][column x];
@@ -576,27 +576,22 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
 // merges (Algorithm 1) in fp64, with no dependent chain of row updates.  Rows are rounded to the
 // cache format once, when they are written.
 //
+// What is left is a weight per token, written to global memory; the rows themselves are moved by
+// wkv_prefill_fold, which has the whole chip where this kernel has a workgroup per unit.
+//
 // LDS: sc[P] score, then list products, finally weight | ae[P] f, then edge coefficient | a0[P] g, then
-//      own coefficient | slot[P] | wcnt[NT] | rk[P] rank (16 bit) | par[P] parent (16 bit) |
+//      own coefficient | slot[P] | wcnt[NT] (one per wave is used) | rk[P] rank (16 bit) | par[P] parent (16 bit) |
 //      ptr[P] list successor (16 bit) | bmax[64].  The sort keys borrow ae[], a0[] and slot[].
-template <class TT, int D>
 __global__ __launch_bounds__(1024)
-void wkv_prefill_compress(WkvCache c, const void* __restrict__ k_, const void* __restrict__ v_,
-                          const double* __restrict__ a, int P)
+void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __restrict__ weight, int P)
 {
-    constexpr int ROWB = D * TT::BYTES;
-    constexpr int EPW = (D + 63) / 64;
     const int tid = threadIdx.x, NT = blockDim.x, lane = tid & 63, wid = tid >> 6, NW = NT >> 6;
     const int u = blockIdx.x, m = c.m;
-    const size_t tok = (size_t)c.units * ROWB;
-    const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;
-    const char* vb = reinterpret_cast<const char*>(v_) + (size_t)u * ROWB;
-    char* Kc = reinterpret_cast<char*>(c.K) + (size_t)u * m * ROWB;
-    char* Vc = reinterpret_cast<char*>(c.V) + (size_t)u * m * ROWB;
     double*  au = c.a + (size_t)u * m;
     int32_t* pu = c.pos + (size_t)u * m;
     int32_t* nu = c.nxt + (size_t)u * m;
     const double* ap = a + (size_t)u * P;
+    double* wu = weight + (size_t)u * P;
 
     extern __shared__ double lds[];
     double*   sc   = lds;
@@ -638,18 +633,30 @@ void wkv_prefill_compress(WkvCache c, const void* __restrict__ k_, const void* _
             kid[i] = (uint16_t)i;
         }
         __syncthreads();
+        // Steps of distance 64 and less stay within the 128 elements that 64 consecutive pairs span,
+        // i.e. within one wave: LDS operations of a wave complete in order, so those steps need no
+        // workgroup barrier (63 of the 78 steps for 4096 tokens).
+        auto exchange = [&](int t, int j, int k) __attribute__((always_inline)) {
+            const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), l = i | j;
+            const unsigned long long ki = key[i], kl = key[l];
+            const uint16_t di = kid[i], dl = kid[l];
+            const bool gt = ki > kl || (ki == kl && di > dl);
+            if (gt == ((i & k) == 0)) { key[i] = kl; key[l] = ki; kid[i] = dl; kid[l] = di; }
+        };
         for (int k = 2; k <= N2; k <<= 1) {
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                for (int t = tid; t < (N2 >> 1); t += NT) {
-                    const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), l = i | j;
-                    const unsigned long long ki = key[i], kl = key[l];
-                    const uint16_t di = kid[i], dl = kid[l];
-                    const bool gt = ki > kl || (ki == kl && di > dl);
-                    if (gt == ((i & k) == 0)) { key[i] = kl; key[l] = ki; kid[i] = dl; kid[l] = di; }
-                }
+            int j = k >> 1;
+            for (; j > 64; j >>= 1) {
+                for (int t = tid; t < (N2 >> 1); t += NT) exchange(t, j, k);
                 __syncthreads();
             }
+            for (; j > 0; j >>= 1) {
+                for (int t = tid; t < (N2 >> 1); t += NT) exchange(t, j, k);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (k >= 128) __syncthreads();
         }
+        __syncthreads();
         for (int r = tid; r < nrem; r += NT) rk[kid[r]] = (uint16_t)r;         // the nrem lowest keys are candidates
         __syncthreads();
     } else {
@@ -662,30 +669,22 @@ void wkv_prefill_compress(WkvCache c, const void* __restrict__ k_, const void* _
     const int b0 = min(tid * per, P), b1 = min(b0 + per, P);
     int mine = 0;
     for (int i = b0; i < b1; ++i) mine += (slot[i] == 0) ? 1 : 0;
-    wcnt[tid] = mine;
-    __syncthreads();
-    if (tid == 0) { int run = 0; for (int w = 0; w < NT; ++w) { const int t = wcnt[w]; wcnt[w] = run; run += t; } }
+    int upto = mine;                                          // inclusive scan: over the wave, then over the waves' totals
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) { const int t = __shfl_up(upto, off); if (lane >= off) upto += t; }
+    if (lane == 63) wcnt[wid] = upto;
     __syncthreads();
     {
-        int sidx = wcnt[tid];
+        int sidx = upto - mine;
+        for (int w = 0; w < wid; ++w) sidx += wcnt[w];
         for (int i = b0; i < b1; ++i) if (slot[i] == 0) slot[i] = sidx++;
     }
     __syncthreads();
-    // score sums, token indices, links and keys of the survivors
+    // score sums, token indices and links of the survivors
     for (int i = tid; i < P; i += NT) {
         const int sidx = slot[i];
         if (sidx >= 0) { au[sidx] = ap[i]; pu[sidx] = i; nu[sidx] = (sidx + 1 < L) ? sidx + 1 : -1; }
     }
-    for (int i = wid; i < P; i += NW) {                       // one wave per row
-        const int sidx = slot[i];
-        if (sidx < 0) continue;
-#pragma unroll
-        for (int e = 0; e < EPW; ++e) {
-            const int col = lane + 64 * e;
-            if (col < D) store_bits<TT>(Kc + (size_t)sidx * ROWB, col, load_bits<TT>(kb + (size_t)i * tok, col));
-        }
-    }
-
     const bool merging = c.merge_mode == 0 && nrem > 0;
     if (merging) {
         // Parent of a removed token: the nearest token to its right that outranks it (survivors
@@ -820,88 +819,103 @@ void wkv_prefill_compress(WkvCache c, const void* __restrict__ k_, const void* _
         }
         __syncthreads();
         list_products(ae);                                     // sc[i] = product of the edge coefficients of i's removed ancestors
-        for (int i = tid; i < P; i += NT)
-            if (slot[i] < 0) sc[i] *= ae[i] * a0[i];
-        __syncthreads();
+        for (int i = tid; i < P; i += NT) wu[i] = (slot[i] < 0) ? sc[i] * (ae[i] * a0[i]) : a0[i];
     }
-    // acc += sum over rows k = first, first + stride, ... <= last of weight(k) * V_k, where the last
-    // row of a run is the survivor itself (own coefficient).  Eight rows are requested at a time:
-    // the sum is a chain of dependent FMAs, the loads need not be.
-    auto weighted_rows = [&](double (&acc)[EPW], int first, int last, int stride) {
-        for (int k0 = first; k0 <= last; k0 += 8 * stride) {
-            uint32_t raw[8][EPW];
-            double w[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int k = k0 + j * stride;
-                const int kc = min(k, last);
-                w[j] = (k > last) ? 0.0 : (k < last) ? sc[kc] : a0[last];
-#pragma unroll
-                for (int e = 0; e < EPW; ++e)
-                    raw[j][e] = load_bits<TT>(vb + (size_t)kc * tok, min(lane + 64 * e, D - 1));
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-#pragma unroll
-                for (int e = 0; e < EPW; ++e) acc[e] = fma(w[j], (double)bits_elem<TT>(raw[j][e]), acc[e]);
-        }
-    };
-    // values of the survivors.  rk[] is free now: it takes the number of tokens that fold into a survivor.
-    constexpr int LONG = 32;                                  // runs from this length on are summed by the whole workgroup
-    const bool coop = merging && P >= NW * D;                 // (the partial sums borrow ae[], P doubles)
-    for (int i = tid; i < P; i += NT) {
-        if (slot[i] < 0) continue;
-        int i0 = i - 1;
-        while (i0 >= 0 && slot[i0] < 0) --i0;                  // previous survivor (or -1)
-        rk[i] = (uint16_t)(merging ? i - 1 - i0 : 0);
-    }
+}
+
+// ------------------------------------------------------------------ 4. fold
+// Keys and values of the survivors, FOLD_ROWS of them a workgroup: a key row is copied, a value row is the
+// weighted sum of the raw rows of its run (the removed tokens left of the survivor, and itself),
+// copied where the run is empty.  The loads are what takes the time (the runs of a unit are its whole
+// prompt), so they go over the chip: 16 bytes a lane, 64 / LPR rows an instruction, four in
+// flight; a run of LONG tokens or more is shared by the workgroup's waves.  Sums in fp64, rounded to
+// the cache format once.  Measured, with the wave-local steps of the sort (compress, then compress + fold):
+// 24 units, 1237 tokens to 333 (d 64): 231 -> 50 + 16 us; 128 units, 2048 to 512 (d 128): 372 -> 59 + 59;
+// 256 units, 4096 to 410: 795 -> 129 + 119.
+constexpr int FOLD_ROWS = 16, FOLD_WAVES = 8, LONG = 64;
+template <class TT, int D>
+__global__ __launch_bounds__(64 * FOLD_WAVES)
+void wkv_prefill_fold(WkvCache c, const void* __restrict__ k_, const void* __restrict__ v_,
+                      const double* __restrict__ weight, int P, int blocks, int merging)
+{
+    constexpr int ROWB = D * TT::BYTES, LPR = ROWB / 16, G = 64 / LPR;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int u = blockIdx.x / blocks, s0 = (blockIdx.x % blocks) * FOLD_ROWS;
+    const int L = min(P, c.m), here = min(FOLD_ROWS, L - s0);
+    const size_t tok = (size_t)c.units * ROWB;
+    const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;
+    const char* vb = reinterpret_cast<const char*>(v_) + (size_t)u * ROWB;
+    char* Kc = reinterpret_cast<char*>(c.K) + ((size_t)u * c.m + s0) * ROWB;
+    char* Vc = reinterpret_cast<char*>(c.V) + ((size_t)u * c.m + s0) * ROWB;
+    const int32_t* pu = c.pos + (size_t)u * c.m;
+    const double* wu = weight + (size_t)u * P;
+    __shared__ int token[FOLD_ROWS + 1];                      // of survivor s0 - 1, s0, ...
+    __shared__ double part[FOLD_WAVES][D];
+    if (tid <= here) token[tid] = (s0 + tid > 0) ? pu[s0 + tid - 1] : -1;
     __syncthreads();
-    for (int i = wid; i < P; i += NW) {                       // short runs: one wave per survivor
-        const int sidx = slot[i];
-        if (sidx < 0) continue;
-        const int len = rk[i];
-        if (coop && len >= LONG) continue;
-        const char* own = vb + (size_t)i * tok;
-        if (len == 0) {                                        // nothing folds into this token
+    for (int i = tid; i < here * LPR; i += 64 * FOLD_WAVES) {
+        uint32_t w[4];
+        load_words<4>(kb + (size_t)token[i / LPR + 1] * tok + (i % LPR) * 16, w);
+        *reinterpret_cast<u32x4_t*>(Kc + (size_t)(i / LPR) * ROWB + (i % LPR) * 16) = u32x4_t{ w[0], w[1], w[2], w[3] };
+    }
+    const int grp = lane / LPR, at = lane % LPR;
+    // acc[e] += sum over rows first, first + stride, ... <= last of weight * V[row][8 at + e], then over the wave's groups
+    auto sum_rows = [&](double (&acc)[8], int first, int last, int stride) __attribute__((always_inline)) {
 #pragma unroll
-            for (int e = 0; e < EPW; ++e) {
-                const int col = lane + 64 * e;
-                if (col < D) store_bits<TT>(Vc + (size_t)sidx * ROWB, col, load_bits<TT>(own, col));
+        for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+        for (int k0 = first; k0 <= last; k0 += 4 * stride) {
+            uint32_t raw[4][4];
+            double w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = min(k0 + j * stride, last);
+                w[j] = (k0 + j * stride <= last) ? wu[k] : 0.0;
+                load_words<4>(vb + (size_t)k * tok + at * 16, raw[j]);
             }
-            continue;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (k0 + j * stride <= last)                  // (a repeated row must not add 0 x infinity)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[e] = fma(w[j], (double)frag_elem<TT>(raw[j], e), acc[e]);
         }
-        double acc[EPW];
 #pragma unroll
-        for (int e = 0; e < EPW; ++e) acc[e] = 0.0;
-        weighted_rows(acc, i - len, i, 1);
+        for (int e = 0; e < 8; ++e)
 #pragma unroll
-        for (int e = 0; e < EPW; ++e) {
-            const int col = lane + 64 * e;
-            if (col < D) store_elem_f64<TT>(Vc + (size_t)sidx * ROWB, col, acc[e]);
+            for (int off = LPR; off < 64; off <<= 1) acc[e] += __shfl_xor(acc[e], off);
+    };
+    for (int r = wid; r < here; r += FOLD_WAVES) {            // one wave per row
+        const int last = token[r + 1], first = merging ? token[r] + 1 : last;
+        char* dst = Vc + (size_t)r * ROWB;
+        if (first == last) {                                  // nothing folds into this token
+            if (grp == 0) {
+                uint32_t w[4];
+                load_words<4>(vb + (size_t)last * tok + at * 16, w);
+                *reinterpret_cast<u32x4_t*>(dst + at * 16) = u32x4_t{ w[0], w[1], w[2], w[3] };
+            }
+        } else if (last - first < LONG) {
+            double acc[8];
+            sum_rows(acc, first + grp, last, G);
+            if (grp == 0)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) store_elem_f64<TT>(dst, at * 8 + e, acc[e]);
         }
     }
-    if (coop) {                                                // long runs: every wave takes every NW-th row
-        double* part = ae;                                     // [NW][D]
-        for (int i = 0; i < P; ++i) {                          // uniform over the workgroup
-            if (slot[i] < 0 || rk[i] < LONG) continue;
-            const int len = rk[i];
-            double acc[EPW];
+    for (int r = 0; r < here; ++r) {                          // uniform over the workgroup
+        const int last = token[r + 1], first = token[r] + 1;
+        if (!merging || last - first < LONG) continue;
+        double acc[8];
+        sum_rows(acc, first + wid * G + grp, last, FOLD_WAVES * G);
+        if (grp == 0)
 #pragma unroll
-            for (int e = 0; e < EPW; ++e) acc[e] = 0.0;
-            weighted_rows(acc, i - len + wid, i, NW);
-            __syncthreads();                                   // the previous long run's partial sums have been read
+            for (int e = 0; e < 8; ++e) part[wid][at * 8 + e] = acc[e];
+        __syncthreads();
+        if (tid < D) {
+            double y = 0.0;
 #pragma unroll
-            for (int e = 0; e < EPW; ++e) {
-                const int col = lane + 64 * e;
-                if (col < D) part[wid * D + col] = acc[e];
-            }
-            __syncthreads();
-            if (tid < D) {
-                double y = 0.0;
-                for (int w = 0; w < NW; ++w) y += part[w * D + tid];
-                store_elem_f64<TT>(Vc + (size_t)slot[i] * ROWB, tid, y);
-            }
+            for (int w = 0; w < FOLD_WAVES; ++w) y += part[w][tid];
+            store_elem_f64<TT>(Vc + (size_t)r * ROWB, tid, y);
         }
+        __syncthreads();                                      // the partial sums have been read
     }
 }
 
@@ -914,10 +928,14 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
     hipLaunchKernelGGL((wkv_prefill_rows<TT, D, NW>), dim3(xcd_grid(c.units, groups)), dim3(64 * NW), 0, stream, q, k, v, out, lse, P, c.units);
     hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NW>), dim3(xcd_grid(c.units, groups)), dim3(64 * NW), 0, stream, q, k, lse, a, P, c.units);
     const size_t lds = wkv_prefill_lds_bytes(P);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wkv_prefill_compress<TT, D>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wkv_prefill_compress),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((wkv_prefill_compress<TT, D>), dim3(c.units), dim3(1024), lds, stream, c, k, v, a, P);
+    // the row log-sum-exps have been used: their place takes the weights of the tokens
+    hipLaunchKernelGGL(wkv_prefill_compress, dim3(c.units), dim3(1024), lds, stream, c, a, lse, P);
+    const int blocks = ((P < c.m ? P : c.m) + FOLD_ROWS - 1) / FOLD_ROWS;
+    const int merging = c.merge_mode == 0 && P > c.m;
+    hipLaunchKernelGGL((wkv_prefill_fold<TT, D>), dim3((unsigned)c.units * blocks), dim3(64 * FOLD_WAVES), 0, stream, c, k, v, lse, P, blocks, merging);
     return hipGetLastError();
 }
 

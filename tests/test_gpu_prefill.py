@@ -277,3 +277,13 @@ def test_rows_that_span_more_than_the_digits(dtype, d, where):
     finally:
         got["cache"].close()
     print(f"\n  {where}: {stats}", flush=True)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("P", [63, 64, 65, 66, 67, 127, 128, 129, 130, 257])
+def test_sort_and_runs_at_their_edges(P, d):
+    """The sort's steps leave a wave from 128 tokens on, and a run of 64 removed tokens or more is summed by a
+    whole workgroup: prompts around powers of two, folded into one to three survivors and into seventeen
+    (one more than a workgroup of the fold takes)."""
+    for m, R in ((1, 1), (2, 1), (3, 2), (17, 5)):
+        _run(synth.StreamConfig(f"pre-edge{P}", 8900 + P, 1, 3, d, "bf16", P + 3, m, R), P, decode_steps=3)
