@@ -38,6 +38,7 @@
 #include "../../include/wkv.h"
 #include "wkv_internal.h"
 #include <mutex>
+#include <type_traits>
 #include "wkv_device.h"
 
 namespace {
@@ -136,22 +137,27 @@ __device__ __forceinline__ void exp_table_init(double* tab) {
 }
 // ------------------------------------------------------------------ logits from 8-bit digits
 // A row of 16-bit numbers is, up to a power of two, a row of integers: n = x * 2^s with the row's own s,
-// chosen so that its largest magnitude lies in [2^26, 2^27).  n is written in four balanced base-256
-// digits (d0..d2 in [-128, 127], d3 in [-8, 8]), and q.k becomes sixteen dot products of digits,
+// chosen so that its largest magnitude has N = 27 (fp16) or 30 (bf16) bits.  n is written in four balanced base-256
+// digits (d0..d2 in [-128, 127], |d3| <= 8 or 64), and q.k becomes sixteen dot products of digits,
 // which v_mfma_i32_16x16x64_i8 forms without any rounding: seven sums S_w over the pairs of weight
-// w = i + j, then A = S0 + 2^8 S1, B = S2 + 2^8 S3, C = S4 + 2^8 S5 + 2^16 S6, each below 2^31 for 128
-// elements (S1 <= 2^22, S3 <= 2^22 + 2^18, S6 <= 2^13), and q.k = (A + 2^16 B + 2^32 C) 2^-(s_q + s_k) with the
-// rounding of two fp64 additions: closer to the exact logit than a chain of D fp64 additions.
+// w = i + j, then A = S0 + 2^8 S1, B = S2 + 2^8 S3, C = S4 + 2^8 S5 + 2^16 S6, and
+// q.k = (A + 2^16 B + 2^32 C) 2^-(s_q + s_k) with the rounding of two or three fp64 additions: closer to the
+// exact logit than a chain of D fp64 additions.  For 128 elements A and B stay below 2^31 (S1 <= 2^22,
+// S3 <= 2^22 + 2^21), and C too for 27 bits (S6 <= 2^13); for 30 bits S6 <= 2^19 joins in fp64.
 // Why: the fp64 matrix instruction takes 64 cycles for 16x16x4 on this part and shares its pipe
 // with the fp64 vector instructions of the softmax; the sixteen digit products take 512 cycles per
 // 16x16x128 tile against 2048, and run beside them.
-// Measured (256 units, 4096 tokens, d 128, fp16): rows 13.1 -> 8.3 ms, scores 10.5 -> 5.65 ms; the int8
-// instructions then fill a third of the time and vector instructions (289 a tile in scores, a
-// third of them slicing) the rest.
+// Measured (256 units, 4096 tokens, d 128, fp16): rows 13.1 -> 8.0 ms, scores 10.5 -> 5.6 ms; with the int8
+// instructions a third of the time, vector instructions bound both: slicing by packed maxima, no clamp in the
+// exponential, two tiles a wave brought 6.9 and 4.5 ms.
 // A row whose elements are not all integers at its scale (an element more than 2^-26 below the
 // largest that uses its last bits; possible for bf16, and for fp16 rows that reach 8) or that holds
 // an infinity or a NaN is marked, and a tile that touches a marked row takes the fp64 instruction.
 constexpr int DIGITS = 4;
+// fp16 has no bit below 2^-24: with 27 bits every row below 8 fits.  bf16 reaches further down; with 27 bits 0.6 % of
+// 16 x 128 tiles of normal numbers hold an element too small, with 30 bits 0.08 % do.  A wave whose own rows
+// are marked is several times slower for its whole loop, which a launch of few workgroups waits for.
+template <class TT> constexpr int int_bits() { return __is_same(TT, TF16) ? 27 : 30; }
 
 typedef int int4v_t __attribute__((ext_vector_type(4)));
 
@@ -159,11 +165,13 @@ typedef int int4v_t __attribute__((ext_vector_type(4)));
 constexpr double LOGIT_UNIT = 92.332482616893656877;                       // 64 / ln 2
 template <int D> __device__ __forceinline__ double logit_scale() { return LOGIT_UNIT / sqrt((double)D); }
 
-// exp(x ln 2 / 64), see exp_nonpos below for the method; x <= 0, -inf or NaN
+// exp(x ln 2 / 64) for x <= 0 (a rounding error above 0 is fine): method above the table.  A finite x below
+// -1e5 or so gives 0 whatever the integer conversion saturates to; -inf would give NaN, so where a
+// logit may be -inf (a masked one, a row with infinities) the argument goes through
+// no_infinity first.  NaN stays NaN.
 __device__ __forceinline__ double exp_units(double x, const double* tab) {
-    const double xc = (x < -69250.0) ? -69250.0 : x;
-    const double kd = __builtin_rint(xc);
-    const double r = xc - kd;
+    const double kd = __builtin_rint(x);
+    const double r = x - kd;
     const int k = (int)kd;
     const double tj = tab[k & 63];
     // ln2/64 = c: c, c^2/2, c^3/6, c^4/24
@@ -173,33 +181,57 @@ __device__ __forceinline__ double exp_units(double x, const double* tab) {
     p = fma(p, r, 1.0);
     return ldexp(tj * p, k >> 6);
 }
+__device__ __forceinline__ double no_infinity(double x) { return (x < -1e6) ? -1e6 : x; }
 
-// The scale s of a row from the bits of its largest |x| (as fp32); bad: the row must not be sliced.
-__device__ __forceinline__ int digit_shift(uint32_t maxbits, bool& bad) {
-    const int e = (int)(maxbits >> 23);                                    // biased exponent of the largest element
-    bad = e == 255 || (e < 32 && maxbits != 0u);
-    return (maxbits == 0u || bad) ? 0 : 26 + 127 - e;
+// What the scale of a row is found from, over packed 16-bit words: the largest |x| and, for bf16, the
+// smallest nonzero one (less one unit, so that zero wraps to the top).
+typedef unsigned short ushort2v_t __attribute__((ext_vector_type(2)));
+template <class TT> struct RowSpan {
+    ushort2v_t mx = {0, 0}, mn = {0xFFFF, 0xFFFF};
+    __device__ __forceinline__ void add(uint32_t w) {
+        const ushort2v_t a = __builtin_bit_cast(ushort2v_t, w & 0x7FFF7FFFu);
+        mx = __builtin_elementwise_max(mx, a);
+        if constexpr (!__is_same(TT, TF16)) mn = __builtin_elementwise_min(mn, (ushort2v_t)(a - ushort2v_t{1, 1}));
+    }
+    __device__ __forceinline__ uint32_t largest() const { return max((uint32_t)mx.x, (uint32_t)mx.y); }
+    __device__ __forceinline__ uint32_t smallest_exponent() const { return (min((uint32_t)mn.x, (uint32_t)mn.y) + 1u) >> 7; }
+};
+
+// Scale 2^s of a row whose largest |x| has the 16 bits `top`: the largest integer gets int_bits bits.
+// bad: the row must not be sliced.  e: biased fp32 exponent of the largest element.
+template <class TT> __device__ __forceinline__ int digit_shift(uint32_t top, int& e, bool& bad) {
+    const uint32_t one[1] = { top };
+    e = (int)(__builtin_bit_cast(uint32_t, frag_elem<TT>(one, 0)) >> 23);
+    bad = e == 255 || (e < 36 && top != 0u);
+    return (top == 0u || bad) ? 0 : int_bits<TT>() - 1 + 127 - e;
+}
+// Whether this lane's elements are no integers at that scale.  fp16 has no bit below 2^-24, so a row that
+// stays below 8 (s >= 24) fits; beyond, the elements are looked at.  bf16: 8 significant bits,
+// the last one 7 below the exponent.
+template <class TT, int NWORDS> __device__ __forceinline__ bool no_integers(const uint32_t (&w)[NWORDS], const RowSpan<TT>& span, int e, float mul) {
+    if constexpr (__is_same(TT, TF16)) {
+        float frac = 0.f;
+        if (__any(e > 129))
+#pragma unroll
+            for (int i = 0; i < 2 * NWORDS; ++i) frac = fmaxf(frac, __builtin_amdgcn_fractf(frag_elem<TT>(w, i) * mul));
+        return frac != 0.f;
+    } else {
+        return (int)span.smallest_exponent() + int_bits<TT>() - 8 < e;
+    }
 }
 
-// Four elements -> the words of the four digit planes (byte i of plane b = digit b of element i);
-// frac collects what did not fit an integer.
-__device__ __forceinline__ void digits4(const float (&x)[4], int s, uint32_t (&w)[DIGITS], float& frac) {
+// Four elements -> the words of the four digit planes (byte i of plane b = digit b of element i)
+__device__ __forceinline__ void digits4(const float (&x)[4], float mul, uint32_t (&w)[DIGITS]) {
     uint32_t t[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float f = ldexpf(x[i], s);
-        frac = fmaxf(frac, __builtin_amdgcn_fractf(f));
-        t[i] = ((uint32_t)(int)f + 0x00808080u) ^ 0x00808080u;             // bytes become balanced digits
-    }
+    for (int i = 0; i < 4; ++i) t[i] = (uint32_t)(int)(x[i] * mul) + 0x00808080u;   // the low bytes become digits + 128
     const uint32_t l01 = __builtin_amdgcn_perm(t[1], t[0], 0x05010400u), h01 = __builtin_amdgcn_perm(t[1], t[0], 0x07030602u);
     const uint32_t l23 = __builtin_amdgcn_perm(t[3], t[2], 0x05010400u), h23 = __builtin_amdgcn_perm(t[3], t[2], 0x07030602u);
-    w[0] = __builtin_amdgcn_perm(l23, l01, 0x05040100u);
-    w[1] = __builtin_amdgcn_perm(l23, l01, 0x07060302u);
-    w[2] = __builtin_amdgcn_perm(h23, h01, 0x05040100u);
+    w[0] = __builtin_amdgcn_perm(l23, l01, 0x05040100u) ^ 0x80808080u;
+    w[1] = __builtin_amdgcn_perm(l23, l01, 0x07060302u) ^ 0x80808080u;
+    w[2] = __builtin_amdgcn_perm(h23, h01, 0x05040100u) ^ 0x80808080u;
     w[3] = __builtin_amdgcn_perm(h23, h01, 0x07060302u);
 }
-
-template <class TT> __device__ __forceinline__ uint32_t abs_bits(float x) { return __builtin_bit_cast(uint32_t, x) & 0x7FFFFFFFu; }
 
 // Operands of one wave's own 16 rows, in registers: lane (g, x) holds elements 64 c + 16 g .. + 15 of row x.
 // scale: unit * 2^-s of row x.  Returns whether a row is marked (uniform).
@@ -210,40 +242,45 @@ __device__ __forceinline__ bool own_digits(const char* base, int row0, int P, si
     constexpr int KS = D / 64;
     const char* src = base + (size_t)min(row0 + x, P - 1) * tok;
     uint32_t w[KS][8];
-    uint32_t mb = 0;
+    RowSpan<TT> span;
 #pragma unroll
     for (int c = 0; c < KS; ++c) {
         load_words<8>(src + (64 * c + 16 * g) * TT::BYTES, w[c]);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) mb = max(mb, abs_bits<TT>(frag_elem<TT>(w[c], e)));
+        for (int i = 0; i < 8; ++i) span.add(w[c][i]);
     }
-    mb = max(mb, (uint32_t)__shfl_xor((int)mb, 16));
-    mb = max(mb, (uint32_t)__shfl_xor((int)mb, 32));
+    uint32_t top = span.largest();
+    top = max(top, (uint32_t)__shfl_xor((int)top, 16));
+    top = max(top, (uint32_t)__shfl_xor((int)top, 32));
     bool bad;
-    const int s = digit_shift(mb, bad);
-    float frac = 0.f;
+    int ex;
+    const int s = digit_shift<TT>(top, ex, bad);
+    const float mul = ldexpf(1.f, s);
 #pragma unroll
-    for (int c = 0; c < KS; ++c)
+    for (int c = 0; c < KS; ++c) {
+        bad |= no_integers<TT>(w[c], span, ex, mul);
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
             float f[4];
             uint32_t pl[DIGITS];
 #pragma unroll
             for (int i = 0; i < 4; ++i) f[i] = frag_elem<TT>(w[c], 4 * e4 + i);
-            digits4(f, s, pl, frac);
+            digits4(f, mul, pl);
 #pragma unroll
             for (int b = 0; b < DIGITS; ++b) dg[c][b][e4] = (int)pl[b];
         }
+    }
     scale = ldexp(unit, -s);
-    return __any(bad || frac != 0.f);
+    return __any(bad);
 }
 
 // Operands of the rows that a workgroup's waves share, in LDS: CHUNK rows (two tiles, or what the
 // workgroup's threads slice in one round if that is more), double-buffered.
 // A digit plane of 64 elements of 16 rows: block g (elements 16 g .. + 15) holds 16 bytes of each
-// row; blocks are 320 bytes apart, so that the sixteen threads that write one row (eight bytes each)
-// and the rows of a wave fall into different banks.
-constexpr int PLANE = 4 * 320;
+// row; blocks are 288 bytes apart, so that the threads that write one row (eight bytes each)
+// do not all fall into the same banks.  (320 bytes, with fewer conflicts, leave room for three
+// workgroups a compute unit where scores' registers allow four: 4.86 against 4.59 ms at 256 x 4096.)
+constexpr int BLOCK = 288, PLANE = 4 * BLOCK;
 template <int D, int NW> constexpr int chunk_tiles() { return (64 * NW) / (D / 8) > 2 * TILE ? (64 * NW) / (D / 8) / TILE : 2; }
 template <int D, int CTILES> struct SharedRows {
     static constexpr int CHUNK = CTILES * TILE;
@@ -272,30 +309,40 @@ template <class TT, int D, int NT, int CTILES> struct ChunkLoad {
         const int j = threadIdx.x % TPR, r = threadIdx.x / TPR;
 #pragma unroll
         for (int i = 0; i < ROUNDS; ++i) {
-            float f[8];
-            uint32_t mb = 0;
+            RowSpan<TT> span;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { f[e] = frag_elem<TT>(w[i], e); mb = max(mb, abs_bits<TT>(f[e])); }
-#pragma unroll
-            for (int off = 1; off < TPR; off <<= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, off));
+            for (int e = 0; e < 4; ++e) span.add(w[i][e]);
+            int top = (int)span.largest();                                 // over the row's 8 or 16 lanes
+            top = max(top, dpp<0xB1>(top));       // quad_perm [1,0,3,2]
+            top = max(top, dpp<0x4E>(top));       // quad_perm [2,3,0,1]
+            top = max(top, dpp<0x141>(top));      // row_half_mirror
+            if constexpr (TPR == 16) top = max(top, dpp<0x140>(top));   // row_mirror
             bool bad;
-            const int s = digit_shift(mb, bad);
-            float frac = 0.f;
+            int ex;
+            const int s = digit_shift<TT>((uint32_t)top, ex, bad);
+            const float mul = ldexpf(1.f, s);
+            bad |= no_integers<TT>(w[i], span, ex, mul);
             uint32_t p0[DIGITS], p1[DIGITS];
-            const float fa[4] = { f[0], f[1], f[2], f[3] }, fb[4] = { f[4], f[5], f[6], f[7] };
-            digits4(fa, s, p0, frac);
-            digits4(fb, s, p1, frac);
+            float fa[4], fb[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { fa[e] = frag_elem<TT>(w[i], e); fb[e] = frag_elem<TT>(w[i], e + 4); }
+            digits4(fa, mul, p0);
+            digits4(fb, mul, p1);
             const int row = i * ROWS + r, t = row / TILE, x = row % TILE;
             const int c = j >> 3, g = (j >> 1) & 3, half = j & 1;
 #pragma unroll
             for (int b = 0; b < DIGITS; ++b)
-                *reinterpret_cast<uint2_t*>(&sh.dg[buf][t][c][b][g * 320 + x * 16 + half * 8]) = uint2_t{ p0[b], p1[b] };
-            const unsigned long long fm = __ballot(bad || frac != 0.f);
+                *reinterpret_cast<uint2_t*>(&sh.dg[buf][t][c][b][g * BLOCK + x * 16 + half * 8]) = uint2_t{ p0[b], p1[b] };
+            const unsigned long long fm = __ballot(bad);
             if (j == 0) {
                 const int lane = threadIdx.x & 63;
                 sh.scale[buf][row] = ldexp(unit, -s);
-                sh.marked[buf][row] = ((fm >> lane) & ((1ull << TPR) - 1)) != 0;
-                if (with_lse) sh.lse[buf][row] = lse[i];
+                bool mark = ((fm >> lane) & ((1ull << TPR) - 1)) != 0;
+                if (with_lse) {
+                    sh.lse[buf][row] = lse[i];
+                    mark |= !(fabs(lse[i]) < INFINITY);
+                }
+                sh.marked[buf][row] = mark;
             }
         }
     }
@@ -303,7 +350,7 @@ template <class TT, int D, int NT, int CTILES> struct ChunkLoad {
 
 // Unscaled S^T tile (rows = keys, columns = queries): register r of lane (g, x) = key 4g + r, query x.
 // SHARED_KEYS: the shared rows are the keys and the own rows the queries, or the other way round.
-template <int D, bool SHARED_KEYS>
+template <class TT, int D, bool SHARED_KEYS>
 __device__ __forceinline__ void digit_tile(const unsigned char (&pl)[D / 64][DIGITS][PLANE], const int4v_t (&own)[D / 64][DIGITS],
                                            int g, int x, double (&s)[4])
 {
@@ -314,7 +361,7 @@ __device__ __forceinline__ void digit_tile(const unsigned char (&pl)[D / 64][DIG
     for (int c = 0; c < D / 64; ++c)
 #pragma unroll
         for (int i = 0; i < DIGITS; ++i) {
-            const int4v_t a = *reinterpret_cast<const int4v_t*>(&pl[c][i][g * 320 + x * 16]);
+            const int4v_t a = *reinterpret_cast<const int4v_t*>(&pl[c][i][g * BLOCK + x * 16]);
 #pragma unroll
             for (int j = 0; j < DIGITS; ++j)
                 S[i + j] = SHARED_KEYS ? __builtin_amdgcn_mfma_i32_16x16x64_i8(a, own[c][j], S[i + j], 0, 0, 0)
@@ -322,8 +369,11 @@ __device__ __forceinline__ void digit_tile(const unsigned char (&pl)[D / 64][DIG
         }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int A = S[0][r] + (S[1][r] << 8), B = S[2][r] + (S[3][r] << 8), C = S[4][r] + (S[5][r] << 8) + (S[6][r] << 16);
-        s[r] = fma(fma((double)C, 65536.0, (double)B), 65536.0, (double)A);
+        const int A = S[0][r] + (S[1][r] << 8), B = S[2][r] + (S[3][r] << 8);
+        double C;
+        if constexpr (int_bits<TT>() <= 27) C = (double)(S[4][r] + (S[5][r] << 8) + (S[6][r] << 16));
+        else C = fma((double)S[6][r], 65536.0, (double)(S[4][r] + (S[5][r] << 8)));
+        s[r] = fma(fma(C, 65536.0, (double)B), 65536.0, (double)A);
     }
 }
 
@@ -336,12 +386,12 @@ __device__ __forceinline__ void exact_tile(const char* kb, const char* qb, int k
     const char* qr = qb + (size_t)min(q0 + x, P - 1) * tok + g * (D / 4) * TT::BYTES;
     double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
-    for (int e0 = 0; e0 < D / 4; e0 += 8) {
-        uint32_t kw[4], qw[4];
-        load_words<4>(kr + e0 * TT::BYTES, kw);
-        load_words<4>(qr + e0 * TT::BYTES, qw);
+    for (int e0 = 0; e0 < D / 4; e0 += 16) {
+        uint32_t kw[8], qw[8];
+        load_words<8>(kr + e0 * TT::BYTES, kw);
+        load_words<8>(qr + e0 * TT::BYTES, qw);
 #pragma unroll
-        for (int e = 0; e < 8; e += 2) {
+        for (int e = 0; e < 16; e += 2) {
             s0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)frag_elem<TT>(kw, e), (double)frag_elem<TT>(qw, e), s0, 0, 0, 0);
             s1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)frag_elem<TT>(kw, e + 1), (double)frag_elem<TT>(qw, e + 1), s1, 0, 0, 0);
         }
@@ -352,9 +402,12 @@ __device__ __forceinline__ void exact_tile(const char* kb, const char* qb, int k
 
 // ------------------------------------------------------------------ 1. rows
 // q, k, v, out: [P][units][D] (token-major, as a decode step sees them one token at a time).
-// lse: [units][P], in units of ln 2 / 64.  One workgroup = NW waves = NW consecutive query tiles of one unit;
-// the keys are sliced into digits once per workgroup and read by every wave from LDS.
-template <class TT, int D, int NW>
+// lse: [units][P], in units of ln 2 / 64.  One workgroup = NW waves of QT consecutive query tiles of one unit;
+// the keys are sliced into digits once per workgroup and read by every wave from LDS.  What bounds
+// this kernel and the next is vector instructions (slicing, recombining the digit sums, the
+// exponentials), so a wave takes two tiles where there is work enough: slicing, value loads and their
+// permutes are then paid once for both.
+template <class TT, int D, int NW, int QT>
 __global__ __launch_bounds__(64 * NW, 2)
 void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, const void* __restrict__ v_,
                       void* __restrict__ out_, double* __restrict__ lse, int P, int units)
@@ -363,13 +416,14 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int g = lane >> 4, x = lane & 15;
     const int ntiles = (P + TILE - 1) / TILE;
-    const int groups = (ntiles + NW - 1) / NW;
+    const int groups = (ntiles + NW * QT - 1) / (NW * QT);
     const int u = xcd_unit(blockIdx.x, groups);
-    const int qt0 = (groups - 1 - (int)((blockIdx.x >> 3) % groups)) * NW;       // long rows are scheduled first
+    const int qt0 = (groups - 1 - (int)((blockIdx.x >> 3) % groups)) * NW * QT;  // long rows are scheduled first
     if (u >= units) return;                                                      // the whole workgroup
-    const int qt = qt0 + wid;
+    const int qt = qt0 + wid * QT;                                               // first tile of the wave
     const bool active = qt < ntiles;                                             // an idle wave still slices keys
-    const int last = min(qt0 + NW - 1, ntiles - 1);                              // the workgroup's last key tile
+    const int mine = min(qt + QT, ntiles) - 1;                                   // its last key tile, and the workgroup's
+    const int last = min(qt0 + NW * QT, ntiles) - 1;
     __shared__ double etab[64];
     __shared__ SharedRows<D, CTILES> sh;
     exp_table_init(etab);
@@ -380,16 +434,24 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
 
     ChunkLoad<TT, D, 64 * NW, CTILES> next;
     next.request(kb, nullptr, 0, P, tok);
-    int4v_t qdg[D / 64][DIGITS];
-    double qscale;
-    const bool qmarked = own_digits<TT, D>(qb, qt * TILE, P, tok, g, x, qdg, qscale, 1.0);
+    int4v_t qdg[QT][D / 64][DIGITS];
+    double qscale[QT];
+    bool qmarked = false;
+#pragma unroll
+    for (int i = 0; i < QT; ++i) qmarked |= own_digits<TT, D>(qb, (qt + i) * TILE, P, tok, g, x, qdg[i], qscale[i], 1.0);
     next.store(sh, 0, false, logit_scale<D>());
 
-    double mrow = -INFINITY, lrow = 0.0;      // running maximum of query x (same in the 4 lanes x, x+16, ...); this lane's share of the sum
+    // running maximum of query x (same in the 4 lanes x, x+16, ...); this lane's share of the sum
+    double mrow[QT], lrow[QT];
     constexpr int NE = D / 16;                // output column sets: lane (g, x) owns columns NE*x .. NE*x+NE-1
-    float4_t o[NE];
+    float4_t o[QT][NE];
 #pragma unroll
-    for (int e = 0; e < NE; ++e) o[e] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < QT; ++i) {
+        mrow[i] = -INFINITY;
+        lrow[i] = 0.0;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) o[i][e] = float4_t{0.f, 0.f, 0.f, 0.f};
+    }
 
     size_t voff[4];
 #pragma unroll
@@ -408,53 +470,86 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
                 load_words<NE / 2>(vb + (size_t)min(kt * TILE + 4 * g + r, P - 1) * tok + x * NE * TT::BYTES, vfrag[r]);
         }
         const int t = kt % CTILES;
-        double s[4];
-        if (__any(sh.marked[buf][t * TILE + x]) || qmarked) {
-            exact_tile<TT, D>(kb, qb, kt * TILE, qt * TILE, P, tok, g, x, s);
+        double s[QT][4];
+        const bool special = __any(sh.marked[buf][t * TILE + x]) || qmarked;       // uniform
+        if (special) {
+#pragma unroll
+            for (int i = 0; i < QT; ++i) exact_tile<TT, D>(kb, qb, kt * TILE, (qt + i) * TILE, P, tok, g, x, s[i]);
         } else {
-            digit_tile<D, true>(sh.dg[buf][t], qdg, g, x, s);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) s[r] *= sh.scale[buf][t * TILE + 4 * g + r] * qscale;
-        }
-        if (kt == qt) {                       // the diagonal tile: key 4g + r may be attended by query x only if <= x
+            for (int i = 0; i < QT; ++i) {
+                if (QT * D > 128) __builtin_amdgcn_sched_barrier(0);       // one tile's sums at a time: the registers do not hold two
+                digit_tile<TT, D, true>(sh.dg[buf][t], qdg[i], g, x, s[i]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) if (4 * g + r > x) s[r] = -INFINITY;
+                for (int r = 0; r < 4; ++r) s[i][r] *= sh.scale[buf][t * TILE + 4 * g + r] * qscale[i];
+            }
         }
-        double tmax = fmax(fmax(s[0], s[1]), fmax(s[2], s[3]));
+        const bool edge = kt >= qt;           // a diagonal tile: key 4g + r may be attended by query x only if not newer
+        if (edge) {
+#pragma unroll
+            for (int i = 0; i < QT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) if ((kt - qt - i) * TILE + 4 * g + r > x) s[i][r] = -INFINITY;
+        }
         // A running maximum that has not moved needs no rescaling, and after the first few key
         // tiles of a row it rarely moves: the maximum over the four lane groups and the rescaling (an exp,
         // the running sum and all output accumulators of the wave) are skipped unless some query needs them.
-        if (__any(tmax > mrow)) {
-            tmax = pair_max<32>(pair_max<16>(tmax));           // all 16 keys of the tile
-            const double mnew = fmax(mrow, tmax);             // finite: key 16 kt + 0 <= every query of a later tile,
+        double tmax[QT];
+        bool moved = false;
+#pragma unroll
+        for (int i = 0; i < QT; ++i) {
+            tmax[i] = fmax(fmax(s[i][0], s[i][1]), fmax(s[i][2], s[i][3]));
+            moved |= tmax[i] > mrow[i];
+        }
+        if (__any(moved)) {
+#pragma unroll
+            for (int i = 0; i < QT; ++i) {
+                const double top = pair_max<32>(pair_max<16>(tmax[i]));        // all 16 keys of the tile
+                const double mnew = fmax(mrow[i], top);       // finite: key 16 kt + 0 <= every query of a later tile,
                                                               // and on the diagonal key x is attended by query x
-            const double resc = exp_units(mrow - mnew, etab);              // 0 on the first tile (mrow = -inf), 1 where nothing moved
-            lrow *= resc;
-            mrow = mnew;
-            const float rf = (float)resc;                     // the output rows this lane holds (queries 4g + r') by their own factor
+                const double resc = exp_units(no_infinity(mrow[i] - mnew), etab);  // 0 on the first tile (mrow = -inf), 1 where nothing moved
+                lrow[i] *= resc;
+                mrow[i] = mnew;
+                const float rf = (float)resc;                 // the output rows this lane holds (queries 4g + r') by their own factor
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float f = __shfl(rf, 4 * g + r);
+                for (int r = 0; r < 4; ++r) {
+                    const float f = __shfl(rf, 4 * g + r);
 #pragma unroll
-                for (int e = 0; e < NE; ++e) o[e][r] *= f;
+                    for (int e = 0; e < NE; ++e) o[i][e][r] *= f;
+                }
             }
         }
-        float p[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) { const double e = exp_units(s[r] - mrow, etab); lrow += e; p[r] = (float)e; }
+        for (int i = 0; i < QT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s[i][r] -= mrow[i];
+        if (special || edge) {
+#pragma unroll
+            for (int i = 0; i < QT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s[i][r] = no_infinity(s[i][r]);
+        }
         // O[query][column] += sum over keys P[query][key] V[key][column] with the 16-bit matrix
         // instruction (k = 16 keys at once): lane (g, x) supplies k-slots 4g + r: as A operand
         // P[query x][key 4g + r], as B operand V[key 4g + r][column NE*x + e], the raw cache values.
         // P goes in as a sum of 16-bit parts.
-        uint2_t pa[weight_parts<TT>()];
-        split16x4<TT>(p, pa);
+        uint2_t pa[QT][weight_parts<TT>()];
+#pragma unroll
+        for (int i = 0; i < QT; ++i) {
+            float p[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { const double e = exp_units(s[i][r], etab); lrow[i] += e; p[r] = (float)e; }
+            split16x4<TT>(p, pa[i]);
+        }
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
             const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;      // high / low halves of two words
             const uint2_t vb2 = { __builtin_amdgcn_perm(vfrag[1][e >> 1], vfrag[0][e >> 1], sel),
                                   __builtin_amdgcn_perm(vfrag[3][e >> 1], vfrag[2][e >> 1], sel) };
 #pragma unroll
-            for (int w = 0; w < weight_parts<TT>(); ++w) o[e] = mfma16<TT>(pa[w], vb2, o[e]);
+            for (int i = 0; i < QT; ++i)
+#pragma unroll
+                for (int w = 0; w < weight_parts<TT>(); ++w) o[i][e] = mfma16<TT>(pa[i][w], vb2, o[i][e]);
         }
     };
     // A chunk is worked on from one buffer while the next one is on its way from memory; it is sliced into
@@ -464,31 +559,35 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         const bool more = kt + CTILES <= last;
         if (more) next.request(kb, nullptr, (kt + CTILES) * TILE, P, tok);
         if (active)
-            for (int t = 0; t < CTILES && kt + t <= qt; ++t) tile(kt + t, buf);
+            for (int t = 0; t < CTILES && kt + t <= mine; ++t) tile(kt + t, buf);
         if (more) next.store(sh, buf ^ 1, false, logit_scale<D>());
     }
     if (!active) return;
 
     // o_t = O / l, log-sum-exp = m + log l
-    lrow = rows_sum(lrow);
-    const float linv = (float)(1.0 / lrow);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int t = qt * TILE + 4 * g + r;
-        const float f = __shfl(linv, 4 * g + r);
-        if (t < P && out_ != nullptr) {
-            char* dst = reinterpret_cast<char*>(out_) + (size_t)t * tok + (size_t)u * ROWB + x * NE * TT::BYTES;
+    for (int i = 0; i < QT; ++i) {
+        const double l = rows_sum(lrow[i]);
+        const float linv = (float)(1.0 / l);
 #pragma unroll
-            for (int e = 0; e < NE; ++e) store_elem<TT>(dst, e, o[e][r] * f);
+        for (int r = 0; r < 4; ++r) {
+            const int t = (qt + i) * TILE + 4 * g + r;
+            const float f = __shfl(linv, 4 * g + r);
+            if (t < P && out_ != nullptr) {
+                char* dst = reinterpret_cast<char*>(out_) + (size_t)t * tok + (size_t)u * ROWB + x * NE * TT::BYTES;
+#pragma unroll
+                for (int e = 0; e < NE; ++e) store_elem<TT>(dst, e, o[i][e][r] * f);
+            }
         }
+        const int tq = (qt + i) * TILE + x;
+        if (g == 0 && tq < P) lse[(size_t)u * P + tq] = mrow[i] + log(l) * LOGIT_UNIT;
     }
-    if (g == 0 && qt * TILE + x < P) lse[(size_t)u * P + qt * TILE + x] = mrow + log(lrow) * LOGIT_UNIT;
 }
 
 // ------------------------------------------------------------------ 2. scores
-// a[u][i] = sum over rows t >= i of exp(s_ti - lse_t).  One wave per key tile, NW of them a workgroup, which
-// shares the sliced queries.
-template <class TT, int D, int NW>
+// a[u][i] = sum over rows t >= i of exp(s_ti - lse_t).  A wave takes KT tiles of keys; NW waves, a workgroup,
+// share the sliced queries.
+template <class TT, int D, int NW, int KT>
 __global__ __launch_bounds__(64 * NW, 2)
 void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_, const double* __restrict__ lse,
                         double* __restrict__ a, int P, int units)
@@ -497,11 +596,11 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int g = lane >> 4, x = lane & 15;
     const int ntiles = (P + TILE - 1) / TILE;
-    const int groups = (ntiles + NW - 1) / NW;
+    const int groups = (ntiles + NW * KT - 1) / (NW * KT);
     const int u = xcd_unit(blockIdx.x, groups);
-    const int kt0 = (int)((blockIdx.x >> 3) % groups) * NW;               // low key tiles have the most rows: first
+    const int kt0 = (int)((blockIdx.x >> 3) % groups) * NW * KT;          // low key tiles have the most rows: first
     if (u >= units) return;                                               // the whole workgroup
-    const int kt = kt0 + wid;
+    const int kt = kt0 + wid * KT;
     const bool active = kt < ntiles;
     __shared__ double etab[64];
     __shared__ SharedRows<D, CTILES> sh;
@@ -513,12 +612,16 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
 
     ChunkLoad<TT, D, 64 * NW, CTILES> next;
     next.request(qb, lseu, kt0 * TILE, P, tok);
-    int4v_t kdg[D / 64][DIGITS];
-    double kx;
-    const bool kmarked = own_digits<TT, D>(kb, kt * TILE, P, tok, g, x, kdg, kx, logit_scale<D>());
-    double kscale[4], acc[4] = {0.0, 0.0, 0.0, 0.0};
+    int4v_t kdg[KT][D / 64][DIGITS];
+    double kscale[KT][4], acc[KT][4];
+    bool kmarked = false;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) kscale[r] = __shfl(kx, 4 * g + r);
+    for (int i = 0; i < KT; ++i) {
+        double kx;
+        kmarked |= own_digits<TT, D>(kb, (kt + i) * TILE, P, tok, g, x, kdg[i], kx, logit_scale<D>());
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { kscale[i][r] = __shfl(kx, 4 * g + r); acc[i][r] = 0.0; }
+    }
     next.store(sh, 0, true, 1.0);
 
     for (int q0 = kt0, buf = 0; q0 < ntiles; q0 += CTILES, buf ^= 1) {
@@ -527,38 +630,52 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
         if (more) next.request(qb, lseu, (q0 + CTILES) * TILE, P, tok);
         if (active)
             for (int qt = max(q0, kt); qt < min(q0 + CTILES, ntiles); ++qt) {
-                const int t = qt % CTILES;
+                const int t = qt - q0;
                 const double l = sh.lse[buf][t * TILE + x];
-                double s[4];
-                if (__any(sh.marked[buf][t * TILE + x]) || kmarked) {
-                    exact_tile<TT, D>(kb, qb, kt * TILE, qt * TILE, P, tok, g, x, s);
+                double s[KT][4];
+                const bool special = __any(sh.marked[buf][t * TILE + x]) || kmarked;   // uniform
+                if (special) {
+#pragma unroll
+                    for (int i = 0; i < KT; ++i) exact_tile<TT, D>(kb, qb, (kt + i) * TILE, qt * TILE, P, tok, g, x, s[i]);
                 } else {
-                    digit_tile<D, false>(sh.dg[buf][t], kdg, g, x, s);
                     const double qs = sh.scale[buf][t * TILE + x];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) s[r] *= kscale[r] * qs;
+                    for (int i = 0; i < KT; ++i) {
+                        digit_tile<TT, D, false>(sh.dg[buf][t], kdg[i], g, x, s[i]);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) s[i][r] *= kscale[i][r] * qs;
+                    }
                 }
-                if (qt == kt || qt == ntiles - 1) {                        // causal, and inside the prompt
+#pragma unroll
+                for (int i = 0; i < KT; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) s[i][r] -= l;
+                if (special || qt < kt + KT || qt == ntiles - 1) {         // causal, and inside the prompt
                     const int tq = qt * TILE + x;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const bool on = tq < P && kt * TILE + 4 * g + r <= tq;
-                        acc[r] += exp_units(on ? s[r] - l : -INFINITY, etab);      // exp(-inf) = 0; no branch
-                    }
-                } else {
+                    for (int i = 0; i < KT; ++i)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[r] += exp_units(s[r] - l, etab);
+                        for (int r = 0; r < 4; ++r) {
+                            const bool on = tq < P && (kt + i) * TILE + 4 * g + r <= tq;
+                            s[i][r] = no_infinity(on ? s[i][r] : -INFINITY);       // exp gives 0; no branch
+                        }
                 }
+#pragma unroll
+                for (int i = 0; i < KT; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[i][r] += exp_units(s[i][r], etab);
             }
         if (more) next.store(sh, buf ^ 1, true, 1.0);
     }
     if (!active) return;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const double c = row_allsum(acc[r]);                               // over the 16 queries x
-        const int key = kt * TILE + 4 * g + r;
-        if (x == 0 && key < P) a[(size_t)u * P + key] = c;
-    }
+    for (int i = 0; i < KT; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const double c = row_allsum(acc[i][r]);                        // over the 16 queries x
+            const int key = (kt + i) * TILE + 4 * g + r;
+            if (x == 0 && key < P) a[(size_t)u * P + key] = c;
+        }
 }
 
 // ------------------------------------------------------------------ 3. compress
@@ -919,14 +1036,25 @@ void wkv_prefill_fold(WkvCache c, const void* __restrict__ k_, const void* __res
     }
 }
 
+// A wave takes two tiles of 16 tokens from 65536 tiles a launch on.  Measured (rows / scores, one tile against two): 256 units
+// x 4096 tokens 7.55 / 4.59 against 6.86 / 4.49 ms; 128 x 2048 (16384 tiles, bf16) 1.26 / 0.80 against 1.32 / 0.97: half as
+// many workgroups, and the last of them run on an emptying chip; 24 x 1237 106 / 102 against 135 / 148 us.
+inline bool two_tiles(int units, int ntiles) { return (long long)units * ntiles >= 65536; }
+
 template <class TT, int D>
 hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, void* out,
                double* lse, double* a, int P, hipStream_t stream)
 {
     constexpr int NW = 4;
-    const int ntiles = (P + TILE - 1) / TILE, groups = (ntiles + NW - 1) / NW;
-    hipLaunchKernelGGL((wkv_prefill_rows<TT, D, NW>), dim3(xcd_grid(c.units, groups)), dim3(64 * NW), 0, stream, q, k, v, out, lse, P, c.units);
-    hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NW>), dim3(xcd_grid(c.units, groups)), dim3(64 * NW), 0, stream, q, k, lse, a, P, c.units);
+    const int ntiles = (P + TILE - 1) / TILE;
+    auto contract = [&](auto tiles) {
+        constexpr int T = decltype(tiles)::value;
+        const int grid = xcd_grid(c.units, (ntiles + NW * T - 1) / (NW * T));
+        hipLaunchKernelGGL((wkv_prefill_rows<TT, D, NW, T>), dim3(grid), dim3(64 * NW), 0, stream, q, k, v, out, lse, P, c.units);
+        hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NW, T>), dim3(grid), dim3(64 * NW), 0, stream, q, k, lse, a, P, c.units);
+    };
+    if (two_tiles(c.units, ntiles)) contract(std::integral_constant<int, 2>{});
+    else contract(std::integral_constant<int, 1>{});
     const size_t lds = wkv_prefill_lds_bytes(P);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wkv_prefill_compress),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -287,3 +287,21 @@ def test_sort_and_runs_at_their_edges(P, d):
     (one more than a workgroup of the fold takes)."""
     for m, R in ((1, 1), (2, 1), (3, 2), (17, 5)):
         _run(synth.StreamConfig(f"pre-edge{P}", 8900 + P, 1, 3, d, "bf16", P + 3, m, R), P, decode_steps=3)
+
+
+@pytest.mark.parametrize("dtype,d,P,units", [("fp16", 128, 129, 7290), ("bf16", 64, 1025, 1017)])
+def test_prompts_with_two_tiles_a_wave(dtype, d, P, units):
+    """From 65536 tiles a launch on, a wave takes two tiles of 16 tokens: an odd number of tiles (the last wave
+    has one), one row in the last tile, units that are no multiple of eight and a row that takes the fp64
+    instruction (one element far above the others).  Five units' inputs, repeated."""
+    cfg = synth.StreamConfig("pre-two", 8800 + P, 1, units, d, dtype, P + 4, 100, 9)
+    few = synth.Stream(synth.StreamConfig("pre-two", 8800 + P, 1, 5, d, dtype, P + 4, 100, 9))
+    q, k, v = (synth.storage_to_f32(x, dtype).copy() for x in few.steps(0, cfg.steps))
+    k[37, :, 1:] *= 2.0 ** -12 if dtype == "fp16" else 2.0 ** -26
+    k[37, :, 0] = 9.0
+    arrays = [x[:, np.arange(units) % 5] for x in (q, k, v)]
+    got = parity.gpu_prefill(cfg, P, units_sel=[0, 1, 3, units // 2, units - 1], arrays=arrays)
+    try:
+        print(f"\n  {parity.compare_prefill(cfg, got, decode_steps=3)}", flush=True)
+    finally:
+        got["cache"].close()
