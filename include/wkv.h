@@ -159,7 +159,7 @@ int wkv_step(wkv_handle* h, const void* q, const void* k_new, const void* v_new,
  *   out     : DEVICE pointer of the same shape, or NULL if the outputs are not wanted.
  * Built for 16-bit caches with head_dim 64 or 128 and the average or cumulative scoring rule
  * (WKV_ESIZE / WKV_EINVAL otherwise); 1 <= n_tokens <= WKV_MAX_PROMPT.
- * Asynchronous like wkv_step: returns after enqueueing three kernels on `stream`; the caller keeps
+ * Asynchronous like wkv_step: returns after enqueueing its kernels on `stream`; the caller keeps
  * q, k, v, out valid until the stream reaches them.  Device scratch (16 bytes per token and unit)
  * belongs to the handle: reserved by wkv_create_ex when wkv_options.max_prompt covers n_tokens,
  * otherwise allocated (and kept) by the first call that needs it -- only that call allocates.

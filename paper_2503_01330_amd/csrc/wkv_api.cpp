@@ -592,26 +592,29 @@ static int load_impl(wkv_handle* h, int64_t tokens, int len, const void* K, cons
     if (rc != WKV_OK) return rc;
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) return fail(WKV_EHIP, "hipDeviceSynchronize: %s", hipGetErrorString(e));
-    // device layout: slot l of a unit holds the l-th token in token order, links run l -> l+1
-    const size_t rb = (size_t)h->opt.head_dim * dtype_bytes(h->opt.dtype);
-    std::vector<int32_t> hp(units * m, -1), hn(units * m, -1);
-    std::vector<double> ha(units * m, 0.0);
-    for (size_t u = 0; u < units; ++u)
-        for (int l = 0; l < len; ++l) {
-            hp[u * m + l] = pos[u * len + l];
-            hn[u * m + l] = (l + 1 < len) ? l + 1 : -1;
-            ha[u * m + l] = score_sum[u * len + l];
-        }
-    if (len > 0) {
+    if (len == 0) {
+        e = wkv_launch_clear(c, nullptr);
+        if (e == hipSuccess) e = hipDeviceSynchronize();
+    } else {
+        // device layout: slot l of a unit holds the l-th token in token order, links run l -> l+1
+        const size_t rb = (size_t)h->opt.head_dim * dtype_bytes(h->opt.dtype);
+        std::vector<int32_t> hp(units * m, -1), hn(units * m, -1);
+        std::vector<double> ha(units * m, 0.0);
+        for (size_t u = 0; u < units; ++u)
+            for (int l = 0; l < len; ++l) {
+                hp[u * m + l] = pos[u * len + l];
+                hn[u * m + l] = (l + 1 < len) ? l + 1 : -1;
+                ha[u * m + l] = score_sum[u * len + l];
+            }
         e = hipMemcpy2D(c.K, m * rb, K, (size_t)len * rb, (size_t)len * rb, units, hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = hipMemcpy2D(c.V, m * rb, V, (size_t)len * rb, (size_t)len * rb, units, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(c.a, ha.data(), ha.size() * sizeof(double), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(c.pos, hp.data(), hp.size() * 4, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(c.nxt, hn.data(), hn.size() * 4, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemset(c.log_pos, 0xFF, (size_t)c.log_cap * units * 4);
+        if (e == hipSuccess) e = hipMemset(c.log_slot, 0xFF, (size_t)c.log_cap * units * 4);
     }
-    if (e == hipSuccess) e = hipMemcpy(c.a, ha.data(), ha.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c.pos, hp.data(), hp.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c.nxt, hn.data(), hn.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(c.log_pos, 0xFF, (size_t)c.log_cap * units * 4);
-    if (e == hipSuccess) e = hipMemset(c.log_slot, 0xFF, (size_t)c.log_cap * units * 4);
     if (e == hipSuccess && c.tdev) {
         e = wkv_launch_set_clock(c, tokens, nullptr);
         if (e == hipSuccess) e = hipDeviceSynchronize();

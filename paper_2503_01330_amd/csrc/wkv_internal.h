@@ -35,6 +35,9 @@ struct WkvCache {
 // Sets a replayable handle's device-side token index (after a prefill or a load): one tiny kernel.
 hipError_t wkv_launch_set_clock(const WkvCache& c, int64_t tokens, hipStream_t stream);
 
+// Bookkeeping arrays and eviction logs as an empty cache has them (K and V rows stay what they are: none is live).
+hipError_t wkv_launch_clear(const WkvCache& c, hipStream_t stream);
+
 // Launches one decode step for every unit.  t = 0-based index of the incoming
 // token.  threads in {256,512,1024}, with m + 1 <= wkv_step_max_entries(threads).
 // stream_loads: cached K/V rows are loaded non-temporally.  Returns the launch's hipError_t.

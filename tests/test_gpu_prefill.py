@@ -305,3 +305,34 @@ def test_prompts_with_two_tiles_a_wave(dtype, d, P, units):
         print(f"\n  {parity.compare_prefill(cfg, got, decode_steps=3)}", flush=True)
     finally:
         got["cache"].close()
+
+
+@pytest.mark.parametrize("kw", [dict(split=1), dict(split=4), dict(split=1, replayable=1)])
+def test_an_emptied_cache_is_a_fresh_one(kw):
+    """Loading an empty state into a full cache (more log entries than slots, fewer slots than a block of the
+    clearing kernel): the next prompt and the steps after it give what a fresh handle gives, bit for bit,
+    and the eviction log starts afresh."""
+    cfg = synth.StreamConfig("pre-empty", 9000, 1, 3, 64, "fp16", 90, 37, 5)
+    a = parity.gpu_prefill(cfg, 60, **kw)
+    b = parity.gpu_prefill(cfg, 60, **kw)
+    try:
+        tq, tk, tv, out = a["dev"]
+        for t in range(60, 75):
+            a["cache"].step(tq[t], tk[t], tv[t], out[t])
+        U, d = cfg.units, cfg.head_dim
+        rows = np.empty((U, 0, d), np.float16)
+        a["cache"].load(0, rows, rows, np.empty((U, 0), np.float64), np.empty((U, 0), np.int32))
+        assert a["cache"].tokens == 0 and a["cache"].length == 0
+        with pytest.raises(RuntimeError):
+            a["cache"].evictions(1)
+        a["cache"].prefill(tq[:60], tk[:60], tv[:60], out[:60])
+        for c, o in ((a["cache"], out), (b["cache"], b["dev"][3])):
+            for t in range(60, 80):
+                c.step(tq[t], tk[t], tv[t], o[t])
+        torch.cuda.synchronize()
+        assert torch.equal(out[:80], b["dev"][3][:80])
+        for what in (wkv.WKV_POS, wkv.WKV_COUNT, wkv.WKV_NMERGED, wkv.WKV_K, wkv.WKV_V, wkv.WKV_SCORE_SUM):
+            assert np.array_equal(a["cache"].state(what), b["cache"].state(what)), what
+        assert all(np.array_equal(x, y) for x, y in zip(a["cache"].evictions(20), b["cache"].evictions(20)))
+    finally:
+        a["cache"].close(); b["cache"].close()
