@@ -274,25 +274,23 @@ __device__ __forceinline__ bool own_digits(const char* base, int row0, int P, si
     return __any(bad);
 }
 
-// Operands of the rows that a workgroup's waves share, in LDS: CHUNK rows (two tiles, or what the
-// workgroup's threads slice in one round if that is more), double-buffered.
+// Operands of the rows that a workgroup's waves share, in LDS: CHUNK rows (two tiles), double-buffered.
 // A digit plane of 64 elements of 16 rows: block g (elements 16 g .. + 15) holds 16 bytes of each
 // row; blocks are 288 bytes apart, so that the threads that write one row (eight bytes each)
 // do not all fall into the same banks.  (320 bytes, with fewer conflicts, leave room for three
 // workgroups a compute unit where scores' registers allow four: 4.86 against 4.59 ms at 256 x 4096.)
 constexpr int BLOCK = 288, PLANE = 4 * BLOCK;
-template <int D, int NW> constexpr int chunk_tiles() { return (64 * NW) / (D / 8) > 2 * TILE ? (64 * NW) / (D / 8) / TILE : 2; }
-template <int D, int CTILES> struct SharedRows {
-    static constexpr int CHUNK = CTILES * TILE;
-    unsigned char dg[2][CTILES][D / 64][DIGITS][PLANE];
+constexpr int CTILES = 2, CHUNK = CTILES * TILE;
+template <int D> struct SharedRows {
+    alignas(16) unsigned char dg[2][CTILES][D / 64][DIGITS][PLANE];
     double scale[2][CHUNK];
     double lse[2][CHUNK];
     int marked[2][CHUNK];
 };
 
 // One round of a workgroup's NT threads: a thread takes eight elements of a row; D / 8 threads a row.
-template <class TT, int D, int NT, int CTILES> struct ChunkLoad {
-    static constexpr int CHUNK = CTILES * TILE, TPR = D / 8, ROWS = NT / TPR, ROUNDS = CHUNK / ROWS;
+template <class TT, int D, int NT> struct ChunkLoad {
+    static constexpr int TPR = D / 8, ROWS = NT / TPR, ROUNDS = CHUNK / ROWS;
     static_assert(CHUNK % ROWS == 0 && ROUNDS >= 1, "a chunk is a whole number of rounds");
     uint32_t w[ROUNDS][4];
     double lse[ROUNDS];
@@ -305,7 +303,7 @@ template <class TT, int D, int NT, int CTILES> struct ChunkLoad {
             if (lsep != nullptr && j == 0) lse[i] = lsep[row];
         }
     }
-    __device__ __forceinline__ void store(SharedRows<D, CTILES>& sh, int buf, bool with_lse, double unit) const {
+    __device__ __forceinline__ void store(SharedRows<D>& sh, int buf, bool with_lse, double unit) const {
         const int j = threadIdx.x % TPR, r = threadIdx.x / TPR;
 #pragma unroll
         for (int i = 0; i < ROUNDS; ++i) {
@@ -407,32 +405,34 @@ __device__ __forceinline__ void exact_tile(const char* kb, const char* qb, int k
 // this kernel and the next is vector instructions (slicing, recombining the digit sums, the
 // exponentials), so a wave takes two tiles where there is work enough: slicing, value loads and their
 // permutes are then paid once for both.
-template <class TT, int D, int NW, int QT>
+// In small launches SPLIT waves share a tile instead, each taking every SPLIT-th tile of keys.
+template <class TT, int D, int NW, int QT, int SPLIT>
 __global__ __launch_bounds__(64 * NW, 2)
 void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, const void* __restrict__ v_,
                       void* __restrict__ out_, double* __restrict__ lse, int P, int units)
 {
-    constexpr int ROWB = D * TT::BYTES, CTILES = chunk_tiles<D, NW>();
+    constexpr int ROWB = D * TT::BYTES;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int g = lane >> 4, x = lane & 15;
     const int ntiles = (P + TILE - 1) / TILE;
-    const int groups = (ntiles + NW * QT - 1) / (NW * QT);
+    constexpr int TPG = NW / SPLIT * QT;                                         // tiles of a workgroup
+    const int groups = (ntiles + TPG - 1) / TPG;
     const int u = xcd_unit(blockIdx.x, groups);
-    const int qt0 = (groups - 1 - (int)((blockIdx.x >> 3) % groups)) * NW * QT;  // long rows are scheduled first
+    const int qt0 = (groups - 1 - (int)((blockIdx.x >> 3) % groups)) * TPG;      // long rows are scheduled first
     if (u >= units) return;                                                      // the whole workgroup
-    const int qt = qt0 + wid * QT;                                               // first tile of the wave
+    const int qt = qt0 + wid / SPLIT * QT, part = wid % SPLIT;                   // first tile of the wave; its share of the keys
     const bool active = qt < ntiles;                                             // an idle wave still slices keys
     const int mine = min(qt + QT, ntiles) - 1;                                   // its last key tile, and the workgroup's
-    const int last = min(qt0 + NW * QT, ntiles) - 1;
+    const int last = min(qt0 + TPG, ntiles) - 1;
     __shared__ double etab[64];
-    __shared__ SharedRows<D, CTILES> sh;
+    __shared__ SharedRows<D> sh;
     exp_table_init(etab);
     const size_t tok = (size_t)units * ROWB;                              // bytes from one token to the next
     const char* qb = reinterpret_cast<const char*>(q_) + (size_t)u * ROWB;
     const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;
     const char* vb = reinterpret_cast<const char*>(v_) + (size_t)u * ROWB;
 
-    ChunkLoad<TT, D, 64 * NW, CTILES> next;
+    ChunkLoad<TT, D, 64 * NW> next;
     next.request(kb, nullptr, 0, P, tok);
     int4v_t qdg[QT][D / 64][DIGITS];
     double qscale[QT];
@@ -559,8 +559,42 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         const bool more = kt + CTILES <= last;
         if (more) next.request(kb, nullptr, (kt + CTILES) * TILE, P, tok);
         if (active)
-            for (int t = 0; t < CTILES && kt + t <= mine; ++t) tile(kt + t, buf);
+            for (int t = part; t < CTILES && kt + t <= mine; t += SPLIT) tile(kt + t, buf);
         if (more) next.store(sh, buf ^ 1, false, logit_scale<D>());
+    }
+    // The parts of a split row: maxima, sums and accumulators go through LDS (the digits have been used) and are put
+    // together by the first part's wave, in order.  A part that saw no key has maximum -inf and adds nothing.
+    if constexpr (SPLIT > 1) {
+        constexpr int PS = (NW - NW / SPLIT) * 64;                         // lanes that hand something over
+        static_assert(QT == 1 && sizeof(sh.dg) >= PS * (NE * 16 + 16), "the parts fit the digits' place");
+        double* dm = reinterpret_cast<double*>(&sh.dg);                    // [2][PS] maximum, sum
+        float* po = reinterpret_cast<float*>(dm + 2 * PS);                // [NE * 4][PS]
+        const int me = (wid - wid / SPLIT - 1) * 64 + lane;                // of a later part; of the first: one row of lanes before
+        __syncthreads();
+        if (part != 0) {
+            dm[me] = mrow[0];
+            dm[PS + me] = lrow[0];
+#pragma unroll
+            for (int e = 0; e < NE; ++e)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) po[(e * 4 + r) * PS + me] = o[0][e][r];
+        }
+        __syncthreads();
+        if (part != 0 || !active) return;
+        for (int w = 1; w < SPLIT; ++w) {
+            const double m2 = dm[me + w * 64], l2 = dm[PS + me + w * 64];
+            if (__all(l2 == 0.0)) continue;                                // uniform: no key of this part (a NaN goes on)
+            const double mnew = fmax(mrow[0], m2);
+            const double f1 = exp_units(no_infinity(mrow[0] - mnew), etab), f2 = exp_units(no_infinity(m2 - mnew), etab);
+            lrow[0] = lrow[0] * f1 + l2 * f2;
+            mrow[0] = mnew;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float g1 = __shfl((float)f1, 4 * g + r), g2 = __shfl((float)f2, 4 * g + r);
+#pragma unroll
+                for (int e = 0; e < NE; ++e) o[0][e][r] = o[0][e][r] * g1 + po[(e * 4 + r) * PS + me + w * 64] * g2;
+            }
+        }
     }
     if (!active) return;
 
@@ -587,30 +621,31 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
 // ------------------------------------------------------------------ 2. scores
 // a[u][i] = sum over rows t >= i of exp(s_ti - lse_t).  A wave takes KT tiles of keys; NW waves, a workgroup,
 // share the sliced queries.
-template <class TT, int D, int NW, int KT>
+template <class TT, int D, int NW, int KT, int SPLIT>
 __global__ __launch_bounds__(64 * NW, 2)
 void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_, const double* __restrict__ lse,
                         double* __restrict__ a, int P, int units)
 {
-    constexpr int ROWB = D * TT::BYTES, CTILES = chunk_tiles<D, NW>();
+    constexpr int ROWB = D * TT::BYTES;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int g = lane >> 4, x = lane & 15;
     const int ntiles = (P + TILE - 1) / TILE;
-    const int groups = (ntiles + NW * KT - 1) / (NW * KT);
+    constexpr int TPG = NW / SPLIT * KT;                                  // tiles of a workgroup
+    const int groups = (ntiles + TPG - 1) / TPG;
     const int u = xcd_unit(blockIdx.x, groups);
-    const int kt0 = (int)((blockIdx.x >> 3) % groups) * NW * KT;          // low key tiles have the most rows: first
+    const int kt0 = (int)((blockIdx.x >> 3) % groups) * TPG;              // low key tiles have the most rows: first
     if (u >= units) return;                                               // the whole workgroup
-    const int kt = kt0 + wid * KT;
+    const int kt = kt0 + wid / SPLIT * KT, part = wid % SPLIT;
     const bool active = kt < ntiles;
     __shared__ double etab[64];
-    __shared__ SharedRows<D, CTILES> sh;
+    __shared__ SharedRows<D> sh;
     exp_table_init(etab);
     const size_t tok = (size_t)units * ROWB;
     const char* qb = reinterpret_cast<const char*>(q_) + (size_t)u * ROWB;
     const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;
     const double* lseu = lse + (size_t)u * P;
 
-    ChunkLoad<TT, D, 64 * NW, CTILES> next;
+    ChunkLoad<TT, D, 64 * NW> next;
     next.request(qb, lseu, kt0 * TILE, P, tok);
     int4v_t kdg[KT][D / 64][DIGITS];
     double kscale[KT][4], acc[KT][4];
@@ -629,7 +664,8 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
         const bool more = q0 + CTILES < ntiles;
         if (more) next.request(qb, lseu, (q0 + CTILES) * TILE, P, tok);
         if (active)
-            for (int qt = max(q0, kt); qt < min(q0 + CTILES, ntiles); ++qt) {
+            for (int qt = q0 + part; qt < min(q0 + CTILES, ntiles); qt += SPLIT) {
+                if (qt < kt) continue;
                 const int t = qt - q0;
                 const double l = sh.lse[buf][t * TILE + x];
                 double s[KT][4];
@@ -666,6 +702,20 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
                     for (int r = 0; r < 4; ++r) acc[i][r] += exp_units(s[i][r], etab);
             }
         if (more) next.store(sh, buf ^ 1, true, 1.0);
+    }
+    if constexpr (SPLIT > 1) {                                            // the parts' sums, added in order by the first part's wave
+        static_assert(KT == 1, "one tile of keys a wave");
+        double* ps = reinterpret_cast<double*>(&sh.dg);                   // [4][NW * 64]
+        const int me = threadIdx.x;
+        __syncthreads();
+        if (part != 0)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ps[r * NW * 64 + me] = acc[0][r];
+        __syncthreads();
+        if (part != 0) return;
+        for (int w = 1; w < SPLIT; ++w)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[0][r] += ps[r * NW * 64 + me + w * 64];
     }
     if (!active) return;
 #pragma unroll
@@ -1036,10 +1086,15 @@ void wkv_prefill_fold(WkvCache c, const void* __restrict__ k_, const void* __res
     }
 }
 
-// A wave takes two tiles of 16 tokens from 65536 tiles a launch on.  Measured (rows / scores, one tile against two): 256 units
-// x 4096 tokens 7.55 / 4.59 against 6.86 / 4.49 ms; 128 x 2048 (16384 tiles, bf16) 1.26 / 0.80 against 1.32 / 0.97: half as
+// Tiles of 16 tokens of a wave, by the tiles a launch has: two from 65536 on.  Measured (rows / scores, one tile against two): 256
+// units x 4096 tokens 7.55 / 4.59 against 6.86 / 4.49 ms; 128 x 2048 (16384 tiles, bf16) 1.26 / 0.80 against 1.32 / 0.97: half as
 // many workgroups, and the last of them run on an emptying chip; 24 x 1237 106 / 102 against 135 / 148 us.
-inline bool two_tiles(int units, int ntiles) { return (long long)units * ntiles >= 65536; }
+inline int tiles_a_wave(long long tiles) { return tiles >= 65536 ? 2 : 1; }
+// Waves that share a tile's loop: two up to 4096 tiles, where a chip of 1024 vector units has few waves each and the
+// launch lasts as long as its longest loop.  Measured (rows / scores, one wave against two, then four): 24 units x
+// 1237 tokens (1872 tiles) 106 / 102, 90 / 81, 100 / 76 us; 128 x 2048 (16384 tiles) 1.31 / 0.83, 1.47 / 0.97, 1.91 / 1.54 ms:
+// every part slices all the rows it shares with fewer waves.
+inline int waves_a_tile(long long tiles) { return tiles <= 4096 ? 2 : 1; }
 
 template <class TT, int D>
 hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, void* out,
@@ -1047,14 +1102,17 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
 {
     constexpr int NW = 4;
     const int ntiles = (P + TILE - 1) / TILE;
-    auto contract = [&](auto tiles) {
-        constexpr int T = decltype(tiles)::value;
-        const int grid = xcd_grid(c.units, (ntiles + NW * T - 1) / (NW * T));
-        hipLaunchKernelGGL((wkv_prefill_rows<TT, D, NW, T>), dim3(grid), dim3(64 * NW), 0, stream, q, k, v, out, lse, P, c.units);
-        hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NW, T>), dim3(grid), dim3(64 * NW), 0, stream, q, k, lse, a, P, c.units);
+    const long long tiles = (long long)c.units * ntiles;
+    auto contract = [&](auto tiles_c, auto split_c) {
+        constexpr int T = decltype(tiles_c)::value, S = decltype(split_c)::value, TPG = NW / S * T;
+        const int grid = xcd_grid(c.units, (ntiles + TPG - 1) / TPG);
+        hipLaunchKernelGGL((wkv_prefill_rows<TT, D, NW, T, S>), dim3(grid), dim3(64 * NW), 0, stream, q, k, v, out, lse, P, c.units);
+        hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NW, T, S>), dim3(grid), dim3(64 * NW), 0, stream, q, k, lse, a, P, c.units);
     };
-    if (two_tiles(c.units, ntiles)) contract(std::integral_constant<int, 2>{});
-    else contract(std::integral_constant<int, 1>{});
+    using std::integral_constant;
+    if (tiles_a_wave(tiles) == 2) contract(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+    else if (waves_a_tile(tiles) == 2) contract(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+    else contract(integral_constant<int, 1>{}, integral_constant<int, 1>{});
     const size_t lds = wkv_prefill_lds_bytes(P);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wkv_prefill_compress),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

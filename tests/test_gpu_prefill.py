@@ -289,9 +289,11 @@ def test_sort_and_runs_at_their_edges(P, d):
         _run(synth.StreamConfig(f"pre-edge{P}", 8900 + P, 1, 3, d, "bf16", P + 3, m, R), P, decode_steps=3)
 
 
-@pytest.mark.parametrize("dtype,d,P,units", [("fp16", 128, 129, 7290), ("bf16", 64, 1025, 1017)])
-def test_prompts_with_two_tiles_a_wave(dtype, d, P, units):
-    """From 65536 tiles a launch on, a wave takes two tiles of 16 tokens: an odd number of tiles (the last wave
+@pytest.mark.parametrize("dtype,d,P,units", [("fp16", 128, 129, 7290), ("bf16", 64, 1025, 1017), ("fp16", 64, 129, 460),
+                                             ("bf16", 128, 129, 455), ("fp16", 128, 129, 455)])
+def test_prompts_of_many_units(dtype, d, P, units):
+    """Up to 4096 tiles of 16 tokens a launch two waves share a tile (most prompts of these tests), then a wave
+    has one, from 65536 on it takes two: launches on either side.  An odd number of tiles (the last wave
     has one), one row in the last tile, units that are no multiple of eight and a row that takes the fp64
     instruction (one element far above the others).  Five units' inputs, repeated."""
     cfg = synth.StreamConfig("pre-two", 8800 + P, 1, units, d, dtype, P + 4, 100, 9)
