@@ -22,7 +22,7 @@
 //      tile of 16 keys, looping over the query tiles below the diagonal, the same contraction
 //      again (recomputing the logits costs less than storing P^2/2 of them);
 //      sums stay in registers, no atomics, fixed order.
-//   3. wkv_prefill_compress: one workgroup per unit: rank of every candidate by (score, token),
+//   3. wkv_prefill_compress (prompts longer than the budget): one workgroup per unit: rank of every candidate by (score, token),
 //      the P - m lowest are removed; survivors get slots in token order; the weight with which every raw row
 //      enters the survivor on its right, as the sequence of pairwise merges in ascending score order gives it.
 //   4. wkv_prefill_fold: 16 survivors a workgroup: key rows copied, value rows summed with those weights.
@@ -729,7 +729,7 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
 }
 
 // ------------------------------------------------------------------ 3. compress
-// One workgroup per unit.  Scores are fixed during the compression, so the P - L tokens that
+// One workgroup per unit, for prompts longer than the budget.  Scores are fixed during the compression, so the P - L tokens that
 // the repeated selection removes are the candidates of lowest (score, token), in that order.
 //
 // Values.  A removed token j folds into the nearest token on its right that is still present
@@ -770,8 +770,7 @@ void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __re
     uint16_t* par  = rk + P;
     uint16_t* ptr  = par + P;                                 // successor in the list a product runs along
     uint16_t* bmax = ptr + P;                                 // [64] highest rank in a block of 64 tokens
-    const int L = (P < m) ? P : m;
-    const int nrem = P - L;                                   // tokens to remove
+    const int L = m, nrem = P - m;                            // tokens that stay, tokens to remove: P > m
     const int lo = c.n_sink, hi = P - c.R;                    // candidates: lo <= token < hi
 
     for (int i = tid; i < P; i += NT) {
@@ -784,7 +783,7 @@ void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __re
     // rank among the candidates by (score, token); the nrem lowest are removed.  A bitonic sort of
     // (score bits, token) in LDS (the key arrays borrow ae[], a0[] and slot[], not yet in use).
     for (int i = tid; i < P; i += NT) rk[i] = 0xFFFF;
-    if (nrem > 0) {
+    {
         unsigned long long* key = reinterpret_cast<unsigned long long*>(ae);   // [N2]
         uint16_t* kid = reinterpret_cast<uint16_t*>(slot);                     // [N2]
         int N2 = 1;
@@ -826,8 +825,6 @@ void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __re
         __syncthreads();
         for (int r = tid; r < nrem; r += NT) rk[kid[r]] = (uint16_t)r;         // the nrem lowest keys are candidates
         __syncthreads();
-    } else {
-        __syncthreads();
     }
     for (int i = tid; i < P; i += NT) slot[i] = (rk[i] != 0xFFFF) ? -1 : 0;
     __syncthreads();
@@ -852,7 +849,7 @@ void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __re
         const int sidx = slot[i];
         if (sidx >= 0) { au[sidx] = ap[i]; pu[sidx] = i; nu[sidx] = (sidx + 1 < L) ? sidx + 1 : -1; }
     }
-    const bool merging = c.merge_mode == 0 && nrem > 0;
+    const bool merging = c.merge_mode == 0;
     if (merging) {
         // Parent of a removed token: the nearest token to its right that outranks it (survivors
         // outrank everything: rank 0xFFFF); also the nearest one to its LEFT that outranks it.  Both by
@@ -996,14 +993,15 @@ void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __re
 // copied where the run is empty.  The loads are what takes the time (the runs of a unit are its whole
 // prompt), so they go over the chip: 16 bytes a lane, 64 / LPR rows an instruction, four in
 // flight; a run of LONG tokens or more is shared by the workgroup's waves.  Sums in fp64, rounded to
-// the cache format once.  Measured, with the wave-local steps of the sort (compress, then compress + fold):
+// the cache format once.  A prompt that fits the cache has no compress kernel before it: the few words of bookkeeping
+// a token are written here (77 tokens: one launch of 5 us less).  Measured, with the wave-local steps of the sort (compress, then compress + fold):
 // 24 units, 1237 tokens to 333 (d 64): 231 -> 50 + 16 us; 128 units, 2048 to 512 (d 128): 372 -> 59 + 59;
 // 256 units, 4096 to 410: 795 -> 129 + 119.
 constexpr int FOLD_ROWS = 16, FOLD_WAVES = 8, LONG = 64;
 template <class TT, int D>
 __global__ __launch_bounds__(64 * FOLD_WAVES)
 void wkv_prefill_fold(WkvCache c, const void* __restrict__ k_, const void* __restrict__ v_,
-                      const double* __restrict__ weight, int P, int blocks, int merging)
+                      const double* __restrict__ weight, const double* __restrict__ a, int P, int blocks, int merging)
 {
     constexpr int ROWB = D * TT::BYTES, LPR = ROWB / 16, G = 64 / LPR;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -1018,7 +1016,20 @@ void wkv_prefill_fold(WkvCache c, const void* __restrict__ k_, const void* __res
     const double* wu = weight + (size_t)u * P;
     __shared__ int token[FOLD_ROWS + 1];                      // of survivor s0 - 1, s0, ...
     __shared__ double part[FOLD_WAVES][D];
-    if (tid <= here) token[tid] = (s0 + tid > 0) ? pu[s0 + tid - 1] : -1;
+    if (P <= c.m) {                                           // uniform: nothing is removed, no compress kernel ran
+        if (tid <= here) token[tid] = s0 + tid - 1;
+        if (tid < here) {
+            const int i = s0 + tid;
+            const size_t at = (size_t)u * c.m + i;
+            const double ai = a[(size_t)u * P + i], s = (c.score_mode == 0) ? ai / (double)(P - i) : ai;
+            if (!(s == s) || s == INFINITY) atomicAdd(&c.status[1], 1);
+            c.a[at] = ai;
+            c.pos[at] = i;
+            c.nxt[at] = (i + 1 < P) ? i + 1 : -1;
+        }
+    } else if (tid <= here) {
+        token[tid] = (s0 + tid > 0) ? pu[s0 + tid - 1] : -1;
+    }
     __syncthreads();
     for (int i = tid; i < here * LPR; i += 64 * FOLD_WAVES) {
         uint32_t w[4];
@@ -1113,15 +1124,17 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
     if (tiles_a_wave(tiles) == 2) contract(integral_constant<int, 2>{}, integral_constant<int, 1>{});
     else if (waves_a_tile(tiles) == 2) contract(integral_constant<int, 1>{}, integral_constant<int, 2>{});
     else contract(integral_constant<int, 1>{}, integral_constant<int, 1>{});
-    const size_t lds = wkv_prefill_lds_bytes(P);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wkv_prefill_compress),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    // the row log-sum-exps have been used: their place takes the weights of the tokens
-    hipLaunchKernelGGL(wkv_prefill_compress, dim3(c.units), dim3(1024), lds, stream, c, a, lse, P);
+    if (P > c.m) {
+        const size_t lds = wkv_prefill_lds_bytes(P);
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wkv_prefill_compress),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        // the row log-sum-exps have been used: their place takes the weights of the tokens
+        hipLaunchKernelGGL(wkv_prefill_compress, dim3(c.units), dim3(1024), lds, stream, c, a, lse, P);
+    }
     const int blocks = ((P < c.m ? P : c.m) + FOLD_ROWS - 1) / FOLD_ROWS;
     const int merging = c.merge_mode == 0 && P > c.m;
-    hipLaunchKernelGGL((wkv_prefill_fold<TT, D>), dim3((unsigned)c.units * blocks), dim3(64 * FOLD_WAVES), 0, stream, c, k, v, lse, P, blocks, merging);
+    hipLaunchKernelGGL((wkv_prefill_fold<TT, D>), dim3((unsigned)c.units * blocks), dim3(64 * FOLD_WAVES), 0, stream, c, k, v, lse, a, P, blocks, merging);
     return hipGetLastError();
 }
 
