@@ -37,8 +37,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0            # MI355X published HBM3E bandwidth
 LAST_LEVEL_CACHE = 256 << 20     # MI355X memory-side cache
-FP64_MFMA_TFLOPS = 78.6          # MI355X published dense peaks
-HALF_MFMA_TFLOPS = 2500.0
+HALF_MFMA_TFLOPS = 2500.0        # MI355X published dense peaks
+INT8_MFMA_TOPS = 5000.0
 
 
 def parse():
@@ -322,29 +322,29 @@ def main():
             times.append(e0.elapsed_time(e1))
             c.close()
         ms = statistics.median(times[1:])
-        # The method's two contractions over the causal half, 2 flops per multiply-add: q.K^T (contracted in
-        # fp64 here, for the score path's precision) and P.V (16-bit MFMA).  Algorithmic time = each once, at
-        # its own dtype's peak.  What the kernels execute is more: q.K^T twice (rows, then column sums) and P.V
-        # with the weights split into 2 (fp16) or 3 (bf16) 16-bit parts.
+        # The method's two contractions over the causal half, 2 flops per multiply-add: q.K^T and P.V, both of
+        # 16-bit numbers.  Algorithmic time = each once at the 16-bit peak.  What the kernels execute is more: q.K^T
+        # twice (rows, then column sums), each as sixteen products of 8-bit digits (exact, for the score
+        # path's precision), and P.V with the weights split into 2 (fp16) or 3 (bf16) 16-bit parts.
         half = 1.0 * cfg.units * P * (P + 1) * cfg.head_dim          # flops of one contraction
-        algo_ms = (half / (FP64_MFMA_TFLOPS * 1e12) + half / (HALF_MFMA_TFLOPS * 1e12)) * 1e3
+        algo_ms = 2 * half / (HALF_MFMA_TFLOPS * 1e12) * 1e3
         parts = 2 if cfg.dtype == "fp16" else 3
-        exec_ms = (2 * half / (FP64_MFMA_TFLOPS * 1e12) + parts * half / (HALF_MFMA_TFLOPS * 1e12)) * 1e3
+        exec_ms = (2 * 16 * half / (INT8_MFMA_TOPS * 1e12) + parts * half / (HALF_MFMA_TFLOPS * 1e12)) * 1e3
         result["prefill"] = {
             "config": {"workload": f"{args.workload}: one layer, prompt of {P} tokens into an empty cache, "
                                    f"batch {cfg.batch} x {cfg.heads} heads x {cfg.head_dim} {cfg.dtype}, budget {cfg.budget}"},
             "value": round(cfg.batch * P / (ms * 1e-3), 1), "unit": "prompt tokens/s per layer", "ms": round(ms, 3),
-            "roofline": {"bound": "mfma", "achieved": round(2 * half / (ms * 1e-3) / 1e12, 2), "peak": FP64_MFMA_TFLOPS,
+            "roofline": {"bound": "mfma", "achieved": round(2 * half / (ms * 1e-3) / 1e12, 2), "peak": HALF_MFMA_TFLOPS,
                          "unit": "TFLOP/s", "frac": round(algo_ms / ms, 4), "traffic": None,
-                         "kernel": "wkv_prefill_rows + wkv_prefill_scores + wkv_prefill_compress (one wkv_prefill call)",
+                         "kernel": "wkv_prefill_rows + _scores + _compress + _fold (one wkv_prefill call)",
                          "flops_per_contraction": half,
                          "algorithmic_ms": round(algo_ms, 3), "executed_flops_ms_at_peak": round(exec_ms, 3),
                          "frac_of_executed": round(exec_ms / ms, 4),
-                         "note": "frac = algorithmic time / measured time, where algorithmic time prices q.K^T once at the "
-                                 "fp64 MFMA peak (78.6 TFLOP/s) and P.V once at the 16-bit MFMA peak (2500 TFLOP/s); "
-                                 "`achieved` is both contractions' flops over the whole call.  The kernels execute q.K^T "
-                                 "twice (rows, then column sums: recomputed rather than stored) and P.V in 2-3 16-bit "
-                                 "parts: frac_of_executed prices those flops instead"},
+                         "note": "frac = algorithmic time / measured time, where algorithmic time prices q.K^T and P.V once "
+                                 "each at the 16-bit MFMA peak (2500 TFLOP/s); `achieved` is both contractions' flops over "
+                                 "the whole call.  The kernels execute q.K^T twice (rows, then column sums: recomputed "
+                                 "rather than stored), each as 16 products of 8-bit digits (5000 TOP/s), and P.V in 2-3 "
+                                 "16-bit parts: frac_of_executed prices those instead"},
         }
         del tq, tk, tv, out
         torch.cuda.empty_cache()
