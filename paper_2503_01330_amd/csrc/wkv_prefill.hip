@@ -1001,11 +1001,11 @@ constexpr int FOLD_ROWS = 16, FOLD_WAVES = 8, LONG = 64;
 template <class TT, int D>
 __global__ __launch_bounds__(64 * FOLD_WAVES)
 void wkv_prefill_fold(WkvCache c, const void* __restrict__ k_, const void* __restrict__ v_,
-                      const double* __restrict__ weight, const double* __restrict__ a, int P, int blocks, int merging)
+                      const double* __restrict__ weight, const double* __restrict__ a, int P, int unit0, int blocks, int merging)
 {
     constexpr int ROWB = D * TT::BYTES, LPR = ROWB / 16, G = 64 / LPR;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int u = blockIdx.x / blocks, s0 = (blockIdx.x % blocks) * FOLD_ROWS;
+    const int u = unit0 + blockIdx.x / blocks, s0 = (blockIdx.x % blocks) * FOLD_ROWS;
     const int L = min(P, c.m), here = min(FOLD_ROWS, L - s0);
     const size_t tok = (size_t)c.units * ROWB;
     const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;
@@ -1134,7 +1134,13 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
     }
     const int blocks = ((P < c.m ? P : c.m) + FOLD_ROWS - 1) / FOLD_ROWS;
     const int merging = c.merge_mode == 0 && P > c.m;
-    hipLaunchKernelGGL((wkv_prefill_fold<TT, D>), dim3((unsigned)c.units * blocks), dim3(64 * FOLD_WAVES), 0, stream, c, k, v, lse, a, P, blocks, merging);
+    // units x blocks workgroups may come to 2^32 threads and more, which a launch does not hold: the count wraps, without an
+    // error (2796203 units x 33 survivors: one workgroup ran).  One launch for every 2^22 workgroups.
+    const int most = (1 << 22) / blocks;                      // units of a launch; blocks <= 256
+    for (int u0 = 0; u0 < c.units; u0 += most) {
+        const int n = c.units - u0 < most ? c.units - u0 : most;
+        hipLaunchKernelGGL((wkv_prefill_fold<TT, D>), dim3(n * blocks), dim3(64 * FOLD_WAVES), 0, stream, c, k, v, lse, a, P, u0, blocks, merging);
+    }
     return hipGetLastError();
 }
 

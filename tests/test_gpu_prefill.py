@@ -338,3 +338,33 @@ def test_an_emptied_cache_is_a_fresh_one(kw):
         assert all(np.array_equal(x, y) for x, y in zip(a["cache"].evictions(20), b["cache"].evictions(20)))
     finally:
         a["cache"].close(); b["cache"].close()
+
+
+def test_more_survivors_than_a_launch_has_threads_for():
+    """2796203 units x 33 survivors are 2^23 + 1 workgroups of 512 threads in the kernel that moves the rows: 2^32 + 512
+    threads, of which one launch would run the last 512.  Five units' inputs, repeated: the step after the prompt gives every unit what the same unit gets
+    in a small handle of the same launch form, bit for bit."""
+    P, m, R, d = 35, 33, 3, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9100)
+    base = torch.randn(P + 1, 5, d, generator=gen, device="cuda").half()
+
+    def next_out(units):
+        x = base[:, torch.arange(units, device="cuda") % 5].contiguous().view(P + 1, units, 1, d)
+        cache = wkv.Cache(units, 1, d, m, R, wkv.WKV_FP16, split=1, threads=256, streaming=wkv.WKV_LOADS_CACHED, log_capacity=1)
+        try:
+            out = torch.empty_like(x[P])
+            cache.prefill(x[:P], x[:P], x[:P], None)
+            cache.step(x[P], x[P], x[P], out)
+            torch.cuda.synchronize()
+            return out.view(units, d)
+        finally:
+            cache.close()
+
+    try:
+        few, many = next_out(30000), next_out(2796203)
+        assert torch.equal(few, few[:5].repeat(6000, 1))
+        assert torch.equal(many[:2796200].view(-1, 5, d), few[:5].expand(559240, 5, d))
+        assert torch.equal(many[2796200:], few[:3])
+    finally:
+        torch.cuda.empty_cache()
