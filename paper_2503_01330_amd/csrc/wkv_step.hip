@@ -890,18 +890,24 @@ __global__ void wkv_clear_kernel(WkvCache c) {
 }
 }  // namespace
 
+// Both report what their own launch returned: hipGetLastError would also give an error that an earlier call of the program
+// has left behind, and wkv_load would fail for it.
 hipError_t wkv_launch_clear(const WkvCache& c, hipStream_t stream)
 {
     const size_t n = (size_t)c.units * (size_t)(c.m > c.log_cap ? c.m : c.log_cap);
     const size_t blocks = (n + 255) / 256;
-    hipLaunchKernelGGL(wkv_clear_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, stream, c);
-    return hipGetLastError();
+    WkvCache cache = c;
+    void* args[] = { &cache };
+    return hipLaunchKernel(reinterpret_cast<const void*>(&wkv_clear_kernel), dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256),
+                           args, 0, stream);
 }
 
 hipError_t wkv_launch_set_clock(const WkvCache& c, int64_t tokens, hipStream_t stream)
 {
-    hipLaunchKernelGGL(wkv_set_clock_kernel, dim3(1), dim3(1), 0, stream, c, (long long)tokens);
-    return hipGetLastError();
+    WkvCache cache = c;
+    long long t = tokens;
+    void* args[] = { &cache, &t };
+    return hipLaunchKernel(reinterpret_cast<const void*>(&wkv_set_clock_kernel), dim3(1), dim3(1), args, 0, stream);
 }
 
 hipError_t wkv_step_prepare(int dtype, int head_dim, size_t lds)

@@ -368,3 +368,18 @@ def test_more_survivors_than_a_launch_has_threads_for():
         assert torch.equal(many[2796200:], few[:3])
     finally:
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("replayable", [0, 1])
+def test_emptying_a_cache_after_a_failed_call_of_the_caller(replayable):
+    """An error that a HIP call of the program has left behind (a device that does not exist) is not this call's: emptying
+    the cache works."""
+    cache = wkv.Cache(1, 3, 64, 37, 5, wkv.WKV_FP16, replayable=replayable)
+    rows = np.empty((3, 0, 64), np.float16)
+    try:
+        assert wkv._lib.hipSetDevice(1 << 20) != 0
+        cache.load(0, rows, rows, np.empty((3, 0), np.float64), np.empty((3, 0), np.int32))
+        assert cache.tokens == 0
+    finally:
+        wkv._lib.hipGetLastError()
+        cache.close()
