@@ -51,7 +51,7 @@ typedef short    short4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t uint2_t  __attribute__((ext_vector_type(2)));
 
 constexpr int TILE = 16;
-constexpr int WKV_PREFILL_MAX_TOKENS = 4096;   // prompt length the compression stages in LDS (WKV_MAX_PROMPT)
+constexpr int WKV_PREFILL_MAX_TOKENS = WKV_MAX_PROMPT;   // prompt length the compression stages in LDS
 
 // element e of a row fragment held as raw 32-bit words (two 16-bit elements per word)
 template <class TT> __device__ __forceinline__ float frag_elem(const uint32_t* w, int e) {
@@ -1125,10 +1125,12 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
     else if (waves_a_tile(tiles) == 2) contract(integral_constant<int, 1>{}, integral_constant<int, 2>{});
     else contract(integral_constant<int, 1>{}, integral_constant<int, 1>{});
     if (P > c.m) {
-        const size_t lds = wkv_prefill_lds_bytes(P);
+        // The kernel's limit is one for all threads of the process and all prompts: always the longest prompt's, so that no
+        // call lowers it between another one's setting and its launch.
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wkv_prefill_compress),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)wkv_prefill_lds_bytes(WKV_PREFILL_MAX_TOKENS));
         if (e != hipSuccess) return e;
+        const size_t lds = wkv_prefill_lds_bytes(P);
         // the row log-sum-exps have been used: their place takes the weights of the tokens
         hipLaunchKernelGGL(wkv_prefill_compress, dim3(c.units), dim3(1024), lds, stream, c, a, lse, P);
     }

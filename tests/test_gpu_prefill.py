@@ -383,3 +383,47 @@ def test_emptying_a_cache_after_a_failed_call_of_the_caller(replayable):
     finally:
         wkv._lib.hipGetLastError()
         cache.close()
+
+
+def test_two_threads_with_prompts_of_their_own_lengths():
+    """Handles are used from a thread each: what one prompt's launches need (workgroup memory by its length) must not be
+    taken back by another's.  A short and a long prompt, 40 times from two threads at once, each on its own stream."""
+    import threading
+    prompts = []
+    for P, seed in ((120, 1), (4096, 2)):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(seed)
+        q, k, v = (torch.randn(P, 4, 1, 64, generator=gen, device="cuda").half() for _ in range(3))
+        cache = wkv.Cache(4, 1, 64, 40, 4, wkv.WKV_FP16, max_prompt=P)
+        want = torch.empty_like(q)
+        cache.prefill(q, k, v, want)
+        torch.cuda.synchronize()
+        prompts.append((cache, q, k, v, want, cache.state(wkv.WKV_POS), cache.state(wkv.WKV_V)))
+    rows = np.empty((4, 0, 64), np.float16)
+    empty = (rows, rows, np.empty((4, 0), np.float64), np.empty((4, 0), np.int32))
+    failed = []
+
+    def work(cache, q, k, v, want, pos, vals):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                out = torch.empty_like(q)
+                for _ in range(40):
+                    cache.load(0, *empty)
+                    cache.prefill(q, k, v, out)
+                    stream.synchronize()
+                    assert torch.equal(out, want) and np.array_equal(cache.state(wkv.WKV_POS), pos)
+                    assert np.array_equal(cache.state(wkv.WKV_V), vals)
+        except BaseException as e:                      # (an assertion in a thread does not reach pytest by itself)
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=p) for p in prompts]
+    try:
+        for th in threads:
+            th.start()
+        for th in threads:
+            th.join()
+        assert not failed, failed
+    finally:
+        for p in prompts:
+            p[0].close()
