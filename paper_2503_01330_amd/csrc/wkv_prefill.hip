@@ -137,27 +137,29 @@ __device__ __forceinline__ void exp_table_init(double* tab) {
 }
 // ------------------------------------------------------------------ logits from 8-bit digits
 // A row of 16-bit numbers is, up to a power of two, a row of integers: n = x * 2^s with the row's own s,
-// chosen so that its largest magnitude has N = 27 (fp16) or 30 (bf16) bits.  n is written in four balanced base-256
-// digits (d0..d2 in [-128, 127], |d3| <= 8 or 64), and q.k becomes sixteen dot products of digits,
+// chosen so that its largest magnitude has 30 bits.  n is written in four balanced base-256
+// digits (d0..d2 in [-128, 127], |d3| <= 64), and q.k becomes sixteen dot products of digits,
 // which v_mfma_i32_16x16x64_i8 forms without any rounding: seven sums S_w over the pairs of weight
 // w = i + j, then A = S0 + 2^8 S1, B = S2 + 2^8 S3, C = S4 + 2^8 S5 + 2^16 S6, and
-// q.k = (A + 2^16 B + 2^32 C) 2^-(s_q + s_k) with the rounding of two or three fp64 additions: closer to the
+// q.k = (A + 2^16 B + 2^32 C) 2^-(s_q + s_k) with the rounding of two fp64 additions: closer to the
 // exact logit than a chain of D fp64 additions.  For 128 elements A and B stay below 2^31 (S1 <= 2^22,
-// S3 <= 2^22 + 2^21), and C too for 27 bits (S6 <= 2^13); for 30 bits S6 <= 2^19 joins in fp64.
+// S3 <= 2^22 + 2^21), and so does S4 + 2^8 S5 (S5 <= 2^21); S6 <= 2^19 joins in fp64, exactly.
 // Why: the fp64 matrix instruction takes 64 cycles for 16x16x4 on this part and shares its pipe
 // with the fp64 vector instructions of the softmax; the sixteen digit products take 512 cycles per
 // 16x16x128 tile against 2048, and run beside them.
 // Measured (256 units, 4096 tokens, d 128, fp16): rows 13.1 -> 8.0 ms, scores 10.5 -> 5.6 ms; with the int8
 // instructions a third of the time, vector instructions bound both: slicing by packed maxima, no clamp in the
 // exponential, two tiles a wave brought 6.9 and 4.5 ms.
-// A row whose elements are not all integers at its scale (an element more than 2^-26 below the
-// largest that uses its last bits; possible for bf16, and for fp16 rows that reach 8) or that holds
+// A row whose elements are not all integers at its scale (an element more than 2^-22 below the
+// largest that uses its last bits; possible for bf16, and for fp16 rows that reach 64) or that holds
 // an infinity or a NaN is marked, and a tile that touches a marked row takes the fp64 instruction.
 constexpr int DIGITS = 4;
-// fp16 has no bit below 2^-24: with 27 bits every row below 8 fits.  bf16 reaches further down; with 27 bits 0.6 % of
-// 16 x 128 tiles of normal numbers hold an element too small, with 30 bits 0.08 % do.  A wave whose own rows
-// are marked is several times slower for its whole loop, which a launch of few workgroups waits for.
-template <class TT> constexpr int int_bits() { return __is_same(TT, TF16) ? 27 : 30; }
+// Bits of a row's integers.  A wave whose own rows are marked is slow for its whole loop, and its workgroup waits for it, so
+// what counts is how many 16 x 128 tiles hold an element too small.  Of normal numbers, 27 | 30 bits: bf16 0.6 % | 0.08 %; fp16
+// none, but with one channel at 20, as keys with rotary embeddings have them, 22 % | none (no fp16 element has a bit below 2^-24:
+// every row below 8 | 64 fits).  Measured, that channel in a prompt of 256 units x 4096 (d 128, fp16): 22.6 | 11.5 ms.  S6 in fp64 instead of
+// int32 costs nothing that shows (11.4 ms without the channel, either way).
+constexpr int INT_BITS = 30;
 
 typedef int int4v_t __attribute__((ext_vector_type(4)));
 
@@ -197,13 +199,13 @@ template <class TT> struct RowSpan {
     __device__ __forceinline__ uint32_t smallest_exponent() const { return (min((uint32_t)mn.x, (uint32_t)mn.y) + 1u) >> 7; }
 };
 
-// Scale 2^s of a row whose largest |x| has the 16 bits `top`: the largest integer gets int_bits bits.
+// Scale 2^s of a row whose largest |x| has the 16 bits `top`: the largest integer gets INT_BITS bits.
 // bad: the row must not be sliced.  e: biased fp32 exponent of the largest element.
 template <class TT> __device__ __forceinline__ int digit_shift(uint32_t top, int& e, bool& bad) {
     const uint32_t one[1] = { top };
     e = (int)(__builtin_bit_cast(uint32_t, frag_elem<TT>(one, 0)) >> 23);
     bad = e == 255 || (e < 36 && top != 0u);
-    return (top == 0u || bad) ? 0 : int_bits<TT>() - 1 + 127 - e;
+    return (top == 0u || bad) ? 0 : INT_BITS - 1 + 127 - e;
 }
 // Whether this lane's elements are no integers at that scale.  fp16 has no bit below 2^-24, so a row that
 // stays below 8 (s >= 24) fits; beyond, the elements are looked at.  bf16: 8 significant bits,
@@ -211,12 +213,12 @@ template <class TT> __device__ __forceinline__ int digit_shift(uint32_t top, int
 template <class TT, int NWORDS> __device__ __forceinline__ bool no_integers(const uint32_t (&w)[NWORDS], const RowSpan<TT>& span, int e, float mul) {
     if constexpr (__is_same(TT, TF16)) {
         float frac = 0.f;
-        if (__any(e > 129))
+        if (__any(e > 132))
 #pragma unroll
             for (int i = 0; i < 2 * NWORDS; ++i) frac = fmaxf(frac, __builtin_amdgcn_fractf(frag_elem<TT>(w, i) * mul));
         return frac != 0.f;
     } else {
-        return (int)span.smallest_exponent() + int_bits<TT>() - 8 < e;
+        return (int)span.smallest_exponent() + INT_BITS - 8 < e;
     }
 }
 
@@ -368,9 +370,7 @@ __device__ __forceinline__ void digit_tile(const unsigned char (&pl)[D / 64][DIG
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int A = S[0][r] + (S[1][r] << 8), B = S[2][r] + (S[3][r] << 8);
-        double C;
-        if constexpr (int_bits<TT>() <= 27) C = (double)(S[4][r] + (S[5][r] << 8) + (S[6][r] << 16));
-        else C = fma((double)S[6][r], 65536.0, (double)(S[4][r] + (S[5][r] << 8)));
+        const double C = fma((double)S[6][r], 65536.0, (double)(S[4][r] + (S[5][r] << 8)));
         s[r] = fma(fma(C, 65536.0, (double)B), 65536.0, (double)A);
     }
 }

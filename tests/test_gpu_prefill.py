@@ -251,7 +251,7 @@ def test_llama_shaped_prompt_sampled_units():
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("where", ["queries", "keys", "one row"])
 def test_rows_that_span_more_than_the_digits(dtype, d, where):
-    """Logits are formed from 8-bit digits of rows brought to integers below 2^27; a row with elements
+    """Logits are formed from 8-bit digits of rows brought to integers below 2^30; a row with elements
     that are no integers at its scale must take the fp64 instruction.  Such a row here: one large
     element (times zero on the other side) and small ones below the last digit, which meet large
     elements, so that dropping what does not fit would move a logit by more than 1e-5 (score sums are held to
@@ -261,7 +261,7 @@ def test_rows_that_span_more_than_the_digits(dtype, d, where):
     cfg = synth.StreamConfig("pre-span", 8700, 1, U, d, dtype, P + 12, m, R)
     g = np.random.default_rng(8700)
     q, k, v = (g.standard_normal((cfg.steps, U, d)).astype(np.float32) for _ in range(3))
-    big, tiny = (60.0, 2.0 ** -13) if dtype == "fp16" else (2.0 ** 10, 2.0 ** -18)
+    big, tiny = (2.0 ** 11, 2.0 ** -13) if dtype == "fp16" else (2.0 ** 10, 2.0 ** -18)
     rows = [97] if where == "one row" else [0, 1, 15, 16, 40, 63, 64, 100, 127, 129]
     side, other = (q, k) if where == "queries" else (k, q)
     side[rows] *= tiny
@@ -300,7 +300,7 @@ def test_prompts_of_many_units(dtype, d, P, units):
     few = synth.Stream(synth.StreamConfig("pre-two", 8800 + P, 1, 5, d, dtype, P + 4, 100, 9))
     q, k, v = (synth.storage_to_f32(x, dtype).copy() for x in few.steps(0, cfg.steps))
     k[37, :, 1:] *= 2.0 ** -12 if dtype == "fp16" else 2.0 ** -26
-    k[37, :, 0] = 9.0
+    k[37, :, 0] = 128.0 if dtype == "fp16" else 9.0
     arrays = [x[:, np.arange(units) % 5] for x in (q, k, v)]
     got = parity.gpu_prefill(cfg, P, units_sel=[0, 1, 3, units // 2, units - 1], arrays=arrays)
     try:
@@ -427,3 +427,39 @@ def test_two_threads_with_prompts_of_their_own_lengths():
     finally:
         for p in prompts:
             p[0].close()
+
+
+@pytest.mark.parametrize("what,limit", [("one channel", 1.25)])
+def test_uneven_keys_take_no_longer(what, limit):
+    """The time of a prompt may depend on its data only so far: keys with one large channel (20 beside normal numbers), which
+    8-bit digits still hold, against keys without.  256 units x 2048 tokens, the fastest of six."""
+    P, U, d, m = 2048, 256, 128, 256
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9300)
+    q, k, v = (torch.randn(P, U, 1, d, generator=gen, device="cuda") for _ in range(3))
+    uneven_q, uneven_k = q.clone(), k.clone()
+    uneven_k[..., 5] += 20.0
+    uneven_q[..., 5] *= 0.05
+    cache = wkv.Cache(U, 1, d, m, 9, wkv.WKV_FP16, max_prompt=P, log_capacity=1)
+    rows = np.empty((U, 0, d), np.float16)
+    empty = (rows, rows, np.empty((U, 0), np.float64), np.empty((U, 0), np.int32))
+
+    def fastest(q, k):
+        q, k, w = q.half(), k.half(), v.half()
+        out, best = torch.empty_like(q), float("inf")
+        for _ in range(6):
+            cache.load(0, *empty)
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            cache.prefill(q, k, w, out)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    try:
+        even, uneven = fastest(q, k), fastest(uneven_q, uneven_k)
+    finally:
+        cache.close()
+    print(f"\n  {what}: {uneven:.2f} ms against {even:.2f}", flush=True)
+    assert uneven <= limit * even
