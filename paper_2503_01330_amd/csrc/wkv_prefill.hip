@@ -375,30 +375,205 @@ __device__ __forceinline__ void digit_tile(const unsigned char (&pl)[D / 64][DIG
     }
 }
 
-// The same tile, scaled, with the fp64 matrix instruction, for tiles that touch a marked row.  Its result
-// register r of lane (g, x) is row g + 4r: row i is given key 4 (i % 4) + i / 4, so that the layout is digit_tile's.
-template <class TT, int D>
-__device__ __forceinline__ void exact_tile(const char* kb, const char* qb, int key0, int q0, int P, size_t tok, int g, int x, double (&s)[4])
+// Tiles that touch a marked row, scaled, with the fp64 matrix instruction: one tile of shared rows against N of the wave's own.  Its
+// result register r of lane (g, x) is row g + 4r: row i is given key 4 (i % 4) + i / 4, so that the layout is digit_tile's.
+// All words are requested ahead of the first product: these tiles wait for memory, not for the instruction (256 units x 4096,
+// d 128, fp16, every key marked, two requests a tile against one: 34.3 against 30.9 ms).
+template <class TT, int D, bool SHARED_KEYS, int N>
+__device__ __forceinline__ void exact_tiles(const char* shared, const char* own, int shared0, int own0, int P, size_t tok, int g, int x, double (&s)[N][4])
 {
-    const char* kr = kb + (size_t)min(key0 + 4 * (x & 3) + (x >> 2), P - 1) * tok + g * (D / 4) * TT::BYTES;
-    const char* qr = qb + (size_t)min(q0 + x, P - 1) * tok + g * (D / 4) * TT::BYTES;
-    double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-    for (int e0 = 0; e0 < D / 4; e0 += 16) {
-        uint32_t kw[8], qw[8];
-        load_words<8>(kr + e0 * TT::BYTES, kw);
-        load_words<8>(qr + e0 * TT::BYTES, qw);
+    constexpr int NWORDS = D / 8;
+    constexpr int CHAINS = N == 1 ? 2 : 1;       // a product that continues the chain of the one before it waits for that one's result
+    const int kx = 4 * (x & 3) + (x >> 2), col = g * (D / 4) * TT::BYTES;
+    uint32_t sw[NWORDS], ow[N][NWORDS];
+    load_words<NWORDS>(shared + (size_t)min(shared0 + (SHARED_KEYS ? kx : x), P - 1) * tok + col, sw);
 #pragma unroll
-        for (int e = 0; e < 16; e += 2) {
-            s0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)frag_elem<TT>(kw, e), (double)frag_elem<TT>(qw, e), s0, 0, 0, 0);
-            s1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)frag_elem<TT>(kw, e + 1), (double)frag_elem<TT>(qw, e + 1), s1, 0, 0, 0);
+    for (int i = 0; i < N; ++i)
+        load_words<NWORDS>(own + (size_t)min(own0 + i * TILE + (SHARED_KEYS ? x : kx), P - 1) * tok + col, ow[i]);
+    double4_t acc[N][CHAINS];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int c = 0; c < CHAINS; ++c) acc[i][c] = double4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < 2 * NWORDS; ++e) {
+        const double sd = (double)frag_elem<TT>(sw, e);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const double od = (double)frag_elem<TT>(ow[i], e);
+            acc[i][e % CHAINS] = SHARED_KEYS ? __builtin_amdgcn_mfma_f64_16x16x4f64(sd, od, acc[i][e % CHAINS], 0, 0, 0)
+                                             : __builtin_amdgcn_mfma_f64_16x16x4f64(od, sd, acc[i][e % CHAINS], 0, 0, 0);
         }
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) s[r] = (s0[r] + s1[r]) * logit_scale<D>();
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[i][r] = (CHAINS == 1 ? acc[i][0][r] : acc[i][0][r] + acc[i][CHAINS - 1][r]) * logit_scale<D>();
+}
+
+// Whether a workgroup takes the fp64 instruction for all it does: every wave's own rows are marked, or both tiles of the first
+// shared chunk are.  (Uniform over the workgroup; the chunk is visible afterwards.)  Tile by tile, with the digits made beside it and
+// nothing requested ahead, a prompt of marked rows only is slower than the fp64 instruction alone was before there were digits; in
+// loops of its own it is not.  Rows + scores, every key marked, tile by tile | in loops of its own | before: 256 units x 4096, d 128,
+// fp16 16.4 + 14.1 | 13.7 + 10.8 | 13.0 + 10.5 ms; 128 x 2048 2.51 + 2.07 | 1.85 + 2.07 | 1.85 + 1.48 ms.
+// Without marked rows the test costs nothing that shows (11.32 | 11.39 ms, 1.916 | 1.919 ms for the whole prompts).
+__device__ __forceinline__ bool mostly_marked(bool own, const int (&marked)[CHUNK]) {
+    static_assert(CHUNK == 32, "two tiles of 16 rows");
+    const bool all = __syncthreads_and(own);
+    const unsigned long long m = __ballot(marked[threadIdx.x & (CHUNK - 1)]);
+    return all || ((m & 0xFFFFu) != 0 && (m & 0xFFFF0000u) != 0);
 }
 
 // ------------------------------------------------------------------ 1. rows
+// Softmax and output accumulators of N consecutive tiles of 16 queries.
+template <class TT, int D, int N> struct Rows {
+    static constexpr int NE = D / 16;         // output column sets: lane (g, x) owns columns NE*x .. NE*x+NE-1
+    double m[N], l[N];                        // running maximum of query x (same in the 4 lanes x, x+16, ...); this lane's share of the sum
+    float4_t o[N][NE];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            m[i] = -INFINITY;
+            l[i] = 0.0;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) o[i][e] = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    // Sixteen more keys.  s: their logits, register r of lane (g, x) = key 4g + r, query x; vfrag: columns NE*x .. of the values of
+    // keys 4g + r.  infinities: whether a logit may be -inf (uniform).
+    __device__ __forceinline__ void add(double (&s)[N][4], const uint32_t (&vfrag)[4][NE / 2], bool infinities, const double* etab, int g) {
+        // A running maximum that has not moved needs no rescaling, and after the first few key
+        // tiles of a row it rarely moves: the maximum over the four lane groups and the rescaling (an exp,
+        // the running sum and all output accumulators of the wave) are skipped unless some query needs them.
+        double tmax[N];
+        bool moved = false;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            tmax[i] = fmax(fmax(s[i][0], s[i][1]), fmax(s[i][2], s[i][3]));
+            moved |= tmax[i] > m[i];
+        }
+        if (__any(moved)) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const double top = pair_max<32>(pair_max<16>(tmax[i]));        // all 16 keys of the tile
+                const double mnew = fmax(m[i], top);          // finite: key 16 kt + 0 <= every query of a later tile,
+                                                              // and on the diagonal key x is attended by query x
+                const double resc = exp_units(no_infinity(m[i] - mnew), etab);  // 0 on the first tile (m = -inf), 1 where nothing moved
+                l[i] *= resc;
+                m[i] = mnew;
+                const float rf = (float)resc;                 // the output rows this lane holds (queries 4g + r') by their own factor
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float f = __shfl(rf, 4 * g + r);
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) o[i][e][r] *= f;
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s[i][r] -= m[i];
+        if (infinities) {
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s[i][r] = no_infinity(s[i][r]);
+        }
+        // O[query][column] += sum over keys P[query][key] V[key][column] with the 16-bit matrix
+        // instruction (k = 16 keys at once): lane (g, x) supplies k-slots 4g + r: as A operand
+        // P[query x][key 4g + r], as B operand V[key 4g + r][column NE*x + e], the raw cache values.
+        // P goes in as a sum of 16-bit parts.
+        uint2_t pa[N][weight_parts<TT>()];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            float p[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { const double e = exp_units(s[i][r], etab); l[i] += e; p[r] = (float)e; }
+            split16x4<TT>(p, pa[i]);
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;      // high / low halves of two words
+            const uint2_t vb2 = { __builtin_amdgcn_perm(vfrag[1][e >> 1], vfrag[0][e >> 1], sel),
+                                  __builtin_amdgcn_perm(vfrag[3][e >> 1], vfrag[2][e >> 1], sel) };
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+#pragma unroll
+                for (int w = 0; w < weight_parts<TT>(); ++w) o[i][e] = mfma16<TT>(pa[i][w], vb2, o[i][e]);
+        }
+    }
+    // o_t = O / l and the log-sum-exp m + log l of the queries from q0 on
+    __device__ __forceinline__ void finish(int q0, int P, char* out, size_t tok, double* lse, int g, int x) const {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const double sum = rows_sum(l[i]);
+            const float linv = (float)(1.0 / sum);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int t = q0 + i * TILE + 4 * g + r;
+                const float f = __shfl(linv, 4 * g + r);
+                if (t < P && out != nullptr) {
+                    char* dst = out + (size_t)t * tok + x * NE * TT::BYTES;
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) store_elem<TT>(dst, e, o[i][e][r] * f);
+                }
+            }
+            const int tq = q0 + i * TILE + x;
+            if (g == 0 && tq < P) lse[tq] = m[i] + log(sum) * LOGIT_UNIT;
+        }
+    }
+};
+
+// The tile of queries qt against all its keys with the fp64 matrix instruction, for workgroups of marked rows: the queries stay in
+// fp64, the next tile's keys and values are requested before this one's are used (two sets of registers take turns).
+template <class TT, int D>
+__device__ __forceinline__ void exact_rows(const char* qb, const char* kb, const char* vb, char* ob, double* lse, int qt, int P, size_t tok,
+                                           const double* etab, int g, int x)
+{
+    constexpr int NWORDS = D / 8, NE = D / 16;
+    const int kx = 4 * (x & 3) + (x >> 2), col = g * (D / 4) * TT::BYTES;     // keys: see exact_tiles
+    double qd[2 * NWORDS];
+    {
+        uint32_t w[NWORDS];
+        load_words<NWORDS>(qb + (size_t)min(qt * TILE + x, P - 1) * tok + col, w);
+#pragma unroll
+        for (int e = 0; e < 2 * NWORDS; ++e) qd[e] = (double)frag_elem<TT>(w, e);
+    }
+    Rows<TT, D, 1> rows;
+    rows.clear();
+    auto request = [&](int kt, uint32_t (&kf)[NWORDS], uint32_t (&vf)[4][NE / 2]) __attribute__((always_inline)) {
+        load_words<NWORDS>(kb + (size_t)min(kt * TILE + kx, P - 1) * tok + col, kf);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) load_words<NE / 2>(vb + (size_t)min(kt * TILE + 4 * g + r, P - 1) * tok + x * NE * TT::BYTES, vf[r]);
+    };
+    auto tile = [&](int kt, const uint32_t (&kf)[NWORDS], const uint32_t (&vf)[4][NE / 2]) __attribute__((always_inline)) {
+        double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < 2 * NWORDS; e += 2) {
+            s0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)frag_elem<TT>(kf, e), qd[e], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)frag_elem<TT>(kf, e + 1), qd[e + 1], s1, 0, 0, 0);
+        }
+        double s[1][4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            s[0][r] = (s0[r] + s1[r]) * logit_scale<D>();
+            if (kt == qt && 4 * g + r > x) s[0][r] = -INFINITY;
+        }
+        rows.add(s, vf, true, etab, g);
+    };
+    uint32_t kf0[NWORDS], vf0[4][NE / 2], kf1[NWORDS], vf1[4][NE / 2];
+    request(0, kf0, vf0);
+    for (int kt = 0; kt <= qt; kt += 2) {
+        request(min(kt + 1, qt), kf1, vf1);                   // past the last tile: a repeat, unused
+        tile(kt, kf0, vf0);
+        if (kt + 1 > qt) break;
+        request(min(kt + 2, qt), kf0, vf0);
+        tile(kt + 1, kf1, vf1);
+    }
+    rows.finish(qt * TILE, P, ob, tok, lse, g, x);
+}
+
 // q, k, v, out: [P][units][D] (token-major, as a decode step sees them one token at a time).
 // lse: [units][P], in units of ln 2 / 64.  One workgroup = NW waves of QT consecutive query tiles of one unit;
 // the keys are sliced into digits once per workgroup and read by every wave from LDS.  What bounds
@@ -431,6 +606,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
     const char* qb = reinterpret_cast<const char*>(q_) + (size_t)u * ROWB;
     const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;
     const char* vb = reinterpret_cast<const char*>(v_) + (size_t)u * ROWB;
+    char* ob = out_ == nullptr ? nullptr : reinterpret_cast<char*>(out_) + (size_t)u * ROWB;
 
     ChunkLoad<TT, D, 64 * NW> next;
     next.request(kb, nullptr, 0, P, tok);
@@ -441,18 +617,17 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
     for (int i = 0; i < QT; ++i) qmarked |= own_digits<TT, D>(qb, (qt + i) * TILE, P, tok, g, x, qdg[i], qscale[i], 1.0);
     next.store(sh, 0, false, logit_scale<D>());
 
-    // running maximum of query x (same in the 4 lanes x, x+16, ...); this lane's share of the sum
-    double mrow[QT], lrow[QT];
-    constexpr int NE = D / 16;                // output column sets: lane (g, x) owns columns NE*x .. NE*x+NE-1
-    float4_t o[QT][NE];
-#pragma unroll
-    for (int i = 0; i < QT; ++i) {
-        mrow[i] = -INFINITY;
-        lrow[i] = 0.0;
-#pragma unroll
-        for (int e = 0; e < NE; ++e) o[i][e] = float4_t{0.f, 0.f, 0.f, 0.f};
+    if constexpr (SPLIT == 1) {
+        if (mostly_marked(qmarked || !active, sh.marked[0])) {
+            if (active)
+#pragma unroll 1
+                for (int t = qt; t <= mine; ++t) exact_rows<TT, D>(qb, kb, vb, ob, lse + (size_t)u * P, t, P, tok, etab, g, x);
+            return;
+        }
     }
-
+    Rows<TT, D, QT> rows;
+    rows.clear();
+    constexpr int NE = rows.NE;
     size_t voff[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) voff[r] = (size_t)(4 * g + r) * tok + x * NE * TT::BYTES;
@@ -473,8 +648,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         double s[QT][4];
         const bool special = __any(sh.marked[buf][t * TILE + x]) || qmarked;       // uniform
         if (special) {
-#pragma unroll
-            for (int i = 0; i < QT; ++i) exact_tile<TT, D>(kb, qb, kt * TILE, (qt + i) * TILE, P, tok, g, x, s[i]);
+            exact_tiles<TT, D, true, QT>(kb, qb, kt * TILE, qt * TILE, P, tok, g, x, s);
         } else {
 #pragma unroll
             for (int i = 0; i < QT; ++i) {
@@ -491,66 +665,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) if ((kt - qt - i) * TILE + 4 * g + r > x) s[i][r] = -INFINITY;
         }
-        // A running maximum that has not moved needs no rescaling, and after the first few key
-        // tiles of a row it rarely moves: the maximum over the four lane groups and the rescaling (an exp,
-        // the running sum and all output accumulators of the wave) are skipped unless some query needs them.
-        double tmax[QT];
-        bool moved = false;
-#pragma unroll
-        for (int i = 0; i < QT; ++i) {
-            tmax[i] = fmax(fmax(s[i][0], s[i][1]), fmax(s[i][2], s[i][3]));
-            moved |= tmax[i] > mrow[i];
-        }
-        if (__any(moved)) {
-#pragma unroll
-            for (int i = 0; i < QT; ++i) {
-                const double top = pair_max<32>(pair_max<16>(tmax[i]));        // all 16 keys of the tile
-                const double mnew = fmax(mrow[i], top);       // finite: key 16 kt + 0 <= every query of a later tile,
-                                                              // and on the diagonal key x is attended by query x
-                const double resc = exp_units(no_infinity(mrow[i] - mnew), etab);  // 0 on the first tile (mrow = -inf), 1 where nothing moved
-                lrow[i] *= resc;
-                mrow[i] = mnew;
-                const float rf = (float)resc;                 // the output rows this lane holds (queries 4g + r') by their own factor
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float f = __shfl(rf, 4 * g + r);
-#pragma unroll
-                    for (int e = 0; e < NE; ++e) o[i][e][r] *= f;
-                }
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < QT; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) s[i][r] -= mrow[i];
-        if (special || edge) {
-#pragma unroll
-            for (int i = 0; i < QT; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) s[i][r] = no_infinity(s[i][r]);
-        }
-        // O[query][column] += sum over keys P[query][key] V[key][column] with the 16-bit matrix
-        // instruction (k = 16 keys at once): lane (g, x) supplies k-slots 4g + r: as A operand
-        // P[query x][key 4g + r], as B operand V[key 4g + r][column NE*x + e], the raw cache values.
-        // P goes in as a sum of 16-bit parts.
-        uint2_t pa[QT][weight_parts<TT>()];
-#pragma unroll
-        for (int i = 0; i < QT; ++i) {
-            float p[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) { const double e = exp_units(s[i][r], etab); lrow[i] += e; p[r] = (float)e; }
-            split16x4<TT>(p, pa[i]);
-        }
-#pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;      // high / low halves of two words
-            const uint2_t vb2 = { __builtin_amdgcn_perm(vfrag[1][e >> 1], vfrag[0][e >> 1], sel),
-                                  __builtin_amdgcn_perm(vfrag[3][e >> 1], vfrag[2][e >> 1], sel) };
-#pragma unroll
-            for (int i = 0; i < QT; ++i)
-#pragma unroll
-                for (int w = 0; w < weight_parts<TT>(); ++w) o[i][e] = mfma16<TT>(pa[i][w], vb2, o[i][e]);
-        }
+        rows.add(s, vfrag, special || edge, etab, g);
     };
     // A chunk is worked on from one buffer while the next one is on its way from memory; it is sliced into
     // the other buffer at the end of the round, which every wave left before the barrier at its start.
@@ -572,53 +687,84 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         const int me = (wid - wid / SPLIT - 1) * 64 + lane;                // of a later part; of the first: one row of lanes before
         __syncthreads();
         if (part != 0) {
-            dm[me] = mrow[0];
-            dm[PS + me] = lrow[0];
+            dm[me] = rows.m[0];
+            dm[PS + me] = rows.l[0];
 #pragma unroll
             for (int e = 0; e < NE; ++e)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) po[(e * 4 + r) * PS + me] = o[0][e][r];
+                for (int r = 0; r < 4; ++r) po[(e * 4 + r) * PS + me] = rows.o[0][e][r];
         }
         __syncthreads();
         if (part != 0 || !active) return;
         for (int w = 1; w < SPLIT; ++w) {
             const double m2 = dm[me + w * 64], l2 = dm[PS + me + w * 64];
             if (__all(l2 == 0.0)) continue;                                // uniform: no key of this part (a NaN goes on)
-            const double mnew = fmax(mrow[0], m2);
-            const double f1 = exp_units(no_infinity(mrow[0] - mnew), etab), f2 = exp_units(no_infinity(m2 - mnew), etab);
-            lrow[0] = lrow[0] * f1 + l2 * f2;
-            mrow[0] = mnew;
+            const double mnew = fmax(rows.m[0], m2);
+            const double f1 = exp_units(no_infinity(rows.m[0] - mnew), etab), f2 = exp_units(no_infinity(m2 - mnew), etab);
+            rows.l[0] = rows.l[0] * f1 + l2 * f2;
+            rows.m[0] = mnew;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float g1 = __shfl((float)f1, 4 * g + r), g2 = __shfl((float)f2, 4 * g + r);
 #pragma unroll
-                for (int e = 0; e < NE; ++e) o[0][e][r] = o[0][e][r] * g1 + po[(e * 4 + r) * PS + me + w * 64] * g2;
+                for (int e = 0; e < NE; ++e) rows.o[0][e][r] = rows.o[0][e][r] * g1 + po[(e * 4 + r) * PS + me + w * 64] * g2;
             }
         }
     }
     if (!active) return;
 
-    // o_t = O / l, log-sum-exp = m + log l
-#pragma unroll
-    for (int i = 0; i < QT; ++i) {
-        const double l = rows_sum(lrow[i]);
-        const float linv = (float)(1.0 / l);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int t = (qt + i) * TILE + 4 * g + r;
-            const float f = __shfl(linv, 4 * g + r);
-            if (t < P && out_ != nullptr) {
-                char* dst = reinterpret_cast<char*>(out_) + (size_t)t * tok + (size_t)u * ROWB + x * NE * TT::BYTES;
-#pragma unroll
-                for (int e = 0; e < NE; ++e) store_elem<TT>(dst, e, o[i][e][r] * f);
-            }
-        }
-        const int tq = (qt + i) * TILE + x;
-        if (g == 0 && tq < P) lse[(size_t)u * P + tq] = mrow[i] + log(l) * LOGIT_UNIT;
-    }
+    rows.finish(qt * TILE, P, ob, tok, lse + (size_t)u * P, g, x);
 }
 
 // ------------------------------------------------------------------ 2. scores
+// The tile of keys kt against all its queries with the fp64 matrix instruction, for workgroups of marked rows: the keys stay in fp64, the
+// next tile of queries is requested before this one is used.  Only for two tiles a wave and d 128, where a SIMD holds two waves
+// anyway: the registers this takes (206) cost the other forms one or two of their three or four (128 units x 2048: scores 0.67 -> 0.72 ms
+// without a marked row, held to 128 registers 0.75).
+template <class TT, int D>
+__device__ __forceinline__ void exact_scores(const char* qb, const char* kb, const double* lse, double* a, int kt, int ntiles, int P, size_t tok,
+                                             const double* etab, int g, int x)
+{
+    constexpr int NWORDS = D / 8;
+    const int kx = 4 * (x & 3) + (x >> 2), col = g * (D / 4) * TT::BYTES;     // keys: see exact_tiles
+    uint32_t next[NWORDS];
+    double kd[2 * NWORDS], next_l, acc[4] = {0.0, 0.0, 0.0, 0.0};
+    load_words<NWORDS>(kb + (size_t)min(kt * TILE + kx, P - 1) * tok + col, next);
+#pragma unroll
+    for (int e = 0; e < 2 * NWORDS; ++e) kd[e] = (double)frag_elem<TT>(next, e);
+    auto request = [&](int qt) __attribute__((always_inline)) {
+        const int t = min(min(qt, ntiles - 1) * TILE + x, P - 1);          // past the last tile: a repeat, unused
+        load_words<NWORDS>(qb + (size_t)t * tok + col, next);
+        next_l = lse[t];
+    };
+    request(kt);
+    for (int qt = kt; qt < ntiles; ++qt) {
+        uint32_t w[NWORDS];
+#pragma unroll
+        for (int i = 0; i < NWORDS; ++i) w[i] = next[i];
+        const double l = next_l;
+        request(qt + 1);
+        double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < 2 * NWORDS; e += 2) {
+            s0 = __builtin_amdgcn_mfma_f64_16x16x4f64(kd[e], (double)frag_elem<TT>(w, e), s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f64_16x16x4f64(kd[e + 1], (double)frag_elem<TT>(w, e + 1), s1, 0, 0, 0);
+        }
+        const int tq = qt * TILE + x;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool on = tq < P && kt * TILE + 4 * g + r <= tq;         // causal, and inside the prompt
+            acc[r] += exp_units(no_infinity(on ? (s0[r] + s1[r]) * logit_scale<D>() - l : -INFINITY), etab);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const double c = row_allsum(acc[r]);                               // over the 16 queries x
+        const int key = kt * TILE + 4 * g + r;
+        if (x == 0 && key < P) a[key] = c;
+    }
+}
+
 // a[u][i] = sum over rows t >= i of exp(s_ti - lse_t).  A wave takes KT tiles of keys; NW waves, a workgroup,
 // share the sliced queries.
 template <class TT, int D, int NW, int KT, int SPLIT>
@@ -659,6 +805,15 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     }
     next.store(sh, 0, true, 1.0);
 
+    if constexpr (D == 128 && KT == 2) {
+        if (mostly_marked(kmarked || !active, sh.marked[0])) {
+            if (active)
+#pragma unroll 1
+                for (int t = kt; t < min(kt + KT, ntiles); ++t)
+                    exact_scores<TT, D>(qb, kb, lseu, a + (size_t)u * P, t, ntiles, P, tok, etab, g, x);
+            return;
+        }
+    }
     for (int q0 = kt0, buf = 0; q0 < ntiles; q0 += CTILES, buf ^= 1) {
         __syncthreads();
         const bool more = q0 + CTILES < ntiles;
@@ -671,8 +826,7 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
                 double s[KT][4];
                 const bool special = __any(sh.marked[buf][t * TILE + x]) || kmarked;   // uniform
                 if (special) {
-#pragma unroll
-                    for (int i = 0; i < KT; ++i) exact_tile<TT, D>(kb, qb, (kt + i) * TILE, qt * TILE, P, tok, g, x, s[i]);
+                    exact_tiles<TT, D, false, KT>(qb, kb, qt * TILE, kt * TILE, P, tok, g, x, s);
                 } else {
                     const double qs = sh.scale[buf][t * TILE + x];
 #pragma unroll

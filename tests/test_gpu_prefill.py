@@ -429,17 +429,23 @@ def test_two_threads_with_prompts_of_their_own_lengths():
             p[0].close()
 
 
-@pytest.mark.parametrize("what,limit", [("one channel", 1.25)])
-def test_uneven_keys_take_no_longer(what, limit):
-    """The time of a prompt may depend on its data only so far: keys with one large channel (20 beside normal numbers), which
-    8-bit digits still hold, against keys without.  256 units x 2048 tokens, the fastest of six."""
-    P, U, d, m = 2048, 256, 128, 256
+@pytest.mark.parametrize("what,limit", [("one channel", 1.25), ("every row", 2.6)])
+def test_time_with_uneven_keys(what, limit):
+    """The time of a prompt may depend on its data only so far, against keys of normal numbers: with one large channel (20), which
+    8-bit digits still hold, a quarter more; with an element beyond the digits in every key, which leaves the fp64
+    instruction for everything, 2.6 times as long (that instruction alone takes 2.15).  256 units x 4096 tokens, the fastest of six."""
+    P, U, d, m = 4096, 256, 128, 256
     gen = torch.Generator(device="cuda")
     gen.manual_seed(9300)
     q, k, v = (torch.randn(P, U, 1, d, generator=gen, device="cuda") for _ in range(3))
     uneven_q, uneven_k = q.clone(), k.clone()
-    uneven_k[..., 5] += 20.0
-    uneven_q[..., 5] *= 0.05
+    if what == "one channel":
+        uneven_k[..., 5] += 20.0
+        uneven_q[..., 5] *= 0.05
+    else:
+        uneven_k[..., 5] = 100.0
+        uneven_k[..., 6] = 2.0 ** -24
+        uneven_q[..., 5] = 0.0
     cache = wkv.Cache(U, 1, d, m, 9, wkv.WKV_FP16, max_prompt=P, log_capacity=1)
     rows = np.empty((U, 0, d), np.float16)
     empty = (rows, rows, np.empty((U, 0), np.float64), np.empty((U, 0), np.int32))
@@ -463,3 +469,51 @@ def test_uneven_keys_take_no_longer(what, limit):
         cache.close()
     print(f"\n  {what}: {uneven:.2f} ms against {even:.2f}", flush=True)
     assert uneven <= limit * even
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("units", [455, 460, 7290])
+def test_marked_rows_in_every_launch_form(units, d, dtype):
+    """The three launch forms (two waves a tile up to 4096 tiles, one, two tiles a wave from 65536 on) at nine tiles a unit, so that the
+    last wave has half a share; units that differ in the rows the digits do not hold: none, one key, a query in the first and
+    in the second tile of a pair, both at once, every key, every query (which take the fp64 instruction for whole workgroups), all
+    rows, and every key of the first 32 only.  What the digits would drop meets large elements and differs from row to row:
+    dropped, it would move score sums by 8e-9 and more (as plain float64 on the CPU says), which are held to 1e-9."""
+    P, T = 129, 133
+    g = np.random.default_rng(9400 + units)
+    q, k, v = (g.standard_normal((T, 9, d)).astype(np.float32) for _ in range(3))
+    q[..., 1] *= 8.0
+    k[..., 1] *= 8.0
+    everything = slice(0, T)
+
+    def mark(x, rows, unit, big):
+        n = x[rows, unit, 1].shape
+        x[rows, unit, big] = 2.0 ** 11                      # the digits end at 2^-18
+        x[rows, unit, 1] = 2.0 ** -20 * (1 + 2 * g.integers(0, 4, n))
+
+    for unit, keys, queries in ((1, 37, None), (2, None, 5), (3, None, 21), (4, 37, 21), (5, everything, None), (6, None, everything),
+                                (7, everything, everything), (8, slice(0, 32), None)):
+        if keys is not None:
+            q[:, unit, 0] = 0.0
+        if queries is not None:
+            k[:, unit, 2] = 0.0
+        if keys is not None:
+            mark(k, keys, unit, 0)
+        if queries is not None:
+            mark(q, queries, unit, 2)
+    cfg = synth.StreamConfig("pre-marked", 9400, 1, units, d, dtype, T, 100, 9)
+    sel = np.concatenate([np.arange(9), np.arange(units - 9, units)])
+    host = [synth.to_storage(x, dtype) for x in (q, k, v)]
+    dev = [parity.to_device(x, dtype)[:, torch.arange(units, device="cuda") % 9].contiguous() for x in host]
+    out = torch.zeros_like(dev[0])
+    cache = wkv.Cache(1, units, d, 100, 9, synth.DTYPE_CODE[dtype], split=1)
+    try:
+        cache.prefill(*(x[:P] for x in dev), out[:P])
+        torch.cuda.synchronize()
+        q, k, v = (synth.storage_to_f32(x, dtype)[:, sel % 9] for x in host)
+        got = dict(out=parity.out_to_f64(out[:P][:, torch.from_numpy(sel).cuda()], dtype), cache=cache, q=q, k=k, v=v, sel=sel,
+                   dev=(*dev, out), P=P)
+        print(f"\n  {parity.compare_prefill(cfg, got, decode_steps=3)}", flush=True)
+    finally:
+        cache.close()
