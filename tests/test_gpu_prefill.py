@@ -517,3 +517,31 @@ def test_marked_rows_in_every_launch_form(units, d, dtype):
         print(f"\n  {parity.compare_prefill(cfg, got, decode_steps=3)}", flush=True)
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("units", [3, 460, 7290])
+def test_an_infinite_value_stays_out_of_the_tiles_before_it(units, dtype, d):
+    """A row attends to no newer token: an infinity in the value of token 19 (the second tile of 16, also the second one of
+    a wave that takes two) leaves the rows of the tile before it what they are without it, bit for bit, in each of the
+    three launch forms."""
+    P, t = 129, torch.float16 if dtype == "fp16" else torch.bfloat16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9200)
+    base = torch.randn(3, P, 5, d, generator=gen, device="cuda").to(t)
+    q, k, v = (x[:, torch.arange(units, device="cuda") % 5].contiguous().view(P, units, 1, d) for x in base)
+    outs = []
+    for _ in range(2):
+        cache = wkv.Cache(units, 1, d, 100, 9, synth.DTYPE_CODE[dtype], log_capacity=1)
+        try:
+            outs.append(torch.empty_like(q))
+            cache.prefill(q, k, v, outs[-1])
+            torch.cuda.synchronize()
+        finally:
+            cache.close()
+        v[19, :, 0, 7] = float("inf")
+    clean, with_inf = outs
+    assert torch.equal(clean[:16], with_inf[:16])
+    assert not torch.isfinite(with_inf[19:, :, 0, 7]).any()     # (infinite, or NaN where a part of the weight is 0)
+    assert torch.isfinite(clean.float()).all()
