@@ -379,7 +379,7 @@ __device__ __forceinline__ void digit_tile(const unsigned char (&pl)[D / 64][DIG
 // result register r of lane (g, x) is row g + 4r: row i is given key 4 (i % 4) + i / 4, so that the layout is digit_tile's.
 // All words are requested ahead of the first product: these tiles wait for memory, not for the instruction (256 units x 4096,
 // d 128, fp16, every key marked, two requests a tile against one: 34.3 against 30.9 ms).
-template <class TT, int D, bool SHARED_KEYS, int N, int FIRST = 0>
+template <class TT, int D, bool SHARED_KEYS, int N>
 __device__ __forceinline__ void exact_tiles(const char* shared, const char* own, int shared0, int own0, int P, size_t tok, int g, int x, double (&s)[N][4])
 {
     constexpr int NWORDS = D / 8;
@@ -388,25 +388,25 @@ __device__ __forceinline__ void exact_tiles(const char* shared, const char* own,
     uint32_t sw[NWORDS], ow[N][NWORDS];
     load_words<NWORDS>(shared + (size_t)min(shared0 + (SHARED_KEYS ? kx : x), P - 1) * tok + col, sw);
 #pragma unroll
-    for (int i = FIRST; i < N; ++i)
+    for (int i = 0; i < N; ++i)
         load_words<NWORDS>(own + (size_t)min(own0 + i * TILE + (SHARED_KEYS ? x : kx), P - 1) * tok + col, ow[i]);
     double4_t acc[N][CHAINS];
 #pragma unroll
-    for (int i = FIRST; i < N; ++i)
+    for (int i = 0; i < N; ++i)
 #pragma unroll
         for (int c = 0; c < CHAINS; ++c) acc[i][c] = double4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int e = 0; e < 2 * NWORDS; ++e) {
         const double sd = (double)frag_elem<TT>(sw, e);
 #pragma unroll
-        for (int i = FIRST; i < N; ++i) {
+        for (int i = 0; i < N; ++i) {
             const double od = (double)frag_elem<TT>(ow[i], e);
             acc[i][e % CHAINS] = SHARED_KEYS ? __builtin_amdgcn_mfma_f64_16x16x4f64(sd, od, acc[i][e % CHAINS], 0, 0, 0)
                                              : __builtin_amdgcn_mfma_f64_16x16x4f64(od, sd, acc[i][e % CHAINS], 0, 0, 0);
         }
     }
 #pragma unroll
-    for (int i = FIRST; i < N; ++i)
+    for (int i = 0; i < N; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) s[i][r] = (CHAINS == 1 ? acc[i][0][r] : acc[i][0][r] + acc[i][CHAINS - 1][r]) * logit_scale<D>();
 }
@@ -439,23 +439,22 @@ template <class TT, int D, int N> struct Rows {
             for (int e = 0; e < NE; ++e) o[i][e] = float4_t{0.f, 0.f, 0.f, 0.f};
         }
     }
-    // Sixteen more keys for the tiles from FIRST on.  s: their logits, register r of lane (g, x) = key 4g + r, query x; vfrag: columns NE*x .. of the values of
-    // keys 4g + r.  infinities: whether a logit may be -inf (uniform).
-    template <int FIRST = 0>
-    __device__ __forceinline__ void add(double (&s)[N][4], const uint32_t (&vfrag)[4][NE / 2], bool infinities, const double* etab, int g) {
+    // Sixteen more keys.  s: their logits, register r of lane (g, x) = key 4g + r, query x; vfrag: columns NE*x .. of the values of
+    // keys 4g + r.  infinities: whether a logit may be -inf (uniform).  lone: see below.
+    __device__ __forceinline__ void add(double (&s)[N][4], const uint32_t (&vfrag)[4][NE / 2], bool infinities, bool lone, const double* etab, int g) {
         // A running maximum that has not moved needs no rescaling, and after the first few key
         // tiles of a row it rarely moves: the maximum over the four lane groups and the rescaling (an exp,
         // the running sum and all output accumulators of the wave) are skipped unless some query needs them.
         double tmax[N];
         bool moved = false;
 #pragma unroll
-        for (int i = FIRST; i < N; ++i) {
+        for (int i = 0; i < N; ++i) {
             tmax[i] = fmax(fmax(s[i][0], s[i][1]), fmax(s[i][2], s[i][3]));
             moved |= tmax[i] > m[i];
         }
         if (__any(moved)) {
 #pragma unroll
-            for (int i = FIRST; i < N; ++i) {
+            for (int i = 0; i < N; ++i) {
                 const double top = pair_max<32>(pair_max<16>(tmax[i]));        // all 16 keys of the tile
                 const double mnew = fmax(m[i], top);          // finite: key 16 kt + 0 <= every query of a later tile,
                                                               // and on the diagonal key x is attended by query x
@@ -472,12 +471,12 @@ template <class TT, int D, int N> struct Rows {
             }
         }
 #pragma unroll
-        for (int i = FIRST; i < N; ++i)
+        for (int i = 0; i < N; ++i)
 #pragma unroll
             for (int r = 0; r < 4; ++r) s[i][r] -= m[i];
         if (infinities) {
 #pragma unroll
-            for (int i = FIRST; i < N; ++i)
+            for (int i = 0; i < N; ++i)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s[i][r] = no_infinity(s[i][r]);
         }
@@ -487,22 +486,28 @@ template <class TT, int D, int N> struct Rows {
         // P goes in as a sum of 16-bit parts.
         uint2_t pa[N][weight_parts<TT>()];
 #pragma unroll
-        for (int i = FIRST; i < N; ++i) {
+        for (int i = 0; i < N; ++i) {
             float p[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) { const double e = exp_units(s[i][r], etab); l[i] += e; p[r] = (float)e; }
             split16x4<TT>(p, pa[i]);
         }
+        // lone (uniform over the wave): the keys are the last tile's of several, newer than every query of the others, which leave
+        // the product out: their weights are 0, but 0 times an infinity among the values is NaN.
+        auto values = [&](auto first) __attribute__((always_inline)) {
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;      // high / low halves of two words
-            const uint2_t vb2 = { __builtin_amdgcn_perm(vfrag[1][e >> 1], vfrag[0][e >> 1], sel),
-                                  __builtin_amdgcn_perm(vfrag[3][e >> 1], vfrag[2][e >> 1], sel) };
+            for (int e = 0; e < NE; ++e) {
+                const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;      // high / low halves of two words
+                const uint2_t vb2 = { __builtin_amdgcn_perm(vfrag[1][e >> 1], vfrag[0][e >> 1], sel),
+                                      __builtin_amdgcn_perm(vfrag[3][e >> 1], vfrag[2][e >> 1], sel) };
 #pragma unroll
-            for (int i = FIRST; i < N; ++i)
+                for (int i = decltype(first)::value; i < N; ++i)
 #pragma unroll
-                for (int w = 0; w < weight_parts<TT>(); ++w) o[i][e] = mfma16<TT>(pa[i][w], vb2, o[i][e]);
-        }
+                    for (int w = 0; w < weight_parts<TT>(); ++w) o[i][e] = mfma16<TT>(pa[i][w], vb2, o[i][e]);
+            }
+        };
+        if (lone) values(std::integral_constant<int, N - 1>{});
+        else values(std::integral_constant<int, 0>{});
     }
     // o_t = O / l and the log-sum-exp m + log l of the queries from q0 on
     __device__ __forceinline__ void finish(int q0, int P, char* out, size_t tok, double* lse, int g, int x) const {
@@ -561,7 +566,7 @@ __device__ __forceinline__ void exact_rows(const char* qb, const char* kb, const
             s[0][r] = (s0[r] + s1[r]) * logit_scale<D>();
             if (kt == qt && 4 * g + r > x) s[0][r] = -INFINITY;
         }
-        rows.add(s, vf, true, etab, g);
+        rows.add(s, vf, true, false, etab, g);
     };
     uint32_t kf0[NWORDS], vf0[4][NE / 2], kf1[NWORDS], vf1[4][NE / 2];
     request(0, kf0, vf0);
@@ -632,10 +637,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
     size_t voff[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) voff[r] = (size_t)(4 * g + r) * tok + x * NE * TT::BYTES;
-    // Key tile kt for the wave's tiles from FIRST on.  (The first of two has no business with the keys of the second, all of which are
-    // newer: their weights would be 0, but 0 times an infinity among their values is NaN.)
-    auto tile = [&](auto first, int kt, int buf) __attribute__((always_inline)) {
-        constexpr int FIRST = decltype(first)::value;
+    auto tile = [&](int kt, int buf) __attribute__((always_inline)) {
         // V fragments: keys 16 kt + 4g + r, columns NE*x .. NE*x+NE-1; requested here, used after the softmax
         // (a lane's offsets in a tile never change; only a tile that reaches past the prompt clamps its rows)
         uint32_t vfrag[4][NE / 2];
@@ -652,10 +654,10 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         double s[QT][4];
         const bool special = __any(sh.marked[buf][t * TILE + x]) || qmarked;       // uniform
         if (special) {
-            exact_tiles<TT, D, true, QT, FIRST>(kb, qb, kt * TILE, qt * TILE, P, tok, g, x, s);
+            exact_tiles<TT, D, true, QT>(kb, qb, kt * TILE, qt * TILE, P, tok, g, x, s);
         } else {
 #pragma unroll
-            for (int i = FIRST; i < QT; ++i) {
+            for (int i = 0; i < QT; ++i) {
                 if (QT * D > 128) __builtin_amdgcn_sched_barrier(0);       // one tile's sums at a time: the registers do not hold two
                 digit_tile<TT, D, true>(sh.dg[buf][t], qdg[i], g, x, s[i]);
 #pragma unroll
@@ -665,11 +667,11 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         const bool edge = kt >= qt;           // a diagonal tile: key 4g + r may be attended by query x only if not newer
         if (edge) {
 #pragma unroll
-            for (int i = FIRST; i < QT; ++i)
+            for (int i = 0; i < QT; ++i)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) if ((kt - qt - i) * TILE + 4 * g + r > x) s[i][r] = -INFINITY;
         }
-        rows.template add<FIRST>(s, vfrag, special || edge, etab, g);
+        rows.add(s, vfrag, special || edge, QT > 1 && kt > qt, etab, g);
     };
     // A chunk is worked on from one buffer while the next one is on its way from memory; it is sliced into
     // the other buffer at the end of the round, which every wave left before the barrier at its start.
@@ -678,10 +680,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         const bool more = kt + CTILES <= last;
         if (more) next.request(kb, nullptr, (kt + CTILES) * TILE, P, tok);
         if (active)
-            for (int t = part; t < CTILES && kt + t <= mine; t += SPLIT) {
-                if (QT == 1 || kt + t <= qt) tile(std::integral_constant<int, 0>{}, kt + t, buf);
-                else tile(std::integral_constant<int, QT - 1>{}, kt + t, buf);
-            }
+            for (int t = part; t < CTILES && kt + t <= mine; t += SPLIT) tile(kt + t, buf);
         if (more) next.store(sh, buf ^ 1, false, logit_scale<D>());
     }
     // The parts of a split row: maxima, sums and accumulators go through LDS (the digits have been used) and are put
