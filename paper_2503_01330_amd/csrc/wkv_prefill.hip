@@ -123,14 +123,14 @@ template <class TT> __device__ __forceinline__ float4_t mfma16(uint2_t a, uint2_
         return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4_t, a), __builtin_bit_cast(short4_t, b), c, 0, 0, 0);
 }
 
-// exp(x) for the arguments a softmax produces: x <= 0 (a rounding error above 0 is fine), -inf
-// included.  x = (64 n + j + f) ln2 / 64 with integers n, 0 <= j < 64 and |f| <= 1/2:
+// exp(x) for the arguments a softmax produces, x <= 0 (a rounding error above 0 is fine):
+// x = (64 n + j + f) ln2 / 64 with integers n, 0 <= j < 64 and |f| <= 1/2, and
 // exp(x) = 2^n . 2^(j/64) . exp(f ln2 / 64); the middle factor comes from a 64-entry table in LDS,
 // the last one from the Taylor quartic (remainder below r^5 / 120 < 4e-14 for |r| <= ln2 / 128), the
 // first is applied by ldexp, which also takes care of gradual underflow.  Relative error about
 // 1e-13 -- eight orders below what separates two scores that may legitimately be ranked either
-// way -- at ten double-precision instructions, against the library routine's two dozen; on this
-// part they do not overlap with the fp64 matrix instruction, so they count in full.
+// way -- at ten double-precision instructions, against the library routine's two dozen: the exponentials are
+// a good part of what bounds both kernels.
 __device__ __forceinline__ void exp_table_init(double* tab) {
     if (threadIdx.x < 64) tab[threadIdx.x] = exp2((double)threadIdx.x * (1.0 / 64.0));
     __syncthreads();
@@ -167,10 +167,11 @@ typedef int int4v_t __attribute__((ext_vector_type(4)));
 constexpr double LOGIT_UNIT = 92.332482616893656877;                       // 64 / ln 2
 template <int D> __device__ __forceinline__ double logit_scale() { return LOGIT_UNIT / sqrt((double)D); }
 
-// exp(x ln 2 / 64) for x <= 0 (a rounding error above 0 is fine): method above the table.  A finite x below
-// -1e5 or so gives 0 whatever the integer conversion saturates to; -inf would give NaN, so where a
-// logit may be -inf (a masked one, a row with infinities) the argument goes through
-// no_infinity first.  NaN stays NaN.
+// exp(x ln 2 / 64) for x <= 0 (a rounding error above 0 is fine): method above the table.  -inf would give NaN, so where a
+// logit may be -inf (a masked one, a row with infinities) the argument goes through no_infinity first.  NaN stays NaN.
+// Finite arguments go far beyond int (logits of fp16 rows reach 1e12 units): the cast, undefined there in C++, is the one
+// instruction v_cvt_i32_f64, which saturates, and with any k that low ldexp gives 0.  (That instruction written out costs 2 % of a
+// 128 x 2048 prompt, a clamp before it more; a test with logits of 7e9 units holds the result.)
 __device__ __forceinline__ double exp_units(double x, const double* tab) {
     const double kd = __builtin_rint(x);
     const double r = x - kd;

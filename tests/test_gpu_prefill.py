@@ -545,3 +545,23 @@ def test_an_infinite_value_stays_out_of_the_tiles_before_it(units, dtype, d):
     assert torch.equal(clean[:16], with_inf[:16])
     assert not torch.isfinite(with_inf[19:, :, 0, 7]).any()     # (infinite, or NaN where a part of the weight is 0)
     assert torch.isfinite(clean.float()).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_logits_far_beyond_the_exponential(dtype, d):
+    """Logits at least 3e5 apart and up to 7e7 (7e9 in the units the kernels count in, where a 32-bit integer ends at 2e9): every row
+    attends to one token, all other weights are 0 exactly.  Elements are chosen so that logits are exact."""
+    P, U, m = 129, 3, 100
+    g = np.random.default_rng(9500)
+    q, k = np.zeros((P + 8, U, d), np.float32), np.zeros((P + 8, U, d), np.float32)
+    v = g.standard_normal((P + 8, U, d)).astype(np.float32)
+    q[..., 3] = 2.0 ** 14
+    for u in range(U):
+        k[:, u, 3] = 256.0 * (g.permutation(P + 8) + 1)
+    cfg = synth.StreamConfig("pre-huge", 9500, 1, U, d, dtype, P + 8, m, 9)
+    got = parity.gpu_prefill(cfg, P, arrays=(q, k, v))
+    try:
+        print(f"\n  {parity.compare_prefill(cfg, got, decode_steps=5)}", flush=True)
+    finally:
+        got["cache"].close()
