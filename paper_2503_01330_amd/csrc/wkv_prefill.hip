@@ -659,7 +659,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         } else {
 #pragma unroll
             for (int i = 0; i < QT; ++i) {
-                if (QT * D > 128) __builtin_amdgcn_sched_barrier(0);       // one tile's sums at a time: the registers do not hold two
+                if (QT > 1) __builtin_amdgcn_sched_barrier(0);       // one tile's sums at a time: the registers do not hold two
                 digit_tile<TT, D, true>(sh.dg[buf][t], qdg[i], g, x, s[i]);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s[i][r] *= sh.scale[buf][t * TILE + 4 * g + r] * qscale[i];
@@ -725,7 +725,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
 
 // ------------------------------------------------------------------ 2. scores
 // The tile of keys kt against all its queries with the fp64 matrix instruction, for workgroups of marked rows: the keys stay in fp64, the
-// next tile of queries is requested before this one is used.  Only for two tiles a wave and d 128, where a SIMD holds two waves
+// next tile of queries is requested before this one is used.  Only for two tiles a wave, where a SIMD holds two waves
 // anyway: the registers this takes (206) cost the other forms one or two of their three or four (128 units x 2048: scores 0.67 -> 0.72 ms
 // without a marked row, held to 128 registers 0.75).
 template <class TT, int D>
@@ -812,7 +812,7 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     }
     next.store(sh, 0, true, 1.0);
 
-    if constexpr (D == 128 && KT == 2) {
+    if constexpr (KT == 2) {
         if (mostly_marked(kmarked || !active, sh.marked[0])) {
             if (active)
 #pragma unroll 1
@@ -1258,15 +1258,23 @@ void wkv_prefill_fold(WkvCache c, const void* __restrict__ k_, const void* __res
     }
 }
 
-// Tiles of 16 tokens of a wave, by the tiles a launch has: two from 65536 on.  Measured (rows / scores, one tile against two): 256
-// units x 4096 tokens 7.55 / 4.59 against 6.86 / 4.49 ms; 128 x 2048 (16384 tiles, bf16) 1.26 / 0.80 against 1.32 / 0.97: half as
-// many workgroups, and the last of them run on an emptying chip; 24 x 1237 106 / 102 against 135 / 148 us.
-inline int tiles_a_wave(long long tiles) { return tiles >= 65536 ? 2 : 1; }
-// Waves that share a tile's loop: two up to 4096 tiles, where a chip of 1024 vector units has few waves each and the
-// launch lasts as long as its longest loop.  Measured (rows / scores, one wave against two, then four): 24 units x
-// 1237 tokens (1872 tiles) 106 / 102, 90 / 81, 100 / 76 us; 128 x 2048 (16384 tiles) 1.31 / 0.83, 1.47 / 0.97, 1.91 / 1.54 ms:
-// every part slices all the rows it shares with fewer waves.
-inline int waves_a_tile(long long tiles) { return tiles <= 4096 ? 2 : 1; }
+// How many tiles of 16 tokens a wave takes.  Two share slicing, value loads and permutes, but are half as many workgroups with twice the
+// last stretch of each (the diagonal, and the loop's end on an emptying chip), so both the loop and the launch must be long.
+// Whole prompts, one tile | two, ms: fp16 d 128: 128 units x 4096 6.20 | 6.04, 256 x 4096 12.07 | 11.41, 192 x 3072 5.42 | 5.32, 1024 x 2048
+// 12.86 | 12.77, 1024 x 1024 3.81 | 4.09, 2048 x 512 2.54 | 2.91; bf16: 128 x 4096 6.75 | 6.95, 192 x 4096 9.78 | 9.71, 256 x 4096
+// 12.63 | 12.33, 384 x 3072 11.18 | 11.13, 512 x 2048 6.89 | 7.07.  Rows of 128 bytes: fp16 256 x 4096 7.75 | 7.64, 384 x 3072 6.76 | 6.87,
+// bf16 384 x 4096 11.88 | 12.04, so never.
+inline bool two_tiles_a_wave(long long tiles, int P) { return P >= 3072 && tiles >= 49152; }
+// Whether two waves share a tile, each taking every other tile of its loop.  Small launches last as long as their longest loop;
+// but every part slices all the rows it shares with fewer waves, which pays until the chip is full: for short prompts early.
+// Whole prompts, one wave | two, us (fp16 d 128; bf16 d 128; fp16 d 64; bf16 d 64):
+//   128 units x 128 (1024 tiles) 65 | 66; 68 | 69; 59 | 58; 60 | 59      128 x 256 (2048) 108 | 129; 138 | 135; 90 | 95; 91 | 97
+//   64 x 384 (1536) 125 | 127; 138 | 133; 105 | 97; 107 | 99             128 x 384 (3072) 166 | 183; 189 | 191; 120 | 135; 124 | 139
+//   24 x 1024 (1536) 271 | 233; 310 | 247; 210 | 188; 216 | 194          48 x 1024 (3072) 330 | 334; 404 | 352; 259 | 229; 268 | 236
+//   96 x 512 (3072) 214 | 217; 245 | 224; 161 | 156; 167 | 162           32 x 2048 (4096) 695 | 671; 804 | 714; 515 | 442; 568 | 468
+//   8 x 4096 (2048) 797 | 723; 1146 | 824; 597 | 481; 605 | 505          16 x 4096 (4096) 1097 | 1223; 1285 | 1305; 843 | 863; 921 | 928
+// bf16 gains longest: some of its tiles hold a marked row (INT_BITS), and the launch waits for those waves.
+inline bool two_waves_a_tile(long long tiles, int P, bool fp16) { return tiles <= (P < 512 ? 1536 : P >= 3072 && fp16 ? 2048 : 4096); }
 
 template <class TT, int D>
 hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, void* out,
@@ -1282,9 +1290,13 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
         hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NW, T, S>), dim3(grid), dim3(64 * NW), 0, stream, q, k, lse, a, P, c.units);
     };
     using std::integral_constant;
-    if (tiles_a_wave(tiles) == 2) contract(integral_constant<int, 2>{}, integral_constant<int, 1>{});
-    else if (waves_a_tile(tiles) == 2) contract(integral_constant<int, 1>{}, integral_constant<int, 2>{});
-    else contract(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+    if (two_waves_a_tile(tiles, P, __is_same(TT, TF16))) {
+        contract(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+    } else if (D == 64 || !two_tiles_a_wave(tiles, P)) {
+        contract(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+    } else {
+        if constexpr (D == 128) contract(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+    }
     if (P > c.m) {
         // The kernel's limit is one for all threads of the process and all prompts: always the longest prompt's, so that no
         // call lowers it between another one's setting and its launch.

@@ -289,13 +289,13 @@ def test_sort_and_runs_at_their_edges(P, d):
         _run(synth.StreamConfig(f"pre-edge{P}", 8900 + P, 1, 3, d, "bf16", P + 3, m, R), P, decode_steps=3)
 
 
-@pytest.mark.parametrize("dtype,d,P,units", [("fp16", 128, 129, 7290), ("bf16", 64, 1025, 1017), ("fp16", 64, 129, 460),
-                                             ("bf16", 128, 129, 455), ("fp16", 128, 129, 455)])
+@pytest.mark.parametrize("dtype,d,P,units", [("fp16", 128, 129, 170), ("bf16", 64, 129, 170), ("fp16", 64, 129, 171), ("bf16", 128, 129, 171),
+                                             ("bf16", 64, 1025, 63), ("fp16", 128, 1025, 64), ("bf16", 64, 1025, 1017)])
 def test_prompts_of_many_units(dtype, d, P, units):
-    """Up to 4096 tiles of 16 tokens a launch two waves share a tile (most prompts of these tests), then a wave
-    has one, from 65536 on it takes two: launches on either side.  An odd number of tiles (the last wave
-    has one), one row in the last tile, units that are no multiple of eight and a row that takes the fp64
-    instruction (one element far above the others).  Five units' inputs, repeated."""
+    """Up to 1536 tiles of 16 tokens a launch (4096 from 512 tokens on) two waves share a tile (most prompts of these tests), then a
+    wave has one: launches on either side.  An odd number of tiles, one row in the last tile, units that are no
+    multiple of eight and a row that takes the fp64 instruction (one element far above the others).  Five units' inputs,
+    repeated."""
     cfg = synth.StreamConfig("pre-two", 8800 + P, 1, units, d, dtype, P + 4, 100, 9)
     few = synth.Stream(synth.StreamConfig("pre-two", 8800 + P, 1, 5, d, dtype, P + 4, 100, 9))
     q, k, v = (synth.storage_to_f32(x, dtype).copy() for x in few.steps(0, cfg.steps))
@@ -473,14 +473,14 @@ def test_time_with_uneven_keys(what, limit):
 
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("units", [455, 460, 7290])
-def test_marked_rows_in_every_launch_form(units, d, dtype):
-    """The three launch forms (two waves a tile up to 4096 tiles, one, two tiles a wave from 65536 on) at nine tiles a unit, so that the
-    last wave has half a share; units that differ in the rows the digits do not hold: none, one key, a query in the first and
+@pytest.mark.parametrize("P,units", [(129, 170), (129, 171), (3073, 256)])
+def test_marked_rows_in_every_launch_form(P, units, d, dtype):
+    """The three launch forms (two waves a tile up to 1536 tiles of a short prompt; one; two tiles a wave from 49152 tiles on, if the
+    prompt has 3072 tokens and rows of 256 bytes) at odd numbers of tiles a unit, so that the last wave has half a share; units that differ in the rows the digits do not hold: none, one key, a query in the first and
     in the second tile of a pair, both at once, every key, every query (which take the fp64 instruction for whole workgroups), all
     rows, and every key of the first 32 only.  What the digits would drop meets large elements and differs from row to row:
     dropped, it would move score sums by 8e-9 and more (as plain float64 on the CPU says), which are held to 1e-9."""
-    P, T = 129, 133
+    T = P + 4
     g = np.random.default_rng(9400 + units)
     q, k, v = (g.standard_normal((T, 9, d)).astype(np.float32) for _ in range(3))
     q[..., 1] *= 8.0
@@ -503,7 +503,7 @@ def test_marked_rows_in_every_launch_form(units, d, dtype):
         if queries is not None:
             mark(q, queries, unit, 2)
     cfg = synth.StreamConfig("pre-marked", 9400, 1, units, d, dtype, T, 100, 9)
-    sel = np.concatenate([np.arange(9), np.arange(units - 9, units)])
+    sel = np.arange(9) if P > 1000 else np.concatenate([np.arange(9), np.arange(units - 9, units)])
     host = [synth.to_storage(x, dtype) for x in (q, k, v)]
     dev = [parity.to_device(x, dtype)[:, torch.arange(units, device="cuda") % 9].contiguous() for x in host]
     out = torch.zeros_like(dev[0])
@@ -521,12 +521,12 @@ def test_marked_rows_in_every_launch_form(units, d, dtype):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
-@pytest.mark.parametrize("units", [3, 460, 7290])
-def test_an_infinite_value_stays_out_of_the_tiles_before_it(units, dtype, d):
+@pytest.mark.parametrize("P,units", [(129, 3), (129, 460), (3073, 256)])
+def test_an_infinite_value_stays_out_of_the_tiles_before_it(P, units, dtype, d):
     """A row attends to no newer token: an infinity in the value of token 19 (the second tile of 16, also the second one of
     a wave that takes two) leaves the rows of the tile before it what they are without it, bit for bit, in each of the
     three launch forms."""
-    P, t = 129, torch.float16 if dtype == "fp16" else torch.bfloat16
+    t = torch.float16 if dtype == "fp16" else torch.bfloat16
     gen = torch.Generator(device="cuda")
     gen.manual_seed(9200)
     base = torch.randn(3, P, 5, d, generator=gen, device="cuda").to(t)
