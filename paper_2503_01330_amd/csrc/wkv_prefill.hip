@@ -724,21 +724,25 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
 }
 
 // ------------------------------------------------------------------ 2. scores
-// The tile of keys kt against all its queries with the fp64 matrix instruction, for workgroups of marked rows: the keys stay in fp64, the
-// next tile of queries is requested before this one is used.  Only for two tiles a wave, where a SIMD holds two waves
-// anyway: the registers this takes (206) cost the other forms one or two of their three or four (128 units x 2048: scores 0.67 -> 0.72 ms
-// without a marked row, held to 128 registers 0.75).
+// The tile of keys kt against all its queries with the fp64 matrix instruction, for workgroups of marked rows: the next tile of
+// queries is requested before this one is used.  Two tiles a wave (d 128): the keys stay in fp64, as a SIMD holds two waves anyway.
+// d 64: the keys are converted anew each round, which keeps the kernel below 128 registers (four waves; 256 units x 4096, every
+// key marked: the prompt 15.5 -> 13.9 ms, 14.7 before there were digits).  One tile a wave and d 128: not used, the kernel has all its 128
+// registers in use, and one more costs it a wave (128 units x 2048: scores 0.67 -> 0.72 ms without a marked row, held to 128 registers 0.75).
 template <class TT, int D>
 __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, const double* lse, double* a, int kt, int ntiles, int P, size_t tok,
                                              const double* etab, int g, int x)
 {
     constexpr int NWORDS = D / 8;
     const int kx = 4 * (x & 3) + (x >> 2), col = g * (D / 4) * TT::BYTES;     // keys: see exact_tiles
-    uint32_t next[NWORDS];
+    uint32_t kw[NWORDS], next[NWORDS];
     double kd[2 * NWORDS], next_l, acc[4] = {0.0, 0.0, 0.0, 0.0};
-    load_words<NWORDS>(kb + (size_t)min(kt * TILE + kx, P - 1) * tok + col, next);
+    load_words<NWORDS>(kb + (size_t)min(kt * TILE + kx, P - 1) * tok + col, kw);
+    auto convert = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < 2 * NWORDS; ++e) kd[e] = (double)frag_elem<TT>(next, e);
+        for (int e = 0; e < 2 * NWORDS; ++e) kd[e] = (double)frag_elem<TT>(kw, e);
+    };
+    if constexpr (D == 128) convert();
     auto request = [&](int qt) __attribute__((always_inline)) {
         const int t = min(min(qt, ntiles - 1) * TILE + x, P - 1);          // past the last tile: a repeat, unused
         load_words<NWORDS>(qb + (size_t)t * tok + col, next);
@@ -751,6 +755,11 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
         for (int i = 0; i < NWORDS; ++i) w[i] = next[i];
         const double l = next_l;
         request(qt + 1);
+        if constexpr (D == 64) {                              // converted anew each round: see above
+#pragma unroll
+            for (int i = 0; i < NWORDS; ++i) asm volatile("" : "+v"(kw[i]));
+            convert();
+        }
         double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int e = 0; e < 2 * NWORDS; e += 2) {
@@ -812,7 +821,7 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     }
     next.store(sh, 0, true, 1.0);
 
-    if constexpr (KT == 2) {
+    if constexpr (SPLIT == 1 && (KT == 2 || D == 64)) {
         if (mostly_marked(kmarked || !active, sh.marked[0])) {
             if (active)
 #pragma unroll 1
