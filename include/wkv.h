@@ -164,7 +164,9 @@ int wkv_step(wkv_handle* h, const void* q, const void* k_new, const void* v_new,
  * belongs to the handle: reserved by wkv_create_ex when wkv_options.max_prompt covers n_tokens,
  * otherwise allocated (and kept) by the first call that needs it -- only that call allocates.
  * The eviction log is not written.  On error the cache is unchanged, except for WKV_EHIP after
- * the launch.
+ * the launch.  The same call gives the same bits every time.  How the kernels share out the rows depends on
+ * units x n_tokens, so a sequence may differ in last bits (outputs by a step of the format, score sums by
+ * 1e-15 or so relative) from the same one in a batch of another size.
  */
 int wkv_prefill(wkv_handle* h, const void* q, const void* k, const void* v, void* out,
                 int n_tokens, void* stream);

@@ -9,19 +9,21 @@
 // by token; beyond that it is a different function (streamed tokens attend to an already
 // compressed cache).
 //
-// Four kernels:
-//   1. wkv_prefill_rows: causal attention, one wave per tile of 16 queries, keys in tiles of 16.
+// Four kernels (three for a prompt that fits the cache):
+//   1. wkv_prefill_rows: causal attention in tiles of 16 queries x 16 keys.  A wave takes one tile of queries, two in long launches of
+//      long prompts, or shares one with another wave in small launches (the rules stand at run()).
 //      The logits are a dense contraction of 16-bit numbers, formed exactly: every row becomes 8-bit
 //      digits (once per workgroup, in LDS), the digits go through the int8 matrix instruction, the
 //      integer sums are put together in fp64 (what makes the later selection reproduce an fp64
-//      reference exactly, as in the decode kernels).  Online softmax in
+//      reference exactly, as in the decode kernels).  Rows that digits do not hold take the fp64 matrix instruction.  Online softmax in
 //      fp64; P.V with v_mfma_f32_16x16x16_f16 / _bf16 (fp32 accumulation): the weights go in as
-//      hi + lo 16-bit pairs straight from the registers the logits arrive in, the values as the raw
+//      two or three 16-bit parts straight from the registers the logits arrive in, the values as the raw
 //      cache words.  Writes o_t and the log-sum-exp of every row.
-//   2. wkv_prefill_scores: the column sums a_i = sum_{t >= i} exp(s_ti - lse_t): one wave per
-//      tile of 16 keys, looping over the query tiles below the diagonal, the same contraction
+//   2. wkv_prefill_scores: the column sums a_i = sum_{t >= i} exp(s_ti - lse_t): tiles of 16 keys, given to waves in the
+//      same way, looping over the query tiles below the diagonal, the same contraction
 //      again (recomputing the logits costs less than storing P^2/2 of them);
-//      sums stay in registers, no atomics, fixed order.
+//      sums stay in registers, no atomics.  The order of a sum is fixed for a launch form, so a result is the same from call to
+//      call, and from one number of units to another as long as the form is.
 //   3. wkv_prefill_compress (prompts longer than the budget): one workgroup per unit: rank of every candidate by (score, token),
 //      the P - m lowest are removed; survivors get slots in token order; the weight with which every raw row
 //      enters the survivor on its right, as the sequence of pairwise merges in ascending score order gives it.
@@ -147,9 +149,9 @@ __device__ __forceinline__ void exp_table_init(double* tab) {
 // Why: the fp64 matrix instruction takes 64 cycles for 16x16x4 on this part and shares its pipe
 // with the fp64 vector instructions of the softmax; the sixteen digit products take 512 cycles per
 // 16x16x128 tile against 2048, and run beside them.
-// Measured (256 units, 4096 tokens, d 128, fp16): rows 13.1 -> 8.0 ms, scores 10.5 -> 5.6 ms; with the int8
-// instructions a third of the time, vector instructions bound both: slicing by packed maxima, no clamp in the
-// exponential, two tiles a wave brought 6.9 and 4.5 ms.
+// Measured (256 units, 4096 tokens, d 128, fp16): rows 13.1 -> 8.0 ms, scores 10.5 -> 5.6 ms; the int8
+// instructions are a third of the time, vector instructions bound both: slicing by packed maxima, no clamp in the
+// exponential, two tiles a wave brought 6.7 and 4.5 ms.
 // A row whose elements are not all integers at its scale (an element more than 2^-22 below the
 // largest that uses its last bits; possible for bf16, and for fp16 rows that reach 64) or that holds
 // an infinity or a NaN is marked, and a tile that touches a marked row takes the fp64 instruction.
@@ -585,8 +587,8 @@ __device__ __forceinline__ void exact_rows(const char* qb, const char* kb, const
 // lse: [units][P], in units of ln 2 / 64.  One workgroup = NW waves of QT consecutive query tiles of one unit;
 // the keys are sliced into digits once per workgroup and read by every wave from LDS.  What bounds
 // this kernel and the next is vector instructions (slicing, recombining the digit sums, the
-// exponentials), so a wave takes two tiles where there is work enough: slicing, value loads and their
-// permutes are then paid once for both.
+// exponentials), so a wave takes two tiles where that pays: slicing, value loads and their
+// permutes are then paid once for both (d 128: all 256 registers of two waves a SIMD, none spilled).
 // In small launches SPLIT waves share a tile instead, each taking every SPLIT-th tile of keys.
 template <class TT, int D, int NW, int QT, int SPLIT>
 __global__ __launch_bounds__(64 * NW, 2)
