@@ -414,17 +414,17 @@ __device__ __forceinline__ void exact_tiles(const char* shared, const char* own,
         for (int r = 0; r < 4; ++r) s[i][r] = (CHAINS == 1 ? acc[i][0][r] : acc[i][0][r] + acc[i][CHAINS - 1][r]) * logit_scale<D>();
 }
 
-// Whether a workgroup takes the fp64 instruction for all it does: every wave's own rows are marked, or both tiles of the first
-// shared chunk are.  (Uniform over the workgroup; the chunk is visible afterwards.)  Tile by tile, with the digits made beside it and
+// Whether a workgroup takes the fp64 instruction for all it does: every wave holds a marked row of its own, or four of the 32 rows of the first
+// shared chunk are marked (at that rate two tiles in three hold one; a row or two at a prompt's beginning say nothing about the rest).  (Uniform over the workgroup; the chunk is visible afterwards.)  Tile by tile, with the digits made beside it and
 // nothing requested ahead, a prompt of marked rows only is slower than the fp64 instruction alone was before there were digits; in
 // loops of its own it is not.  Rows + scores, every key marked, tile by tile | in loops of its own | before: 256 units x 4096, d 128,
 // fp16 16.4 + 14.1 | 13.7 + 10.8 | 13.0 + 10.5 ms; 128 x 2048 2.51 + 2.07 | 1.85 + 2.07 | 1.85 + 1.48 ms.
 // Without marked rows the test costs nothing that shows (11.32 | 11.39 ms, 1.916 | 1.919 ms for the whole prompts).
 __device__ __forceinline__ bool mostly_marked(bool own, const int (&marked)[CHUNK]) {
-    static_assert(CHUNK == 32, "two tiles of 16 rows");
+    static_assert(CHUNK == 32, "half a wave");
     const bool all = __syncthreads_and(own);
-    const unsigned long long m = __ballot(marked[threadIdx.x & (CHUNK - 1)]);
-    return all || ((m & 0xFFFFu) != 0 && (m & 0xFFFF0000u) != 0);
+    const unsigned long long m = __ballot(marked[threadIdx.x & (CHUNK - 1)]);      // (both halves of the wave look at the same rows)
+    return all || __popc((unsigned)m) >= 4;
 }
 
 // ------------------------------------------------------------------ 1. rows
