@@ -419,12 +419,15 @@ __device__ __forceinline__ void exact_tiles(const char* shared, const char* own,
 // nothing requested ahead, a prompt of marked rows only is slower than the fp64 instruction alone was before there were digits; in
 // loops of its own it is not.  Rows + scores, every key marked, tile by tile | in loops of its own | before: 256 units x 4096, d 128,
 // fp16 16.4 + 14.1 | 13.7 + 10.8 | 13.0 + 10.5 ms; 128 x 2048 2.51 + 2.07 | 1.85 + 2.07 | 1.85 + 1.48 ms.
-// Without marked rows the test costs nothing that shows (11.32 | 11.39 ms, 1.916 | 1.919 ms for the whole prompts).
-__device__ __forceinline__ bool mostly_marked(bool own, const int (&marked)[CHUNK]) {
-    static_assert(CHUNK == 32, "half a wave");
-    const bool all = __syncthreads_and(own);
-    const unsigned long long m = __ballot(marked[threadIdx.x & (CHUNK - 1)]);      // (both halves of the wave look at the same rows)
-    return all || __popc((unsigned)m) >= 4;
+// Without marked rows the test costs nothing that shows (11.32 | 11.32 ms, 1.91 | 1.92 ms for the whole prompts); with __syncthreads_and
+// instead of one barrier and two ballots 11.40 ms.
+template <int NW> __device__ __forceinline__ bool mostly_marked(bool own, const int (&marked)[CHUNK]) {
+    static_assert(CHUNK == 32 && NW <= 32, "half a wave");
+    __shared__ int waves[NW];
+    if ((threadIdx.x & 63) == 0) waves[threadIdx.x >> 6] = own;
+    __syncthreads();
+    const unsigned m = (unsigned)__ballot(marked[threadIdx.x & (CHUNK - 1)]);      // (both halves of the wave look at the same rows)
+    return __all(waves[threadIdx.x & (NW - 1)]) || __popc(m) >= 4;
 }
 
 // ------------------------------------------------------------------ 1. rows
@@ -627,7 +630,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
     next.store(sh, 0, false, logit_scale<D>());
 
     if constexpr (SPLIT == 1) {
-        if (mostly_marked(qmarked || !active, sh.marked[0])) {
+        if (mostly_marked<NW>(qmarked || !active, sh.marked[0])) {
             if (active)
 #pragma unroll 1
                 for (int t = qt; t <= mine; ++t) exact_rows<TT, D>(qb, kb, vb, ob, lse + (size_t)u * P, t, P, tok, etab, g, x);
@@ -637,9 +640,8 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
     Rows<TT, D, QT> rows;
     rows.clear();
     constexpr int NE = rows.NE;
-    size_t voff[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) voff[r] = (size_t)(4 * g + r) * tok + x * NE * TT::BYTES;
+    // a lane's place in a tile of values; the four rows are a uniform stride apart (four offsets held ready take six registers more)
+    const size_t voff = (size_t)(4 * g) * tok + x * NE * TT::BYTES;
     auto tile = [&](int kt, int buf) __attribute__((always_inline)) {
         // V fragments: keys 16 kt + 4g + r, columns NE*x .. NE*x+NE-1; requested here, used after the softmax
         // (a lane's offsets in a tile never change; only a tile that reaches past the prompt clamps its rows)
@@ -647,7 +649,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         if (kt * TILE + TILE <= P) {                          // uniform
             const char* vt = vb + (size_t)(kt * TILE) * tok;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) load_words<NE / 2>(vt + voff[r], vfrag[r]);
+            for (int r = 0; r < 4; ++r) load_words<NE / 2>(vt + r * tok + voff, vfrag[r]);
         } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -824,7 +826,7 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     next.store(sh, 0, true, 1.0);
 
     if constexpr (SPLIT == 1 && (KT == 2 || D == 64)) {
-        if (mostly_marked(kmarked || !active, sh.marked[0])) {
+        if (mostly_marked<NW>(kmarked || !active, sh.marked[0])) {
             if (active)
 #pragma unroll 1
                 for (int t = kt; t < min(kt + KT, ntiles); ++t)
