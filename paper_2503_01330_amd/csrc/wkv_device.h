@@ -139,6 +139,12 @@ template <int CTRL, class X> __device__ __forceinline__ X dpp(X x) {
     return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
 }
 
+// The same where every lane of the pattern has a source: nothing of the destination's old value is needed, so the
+// exchange can become part of the instruction that uses it.
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_in(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+
 // Sum over the 16 lanes of a DPP row; every lane ends with the same bits.
 template <class X> __device__ __forceinline__ X row_allsum(X x) {
     x += dpp<0xB1>(x);    // quad_perm [1,0,3,2]

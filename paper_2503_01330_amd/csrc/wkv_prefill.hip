@@ -91,17 +91,15 @@ typedef float    float2v_t __attribute__((ext_vector_type(2)));
 typedef __bf16   bf16x2_t  __attribute__((ext_vector_type(2)));
 template <class TT> constexpr int weight_parts() { return __is_same(TT, TF16) ? 2 : 3; }
 template <class TT> __device__ __forceinline__ void split16x4(const float (&p)[4], uint2_t (&part)[weight_parts<TT>()]) {
-    constexpr uint32_t keep = __is_same(TT, TF16) ? 0xFFFFE000u : 0xFFFF0000u;
-    auto cut = [](float x) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & keep); };
     if constexpr (__is_same(TT, TF16)) {
-        float h[4], l[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) { h[r] = cut(p[r]); l[r] = p[r] - h[r]; }
-        part[0] = uint2_t{ __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(h[0], h[1])),
-                           __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(h[2], h[3])) };
-        part[1] = uint2_t{ __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(l[0], l[1])),
-                           __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(l[2], l[3])) };
+        auto cut2 = [](float a, float b) { return __builtin_bit_cast(half2v_t, __builtin_amdgcn_cvt_pkrtz(a, b)); };
+        const half2v_t h01 = cut2(p[0], p[1]), h23 = cut2(p[2], p[3]);
+        float l[4];
+        l[0] = p[0] - (float)h01.x; l[1] = p[1] - (float)h01.y; l[2] = p[2] - (float)h23.x; l[3] = p[3] - (float)h23.y;
+        part[0] = uint2_t{ __builtin_bit_cast(uint32_t, h01), __builtin_bit_cast(uint32_t, h23) };
+        part[1] = uint2_t{ __builtin_bit_cast(uint32_t, cut2(l[0], l[1])), __builtin_bit_cast(uint32_t, cut2(l[2], l[3])) };
     } else {
+        auto cut = [](float x) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & 0xFFFF0000u); };
         auto pack = [](float a, float b) {                   // the upper halves of two words: exact for cut values
             return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, b), __builtin_bit_cast(uint32_t, a), 0x07060302u);
         };
@@ -125,16 +123,18 @@ template <class TT> __device__ __forceinline__ float4_t mfma16(uint2_t a, uint2_
         return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4_t, a), __builtin_bit_cast(short4_t, b), c, 0, 0, 0);
 }
 
-// exp(x) for the arguments a softmax produces, x <= 0 (a rounding error above 0 is fine):
-// x = (64 n + j + f) ln2 / 64 with integers n, 0 <= j < 64 and |f| <= 1/2, and
-// exp(x) = 2^n . 2^(j/64) . exp(f ln2 / 64); the middle factor comes from a 64-entry table in LDS,
-// the last one from the Taylor quartic (remainder below r^5 / 120 < 4e-14 for |r| <= ln2 / 128), the
-// first is applied by ldexp, which also takes care of gradual underflow.  Relative error about
-// 1e-13 -- eight orders below what separates two scores that may legitimately be ranked either
-// way -- at ten double-precision instructions, against the library routine's two dozen: the exponentials are
-// a good part of what bounds both kernels.
+// exp(x) for the arguments a softmax produces, x <= 0 or a little above:
+// x = (256 n + j + f) ln2 / 256 with integers n, 0 <= j < 256 and |f| <= 1/2, and
+// exp(x) = 2^n . 2^(j/256) . exp(f ln2 / 256); the middle factor comes from a table in LDS, the last one from a cubic
+// (the Taylor cubic with the share of the fourth term that a square can take: off by 2.4e-14 at most for |f| <= 1/2), the
+// first is applied by ldexp, which also takes care of gradual underflow.  Relative error below 3e-14 -- eight orders below
+// what separates two scores that may legitimately be ranked either way -- at nine double-precision instructions, against the
+// library routine's two dozen: the exponentials are a good part of what bounds both kernels.  256 entries, and not 64: a
+// quartic's last step goes, and the entry's place is one byte of n, which the shift that makes its address selects by itself.
+constexpr int EXP_STEPS = 256;
 __device__ __forceinline__ void exp_table_init(double* tab) {
-    if (threadIdx.x < 64) tab[threadIdx.x] = exp2((double)threadIdx.x * (1.0 / 64.0));
+    static_assert(EXP_STEPS == 256, "one entry a thread of a workgroup");
+    tab[threadIdx.x & 255] = exp2((double)(threadIdx.x & 255) * (1.0 / EXP_STEPS));
     __syncthreads();
 }
 // ------------------------------------------------------------------ logits from 8-bit digits
@@ -165,26 +165,25 @@ constexpr int INT_BITS = 30;
 
 typedef int int4v_t __attribute__((ext_vector_type(4)));
 
-// Logits are kept in units of ln 2 / 64: the exponential below then starts with a rounding, not a product.
-constexpr double LOGIT_UNIT = 92.332482616893656877;                       // 64 / ln 2
+// Logits are kept in units of ln 2 / 256: the exponential below then starts with a rounding, not a product.
+constexpr double LOGIT_UNIT = 369.3299304675746;                           // 256 / ln 2
 template <int D> __device__ __forceinline__ double logit_scale() { return LOGIT_UNIT / sqrt((double)D); }
 
-// exp(x ln 2 / 64) for x <= 0 (a rounding error above 0 is fine): method above the table.  -inf would give NaN, so where a
+// exp(x ln 2 / 256): method above the table.  -inf would give NaN, so where a
 // logit may be -inf (a masked one, a row with infinities) the argument goes through no_infinity first.  NaN stays NaN.
 // Finite arguments go far beyond int (logits of fp16 rows reach 1e12 units): the cast, undefined there in C++, is the one
 // instruction v_cvt_i32_f64, which saturates, and with any k that low ldexp gives 0.  (That instruction written out costs 2 % of a
-// 128 x 2048 prompt, a clamp before it more; a test with logits of 7e9 units holds the result.)
+// 128 x 2048 prompt, a clamp before it more; a test with logits of 3e10 units holds the result.)
 __device__ __forceinline__ double exp_units(double x, const double* tab) {
     const double kd = __builtin_rint(x);
     const double r = x - kd;
     const int k = (int)kd;
-    const double tj = tab[k & 63];
-    // ln2/64 = c: c, c^2/2, c^3/6, c^4/24
-    double p = fma(r, 5.732851688640402e-10, 2.1173137155464776e-07);
-    p = fma(p, r, 5.86490495505617e-05);
-    p = fma(p, r, 0.010830424696249145);
+    const double tj = tab[k & 255];
+    // ln2/256 = c: c, c^2 (1/2 + 0.8284 (c/2)^2 / 24), c^3/6
+    double p = fma(r, 3.308302680541371e-09, 3.665566060704036e-06);
+    p = fma(p, r, 0.0027076061740622863);
     p = fma(p, r, 1.0);
-    return ldexp(tj * p, k >> 6);
+    return ldexp(tj * p, k >> 8);
 }
 __device__ __forceinline__ double no_infinity(double x) { return (x < -1e6) ? -1e6 : x; }
 
@@ -293,60 +292,61 @@ template <int D> struct SharedRows {
     int marked[2][CHUNK];
 };
 
-// One round of a workgroup's NT threads: a thread takes eight elements of a row; D / 8 threads a row.
+// The share of a chunk of one of the workgroup's NT threads: EPT consecutive elements of a row; TPR threads a row.  (Sixteen
+// elements where the row is long enough: what is paid once a thread and row, the maximum over the row's lanes, its scale, its mark, is as
+// many instructions as six elements are.)
 template <class TT, int D, int NT> struct ChunkLoad {
-    static constexpr int TPR = D / 8, ROWS = NT / TPR, ROUNDS = CHUNK / ROWS;
-    static_assert(CHUNK % ROWS == 0 && ROUNDS >= 1, "a chunk is a whole number of rounds");
-    uint32_t w[ROUNDS][4];
-    double lse[ROUNDS];
+    static constexpr int EPT = CHUNK * D / NT, TPR = D / EPT, W = EPT / 2;
+    static_assert((EPT == 8 || EPT == 16) && NT == CHUNK * TPR, "a thread takes half a block of a digit plane, or a whole one");
+    uint32_t w[W];
+    double lse;
     __device__ __forceinline__ void request(const char* base, const double* lsep, int row0, int P, size_t tok) {
-        const int j = threadIdx.x % TPR, r = threadIdx.x / TPR;
-#pragma unroll
-        for (int i = 0; i < ROUNDS; ++i) {
-            const int row = min(row0 + i * ROWS + r, P - 1);
-            load_words<4>(base + (size_t)row * tok + j * 8 * TT::BYTES, w[i]);
-            if (lsep != nullptr && j == 0) lse[i] = lsep[row];
-        }
+        const int j = threadIdx.x % TPR, row = min(row0 + (int)threadIdx.x / TPR, P - 1);
+        load_words<W>(base + (size_t)row * tok + j * EPT * TT::BYTES, w);
+        if (lsep != nullptr && j == 0) lse = lsep[row];
     }
     __device__ __forceinline__ void store(SharedRows<D>& sh, int buf, bool with_lse, double unit) const {
-        const int j = threadIdx.x % TPR, r = threadIdx.x / TPR;
+        const int j = threadIdx.x % TPR, row = threadIdx.x / TPR;
+        RowSpan<TT> span;
 #pragma unroll
-        for (int i = 0; i < ROUNDS; ++i) {
-            RowSpan<TT> span;
+        for (int e = 0; e < W; ++e) span.add(w[e]);
+        uint32_t top = span.largest();                            // over the row's lanes
+        top = max(top, dpp_in<0xB1>(top));        // quad_perm [1,0,3,2]
+        top = max(top, dpp_in<0x4E>(top));        // quad_perm [2,3,0,1]
+        top = max(top, dpp_in<0x141>(top));       // row_half_mirror
+        if constexpr (TPR == 16) top = max(top, dpp_in<0x140>(top));      // row_mirror
+        static_assert(TPR == 8 || TPR == 16, "a row's lanes are half a DPP row, or one");
+        bool bad;
+        int ex;
+        const int s = digit_shift<TT>(top, ex, bad);
+        const float mul = ldexpf(1.f, s);
+        bad |= no_integers<TT>(w, span, ex, mul);
+        const int t = row / TILE, x = row % TILE, first = j * EPT;
+        const int c = first >> 6, g = (first >> 4) & 3, half = first & 15;
+        uint32_t pl[EPT / 4][DIGITS];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) span.add(w[i][e]);
-            int top = (int)span.largest();                                 // over the row's 8 or 16 lanes
-            top = max(top, dpp<0xB1>(top));       // quad_perm [1,0,3,2]
-            top = max(top, dpp<0x4E>(top));       // quad_perm [2,3,0,1]
-            top = max(top, dpp<0x141>(top));      // row_half_mirror
-            if constexpr (TPR == 16) top = max(top, dpp<0x140>(top));   // row_mirror
-            bool bad;
-            int ex;
-            const int s = digit_shift<TT>((uint32_t)top, ex, bad);
-            const float mul = ldexpf(1.f, s);
-            bad |= no_integers<TT>(w[i], span, ex, mul);
-            uint32_t p0[DIGITS], p1[DIGITS];
-            float fa[4], fb[4];
+        for (int e4 = 0; e4 < EPT / 4; ++e4) {
+            float f[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { fa[e] = frag_elem<TT>(w[i], e); fb[e] = frag_elem<TT>(w[i], e + 4); }
-            digits4(fa, mul, p0);
-            digits4(fb, mul, p1);
-            const int row = i * ROWS + r, t = row / TILE, x = row % TILE;
-            const int c = j >> 3, g = (j >> 1) & 3, half = j & 1;
+            for (int e = 0; e < 4; ++e) f[e] = frag_elem<TT>(w, 4 * e4 + e);
+            digits4(f, mul, pl[e4]);
+        }
 #pragma unroll
-            for (int b = 0; b < DIGITS; ++b)
-                *reinterpret_cast<uint2_t*>(&sh.dg[buf][t][c][b][g * BLOCK + x * 16 + half * 8]) = uint2_t{ p0[b], p1[b] };
-            const unsigned long long fm = __ballot(bad);
-            if (j == 0) {
-                const int lane = threadIdx.x & 63;
-                sh.scale[buf][row] = ldexp(unit, -s);
-                bool mark = ((fm >> lane) & ((1ull << TPR) - 1)) != 0;
-                if (with_lse) {
-                    sh.lse[buf][row] = lse[i];
-                    mark |= !(fabs(lse[i]) < INFINITY);
-                }
-                sh.marked[buf][row] = mark;
+        for (int b = 0; b < DIGITS; ++b) {
+            unsigned char* dst = &sh.dg[buf][t][c][b][g * BLOCK + x * 16 + half];
+            if constexpr (EPT == 16) *reinterpret_cast<u32x4_t*>(dst) = u32x4_t{ pl[0][b], pl[1][b], pl[2][b], pl[3][b] };
+            else *reinterpret_cast<uint2_t*>(dst) = uint2_t{ pl[0][b], pl[1][b] };
+        }
+        const unsigned long long fm = __ballot(bad);
+        if (j == 0) {
+            const int lane = threadIdx.x & 63;
+            sh.scale[buf][row] = ldexp(unit, -s);
+            bool mark = ((fm >> lane) & ((1ull << TPR) - 1)) != 0;
+            if (with_lse) {
+                sh.lse[buf][row] = lse;
+                mark |= !(fabs(lse) < INFINITY);
             }
+            sh.marked[buf][row] = mark;
         }
     }
 };
@@ -433,8 +433,9 @@ template <int NW> __device__ __forceinline__ bool mostly_marked(bool own, const 
 // ------------------------------------------------------------------ 1. rows
 // Softmax and output accumulators of N consecutive tiles of 16 queries.
 template <class TT, int D, int N> struct Rows {
+    static constexpr double AHEAD = 8.0 * EXP_STEPS;
     static constexpr int NE = D / 16;         // output column sets: lane (g, x) owns columns NE*x .. NE*x+NE-1
-    double m[N], l[N];                        // running maximum of query x (same in the 4 lanes x, x+16, ...); this lane's share of the sum
+    double m[N], l[N];                        // reference of query x (same in the 4 lanes x, x+16, ...); this lane's share of the sum
     float4_t o[N][NE];
     __device__ __forceinline__ void clear() {
 #pragma unroll
@@ -448,15 +449,17 @@ template <class TT, int D, int N> struct Rows {
     // Sixteen more keys.  s: their logits, register r of lane (g, x) = key 4g + r, query x; vfrag: columns NE*x .. of the values of
     // keys 4g + r.  infinities: whether a logit may be -inf (uniform).  lone: see below.
     __device__ __forceinline__ void add(double (&s)[N][4], const uint32_t (&vfrag)[4][NE / 2], bool infinities, bool lone, const double* etab, int g) {
-        // A running maximum that has not moved needs no rescaling, and after the first few key
-        // tiles of a row it rarely moves: the maximum over the four lane groups and the rescaling (an exp,
-        // the running sum and all output accumulators of the wave) are skipped unless some query needs them.
+        // Weights are relative to a reference m, the row's maximum when it was last looked for; that is when a logit exceeds it by
+        // more than AHEAD units, so weights stay below 2^8 (and one of them is 1 or more: the 16-bit parts that P.V takes lose no more
+        // than with the running maximum itself).  Following the maximum costs a rescaling of the sum and all output
+        // accumulators in every tile in which any of the wave's rows has a new one, 16 / k of the k-th tiles with random logits:
+        // half the tiles of a prompt of 4096 where a wave has 32 rows.
         double tmax[N];
         bool moved = false;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             tmax[i] = fmax(fmax(s[i][0], s[i][1]), fmax(s[i][2], s[i][3]));
-            moved |= tmax[i] > m[i];
+            moved |= tmax[i] > m[i] + AHEAD;
         }
         if (__any(moved)) {
 #pragma unroll
@@ -587,7 +590,7 @@ __device__ __forceinline__ void exact_rows(const char* qb, const char* kb, const
 }
 
 // q, k, v, out: [P][units][D] (token-major, as a decode step sees them one token at a time).
-// lse: [units][P], in units of ln 2 / 64.  One workgroup = NW waves of QT consecutive query tiles of one unit;
+// lse: [units][P], in units of ln 2 / 256.  One workgroup = NW waves of QT consecutive query tiles of one unit;
 // the keys are sliced into digits once per workgroup and read by every wave from LDS.  What bounds
 // this kernel and the next is vector instructions (slicing, recombining the digit sums, the
 // exponentials), so a wave takes two tiles where that pays: slicing, value loads and their
@@ -611,7 +614,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
     const bool active = qt < ntiles;                                             // an idle wave still slices keys
     const int mine = min(qt + QT, ntiles) - 1;                                   // its last key tile, and the workgroup's
     const int last = min(qt0 + TPG, ntiles) - 1;
-    __shared__ double etab[64];
+    __shared__ double etab[EXP_STEPS];
     __shared__ SharedRows<D> sh;
     exp_table_init(etab);
     const size_t tok = (size_t)units * ROWB;                              // bytes from one token to the next
@@ -803,7 +806,7 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     if (u >= units) return;                                               // the whole workgroup
     const int kt = kt0 + wid / SPLIT * KT, part = wid % SPLIT;
     const bool active = kt < ntiles;
-    __shared__ double etab[64];
+    __shared__ double etab[EXP_STEPS];
     __shared__ SharedRows<D> sh;
     exp_table_init(etab);
     const size_t tok = (size_t)units * ROWB;
