@@ -10,7 +10,7 @@
 // compressed cache).
 //
 // Four kernels (three for a prompt that fits the cache):
-//   1. wkv_prefill_rows: causal attention in tiles of 16 queries x 16 keys.  A wave takes one tile of queries, two in long launches of
+//   1. wkv_prefill_rows: causal attention in tiles of 16 queries x 16 keys.  A wave takes one tile of queries, two in large launches of
 //      long prompts, or shares one with another wave in small launches (the rules stand at run()).
 //      The logits are a dense contraction of 16-bit numbers, formed exactly: every row becomes 8-bit
 //      digits (once per workgroup, in LDS), the digits go through the int8 matrix instruction, the
@@ -19,8 +19,8 @@
 //      fp64; P.V with v_mfma_f32_16x16x16_f16 / _bf16 (fp32 accumulation): the weights go in as
 //      two or three 16-bit parts straight from the registers the logits arrive in, the values as the raw
 //      cache words.  Writes o_t and the log-sum-exp of every row.
-//   2. wkv_prefill_scores: the column sums a_i = sum_{t >= i} exp(s_ti - lse_t): tiles of 16 keys, given to waves in the
-//      same way, looping over the query tiles below the diagonal, the same contraction
+//   2. wkv_prefill_scores: the column sums a_i = sum_{t >= i} exp(s_ti - lse_t): tiles of 16 keys, one a wave or
+//      shared by two in small launches, looping over the query tiles below the diagonal, the same contraction
 //      again (recomputing the logits costs less than storing P^2/2 of them);
 //      sums stay in registers, no atomics.  The order of a sum is fixed for a launch form, so a result is the same from call to
 //      call, and from one number of units to another as long as the form is.
@@ -123,6 +123,17 @@ template <class TT> __device__ __forceinline__ float4_t mfma16(uint2_t a, uint2_
         return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4_t, a), __builtin_bit_cast(short4_t, b), c, 0, 0, 0);
 }
 
+// The same with eight a lane: what two operands of four hold, one behind the other.
+typedef _Float16 half8_t  __attribute__((ext_vector_type(8)));
+typedef __bf16   bf16x8_t __attribute__((ext_vector_type(8)));
+template <class TT> __device__ __forceinline__ float4_t mfma16(uint2_t a0, uint2_t a1, u32x4_t b, float4_t c) {
+    const u32x4_t a = { a0.x, a0.y, a1.x, a1.y };
+    if constexpr (__is_same(TT, TF16))
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
 // exp(x) for the arguments a softmax produces, x <= 0 or a little above:
 // x = (256 n + j + f) ln2 / 256 with integers n, 0 <= j < 256 and |f| <= 1/2, and
 // exp(x) = 2^n . 2^(j/256) . exp(f ln2 / 256); the middle factor comes from a table in LDS, the last one from a cubic
@@ -139,29 +150,34 @@ __device__ __forceinline__ void exp_table_init(double* tab) {
 }
 // ------------------------------------------------------------------ logits from 8-bit digits
 // A row of 16-bit numbers is, up to a power of two, a row of integers: n = x * 2^s with the row's own s,
-// chosen so that its largest magnitude has 30 bits.  n is written in four balanced base-256
-// digits (d0..d2 in [-128, 127], |d3| <= 64), and q.k becomes sixteen dot products of digits,
+// chosen so that its largest magnitude has 31 bits.  n is written in four balanced base-256
+// digits (d0..d2 in [-128, 127], d3 in [-127, 127]), and q.k becomes sixteen dot products of digits,
 // which v_mfma_i32_16x16x64_i8 forms without any rounding: seven sums S_w over the pairs of weight
 // w = i + j, then A = S0 + 2^8 S1, B = S2 + 2^8 S3, C = S4 + 2^8 S5 + 2^16 S6, and
 // q.k = (A + 2^16 B + 2^32 C) 2^-(s_q + s_k) with the rounding of two fp64 additions: closer to the
-// exact logit than a chain of D fp64 additions.  For 128 elements A and B stay below 2^31 (S1 <= 2^22,
-// S3 <= 2^22 + 2^21), and so does S4 + 2^8 S5 (S5 <= 2^21); S6 <= 2^19 joins in fp64, exactly.
+// exact logit than a chain of D fp64 additions.  For 128 elements A, B and S4 + 2^8 S5 stay below 2^31 (the largest is B: S3 <= 128 (2 127 128 + 2 128^2)
+// and S2 <= 3 128^3 make 2145386496 at most); S6 joins in fp64, exactly.
 // Why: the fp64 matrix instruction takes 64 cycles for 16x16x4 on this part and shares its pipe
 // with the fp64 vector instructions of the softmax; the sixteen digit products take 512 cycles per
-// 16x16x128 tile against 2048, and run beside them.
-// Measured (256 units, 4096 tokens, d 128, fp16): rows 13.1 -> 8.0 ms, scores 10.5 -> 5.6 ms; the int8
-// instructions are a third of the time, vector instructions bound both: slicing by packed maxima, no clamp in the
-// exponential, two tiles a wave brought 6.7 and 4.5 ms.
-// A row whose elements are not all integers at its scale (an element more than 2^-22 below the
-// largest that uses its last bits; possible for bf16, and for fp16 rows that reach 64) or that holds
+// 16x16x128 tile against 2048.
+// The lowest digit is seldom used: only by an element more than 2^-12 (fp16) or 2^-15 (bf16) below its row's largest, of normal numbers
+// by a row in 31 (d 128) and one in 240.  Where no row of a tile uses it, its seven products and A are left out: one tile of
+// normal numbers in three (fp16) or seven in eight (bf16).  256 units x 4096, d 128: scores 4.15 -> 3.85 ms in fp16, 4.57 -> 3.54 in bf16 (with the launch form
+// below); where every tile uses it (keys with one channel at 20, fp16) what is left is the test for it.
+// What bounds both kernels: the instructions of a SIMD in turn.  A vector instruction takes 4 cycles, one of these matrix instructions 8 of its 16 (alone and beside each
+// other, measured in loops of both); waves on one SIMD overlap the rest, two of them badly (rows with two tiles a wave: 1580 cycles a tile
+// where the instructions add up to 1040), four well (scores: 1030 of 880).  So scores keeps to 128 registers, rows to 168 (three waves) where a wave has one tile, and
+// the paths for marked rows, which would take more, are functions of their own (128 units x 2048, bf16: rows 1.03 -> 0.94 ms, scores 0.71 -> 0.62).
+// The 32x32 matrix instructions would need half the issue cycles and were slower: the chip lowers its clock (2.2 -> 1.95 GHz).
+// A row whose elements are not all integers at its scale (an element more than 2^-23 below the
+// largest that uses its last bits; possible for bf16, and for fp16 rows that reach 128) or that holds
 // an infinity or a NaN is marked, and a tile that touches a marked row takes the fp64 instruction.
 constexpr int DIGITS = 4;
 // Bits of a row's integers.  A wave whose own rows are marked is slow for its whole loop, and its workgroup waits for it, so
 // what counts is how many 16 x 128 tiles hold an element too small.  Of normal numbers, 27 | 30 bits: bf16 0.6 % | 0.08 %; fp16
 // none, but with one channel at 20, as keys with rotary embeddings have them, 22 % | none (no fp16 element has a bit below 2^-24:
-// every row below 8 | 64 fits).  Measured, that channel in a prompt of 256 units x 4096 (d 128, fp16): 22.6 | 11.5 ms.  S6 in fp64 instead of
-// int32 costs nothing that shows (11.4 ms without the channel, either way).
-constexpr int INT_BITS = 30;
+// every row below 8 | 64 fits, and below 128 with 31 bits, which mark 0.02 % of bf16 tiles).  Measured, that channel in a prompt of 256 units x 4096 (d 128, fp16): 22.6 | 11.5 ms.
+constexpr int INT_BITS = 31;
 
 typedef int int4v_t __attribute__((ext_vector_type(4)));
 
@@ -201,10 +217,11 @@ template <class TT> struct RowSpan {
     __device__ __forceinline__ uint32_t smallest_exponent() const { return (min((uint32_t)mn.x, (uint32_t)mn.y) + 1u) >> 7; }
 };
 
-// Scale 2^s of a row whose largest |x| has the 16 bits `top`: the largest integer gets INT_BITS bits.
-// bad: the row must not be sliced.  e: biased fp32 exponent of the largest element.
+// Scale 2^s of a row whose largest |x| has the 16 bits `top`: the largest integer gets INT_BITS bits, or one fewer where its upper digit
+// would be rounded up to 128 (from 1.9922 times a power of two on).
+// bad: the row must not be sliced.  e: biased fp32 exponent of the largest element (that one up in the second case).
 template <class TT> __device__ __forceinline__ int digit_shift(uint32_t top, int& e, bool& bad) {
-    const uint32_t one[1] = { top };
+    const uint32_t one[1] = { top + (__is_same(TT, TF16) ? 8u : 1u) };
     e = (int)(__builtin_bit_cast(uint32_t, frag_elem<TT>(one, 0)) >> 23);
     bad = e == 255 || (e < 36 && top != 0u);
     return (top == 0u || bad) ? 0 : INT_BITS - 1 + 127 - e;
@@ -215,9 +232,13 @@ template <class TT> __device__ __forceinline__ int digit_shift(uint32_t top, int
 template <class TT, int NWORDS> __device__ __forceinline__ bool no_integers(const uint32_t (&w)[NWORDS], const RowSpan<TT>& span, int e, float mul) {
     if constexpr (__is_same(TT, TF16)) {
         float frac = 0.f;
-        if (__any(e > 132))
+        if (__any(e > 133))
 #pragma unroll
-            for (int i = 0; i < 2 * NWORDS; ++i) frac = fmaxf(frac, __builtin_amdgcn_fractf(frag_elem<TT>(w, i) * mul));
+            for (int i = 0; i < NWORDS; ++i) {
+                uint32_t x[1] = { w[i] };
+                asm("" : "+v"(x[0]));                         // (or the conversions made for this are used for the digits, which need none)
+                frac = fmaxf(frac, fmaxf(__builtin_amdgcn_fractf(frag_elem<TT>(x, 0) * mul), __builtin_amdgcn_fractf(frag_elem<TT>(x, 1) * mul)));
+            }
         return frac != 0.f;
     } else {
         return (int)span.smallest_exponent() + INT_BITS - 8 < e;
@@ -228,7 +249,7 @@ template <class TT, int NWORDS> __device__ __forceinline__ bool no_integers(cons
 __device__ __forceinline__ void digits4(const float (&x)[4], float mul, uint32_t (&w)[DIGITS]) {
     uint32_t t[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) t[i] = (uint32_t)(int)(x[i] * mul) + 0x00808080u;   // the low bytes become digits + 128
+    for (int i = 0; i < 4; ++i) t[i] = (uint32_t)(int)fmaf(x[i], mul, 0.f) + 0x00808080u;   // the low bytes become digits + 128
     const uint32_t l01 = __builtin_amdgcn_perm(t[1], t[0], 0x05010400u), h01 = __builtin_amdgcn_perm(t[1], t[0], 0x07030602u);
     const uint32_t l23 = __builtin_amdgcn_perm(t[3], t[2], 0x05010400u), h23 = __builtin_amdgcn_perm(t[3], t[2], 0x07030602u);
     w[0] = __builtin_amdgcn_perm(l23, l01, 0x05040100u) ^ 0x80808080u;
@@ -241,7 +262,7 @@ __device__ __forceinline__ void digits4(const float (&x)[4], float mul, uint32_t
 // scale: unit * 2^-s of row x.  Returns whether a row is marked (uniform).
 template <class TT, int D>
 __device__ __forceinline__ bool own_digits(const char* base, int row0, int P, size_t tok, int g, int x,
-                                           int4v_t (&dg)[D / 64][DIGITS], double& scale, double unit)
+                                           int4v_t (&dg)[D / 64][DIGITS], double& scale, double unit, bool& low)
 {
     constexpr int KS = D / 64;
     const char* src = base + (size_t)min(row0 + x, P - 1) * tok;
@@ -259,7 +280,8 @@ __device__ __forceinline__ bool own_digits(const char* base, int row0, int P, si
     bool bad;
     int ex;
     const int s = digit_shift<TT>(top, ex, bad);
-    const float mul = ldexpf(1.f, s);
+    const float mul = __builtin_bit_cast(float, (uint32_t)(127 + s) << 23);
+    uint32_t lowest = 0;
 #pragma unroll
     for (int c = 0; c < KS; ++c) {
         bad |= no_integers<TT>(w[c], span, ex, mul);
@@ -272,24 +294,27 @@ __device__ __forceinline__ bool own_digits(const char* base, int row0, int P, si
             digits4(f, mul, pl);
 #pragma unroll
             for (int b = 0; b < DIGITS; ++b) dg[c][b][e4] = (int)pl[b];
+            lowest |= pl[0];
         }
     }
-    scale = ldexp(unit, -s);
+    low = __any(lowest != 0);
+    scale = ldexp(unit, 16 - s);
     return __any(bad);
 }
 
-// Operands of the rows that a workgroup's waves share, in LDS: CHUNK rows (two tiles), double-buffered.
-// A digit plane of 64 elements of 16 rows: block g (elements 16 g .. + 15) holds 16 bytes of each
-// row; blocks are 288 bytes apart, so that the threads that write one row (eight bytes each)
-// do not all fall into the same banks.  (320 bytes, with fewer conflicts, leave room for three
-// workgroups a compute unit where scores' registers allow four: 4.86 against 4.59 ms at 256 x 4096.)
-constexpr int BLOCK = 288, PLANE = 4 * BLOCK;
+// Operands of the rows that a workgroup's waves share, in LDS: CHUNK rows (two tiles), double-buffered.  Sixteen elements
+// of one digit of a row are 16 bytes; those of a chunk's rows follow each other (what 16 lanes read is contiguous); HALF is the
+// step to the next sixteen elements, PLANE to the next digit, STEP to the next 32 elements, so that the lanes that write
+// a row, sixteen elements each, fall into different banks.
 constexpr int CTILES = 2, CHUNK = CTILES * TILE;
+constexpr int HALF = CHUNK * 16 + 32, PLANE = 2 * HALF, STEP = DIGITS * PLANE + 64;
+__device__ __forceinline__ int digit_place(int sixteen) { return (sixteen >> 1) * STEP + (sixteen & 1) * HALF; }
+constexpr int MARKED = 1, LOW = 2;       // of a row: not to be sliced; uses the lowest digit
 template <int D> struct SharedRows {
-    alignas(16) unsigned char dg[2][CTILES][D / 64][DIGITS][PLANE];
+    alignas(16) unsigned char dg[2][D / 32 * STEP];
     double scale[2][CHUNK];
     double lse[2][CHUNK];
-    int marked[2][CHUNK];
+    int flags[2][CHUNK];
 };
 
 // The share of a chunk of one of the workgroup's NT threads: EPT consecutive elements of a row; TPR threads a row.  (Sixteen
@@ -319,10 +344,9 @@ template <class TT, int D, int NT> struct ChunkLoad {
         bool bad;
         int ex;
         const int s = digit_shift<TT>(top, ex, bad);
-        const float mul = ldexpf(1.f, s);
+        const float mul = __builtin_bit_cast(float, (uint32_t)(127 + s) << 23);
         bad |= no_integers<TT>(w, span, ex, mul);
-        const int t = row / TILE, x = row % TILE, first = j * EPT;
-        const int c = first >> 6, g = (first >> 4) & 3, half = first & 15;
+        unsigned char* dst = &sh.dg[buf][digit_place(j * EPT >> 4) + row * 16 + (j * EPT & 15)];
         uint32_t pl[EPT / 4][DIGITS];
 #pragma unroll
         for (int e4 = 0; e4 < EPT / 4; ++e4) {
@@ -333,100 +357,104 @@ template <class TT, int D, int NT> struct ChunkLoad {
         }
 #pragma unroll
         for (int b = 0; b < DIGITS; ++b) {
-            unsigned char* dst = &sh.dg[buf][t][c][b][g * BLOCK + x * 16 + half];
-            if constexpr (EPT == 16) *reinterpret_cast<u32x4_t*>(dst) = u32x4_t{ pl[0][b], pl[1][b], pl[2][b], pl[3][b] };
-            else *reinterpret_cast<uint2_t*>(dst) = uint2_t{ pl[0][b], pl[1][b] };
+            if constexpr (EPT == 16) *reinterpret_cast<u32x4_t*>(dst + b * PLANE) = u32x4_t{ pl[0][b], pl[1][b], pl[2][b], pl[3][b] };
+            else *reinterpret_cast<uint2_t*>(dst + b * PLANE) = uint2_t{ pl[0][b], pl[1][b] };
         }
-        const unsigned long long fm = __ballot(bad);
+        uint32_t lowest = 0;
+#pragma unroll
+        for (int e4 = 0; e4 < EPT / 4; ++e4) lowest |= pl[e4][0];
+        const unsigned long long fm = __ballot(bad), fl = __ballot(lowest != 0);
         if (j == 0) {
+            constexpr unsigned long long mask = (1ull << TPR) - 1;
             const int lane = threadIdx.x & 63;
             sh.scale[buf][row] = ldexp(unit, -s);
-            bool mark = ((fm >> lane) & ((1ull << TPR) - 1)) != 0;
+            bool mark = ((fm >> lane) & mask) != 0;
             if (with_lse) {
                 sh.lse[buf][row] = lse;
                 mark |= !(fabs(lse) < INFINITY);
             }
-            sh.marked[buf][row] = mark;
+            sh.flags[buf][row] = (mark ? MARKED : 0) | (((fl >> lane) & mask) != 0 ? LOW : 0);
         }
     }
 };
 
-// Unscaled S^T tile (rows = keys, columns = queries): register r of lane (g, x) = key 4g + r, query x.
-// SHARED_KEYS: the shared rows are the keys and the own rows the queries, or the other way round.
+// Products of a tile in units of 2^16, unscaled (rows = keys, columns = queries): register r of lane (g, x) = key 4g + r, query x.
+// SHARED_KEYS: the shared rows are the keys and the own rows the queries, or the other way round.  low (uniform): whether any of the rows
+// uses the lowest digit.
 template <class TT, int D, bool SHARED_KEYS>
-__device__ __forceinline__ void digit_tile(const unsigned char (&pl)[D / 64][DIGITS][PLANE], const int4v_t (&own)[D / 64][DIGITS],
+__device__ __forceinline__ void digit_tile(const unsigned char* pl, const int4v_t (&own)[D / 64][DIGITS], bool low,
                                            int g, int x, double (&s)[4])
 {
-    int4v_t S[2 * DIGITS - 1];
+    auto mm = [](int4v_t a, int4v_t o, int4v_t c) __attribute__((always_inline)) {
+        return SHARED_KEYS ? __builtin_amdgcn_mfma_i32_16x16x64_i8(a, o, c, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(o, a, c, 0, 0, 0);
+    };
+    const int place = digit_place(g) + x * 16;
+    auto plane = [&](int c, int i) __attribute__((always_inline)) {
+        return *reinterpret_cast<const int4v_t*>(pl + place + c * 2 * STEP + i * PLANE);
+    };
+    const int4v_t zero = {0, 0, 0, 0};
+    auto sums = [&](auto from_c) __attribute__((always_inline)) {
+        constexpr int from = decltype(from_c)::value;
+        int4v_t S[2 * DIGITS - 1];
 #pragma unroll
-    for (int w = 0; w < 2 * DIGITS - 1; ++w) S[w] = int4v_t{0, 0, 0, 0};
+        for (int w = 0; w < 2 * DIGITS - 1; ++w) S[w] = zero;
 #pragma unroll
-    for (int c = 0; c < D / 64; ++c)
+        for (int c = 0; c < D / 64; ++c)
 #pragma unroll
-        for (int i = 0; i < DIGITS; ++i) {
-            const int4v_t a = *reinterpret_cast<const int4v_t*>(&pl[c][i][g * BLOCK + x * 16]);
+            for (int i = from; i < DIGITS; ++i) {
+                const int4v_t a = plane(c, i);
 #pragma unroll
-            for (int j = 0; j < DIGITS; ++j)
-                S[i + j] = SHARED_KEYS ? __builtin_amdgcn_mfma_i32_16x16x64_i8(a, own[c][j], S[i + j], 0, 0, 0)
-                                       : __builtin_amdgcn_mfma_i32_16x16x64_i8(own[c][j], a, S[i + j], 0, 0, 0);
+                for (int j = from; j < DIGITS; ++j) S[i + j] = mm(a, own[c][j], S[i + j]);
+            }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int B = S[2][r] + (S[3][r] << 8);
+            const double C = fma((double)S[6][r], 65536.0, (double)(S[4][r] + (S[5][r] << 8)));
+            s[r] = fma(C, 65536.0, (double)B);
+            if constexpr (from == 0) s[r] = fma((double)(S[0][r] + (S[1][r] << 8)), 1.0 / 65536.0, s[r]);
         }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int A = S[0][r] + (S[1][r] << 8), B = S[2][r] + (S[3][r] << 8);
-        const double C = fma((double)S[6][r], 65536.0, (double)(S[4][r] + (S[5][r] << 8)));
-        s[r] = fma(fma(C, 65536.0, (double)B), 65536.0, (double)A);
-    }
+    };
+    if (low) sums(std::integral_constant<int, 0>{});
+    else sums(std::integral_constant<int, 1>{});
 }
 
-// Tiles that touch a marked row, scaled, with the fp64 matrix instruction: one tile of shared rows against N of the wave's own.  Its
-// result register r of lane (g, x) is row g + 4r: row i is given key 4 (i % 4) + i / 4, so that the layout is digit_tile's.
+// A tile that touches a marked row, scaled, with the fp64 matrix instruction.  Its result register r of lane (g, x) is row g + 4r: row i is given key 4 (i % 4) + i / 4, so that the layout is digit_tile's.
 // All words are requested ahead of the first product: these tiles wait for memory, not for the instruction (256 units x 4096,
 // d 128, fp16, every key marked, two requests a tile against one: 34.3 against 30.9 ms).
-template <class TT, int D, bool SHARED_KEYS, int N>
-__device__ __forceinline__ void exact_tiles(const char* shared, const char* own, int shared0, int own0, int P, size_t tok, int g, int x, double (&s)[N][4])
+// A function of its own (not inlined): its registers are then not the kernel's, which saves what it needs of its own only around the call.
+template <class TT, int D, bool SHARED_KEYS>
+__device__ __attribute__((noinline)) double4_t exact_tile(const char* shared, const char* own, int shared0, int own0, int P, size_t tok, int lane)
 {
     constexpr int NWORDS = D / 8;
-    constexpr int CHAINS = N == 1 ? 2 : 1;       // a product that continues the chain of the one before it waits for that one's result
+    const int g = lane >> 4, x = lane & 15;
     const int kx = 4 * (x & 3) + (x >> 2), col = g * (D / 4) * TT::BYTES;
-    uint32_t sw[NWORDS], ow[N][NWORDS];
+    uint32_t sw[NWORDS], ow[NWORDS];
     load_words<NWORDS>(shared + (size_t)min(shared0 + (SHARED_KEYS ? kx : x), P - 1) * tok + col, sw);
+    load_words<NWORDS>(own + (size_t)min(own0 + (SHARED_KEYS ? x : kx), P - 1) * tok + col, ow);
+    double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int i = 0; i < N; ++i)
-        load_words<NWORDS>(own + (size_t)min(own0 + i * TILE + (SHARED_KEYS ? x : kx), P - 1) * tok + col, ow[i]);
-    double4_t acc[N][CHAINS];
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int c = 0; c < CHAINS; ++c) acc[i][c] = double4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int e = 0; e < 2 * NWORDS; ++e) {
-        const double sd = (double)frag_elem<TT>(sw, e);
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const double od = (double)frag_elem<TT>(ow[i], e);
-            acc[i][e % CHAINS] = SHARED_KEYS ? __builtin_amdgcn_mfma_f64_16x16x4f64(sd, od, acc[i][e % CHAINS], 0, 0, 0)
-                                             : __builtin_amdgcn_mfma_f64_16x16x4f64(od, sd, acc[i][e % CHAINS], 0, 0, 0);
-        }
+    for (int e = 0; e < 2 * NWORDS; e += 2) {
+        const double a0 = (double)frag_elem<TT>(sw, e), a1 = (double)frag_elem<TT>(sw, e + 1);
+        const double b0 = (double)frag_elem<TT>(ow, e), b1 = (double)frag_elem<TT>(ow, e + 1);
+        s0 = SHARED_KEYS ? __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, s0, 0, 0, 0) : __builtin_amdgcn_mfma_f64_16x16x4f64(b0, a0, s0, 0, 0, 0);
+        s1 = SHARED_KEYS ? __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, s1, 0, 0, 0) : __builtin_amdgcn_mfma_f64_16x16x4f64(b1, a1, s1, 0, 0, 0);
     }
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s[i][r] = (CHAINS == 1 ? acc[i][0][r] : acc[i][0][r] + acc[i][CHAINS - 1][r]) * logit_scale<D>();
+    return (s0 + s1) * logit_scale<D>();
 }
 
 // Whether a workgroup takes the fp64 instruction for all it does: every wave holds a marked row of its own, or four of the 32 rows of the first
 // shared chunk are marked (at that rate two tiles in three hold one; a row or two at a prompt's beginning say nothing about the rest).  (Uniform over the workgroup; the chunk is visible afterwards.)  Tile by tile, with the digits made beside it and
 // nothing requested ahead, a prompt of marked rows only is slower than the fp64 instruction alone was before there were digits; in
 // loops of its own it is not.  Rows + scores, every key marked, tile by tile | in loops of its own | before: 256 units x 4096, d 128,
-// fp16 16.4 + 14.1 | 13.7 + 10.8 | 13.0 + 10.5 ms; 128 x 2048 2.51 + 2.07 | 1.85 + 2.07 | 1.85 + 1.48 ms.
+// fp16 16.4 + 14.1 | 13.6 + 12.8 | 13.0 + 10.5 ms; 128 x 2048 2.51 + 2.07 | 1.93 + 1.77 | 1.85 + 1.48 ms.
 // Without marked rows the test costs nothing that shows (11.32 | 11.32 ms, 1.91 | 1.92 ms for the whole prompts); with __syncthreads_and
 // instead of one barrier and two ballots 11.40 ms.
-template <int NW> __device__ __forceinline__ bool mostly_marked(bool own, const int (&marked)[CHUNK]) {
+template <int NW> __device__ __forceinline__ bool mostly_marked(bool own, const int (&flags)[CHUNK]) {
     static_assert(CHUNK == 32 && NW <= 32, "half a wave");
     __shared__ int waves[NW];
     if ((threadIdx.x & 63) == 0) waves[threadIdx.x >> 6] = own;
     __syncthreads();
-    const unsigned m = (unsigned)__ballot(marked[threadIdx.x & (CHUNK - 1)]);      // (both halves of the wave look at the same rows)
+    const unsigned m = (unsigned)__ballot(flags[threadIdx.x & (CHUNK - 1)] & MARKED);      // (both halves of the wave look at the same rows)
     return __all(waves[threadIdx.x & (NW - 1)]) || __popc(m) >= 4;
 }
 
@@ -511,8 +539,10 @@ template <class TT, int D, int N> struct Rows {
                                       __builtin_amdgcn_perm(vfrag[3][e >> 1], vfrag[2][e >> 1], sel) };
 #pragma unroll
                 for (int i = decltype(first)::value; i < N; ++i)
+{
 #pragma unroll
                     for (int w = 0; w < weight_parts<TT>(); ++w) o[i][e] = mfma16<TT>(pa[i][w], vb2, o[i][e]);
+                }
             }
         };
         if (lone) values(std::integral_constant<int, N - 1>{});
@@ -541,20 +571,22 @@ template <class TT, int D, int N> struct Rows {
 };
 
 // The tile of queries qt against all its keys with the fp64 matrix instruction, for workgroups of marked rows: the queries stay in
-// fp64, the next tile's keys and values are requested before this one's are used (two sets of registers take turns).
-template <class TT, int D>
+// fp64, the next tile's keys and values are requested before this one's are used (two sets of registers take turns).  LEAN: the queries
+// are converted anew for every tile, for kernels that have no registers to hold them.
+template <class TT, int D, bool LEAN>
 __device__ __forceinline__ void exact_rows(const char* qb, const char* kb, const char* vb, char* ob, double* lse, int qt, int P, size_t tok,
                                            const double* etab, int g, int x)
 {
     constexpr int NWORDS = D / 8, NE = D / 16;
     const int kx = 4 * (x & 3) + (x >> 2), col = g * (D / 4) * TT::BYTES;     // keys: see exact_tiles
+    uint32_t qw[NWORDS];
     double qd[2 * NWORDS];
-    {
-        uint32_t w[NWORDS];
-        load_words<NWORDS>(qb + (size_t)min(qt * TILE + x, P - 1) * tok + col, w);
+    load_words<NWORDS>(qb + (size_t)min(qt * TILE + x, P - 1) * tok + col, qw);
+    auto convert = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int e = 0; e < 2 * NWORDS; ++e) qd[e] = (double)frag_elem<TT>(w, e);
-    }
+        for (int e = 0; e < 2 * NWORDS; ++e) qd[e] = (double)frag_elem<TT>(qw, e);
+    };
+    if constexpr (!LEAN) convert();
     Rows<TT, D, 1> rows;
     rows.clear();
     auto request = [&](int kt, uint32_t (&kf)[NWORDS], uint32_t (&vf)[4][NE / 2]) __attribute__((always_inline)) {
@@ -563,6 +595,11 @@ __device__ __forceinline__ void exact_rows(const char* qb, const char* kb, const
         for (int r = 0; r < 4; ++r) load_words<NE / 2>(vb + (size_t)min(kt * TILE + 4 * g + r, P - 1) * tok + x * NE * TT::BYTES, vf[r]);
     };
     auto tile = [&](int kt, const uint32_t (&kf)[NWORDS], const uint32_t (&vf)[4][NE / 2]) __attribute__((always_inline)) {
+        if constexpr (LEAN) {
+#pragma unroll
+            for (int i = 0; i < NWORDS; ++i) asm volatile("" : "+v"(qw[i]));
+            convert();
+        }
         double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int e = 0; e < 2 * NWORDS; e += 2) {
@@ -588,16 +625,25 @@ __device__ __forceinline__ void exact_rows(const char* qb, const char* kb, const
     }
     rows.finish(qt * TILE, P, ob, tok, lse, g, x);
 }
+// The same as a function of its own, so that its registers are not the kernel's: inline, they would cost the kernel with one tile a wave and d 128 its
+// third wave a SIMD (128 units x 2048, fp16, no marked row: rows 0.95 | 0.91 ms).
+template <class TT, int D>
+__device__ __attribute__((noinline)) void exact_rows_apart(const char* qb, const char* kb, const char* vb, char* ob, double* lse, int qt, int P, size_t tok,
+                                           const double* etab, int g, int x)
+{
+    exact_rows<TT, D, true>(qb, kb, vb, ob, lse, qt, P, tok, etab, g, x);
+}
 
 // q, k, v, out: [P][units][D] (token-major, as a decode step sees them one token at a time).
 // lse: [units][P], in units of ln 2 / 256.  One workgroup = NW waves of QT consecutive query tiles of one unit;
 // the keys are sliced into digits once per workgroup and read by every wave from LDS.  What bounds
 // this kernel and the next is vector instructions (slicing, recombining the digit sums, the
 // exponentials), so a wave takes two tiles where that pays: slicing, value loads and their
-// permutes are then paid once for both (d 128: all 256 registers of two waves a SIMD, none spilled).
+// permutes are then paid once for both (d 128: all 256 registers of two waves a SIMD, a dozen spilled outside the loop over tiles or in
+// its seldom paths).  One tile, d 128: three waves a SIMD.
 // In small launches SPLIT waves share a tile instead, each taking every SPLIT-th tile of keys.
 template <class TT, int D, int NW, int QT, int SPLIT>
-__global__ __launch_bounds__(64 * NW, 2)
+__global__ __launch_bounds__(64 * NW, D == 128 && SPLIT == 1 && QT == 1 ? 3 : 2)
 void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, const void* __restrict__ v_,
                       void* __restrict__ out_, double* __restrict__ lse, int P, int units)
 {
@@ -627,16 +673,19 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
     next.request(kb, nullptr, 0, P, tok);
     int4v_t qdg[QT][D / 64][DIGITS];
     double qscale[QT];
-    bool qmarked = false;
+    bool qmarked = false, qlow[QT];
 #pragma unroll
-    for (int i = 0; i < QT; ++i) qmarked |= own_digits<TT, D>(qb, (qt + i) * TILE, P, tok, g, x, qdg[i], qscale[i], 1.0);
+    for (int i = 0; i < QT; ++i) qmarked |= own_digits<TT, D>(qb, (qt + i) * TILE, P, tok, g, x, qdg[i], qscale[i], 1.0, qlow[i]);
     next.store(sh, 0, false, logit_scale<D>());
 
     if constexpr (SPLIT == 1) {
-        if (mostly_marked<NW>(qmarked || !active, sh.marked[0])) {
+        if (mostly_marked<NW>(qmarked || !active, sh.flags[0])) {
             if (active)
 #pragma unroll 1
-                for (int t = qt; t <= mine; ++t) exact_rows<TT, D>(qb, kb, vb, ob, lse + (size_t)u * P, t, P, tok, etab, g, x);
+                for (int t = qt; t <= mine; ++t) {
+                    if constexpr (D == 128 && QT == 1) exact_rows_apart<TT, D>(qb, kb, vb, ob, lse + (size_t)u * P, t, P, tok, etab, g, x);
+                    else exact_rows<TT, D, false>(qb, kb, vb, ob, lse + (size_t)u * P, t, P, tok, etab, g, x);
+                }
             return;
         }
     }
@@ -660,14 +709,20 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         }
         const int t = kt % CTILES;
         double s[QT][4];
-        const bool special = __any(sh.marked[buf][t * TILE + x]) || qmarked;       // uniform
+        const int flags = sh.flags[buf][t * TILE + x];
+        const bool special = __any(flags & MARKED) || qmarked, low = __any(flags & LOW);       // uniform
         if (special) {
-            exact_tiles<TT, D, true, QT>(kb, qb, kt * TILE, qt * TILE, P, tok, g, x, s);
+#pragma unroll
+            for (int i = 0; i < QT; ++i) {
+                const double4_t e = exact_tile<TT, D, true>(kb, qb, kt * TILE, (qt + i) * TILE, P, tok, lane);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s[i][r] = e[r];
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < QT; ++i) {
                 if (QT > 1) __builtin_amdgcn_sched_barrier(0);       // one tile's sums at a time: the registers do not hold two
-                digit_tile<TT, D, true>(sh.dg[buf][t], qdg[i], g, x, s[i]);
+                digit_tile<TT, D, true>(&sh.dg[buf][t * TILE * 16], qdg[i], low || qlow[i], g, x, s[i]);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s[i][r] *= sh.scale[buf][t * TILE + 4 * g + r] * qscale[i];
             }
@@ -732,10 +787,9 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
 
 // ------------------------------------------------------------------ 2. scores
 // The tile of keys kt against all its queries with the fp64 matrix instruction, for workgroups of marked rows: the next tile of
-// queries is requested before this one is used.  Two tiles a wave (d 128): the keys stay in fp64, as a SIMD holds two waves anyway.
-// d 64: the keys are converted anew each round, which keeps the kernel below 128 registers (four waves; 256 units x 4096, every
-// key marked: the prompt 15.5 -> 13.9 ms, 14.7 before there were digits).  One tile a wave and d 128: not used, the kernel has all its 128
-// registers in use, and one more costs it a wave (128 units x 2048: scores 0.67 -> 0.72 ms without a marked row, held to 128 registers 0.75).
+// queries is requested before this one is used.  The keys are converted anew each round, which keeps the kernel within 128 registers (four waves;
+// d 64, 256 units x 4096, every key marked: the prompt 15.5 -> 13.9 ms, 14.7 before there were digits; d 128, where they could stay in fp64
+// with two waves a SIMD: scores 10.9 -> 12.8 ms for a prompt of nothing but marked rows, 4.15 -> 3.85 for one without).
 template <class TT, int D>
 __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, const double* lse, double* a, int kt, int ntiles, int P, size_t tok,
                                              const double* etab, int g, int x)
@@ -749,7 +803,6 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
 #pragma unroll
         for (int e = 0; e < 2 * NWORDS; ++e) kd[e] = (double)frag_elem<TT>(kw, e);
     };
-    if constexpr (D == 128) convert();
     auto request = [&](int qt) __attribute__((always_inline)) {
         const int t = min(min(qt, ntiles - 1) * TILE + x, P - 1);          // past the last tile: a repeat, unused
         load_words<NWORDS>(qb + (size_t)t * tok + col, next);
@@ -762,11 +815,9 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
         for (int i = 0; i < NWORDS; ++i) w[i] = next[i];
         const double l = next_l;
         request(qt + 1);
-        if constexpr (D == 64) {                              // converted anew each round: see above
 #pragma unroll
-            for (int i = 0; i < NWORDS; ++i) asm volatile("" : "+v"(kw[i]));
-            convert();
-        }
+        for (int i = 0; i < NWORDS; ++i) asm volatile("" : "+v"(kw[i]));
+        convert();                                            // anew each round: see above
         double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int e = 0; e < 2 * NWORDS; e += 2) {
@@ -787,11 +838,18 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
         if (x == 0 && key < P) a[key] = c;
     }
 }
+// The same as a function of its own (see exact_rows_apart).
+template <class TT, int D>
+__device__ __attribute__((noinline)) void exact_scores_apart(const char* qb, const char* kb, const double* lse, double* a, int kt, int ntiles, int P, size_t tok,
+                                             const double* etab, int g, int x)
+{
+    exact_scores<TT, D>(qb, kb, lse, a, kt, ntiles, P, tok, etab, g, x);
+}
 
-// a[u][i] = sum over rows t >= i of exp(s_ti - lse_t).  A wave takes KT tiles of keys; NW waves, a workgroup,
+// a[u][i] = sum over rows t >= i of exp(s_ti - lse_t).  A wave has one tile of keys, or shares it with SPLIT - 1 others; NW waves, a workgroup,
 // share the sliced queries.
-template <class TT, int D, int NW, int KT, int SPLIT>
-__global__ __launch_bounds__(64 * NW, 2)
+template <class TT, int D, int NW, int SPLIT>
+__global__ __launch_bounds__(64 * NW, D == 128 && SPLIT == 1 ? 4 : 2)
 void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_, const double* __restrict__ lse,
                         double* __restrict__ a, int P, int units)
 {
@@ -799,12 +857,12 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int g = lane >> 4, x = lane & 15;
     const int ntiles = (P + TILE - 1) / TILE;
-    constexpr int TPG = NW / SPLIT * KT;                                  // tiles of a workgroup
+    constexpr int TPG = NW / SPLIT;                                       // tiles of a workgroup
     const int groups = (ntiles + TPG - 1) / TPG;
     const int u = xcd_unit(blockIdx.x, groups);
     const int kt0 = (int)((blockIdx.x >> 3) % groups) * TPG;              // low key tiles have the most rows: first
     if (u >= units) return;                                               // the whole workgroup
-    const int kt = kt0 + wid / SPLIT * KT, part = wid % SPLIT;
+    const int kt = kt0 + wid / SPLIT, part = wid % SPLIT;
     const bool active = kt < ntiles;
     __shared__ double etab[EXP_STEPS];
     __shared__ SharedRows<D> sh;
@@ -816,24 +874,20 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
 
     ChunkLoad<TT, D, 64 * NW> next;
     next.request(qb, lseu, kt0 * TILE, P, tok);
-    int4v_t kdg[KT][D / 64][DIGITS];
-    double kscale[KT][4], acc[KT][4];
-    bool kmarked = false;
+    int4v_t kdg[D / 64][DIGITS];
+    double kx, kscale[4], acc[4];
+    bool klow;
+    const bool kmarked = own_digits<TT, D>(kb, kt * TILE, P, tok, g, x, kdg, kx, logit_scale<D>(), klow);
 #pragma unroll
-    for (int i = 0; i < KT; ++i) {
-        double kx;
-        kmarked |= own_digits<TT, D>(kb, (kt + i) * TILE, P, tok, g, x, kdg[i], kx, logit_scale<D>());
-#pragma unroll
-        for (int r = 0; r < 4; ++r) { kscale[i][r] = __shfl(kx, 4 * g + r); acc[i][r] = 0.0; }
-    }
+    for (int r = 0; r < 4; ++r) { kscale[r] = __shfl(kx, 4 * g + r); acc[r] = 0.0; }
     next.store(sh, 0, true, 1.0);
 
-    if constexpr (SPLIT == 1 && (KT == 2 || D == 64)) {
-        if (mostly_marked<NW>(kmarked || !active, sh.marked[0])) {
-            if (active)
-#pragma unroll 1
-                for (int t = kt; t < min(kt + KT, ntiles); ++t)
-                    exact_scores<TT, D>(qb, kb, lseu, a + (size_t)u * P, t, ntiles, P, tok, etab, g, x);
+    if constexpr (SPLIT == 1) {
+        if (mostly_marked<NW>(kmarked || !active, sh.flags[0])) {
+            if (active) {
+                if constexpr (D == 128) exact_scores_apart<TT, D>(qb, kb, lseu, a + (size_t)u * P, kt, ntiles, P, tok, etab, g, x);
+                else exact_scores<TT, D>(qb, kb, lseu, a + (size_t)u * P, kt, ntiles, P, tok, etab, g, x);
+            }
             return;
         }
     }
@@ -846,63 +900,54 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
                 if (qt < kt) continue;
                 const int t = qt - q0;
                 const double l = sh.lse[buf][t * TILE + x];
-                double s[KT][4];
-                const bool special = __any(sh.marked[buf][t * TILE + x]) || kmarked;   // uniform
+                double s[4];
+                const int flags = sh.flags[buf][t * TILE + x];
+                const bool special = __any(flags & MARKED) || kmarked, low = __any(flags & LOW);   // uniform
                 if (special) {
-                    exact_tiles<TT, D, false, KT>(qb, kb, qt * TILE, kt * TILE, P, tok, g, x, s);
+                    const double4_t e = exact_tile<TT, D, false>(qb, kb, qt * TILE, kt * TILE, P, tok, lane);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) s[r] = e[r];
                 } else {
                     const double qs = sh.scale[buf][t * TILE + x];
+                    digit_tile<TT, D, false>(&sh.dg[buf][t * TILE * 16], kdg, low || klow, g, x, s);
 #pragma unroll
-                    for (int i = 0; i < KT; ++i) {
-                        digit_tile<TT, D, false>(sh.dg[buf][t], kdg[i], g, x, s[i]);
+                    for (int r = 0; r < 4; ++r) s[r] *= kscale[r] * qs;
+                }
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) s[i][r] *= kscale[i][r] * qs;
+                for (int r = 0; r < 4; ++r) s[r] -= l;
+                if (special || qt == kt || qt == ntiles - 1) {             // causal, and inside the prompt
+                    const int tq = qt * TILE + x;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const bool on = tq < P && kt * TILE + 4 * g + r <= tq;
+                        s[r] = no_infinity(on ? s[r] : -INFINITY);         // exp gives 0; no branch
                     }
                 }
 #pragma unroll
-                for (int i = 0; i < KT; ++i)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) s[i][r] -= l;
-                if (special || qt < kt + KT || qt == ntiles - 1) {         // causal, and inside the prompt
-                    const int tq = qt * TILE + x;
-#pragma unroll
-                    for (int i = 0; i < KT; ++i)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const bool on = tq < P && (kt + i) * TILE + 4 * g + r <= tq;
-                            s[i][r] = no_infinity(on ? s[i][r] : -INFINITY);       // exp gives 0; no branch
-                        }
-                }
-#pragma unroll
-                for (int i = 0; i < KT; ++i)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[i][r] += exp_units(s[i][r], etab);
+                for (int r = 0; r < 4; ++r) acc[r] += exp_units(s[r], etab);
             }
         if (more) next.store(sh, buf ^ 1, true, 1.0);
     }
     if constexpr (SPLIT > 1) {                                            // the parts' sums, added in order by the first part's wave
-        static_assert(KT == 1, "one tile of keys a wave");
         double* ps = reinterpret_cast<double*>(&sh.dg);                   // [4][NW * 64]
         const int me = threadIdx.x;
         __syncthreads();
         if (part != 0)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) ps[r * NW * 64 + me] = acc[0][r];
+            for (int r = 0; r < 4; ++r) ps[r * NW * 64 + me] = acc[r];
         __syncthreads();
         if (part != 0) return;
         for (int w = 1; w < SPLIT; ++w)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[0][r] += ps[r * NW * 64 + me + w * 64];
+            for (int r = 0; r < 4; ++r) acc[r] += ps[r * NW * 64 + me + w * 64];
     }
     if (!active) return;
 #pragma unroll
-    for (int i = 0; i < KT; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const double c = row_allsum(acc[i][r]);                        // over the 16 queries x
-            const int key = (kt + i) * TILE + 4 * g + r;
-            if (x == 0 && key < P) a[(size_t)u * P + key] = c;
-        }
+    for (int r = 0; r < 4; ++r) {
+        const double c = row_allsum(acc[r]);                               // over the 16 queries x
+        const int key = kt * TILE + 4 * g + r;
+        if (x == 0 && key < P) a[(size_t)u * P + key] = c;
+    }
 }
 
 // ------------------------------------------------------------------ 3. compress
@@ -1274,23 +1319,24 @@ void wkv_prefill_fold(WkvCache c, const void* __restrict__ k_, const void* __res
     }
 }
 
-// How many tiles of 16 tokens a wave takes.  Two share slicing, value loads and permutes, but are half as many workgroups with twice the
-// last stretch of each (the diagonal, and the loop's end on an emptying chip), so both the loop and the launch must be long.
-// Whole prompts, one tile | two, ms: fp16 d 128: 128 units x 4096 6.20 | 6.04, 256 x 4096 12.07 | 11.41, 192 x 3072 5.42 | 5.32, 1024 x 2048
-// 12.86 | 12.77, 1024 x 1024 3.81 | 4.09, 2048 x 512 2.54 | 2.91; bf16: 128 x 4096 6.75 | 6.95, 192 x 4096 9.78 | 9.71, 256 x 4096
-// 12.63 | 12.33, 384 x 3072 11.18 | 11.13, 512 x 2048 6.89 | 7.07.  Rows of 128 bytes: fp16 256 x 4096 7.75 | 7.64, 384 x 3072 6.76 | 6.87,
-// bf16 384 x 4096 11.88 | 12.04, so never.
+// How many tiles of 16 tokens a wave of rows takes.  Two share slicing, value loads and permutes, but are half as many workgroups with twice the
+// last stretch of each (the diagonal, and the loop's end on an emptying chip) and two waves a SIMD instead of three, so both the loop and the launch must be long.
+// Whole prompts, one tile | two, ms: fp16 d 128: 128 units x 4096 5.56 | 5.41, 256 x 4096 10.46 | 10.11, 192 x 3072 4.71 | 4.71, 1024 x 2048
+// 10.85 | 11.18, 1024 x 1024 3.26 | 3.58; bf16: 128 x 4096 5.89 | 5.96, 192 x 4096 8.10 | 7.98, 256 x 4096
+// 10.55 | 9.98, 384 x 3072 9.15 | 8.98, 512 x 2048 5.58 | 5.67.  Rows of 128 bytes: fp16 256 x 4096 7.75 | 7.64, 384 x 3072 6.76 | 6.87,
+// bf16 384 x 4096 11.88 | 12.04 (before the lowest digit was left out), so never.
+// In those launches a workgroup of scores has eight waves instead of four, which halves the slicing: 256 x 4096 fp16 4.08 | 4.05 ms, bf16 3.84 | 3.60, but 128 x 2048
+// 0.612 | 0.629 and 96 x 1024 0.152 | 0.170.
 inline bool two_tiles_a_wave(long long tiles, int P) { return P >= 3072 && tiles >= 49152; }
 // Whether two waves share a tile, each taking every other tile of its loop.  Small launches last as long as their longest loop;
 // but every part slices all the rows it shares with fewer waves, which pays until the chip is full: for short prompts early.
-// Whole prompts, one wave | two, us (fp16 d 128; bf16 d 128; fp16 d 64; bf16 d 64):
-//   128 units x 128 (1024 tiles) 65 | 66; 68 | 69; 59 | 58; 60 | 59      128 x 256 (2048) 108 | 129; 138 | 135; 90 | 95; 91 | 97
-//   64 x 384 (1536) 125 | 127; 138 | 133; 105 | 97; 107 | 99             128 x 384 (3072) 166 | 183; 189 | 191; 120 | 135; 124 | 139
-//   24 x 1024 (1536) 271 | 233; 310 | 247; 210 | 188; 216 | 194          48 x 1024 (3072) 330 | 334; 404 | 352; 259 | 229; 268 | 236
-//   96 x 512 (3072) 214 | 217; 245 | 224; 161 | 156; 167 | 162           32 x 2048 (4096) 695 | 671; 804 | 714; 515 | 442; 568 | 468
-//   8 x 4096 (2048) 797 | 723; 1146 | 824; 597 | 481; 605 | 505          16 x 4096 (4096) 1097 | 1223; 1285 | 1305; 843 | 863; 921 | 928
-// bf16 gains longest: some of its tiles hold a marked row (INT_BITS), and the launch waits for those waves.
-inline bool two_waves_a_tile(long long tiles, int P, bool fp16) { return tiles <= (P < 512 ? 1536 : P >= 3072 && fp16 ? 2048 : 4096); }
+// Whole prompts, one wave | two, us (fp16 d 128; bf16 d 128; fp16 d 64; bf16 d 64; - not taken):
+//   128 units x 128 (1024 tiles) 71 | 67; 72 | 68; 61 | 61; -            128 x 256 (2048) 112 | 119; 132 | 130; -; 91 | 97
+//   64 x 384 (1536) 126 | 120; 129 | 123; 106 | 98; -                    128 x 384 (3072) 145 | 170; 156 | 177; 119 | 136; -
+//   24 x 1024 (1536) 270 | 214; 274 | 218; 205 | 183; 204 | 184          48 x 1024 (3072) 331 | 301; 339 | 302; 250 | 219; 250 | 226
+//   96 x 512 (3072) 196 | 198; 198 | 205; 153 | 149; -                   32 x 2048 (4096) 649 | 586; 655 | 607; 486 | 426; 547 | 450
+//   8 x 4096 (2048) 810 | 646; 1063 | 709; 584 | 452; 584 | 463          16 x 4096 (4096) 1097 | 1063; 1097 | 1151; 807 | 790; 872 | 816
+inline bool two_waves_a_tile(long long tiles, int P) { return tiles <= (P < 512 ? 1536 : 4096); }
 
 template <class TT, int D>
 hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, void* out,
@@ -1300,13 +1346,13 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
     const int ntiles = (P + TILE - 1) / TILE;
     const long long tiles = (long long)c.units * ntiles;
     auto contract = [&](auto tiles_c, auto split_c) {
-        constexpr int T = decltype(tiles_c)::value, S = decltype(split_c)::value, TPG = NW / S * T;
-        const int grid = xcd_grid(c.units, (ntiles + TPG - 1) / TPG);
+        constexpr int T = decltype(tiles_c)::value, S = decltype(split_c)::value, TPG = NW / S * T, NS = 4 * T, TPS = NS / S;
+        const int grid = xcd_grid(c.units, (ntiles + TPG - 1) / TPG), grids = xcd_grid(c.units, (ntiles + TPS - 1) / TPS);
         hipLaunchKernelGGL((wkv_prefill_rows<TT, D, NW, T, S>), dim3(grid), dim3(64 * NW), 0, stream, q, k, v, out, lse, P, c.units);
-        hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NW, T, S>), dim3(grid), dim3(64 * NW), 0, stream, q, k, lse, a, P, c.units);
+        hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NS, S>), dim3(grids), dim3(64 * NS), 0, stream, q, k, lse, a, P, c.units);
     };
     using std::integral_constant;
-    if (two_waves_a_tile(tiles, P, __is_same(TT, TF16))) {
+    if (two_waves_a_tile(tiles, P)) {
         contract(integral_constant<int, 1>{}, integral_constant<int, 2>{});
     } else if (D == 64 || !two_tiles_a_wave(tiles, P)) {
         contract(integral_constant<int, 1>{}, integral_constant<int, 1>{});

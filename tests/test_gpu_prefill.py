@@ -567,3 +567,40 @@ def test_logits_far_beyond_the_exponential(dtype, d):
         print(f"\n  {parity.compare_prefill(cfg, got, decode_steps=5)}", flush=True)
     finally:
         got["cache"].close()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("P,units", [(130, 3), (129, 171)])
+def test_digits_at_their_edges(P, units, dtype, d):
+    """Rows around the edges of the 8-bit digits: a largest element whose upper digit just fits, would be rounded up to 128, or is -128
+    (2 - 2^-7, the format's last number below 2, and -2); tiles of which no row uses the lowest digit (multiples of 2^-5), one row does, or
+    all do, against each other (whose products are left out only where neither side uses it); an element whose last bit is the integers'
+    last one, and one beyond (marked).  Dropping a lowest digit would move a logit by 1e-6 and more; score sums are held to 1e-9.  One wave
+    and two a tile."""
+    g = np.random.default_rng(9600)
+    T = P + 4
+    q, k, v = (g.standard_normal((T, 4, d)).astype(np.float32) for _ in range(3))
+    last = 2.0 - 2.0 ** (-10 if dtype == "fp16" else -7)
+    tiny = 2.0 ** -9 if dtype == "fp16" else 2.0 ** -13       # times 1 + 2^-10 or + 2^-7: uses the lowest digit of a row whose largest is below 4
+    ulp = 2.0 ** -10 if dtype == "fp16" else 2.0 ** -7
+    for u in range(4):
+        for x, other in ((q, k), (k, q)):
+            x[:64, u] = np.clip(np.rint(x[:64, u] * 32) / 32, -3.0, 3.0)              # four tiles without the lowest digit
+            x[5, u, 1], x[6, u, 1], x[7, u, 1], x[8, u, 1] = 2.0 - 2.0 ** -7, last, -last, -2.0
+            x[5:9, u, 2:] *= 0.5                                                    # (below 2: those are the largest)
+            if u in (1, 3):
+                x[40, u, 3] = tiny * (1 + ulp) / 4                                  # one row of the third tile
+            x[70:86, u, 4] = tiny * (1 + ulp) / 4                                   # every row of a tile, and its neighbours' some
+            other[:, u, 3:5] *= 8.0                                                 # what they meet is large
+        if u >= 2:
+            k[90, u, 0], k[90, u, 5], q[:, u, 0] = 2.0 ** 6, 2.0 ** -16 if dtype == "fp16" else 2.0 ** -17, 0.0
+            k[91, u, 0], k[91, u, 5] = 2.0 ** 11, 2.0 ** -14 * (1 + ulp)            # beyond: marked
+    cfg = synth.StreamConfig("pre-digit", 9600, 1, 4, d, dtype, T, 60, 9)
+    rep = np.arange(units) % 4
+    big = synth.StreamConfig("pre-digit", 9600, 1, units, d, dtype, T, 60, 9)
+    got = parity.gpu_prefill(big, P, arrays=tuple(np.ascontiguousarray(x[:, rep]) for x in (q, k, v)), units_sel=np.arange(min(units, 4)) if units > 4 else None)
+    try:
+        print(f"\n  {parity.compare_prefill(big, got, decode_steps=3)}", flush=True)
+    finally:
+        got["cache"].close()
