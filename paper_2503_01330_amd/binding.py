@@ -14,7 +14,7 @@ import numpy as np
 # PyTorch ships its own copy of the HIP runtime.  The tensors handed to wkv_step live in that
 # runtime's context, so it has to be the one libwkv binds to: load torch first, and the
 # dynamic loader resolves libwkv's libamdhip64 dependency to the copy already in the process.
-import torch  # noqa: F401  (imported for its side effect on library resolution)
+import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libwkv.so")
@@ -53,6 +53,7 @@ _lib = C.CDLL(LIB_PATH)
 _lib.wkv_create.argtypes = [C.POINTER(C.c_void_p)] + [C.c_int] * 6
 _lib.wkv_create_ex.argtypes = [C.POINTER(C.c_void_p), C.POINTER(wkv_options)]
 _lib.wkv_step.argtypes = [C.c_void_p] * 6
+_step = _lib.wkv_step
 _lib.wkv_prefill.argtypes = [C.c_void_p] * 5 + [C.c_int, C.c_void_p]
 _lib.wkv_prefill_noalloc.argtypes = [C.c_void_p] * 5 + [C.c_int, C.c_void_p]
 _lib.wkv_state.argtypes = [C.c_void_p, C.c_int, C.c_void_p, C.c_size_t]
@@ -154,6 +155,16 @@ def wkv_launch_shape(opt: wkv_options):
     return g.value, t.value
 
 
+# The calling thread's current stream as an address.  torch.cuda.current_stream() makes an object of it first, 2.7 us, which is
+# more than the library takes to enqueue a small cache's step; torch has the address itself for its own launchers.
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    def _current_stream(_raw=torch._C._cuda_getCurrentRawStream, _device=torch._C._cuda_getDevice) -> int:
+        return _raw(_device())
+else:
+    def _current_stream() -> int:
+        return torch.cuda.current_stream().cuda_stream
+
+
 _NP_STORE = {WKV_FP32: np.float32, WKV_FP16: np.float16, WKV_BF16: np.uint16}
 
 
@@ -167,17 +178,17 @@ class Cache:
 
     def step(self, q, k_new, v_new, out, stream=None):
         """q, k_new, v_new, out: torch tensors on the GPU, contiguous [batch, heads, head_dim]."""
-        if stream is None:
-            import torch
-            stream = torch.cuda.current_stream().cuda_stream
-        wkv_step(self.h, q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), out.data_ptr(), stream)
+        # (no layer in between: a small cache's step takes the GPU 7 us, and this call is all the host does for it)
+        rc = _step(self.h, q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), out.data_ptr(),
+                   _current_stream() if stream is None else stream)
+        if rc:
+            _check(rc)
 
     def prefill(self, q, k, v, out=None, stream=None, noalloc=False):
         """q, k, v (and out, if wanted): torch tensors on the GPU, contiguous [n_tokens, batch, heads, head_dim]
         (or [n_tokens, units, head_dim]); the cache must be empty.  noalloc: through wkv_prefill_noalloc."""
         if stream is None:
-            import torch
-            stream = torch.cuda.current_stream().cuda_stream
+            stream = _current_stream()
         (wkv_prefill_noalloc if noalloc else wkv_prefill)(
             self.h, q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr() if out is not None else 0,
             q.shape[0], stream)
