@@ -112,7 +112,14 @@ int validate(const wkv_options& o, int* threads, int* split)
         // units: 512 threads (measured 2-9 % ahead of 256 for rows of 256 bytes at 1024-8192
         // units), except for 128-byte rows, where 256 threads are 20 % ahead; slices: 512
         const int row_bytes = o.head_dim * dtype_bytes(o.dtype);
-        th = sp > 1 ? 512 : units >= 1024 ? (row_bytes < 256 ? 256 : 512) : units > 256 ? 512 : 1024;
+        // Few units and few entries: 512 threads as well.  There is then a round of rows or two either way, and what a step takes is its chain of
+        // barriers and reductions over the waves; half as many waves make it shorter.  us per step, 512 | 1024 threads, 8 units (200):
+        // fp16 d 64: m 64 5.75 | 7.09 (5.89 | 7.25), 127 6.68 | 7.35 (7.13 | 7.69), 200 7.06 | 8.03 (7.84 | 8.39), 255 7.96 | 8.12 (8.73 | 8.67),
+        // 256 8.38 | 8.05 (9.13 | 8.41); bf16 d 128: 64 6.10 | 7.30 (6.24 | 7.50), 200 7.74 | 8.48 (8.86 | 9.22), 255 8.73 | 8.58 (9.87 | 9.67);
+        // fp16 d 256: 200 8.91 | 9.47 (10.3 | 10.7), 255 10.2 | 10.3 (12.4 | 12.1); fp32 d 128: 200 8.32 | 8.87 (10.6 | 12.2).  From about 250 slots
+        // on the two are level or 1024 threads ahead (8 x 300: 1-3 % behind for rows of 256 bytes and less, 200 x 300 ahead).
+        constexpr int FEW_ENTRIES = 224;
+        th = sp > 1 ? 512 : units >= 1024 ? (row_bytes < 256 ? 256 : 512) : units > 256 || o.budget <= FEW_ENTRIES ? 512 : 1024;
         // from 768 to about 1200 units, 256 threads where m + 1 sits clearly closer above a multiple
         // of their (smaller) round than of the 512-thread one (m = 410: 448 against 512 rows):
         // 768 x 410 30.5 -> 29.3 us, 1024 x 410 39.4 -> 37.5, 1024 x 520 49.3 -> 46.8; where the two
@@ -132,7 +139,7 @@ int validate(const wkv_options& o, int* threads, int* split)
     return WKV_OK;
 }
 
-struct Sizes { size_t kv, a, i32, log, status, lg, po, ps, cnt, total; };
+struct Sizes { size_t kv, a, i32, log, status, lg, po, ps, cnt, clock, total; };
 
 Sizes sizes(const wkv_options& o, int split)
 {
@@ -151,8 +158,8 @@ Sizes sizes(const wkv_options& o, int split)
     s.cnt = split > 1 ? units * sizeof(uint32_t) : 0;
     // wkv_prefill's scratch, when reserved at creation
     const size_t pf = 2 * units * (size_t)(o.max_prompt > 0 ? o.max_prompt : 0) * sizeof(double);
-    s.total = 2 * s.kv + s.a + 2 * s.i32 + 2 * s.log + s.status + s.lg + s.po + 3 * s.ps + s.cnt + pf +
-              (o.replayable ? 16 : 0);
+    s.clock = o.replayable ? 16 : 0;
+    s.total = 2 * s.kv + s.a + 2 * s.i32 + 2 * s.log + s.status + s.lg + s.po + 3 * s.ps + s.cnt + pf + s.clock;
     return s;
 }
 
@@ -166,6 +173,7 @@ struct wkv_handle {
     int threads;
     int64_t t;        // tokens processed
     int64_t log_from; // first step whose eviction log entry is valid (after wkv_load)
+    void* block;      // the device memory of c and sp
     double* pf_scratch;  // wkv_prefill's scratch: [2][units][pf_tokens] fp64, or null
     int pf_tokens;
 };
@@ -282,6 +290,7 @@ int wkv_create_ex(wkv_handle** hp, const wkv_options* opt)
     h->threads = threads;
     h->t = 0;
     h->log_from = 0;
+    h->block = nullptr;
     h->pf_scratch = nullptr;
     h->pf_tokens = 0;
     hipError_t e = hipGetDevice(&h->device);
@@ -317,51 +326,44 @@ int wkv_create_ex(wkv_handle** hp, const wkv_options* opt)
     c.R = opt->recent_window; c.n_sink = opt->n_sink; c.score_mode = opt->score_mode;
     c.merge_mode = opt->merge_mode; c.log_cap = h->opt.log_capacity;
 
+    // One block of device memory for everything (a call each to allocate, fill and free sixteen buffers was most of what
+    // creating and destroying a small handle took: 68 + 60 us; see wkv_destroy): what starts at zero first, then what starts at -1.
     struct { void** p; size_t n; int fill; } bufs[] = {
-        { &c.K, s.kv, 0 }, { &c.V, s.kv, 0 }, { (void**)&c.a, s.a, 0 },
-        { (void**)&c.pos, s.i32, 0xFF }, { (void**)&c.nxt, s.i32, 0xFF },
-        { (void**)&c.log_pos, s.log, 0xFF },
-        { (void**)&c.log_slot, s.log, 0xFF }, { (void**)&c.status, s.status, 0 },
+        { &c.K, s.kv, 0 }, { &c.V, s.kv, 0 }, { (void**)&c.a, s.a, 0 }, { (void**)&c.status, s.status, 0 },
         { (void**)&sp.lg, s.lg, 0 }, { &sp.po, s.po, 0 }, { (void**)&sp.pm, s.ps, 0 },
         { (void**)&sp.pl, s.ps, 0 }, { (void**)&sp.pe, s.ps, 0 }, { (void**)&sp.cnt, s.cnt, 0 },
+        { (void**)&c.tdev, s.clock, 0 },     // token index, and the ticket counter behind it
+        { (void**)&c.pos, s.i32, 0xFF }, { (void**)&c.nxt, s.i32, 0xFF },
+        { (void**)&c.log_pos, s.log, 0xFF }, { (void**)&c.log_slot, s.log, 0xFF },
     };
-    for (auto& b : bufs) {
-        if (b.n == 0) continue;
-        e = hipMalloc(b.p, b.n);
-        if (e == hipSuccess) e = hipMemset(*b.p, b.fill, b.n);
-        if (e != hipSuccess) {
-            const bool oom = (e == hipErrorOutOfMemory);
-            rc = fail(oom ? WKV_ENOMEM : WKV_EHIP, "device allocation of %zu bytes: %s", b.n, hipGetErrorString(e));
-            (void)hipGetLastError();
-            for (auto& b2 : bufs) if (*b2.p) (void)hipFree(*b2.p);
-            delete h;
-            return rc;
+    constexpr size_t ALIGN = 256;
+    size_t filled[2] = { 0, 0 };              // bytes that start at zero, at -1
+    for (auto& b : bufs) filled[b.fill != 0] += (b.n + ALIGN - 1) / ALIGN * ALIGN;
+    e = hipMalloc(&h->block, filled[0] + filled[1]);
+    if (e == hipSuccess) e = hipMemset(h->block, 0, filled[0]);
+    if (e == hipSuccess) e = hipMemset((char*)h->block + filled[0], 0xFF, filled[1]);
+    if (e != hipSuccess) {
+        rc = fail(e == hipErrorOutOfMemory ? WKV_ENOMEM : WKV_EHIP, "device allocation of %zu bytes: %s", filled[0] + filled[1], hipGetErrorString(e));
+        (void)hipGetLastError();
+        if (h->block) (void)hipFree(h->block);
+        delete h;
+        return rc;
+    }
+    {
+        char* at = (char*)h->block;
+        for (auto& b : bufs) {
+            if (b.n != 0) *b.p = at;
+            at += (b.n + ALIGN - 1) / ALIGN * ALIGN;
         }
     }
+    if (c.tdev) c.tick = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(c.tdev) + 8);
     if (opt->max_prompt > 0) {
         rc = prefill_reserve(h, opt->max_prompt);
         if (rc != WKV_OK) {
-            for (auto& b2 : bufs) if (*b2.p) (void)hipFree(*b2.p);
+            (void)hipFree(h->block);
             delete h;
             return rc;
         }
-    }
-    if (opt->replayable) {
-        // token index and ticket counter on the device (both start at zero)
-        void* clk = nullptr;
-        e = hipMalloc(&clk, 16);
-        if (e == hipSuccess) e = hipMemset(clk, 0, 16);
-        if (e != hipSuccess) {
-            rc = fail(e == hipErrorOutOfMemory ? WKV_ENOMEM : WKV_EHIP, "device allocation of the step counter: %s", hipGetErrorString(e));
-            (void)hipGetLastError();
-            if (clk) (void)hipFree(clk);
-            for (auto& b2 : bufs) if (*b2.p) (void)hipFree(*b2.p);
-            if (h->pf_scratch) (void)hipFree(h->pf_scratch);
-            delete h;
-            return rc;
-        }
-        c.tdev = static_cast<int64_t*>(clk);
-        c.tick = reinterpret_cast<uint32_t*>(static_cast<char*>(clk) + 8);
     }
     count_live(h->device, 2 * (long long)s.kv);
     *hp = h;
@@ -656,12 +658,8 @@ int wkv_destroy(wkv_handle* h)
     int cur = -1;
     const bool moved = hipGetDevice(&cur) == hipSuccess && cur != h->device && hipSetDevice(h->device) == hipSuccess;
     (void)hipDeviceSynchronize();
-    WkvCache& c = h->c;
-    void* bufs[] = { c.K, c.V, c.a, c.pos, c.nxt, c.log_pos, c.log_slot, c.status,
-                     h->sp.lg, h->sp.po, h->sp.pm, h->sp.pl, h->sp.pe, h->sp.cnt };
-    for (void* b : bufs) if (b) (void)hipFree(b);
+    (void)hipFree(h->block);
     if (h->pf_scratch) (void)hipFree(h->pf_scratch);
-    if (c.tdev) (void)hipFree(c.tdev);
     count_live(h->device, -2 * (long long)sizes(h->opt, h->sp.S).kv);
     if (moved) (void)hipSetDevice(cur);
     delete h;

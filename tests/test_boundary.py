@@ -107,3 +107,13 @@ def test_bench_refuses_more_than_one_gpu():
     import sys
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_launch_shape_follows_the_budget_of_few_units():
+    """Host-only: up to 256 units, 512 threads while the budget is small, 1024 beyond; many units and slices are not affected."""
+    def shape(units, m, **kw):
+        return wkv.wkv_launch_shape(wkv.make_options(1, units, 64, m, 8, wkv.WKV_BF16, **kw))
+    assert shape(60, 224) == (60, 512) and shape(60, 225) == (60, 1024)
+    assert shape(256, 224) == (256, 512) and shape(257, 225) == (257, 512)
+    assert shape(1024, 64) == (1024, 256)
+    assert shape(60, 64, threads=1024) == (60, 1024)

@@ -105,6 +105,15 @@ def test_budgets_around_blocks_and_rounds(threads):
         _run(cfg, threads=threads)
 
 
+@pytest.mark.parametrize("units", [3, 256])
+@pytest.mark.parametrize("dtype,d", [("fp16", 64), ("bf16", 128), ("fp16", 256), ("fp32", 128)])
+def test_default_shape_of_small_budgets(dtype, d, units):
+    """The workgroup size changes above 224 slots; budgets on both sides of that line and of a round of 512 threads."""
+    for m in (127, 128, 224, 225):
+        cfg = synth.StreamConfig(f"few{m}", 7950 + m, 1, units, d, dtype, m + 12, m, 7)
+        _run(cfg, units_sel=np.array([0, units // 2, units - 1]))
+
+
 @pytest.mark.parametrize("split", [2, 4, 8, 16])
 def test_sliced_units_small_shapes(split):
     """Every slice count against the oracle: slices that are empty while the cache fills (and for
