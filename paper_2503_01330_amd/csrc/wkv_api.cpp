@@ -9,10 +9,9 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
-#include <numeric>
 #include <string>
-#include <vector>
 
 namespace {
 
@@ -179,6 +178,70 @@ struct wkv_handle {
 };
 
 namespace {
+
+// Pinned memory through which readbacks and uploads go: a few slots of a chunk of units (about a megabyte, or one unit), and an event each.
+// The memory of the first one is kept for the next (made anew for each, its pages cost 230 us of a 5.7 MB matrix' 400): one
+// block of at most KEPT bytes in the process, lent to one call at a time (another thread's call gets memory of its
+// own meanwhile), freed with the last handle.
+struct Kept {
+    std::mutex mu;
+    char* p = nullptr;
+    size_t n = 0;
+    int handles = 0;
+    bool lent = false;
+    void created() { std::lock_guard<std::mutex> lock(mu); ++handles; }
+    void destroyed()
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (--handles == 0 && p && !lent) { (void)hipHostFree(p); p = nullptr; n = 0; }
+    }
+} g_kept;
+
+struct Staging {
+    static constexpr size_t SLOTS = 4, CHUNK = 1 << 20, KEPT = SLOTS * (2 << 20);
+    char* p = nullptr;
+    hipEvent_t event[SLOTS] = {};
+    size_t units = 0, chunks = 0, slots = 0, stride = 0;       // units of a chunk
+    bool borrowed = false;
+    hipError_t open(size_t all, size_t unit_bytes)
+    {
+        units = std::min(all, std::max<size_t>(1, CHUNK / unit_bytes));
+        chunks = (all + units - 1) / units;
+        slots = std::min(SLOTS, chunks);
+        stride = (units * unit_bytes + 255) / 256 * 256;
+        const size_t need = slots * stride;
+        hipError_t e = hipSuccess;
+        {
+            std::lock_guard<std::mutex> lock(g_kept.mu);
+            if (!g_kept.lent && need <= KEPT) {
+                if (g_kept.n < need) {                         // (a larger one than this call needs, for the next)
+                    if (g_kept.p) (void)hipHostFree(g_kept.p);
+                    g_kept.n = 0;
+                    e = hipHostMalloc((void**)&g_kept.p, KEPT, hipHostMallocPortable);
+                    if (e != hipSuccess) { g_kept.p = nullptr; return e; }
+                    g_kept.n = KEPT;
+                }
+                p = g_kept.p;
+                g_kept.lent = borrowed = true;
+            }
+        }
+        if (!borrowed) e = hipHostMalloc((void**)&p, need, hipHostMallocDefault);
+        for (size_t i = 0; i < slots && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&event[i], hipEventDisableTiming);
+        return e;
+    }
+    char* slot(size_t chunk) const { return p + chunk % slots * stride; }
+    size_t count(size_t chunk, size_t all) const { return std::min(units, all - chunk * units); }
+    ~Staging()
+    {
+        if (p == nullptr) return;
+        (void)hipStreamSynchronize(nullptr);                   // (a call that failed half way may have left work behind)
+        for (hipEvent_t ev : event) if (ev) (void)hipEventDestroy(ev);
+        if (!borrowed) { (void)hipHostFree(p); return; }
+        std::lock_guard<std::mutex> lock(g_kept.mu);
+        g_kept.lent = false;
+        if (g_kept.handles == 0) { (void)hipHostFree(g_kept.p); g_kept.p = nullptr; g_kept.n = 0; }
+    }
+};
 
 // The handle's memory and the kernels' attributes belong to one device; calls come from it.
 int on_device(const wkv_handle* h)
@@ -366,6 +429,7 @@ int wkv_create_ex(wkv_handle** hp, const wkv_options* opt)
         }
     }
     count_live(h->device, 2 * (long long)s.kv);
+    g_kept.created();
     *hp = h;
     return WKV_OK;
 }
@@ -447,7 +511,7 @@ int wkv_prefill_noalloc(wkv_handle* h, const void* q, const void* k, const void*
 static int state_impl(wkv_handle* h, int what, void* dst, size_t bytes)
 {
     const WkvCache& c = h->c;
-    const size_t units = c.units, cap = c.m;
+    const size_t units = c.units;
     if (c.tdev) {
         // replayable handle: the device counts the steps (graph replays advance it without the host)
         int rc0 = on_device(h);
@@ -507,62 +571,26 @@ static int state_impl(wkv_handle* h, int what, void* dst, size_t bytes)
     if (bytes < need) return fail(WKV_ESIZE, "need %zu bytes, got %zu", need, bytes);
     if (len == 0) return WKV_OK;
 
-    // token order of the live slots (physical slots 0..len-1) of every unit
-    std::vector<int32_t> pos(units * cap);
-    e = hipMemcpy(pos.data(), c.pos, pos.size() * 4, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail(WKV_EHIP, "hipMemcpy: %s", hipGetErrorString(e));
-    std::vector<int32_t> order(units * len);
-    for (size_t u = 0; u < units; ++u) {
-        int32_t* idx = order.data() + u * len;
-        std::iota(idx, idx + len, 0);
-        const int32_t* pu = pos.data() + u * cap;
-        std::sort(idx, idx + len, [pu](int32_t x, int32_t y) { return pu[x] < pu[y]; });
-    }
-
-    auto gather = [&](const void* dev, size_t elem, auto&& emit) -> int {
-        std::vector<char> raw(units * cap * elem);
-        hipError_t e2 = hipMemcpy(raw.data(), dev, raw.size(), hipMemcpyDeviceToHost);
-        if (e2 != hipSuccess) return fail(WKV_EHIP, "hipMemcpy: %s", hipGetErrorString(e2));
-        for (size_t u = 0; u < units; ++u)
-            for (size_t l = 0; l < len; ++l)
-                emit(u * len + l, raw.data() + (u * cap + order[u * len + l]) * elem);
-        return WKV_OK;
-    };
-    switch (what) {
-    case WKV_K: case WKV_V: {
-        const size_t rb = d * eb;
-        return gather(what == WKV_K ? c.K : c.V, rb,
-                      [&](size_t o, const char* src) { memcpy((char*)dst + o * rb, src, rb); });
-    }
-    case WKV_SCORE_SUM:
-        return gather(c.a, sizeof(double),
-                      [&](size_t o, const char* src) { memcpy((char*)dst + o * 8, src, 8); });
-    case WKV_POS:
-        return gather(c.pos, 4, [&](size_t o, const char* src) { memcpy((char*)dst + o * 4, src, 4); });
-    case WKV_NMERGED: {
-        // Raw values folded into a slot.  Merging only ever joins a token with its right
-        // neighbour, so a slot holds the contiguous run of tokens that ends at its own key:
-        // the count is the distance to the previous retained key.  Without merging it is 1.
-        const bool merging = h->opt.merge_mode == WKV_MERGE_CONVEX;
-        for (size_t u = 0; u < units; ++u) {
-            int32_t prev = -1;
-            for (size_t l = 0; l < len; ++l) {
-                const int32_t p = pos[u * cap + order[u * len + l]];
-                const int32_t n = merging ? p - prev : 1;
-                memcpy((char*)dst + (u * len + l) * 4, &n, 4);
-                prev = p;
-            }
+    // A kernel puts a few units' slots in token order into pinned memory while the previous ones' are copied to the caller
+    const size_t unit_bytes = need / units;
+    Staging st;
+    e = st.open(units, unit_bytes);
+    for (size_t i = 0; i < st.chunks + st.slots && e == hipSuccess; ++i) {
+        if (i >= st.slots) {                            // chunk i - slots has its slot: wait for it, copy it out
+            const size_t j = i - st.slots;
+            e = hipEventSynchronize(st.event[j % st.slots]);
+            if (e == hipSuccess) memcpy((char*)dst + j * st.units * unit_bytes, st.slot(j), st.count(j, units) * unit_bytes);
         }
-        return WKV_OK;
+        if (i < st.chunks && e == hipSuccess) {
+            e = wkv_launch_gather(c, what, (int)(d * eb), (int)(i * st.units), (int)st.count(i, units), (int)len, T, st.slot(i), nullptr);
+            if (e == hipSuccess) e = hipEventRecord(st.event[i % st.slots], nullptr);
+        }
     }
-    case WKV_COUNT:     // n = steps attended = tokens - pos (every live slot is attended once per step)
-        return gather(c.pos, 4, [&](size_t o, const char* src) {
-            int32_t p; memcpy(&p, src, 4);
-            const int32_t n = (int32_t)(T - p);
-            memcpy((char*)dst + o * 4, &n, 4);
-        });
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(e == hipErrorOutOfMemory ? WKV_ENOMEM : WKV_EHIP, "reading the state: %s", hipGetErrorString(e));
     }
-    return fail(WKV_EINVAL, "unknown state item %d", what);
+    return WKV_OK;
 }
 
 int wkv_state(wkv_handle* h, int what, void* dst, size_t bytes)
@@ -579,7 +607,7 @@ static int load_impl(wkv_handle* h, int64_t tokens, int len, const void* K, cons
                      const double* score_sum, const int32_t* pos)
 {
     WkvCache& c = h->c;
-    const size_t units = c.units, m = c.m;
+    const size_t units = c.units;
     if (tokens < 0 || tokens >= 0x7FFFFFF0LL) return fail(WKV_EINVAL, "tokens out of range");
     if (len != (int)std::min<int64_t>(tokens, c.m)) return fail(WKV_EINVAL, "len must equal min(tokens, budget)");
     if (len > 0 && (!K || !V || !score_sum || !pos)) return fail(WKV_EINVAL, "null state array");
@@ -598,30 +626,47 @@ static int load_impl(wkv_handle* h, int64_t tokens, int len, const void* K, cons
         e = wkv_launch_clear(c, nullptr);
         if (e == hipSuccess) e = hipDeviceSynchronize();
     } else {
-        // device layout: slot l of a unit holds the l-th token in token order, links run l -> l+1
+        // device layout: slot l of a unit holds the l-th token in token order, links run l -> l+1.  Through pinned memory, a few
+        // units at a time: a kernel places them while the next ones are copied there.
         const size_t rb = (size_t)h->opt.head_dim * dtype_bytes(h->opt.dtype);
-        std::vector<int32_t> hp(units * m, -1), hn(units * m, -1);
-        std::vector<double> ha(units * m, 0.0);
-        for (size_t u = 0; u < units; ++u)
-            for (int l = 0; l < len; ++l) {
-                hp[u * m + l] = pos[u * len + l];
-                hn[u * m + l] = (l + 1 < len) ? l + 1 : -1;
-                ha[u * m + l] = score_sum[u * len + l];
+        e = wkv_launch_clear(c, nullptr);
+        auto upload = [&](size_t unit_bytes, auto&& fill, auto&& place) {
+            Staging st;
+            hipError_t e2 = st.open(units, unit_bytes);
+            for (size_t i = 0; i < st.chunks && e2 == hipSuccess; ++i) {
+                if (i >= st.slots) e2 = hipEventSynchronize(st.event[i % st.slots]);     // its last contents have been placed
+                if (e2 != hipSuccess) break;
+                fill(st.slot(i), i * st.units, st.count(i, units));
+                e2 = place(st.slot(i), (int)(i * st.units), (int)st.count(i, units));
+                if (e2 == hipSuccess) e2 = hipEventRecord(st.event[i % st.slots], nullptr);
             }
-        e = hipMemcpy2D(c.K, m * rb, K, (size_t)len * rb, (size_t)len * rb, units, hipMemcpyHostToDevice);
+            const hipError_t e3 = hipDeviceSynchronize();                                // before the memory goes
+            return e2 != hipSuccess ? e2 : e3;
+        };
+        for (int what : { WKV_K, WKV_V }) {
+            const char* src = static_cast<const char*>(what == WKV_K ? K : V);
+            if (e == hipSuccess)
+                e = upload(len * rb, [&](char* to, size_t u0, size_t n) { memcpy(to, src + u0 * len * rb, n * len * rb); },
+                           [&](const char* from, int u0, int n) { return wkv_launch_place_rows(c, what, (int)rb, u0, n, len, from, nullptr); });
+        }
+        // score sums of a chunk's units, then their token indices
         if (e == hipSuccess)
-            e = hipMemcpy2D(c.V, m * rb, V, (size_t)len * rb, (size_t)len * rb, units, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemcpy(c.a, ha.data(), ha.size() * sizeof(double), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemcpy(c.pos, hp.data(), hp.size() * 4, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemcpy(c.nxt, hn.data(), hn.size() * 4, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemset(c.log_pos, 0xFF, (size_t)c.log_cap * units * 4);
-        if (e == hipSuccess) e = hipMemset(c.log_slot, 0xFF, (size_t)c.log_cap * units * 4);
+            e = upload(len * 12, [&](char* to, size_t u0, size_t n) {
+                           memcpy(to, score_sum + u0 * len, n * len * 8);
+                           memcpy(to + n * len * 8, pos + u0 * len, n * len * 4);
+                       },
+                       [&](const char* from, int u0, int n) {
+                           return wkv_launch_place_items(c, u0, n, len, (const double*)from, (const int32_t*)(from + (size_t)n * len * 8), nullptr);
+                       });
     }
     if (e == hipSuccess && c.tdev) {
         e = wkv_launch_set_clock(c, tokens, nullptr);
         if (e == hipSuccess) e = hipDeviceSynchronize();
     }
-    if (e != hipSuccess) return fail(WKV_EHIP, "uploading the state: %s (the cache may be partly overwritten)", hipGetErrorString(e));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(e == hipErrorOutOfMemory ? WKV_ENOMEM : WKV_EHIP, "uploading the state: %s (the cache may be partly overwritten)", hipGetErrorString(e));
+    }
     h->t = tokens;
     h->log_from = tokens;
     return WKV_OK;
@@ -660,6 +705,7 @@ int wkv_destroy(wkv_handle* h)
     (void)hipDeviceSynchronize();
     (void)hipFree(h->block);
     if (h->pf_scratch) (void)hipFree(h->pf_scratch);
+    g_kept.destroyed();
     count_live(h->device, -2 * (long long)sizes(h->opt, h->sp.S).kv);
     if (moved) (void)hipSetDevice(cur);
     delete h;

@@ -93,6 +93,16 @@ size_t wkv_prefill_lds_bytes(int P);
 hipError_t wkv_prefill_static_scratch(int device, double** ptr);
 
 
+// ---- readback and upload (wkv_state.hip): live slots 0 .. len - 1 of `units` units from unit0 on, in token order, to or from
+// memory of [units][len] items that the GPU reaches (pinned host memory).  what: WKV_K / WKV_V (rows of row_bytes), or for the
+// gather one of the items with a number a slot.  place_*: into an otherwise empty cache.
+hipError_t wkv_launch_gather(const WkvCache& c, int what, int row_bytes, int unit0, int units, int len, int64_t tokens, void* dst,
+                             hipStream_t stream);
+hipError_t wkv_launch_place_rows(const WkvCache& c, int what, int row_bytes, int unit0, int units, int len, const void* src,
+                                 hipStream_t stream);
+hipError_t wkv_launch_place_items(const WkvCache& c, int unit0, int units, int len, const double* sums, const int32_t* pos,
+                                  hipStream_t stream);
+
 // ---- measurement aid (wkv_probe.hip): `workgroups` x `threads` read `bytes` of device memory,
 // each workgroup its own contiguous share, and do nothing else.
 hipError_t wkv_launch_probe_read(const void* src, size_t bytes, int workgroups, int threads, bool nontemporal,

@@ -501,3 +501,83 @@ def test_plain_c_caller():
     assert os.path.exists(exe), "build it first: python -c 'import __graft_entry__ as g; g.build()'"
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "c_abi ok" in r.stdout, r.stdout + r.stderr
+
+
+def _made_up_state(units, m, length, d, dtype, seed):
+    g = np.random.default_rng(seed)
+    def rows():
+        r = g.standard_normal((units, length, d)).astype(np.float32)
+        return (r.view(np.uint32) >> 16).astype(np.uint16) if dtype == "bf16" else r.astype({"fp16": np.float16, "fp32": np.float32}[dtype])
+
+    tokens = length if length < m else 3 * m
+    pos = np.stack([np.sort(g.choice(tokens - 1, length - 1, replace=False)) if length > 1 else np.empty(0, np.int64) for _ in range(units)])
+    pos = np.concatenate([pos, np.full((units, 1), tokens - 1)], 1).astype(np.int32)
+    return tokens, rows(), rows(), g.random((units, length)), pos
+
+
+@pytest.mark.parametrize("units,m,length,d,dtype", [
+    (3, 1, 1, 64, "fp16"), (5, 70, 64, 128, "bf16"), (4, 65, 65, 256, "fp16"), (7, 300, 257, 64, "fp32"),
+    (5, 700, 700, 256, "fp16"),         # two units a chunk, the last chunk has one
+    (1, 4095, 4095, 256, "bf16"),       # a unit of more than a chunk
+    (9, 4095, 4000, 128, "fp32"),       # more chunks than slots, of more than a megabyte each
+    (300, 410, 410, 128, "fp16"),       # many chunks of several units
+])
+def test_state_goes_in_and_out_in_token_order(units, m, length, d, dtype):
+    """wkv_load and wkv_state over the sizes at which they change chunks, whole caches and partly filled ones; then a few steps, after which
+    slots are no longer in token order (a cache made by streaming is held to the oracle by every other test): what is read must be in token order
+    and consistent with itself, and loading it must give the same again."""
+    tokens, K, V, a, pos = _made_up_state(units, m, length, d, dtype, 8300 + m)
+    mk = lambda: wkv.Cache(1, units, d, m, 1, synth.DTYPE_CODE[dtype], log_capacity=8)
+    items = (wkv.WKV_K, wkv.WKV_V, wkv.WKV_SCORE_SUM, wkv.WKV_POS, wkv.WKV_COUNT, wkv.WKV_NMERGED)
+    c, e = mk(), mk()
+    try:
+        c.load(tokens, K, V, a, pos)
+        got = [c.state(w) for w in items]
+        for x, y in zip(got, (K, V, a, pos, tokens - pos, np.diff(pos, axis=1, prepend=-1))):
+            assert np.array_equal(x, y)
+        x = torch.randn(units, d, device="cuda").to(getattr(torch, {"fp16": "float16", "fp32": "float32", "bf16": "bfloat16"}[dtype])) * 0.1
+        out = torch.empty_like(x)
+        for _ in range(5):
+            c.step(x, x, x, out)
+        got = dict(zip(items, (c.state(w) for w in items)))
+        p = got[wkv.WKV_POS]
+        assert (np.diff(p, axis=1) > 0).all() and (p[:, -1] == tokens + 4).all()
+        assert np.array_equal(got[wkv.WKV_COUNT], tokens + 5 - p)
+        old = [np.flatnonzero(p[u] < tokens) for u in range(units)]
+        for u in (0, units // 2, units - 1):
+            where = np.searchsorted(pos[u], p[u][old[u]])
+            assert np.array_equal(got[wkv.WKV_K][u][old[u]], K[u][where]), "keys are not those of their tokens"
+            assert (got[wkv.WKV_SCORE_SUM][u][old[u]] >= a[u][where]).all()
+        e.load(c.tokens, *(got[w] for w in items[:4]))
+        for w in items:
+            assert np.array_equal(e.state(w), got[w])
+    finally:
+        c.close()
+        e.close()
+
+
+def test_two_threads_read_and_load_at_once():
+    """The pinned memory of one readback is kept for the next: a second thread's calls, at the same time, get memory of their own."""
+    import threading
+    made = [_made_up_state(6, 300, 300, 128, "fp16", 8400 + i) for i in range(2)]
+    caches = [wkv.Cache(1, 6, 128, 300, 9, wkv.WKV_FP16) for _ in made]
+    failed = []
+
+    def work(i):
+        try:
+            tokens, K, V, a, pos = made[i]
+            for _ in range(30):
+                caches[i].load(tokens, K, V, a, pos)
+                for w, x in ((wkv.WKV_K, K), (wkv.WKV_V, V), (wkv.WKV_SCORE_SUM, a), (wkv.WKV_POS, pos)):
+                    assert np.array_equal(caches[i].state(w), x)
+        except Exception as exc:                                    # noqa: BLE001
+            failed.append(exc)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for c in caches:
+        c.close()
+    assert not failed, failed
