@@ -965,12 +965,16 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
 // merges (Algorithm 1) in fp64, with no dependent chain of row updates.  Rows are rounded to the
 // cache format once, when they are written.
 //
+// What bounds it is LDS: the sort's traffic and the dependent looks of the two searches.  us, 24 units x 1237 | 128 x 2048 | 256 x 4096: pairs a step and
+// searches entry by entry, then 64 at a time 52 | 74 | 148 (of it sort 20 | 21 | 43, searches 15 | 30 | 62); four elements through two steps
+// at a time, groups of 8 in between 36 | 45 | 90.
+//
 // What is left is a weight per token, written to global memory; the rows themselves are moved by
 // wkv_prefill_fold, which has the whole chip where this kernel has a workgroup per unit.
 //
 // LDS: sc[P] score, then list products, finally weight | ae[P] f, then edge coefficient | a0[P] g, then
 //      own coefficient | slot[P] | wcnt[NT] (one per wave is used) | rk[P] rank (16 bit) | par[P] parent (16 bit) |
-//      ptr[P] list successor (16 bit) | bmax[64].  The sort keys borrow ae[], a0[] and slot[].
+//      ptr[P] list successor (16 bit) | bmax[64]; gmax[512] takes wcnt's place.  The sort keys borrow ae[], a0[] and slot[].
 __global__ __launch_bounds__(1024)
 void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __restrict__ weight, int P)
 {
@@ -1021,28 +1025,56 @@ void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __re
             kid[i] = (uint16_t)i;
         }
         __syncthreads();
-        // Steps of distance 64 and less stay within the 128 elements that 64 consecutive pairs span,
-        // i.e. within one wave: LDS operations of a wave complete in order, so those steps need no
-        // workgroup barrier (63 of the 78 steps for 4096 tokens).
-        auto exchange = [&](int t, int j, int k) __attribute__((always_inline)) {
-            const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), l = i | j;
-            const unsigned long long ki = key[i], kl = key[l];
-            const uint16_t di = kid[i], dl = kid[l];
-            const bool gt = ki > kl || (ki == kl && di > dl);
-            if (gt == ((i & k) == 0)) { key[i] = kl; key[l] = ki; kid[i] = dl; kid[l] = di; }
+        // What takes the time is LDS traffic, so a thread takes four elements through two steps at a time (distances j and j / 2).
+        // Steps of distance 128 and less stay within the 256 elements that a wave's quadruples (or pairs, two a lane) span:
+        // LDS operations of a wave complete in order, so those need no workgroup barrier.
+        auto order = [](unsigned long long& ka, uint16_t& ia, unsigned long long& kb, uint16_t& ib, bool up) __attribute__((always_inline)) {
+            const bool gt = ka > kb || (ka == kb && ia > ib), swap = gt == up;
+            const unsigned long long k0 = swap ? kb : ka, k1 = swap ? ka : kb;
+            const uint16_t i0 = swap ? ib : ia, i1 = swap ? ia : ib;
+            ka = k0; kb = k1; ia = i0; ib = i1;
         };
-        for (int k = 2; k <= N2; k <<= 1) {
-            int j = k >> 1;
-            for (; j > 64; j >>= 1) {
-                for (int t = tid; t < (N2 >> 1); t += NT) exchange(t, j, k);
-                __syncthreads();
+        auto one_step = [&](int j, int k) __attribute__((always_inline)) {
+            for (int half = 0; half < 2; ++half) {
+                const int t = wid * 128 + half * 64 + lane;
+                if (t >= (N2 >> 1)) break;
+                const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), l = i | j;
+                unsigned long long ki = key[i], kl = key[l];
+                uint16_t di = kid[i], dl = kid[l];
+                order(ki, di, kl, dl, (i & k) == 0);
+                key[i] = ki; key[l] = kl; kid[i] = di; kid[l] = dl;
             }
-            for (; j > 0; j >>= 1) {
-                for (int t = tid; t < (N2 >> 1); t += NT) exchange(t, j, k);
+        };
+        auto two_steps = [&](int j, int k) __attribute__((always_inline)) {
+            const int h = j >> 1;
+            if (tid < (N2 >> 2)) {
+                const int i = ((tid & ~(h - 1)) << 2) | (tid & (h - 1));
+                const bool up = (i & k) == 0;
+                unsigned long long q[4];
+                uint16_t d[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { q[e] = key[i + e * h]; d[e] = kid[i + e * h]; }
+                order(q[0], d[0], q[2], d[2], up);
+                order(q[1], d[1], q[3], d[3], up);
+                order(q[0], d[0], q[1], d[1], up);
+                order(q[2], d[2], q[3], d[3], up);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { key[i + e * h] = q[e]; kid[i + e * h] = d[e]; }
+            }
+        };
+        auto settle = [&](int j) __attribute__((always_inline)) {
+            if (j > 128) {
+                __syncthreads();
+            } else {
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
             }
-            if (k >= 128) __syncthreads();
+        };
+        for (int k = 2, steps = 1; k <= N2; k <<= 1, ++steps) {
+            int j = k >> 1;
+            if (steps & 1) { one_step(j, k); settle(j); j >>= 1; }
+            for (; j >= 2; j >>= 2) { two_steps(j, k); settle(j); }
+            if (k >= 256) __syncthreads();                    // the next k starts with a distance of 256 or more
         }
         __syncthreads();
         for (int r = tid; r < nrem; r += NT) rk[kid[r]] = (uint16_t)r;         // the nrem lowest keys are candidates
@@ -1075,15 +1107,19 @@ void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __re
     if (merging) {
         // Parent of a removed token: the nearest token to its right that outranks it (survivors
         // outrank everything: rank 0xFFFF); also the nearest one to its LEFT that outranks it.  Both by
-        // a search that skips whole blocks of 64 tokens whose highest rank is too low, so a token
-        // looks at < 200 entries however long the runs are.
+        // a search that skips whole groups of 8 and blocks of 64 tokens whose highest rank is too low: each look waits for LDS, and a
+        // wave for the lane with the most of them, so a token looks at no more than 100 entries however long the runs are.
         constexpr int NIL = 0xFFFF;
         const int nblk = (P + 63) >> 6;
+        uint16_t* gmax = reinterpret_cast<uint16_t*>(wcnt);   // [512] highest rank in a group of 8 (the counts have been used)
         for (int b = wid; b < nblk; b += NW) {
             const int i = b * 64 + lane;
             int r = (i < P) ? (int)rk[i] : 0;
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) r = max(r, __shfl_xor(r, off));
+            for (int off = 1; off < 8; off <<= 1) r = max(r, __shfl_xor(r, off));
+            if ((lane & 7) == 0) gmax[b * 8 + (lane >> 3)] = (uint16_t)r;
+#pragma unroll
+            for (int off = 8; off < 64; off <<= 1) r = max(r, __shfl_xor(r, off));
             if (lane == 0) bmax[b] = (uint16_t)r;
         }
         __syncthreads();
@@ -1091,27 +1127,41 @@ void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __re
             int right = i, left = NIL;                        // a survivor is its own parent
             if (slot[i] < 0) {
                 const int ri = rk[i];
-                {
-                    const int e = min((i | 63) + 1, P);
+                {                                             // a survivor lies to the right (the newest tokens are never removed): every search ends
+                    const int e = (i | 7) + 1;
                     int k = i + 1;
                     while (k < e && rk[k] <= ri) ++k;
-                    if (k == e) {                              // a survivor lies to the right (the newest tokens are never removed)
-                        int b = (i >> 6) + 1;
-                        while (b < nblk - 1 && bmax[b] <= ri) ++b;
-                        k = b * 64;
-                        while (k < P - 1 && rk[k] <= ri) ++k;
+                    if (k == e) {
+                        const int ge = ((i >> 6) + 1) * 8;
+                        int n = (i >> 3) + 1;
+                        while (n < ge && gmax[n] <= ri) ++n;
+                        if (n == ge) {
+                            int b = (i >> 6) + 1;
+                            while (bmax[b] <= ri) ++b;
+                            n = b * 8;
+                            while (gmax[n] <= ri) ++n;
+                        }
+                        k = n * 8;
+                        while (rk[k] <= ri) ++k;
                     }
                     right = k;
                 }
                 {
-                    const int e = (i & ~63) - 1;
+                    const int e = (i & ~7) - 1;
                     int k = i - 1;
                     while (k > e && rk[k] <= ri) --k;
                     if (k == e) {
-                        int b = (i >> 6) - 1;
-                        while (b >= 0 && bmax[b] <= ri) --b;
-                        if (b >= 0) { k = b * 64 + 63; while (rk[k] <= ri) --k; }   // bmax[b] > ri: the scan ends inside block b
-                        else k = -1;
+                        const int ge = (i >> 6) * 8 - 1;
+                        int n = (i >> 3) - 1;
+                        while (n > ge && gmax[n] <= ri) --n;
+                        if (n == ge) {
+                            int b = (i >> 6) - 1;
+                            while (b >= 0 && bmax[b] <= ri) --b;
+                            n = -1;
+                            if (b >= 0) { n = b * 8 + 7; while (gmax[n] <= ri) --n; }      // bmax[b] > ri: ends inside block b
+                        }
+                        k = -1;
+                        if (n >= 0) { k = n * 8 + 7; while (rk[k] <= ri) --k; }
                     }
                     left = (k >= 0) ? k : NIL;
                 }
@@ -1218,7 +1268,7 @@ void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __re
 // the cache format once.  A prompt that fits the cache has no compress kernel before it: the few words of bookkeeping
 // a token are written here (77 tokens: one launch of 5 us less).  Measured, with the wave-local steps of the sort (compress, then compress + fold):
 // 24 units, 1237 tokens to 333 (d 64): 231 -> 50 + 16 us; 128 units, 2048 to 512 (d 128): 372 -> 59 + 59;
-// 256 units, 4096 to 410: 795 -> 129 + 119.
+// 256 units, 4096 to 410: 795 -> 129 + 119 (the compress kernel's share by now: see there).
 constexpr int FOLD_ROWS = 16, FOLD_WAVES = 8, LONG = 64;
 template <class TT, int D>
 __global__ __launch_bounds__(64 * FOLD_WAVES)
