@@ -87,7 +87,7 @@ typedef struct wkv_options {
     int score_mode;              /* optional: WKV_SCORE_*; non-average modes require WKV_MERGE_NONE */
     int merge_mode;              /* optional: WKV_MERGE_*                                          */
     int log_capacity;            /* optional: steps of eviction log kept (ring), default 1024      */
-    int threads;                 /* optional: workgroup size 256/512/1024, default chosen by units */
+    int threads;                 /* optional: workgroup size 256/512/1024, default by units and budget */
     int split;                   /* optional: workgroups per unit, 1/2/4/8/16; default: 1 unless   */
                                  /*   the units alone would leave most of the GPU idle             */
     int streaming;               /* optional: WKV_LOADS_*: how wkv_step loads the cached K/V rows  */
@@ -205,7 +205,9 @@ int wkv_prefill_noalloc(wkv_handle* h, const void* q, const void* k, const void*
  * device memory.  For the two eviction logs, n = bytes / (4*units) most recent
  * steps are returned, oldest first; n must not exceed min(tokens, log_capacity).
  * For everything else `bytes` must be at least the size listed above
- * (WKV_ESIZE otherwise; nothing is written then).  Like every call that takes a handle, it
+ * (WKV_ESIZE otherwise; nothing is written then).  Slot arrays travel through pinned host memory: a few
+ * megabytes of it are kept from the first such call (or wkv_load) on, until the process's last handle is
+ * destroyed; calls on several threads at once are fine.  Like every call that takes a handle, it
  * must come with the handle's device current (WKV_EINVAL otherwise); wkv_destroy alone does
  * not mind.
  */

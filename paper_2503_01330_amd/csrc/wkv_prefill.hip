@@ -123,17 +123,6 @@ template <class TT> __device__ __forceinline__ float4_t mfma16(uint2_t a, uint2_
         return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4_t, a), __builtin_bit_cast(short4_t, b), c, 0, 0, 0);
 }
 
-// The same with eight a lane: what two operands of four hold, one behind the other.
-typedef _Float16 half8_t  __attribute__((ext_vector_type(8)));
-typedef __bf16   bf16x8_t __attribute__((ext_vector_type(8)));
-template <class TT> __device__ __forceinline__ float4_t mfma16(uint2_t a0, uint2_t a1, u32x4_t b, float4_t c) {
-    const u32x4_t a = { a0.x, a0.y, a1.x, a1.y };
-    if constexpr (__is_same(TT, TF16))
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-}
-
 // exp(x) for the arguments a softmax produces, x <= 0 or a little above:
 // x = (256 n + j + f) ln2 / 256 with integers n, 0 <= j < 256 and |f| <= 1/2, and
 // exp(x) = 2^n . 2^(j/256) . exp(f ln2 / 256); the middle factor comes from a table in LDS, the last one from the Taylor
@@ -166,8 +155,8 @@ __device__ __forceinline__ void exp_table_init(double* tab) {
 // normal numbers in three (fp16) or seven in eight (bf16).  256 units x 4096, d 128: scores 4.15 -> 3.85 ms in fp16, 4.57 -> 3.54 in bf16 (with the launch form
 // below); where every tile uses it (keys with one channel at 20, fp16) what is left is the test for it.
 // What bounds both kernels: the instructions of a SIMD in turn.  A vector instruction takes 4 cycles, one of these matrix instructions 8 of its 16 (alone and beside each
-// other, measured in loops of both); waves on one SIMD overlap the rest, two of them badly (rows with two tiles a wave: 1580 cycles a tile
-// where the instructions add up to 1040), four well (scores: 1030 of 880).  So scores keeps to 128 registers, rows to 168 (three waves) where a wave has one tile, and
+// other, measured in loops of both); waves on one SIMD overlap the rest, two of them badly (rows with two tiles a wave: 1640 cycles a tile
+// where the instructions add up to 1010), four well (scores: 1050 of 860).  So scores keeps to 128 registers, rows to 168 (three waves) where a wave has one tile, and
 // the paths for marked rows, which would take more, are functions of their own (128 units x 2048, bf16: rows 1.03 -> 0.94 ms, scores 0.71 -> 0.62).
 // The 32x32 matrix instructions would need half the issue cycles and were slower: the chip lowers its clock (2.2 -> 1.95 GHz).
 // A row whose elements are not all integers at its scale (an element more than 2^-23 below the
@@ -580,7 +569,7 @@ __device__ __forceinline__ void exact_rows(const char* qb, const char* kb, const
                                            const double* etab, int g, int x)
 {
     constexpr int NWORDS = D / 8, NE = D / 16;
-    const int kx = 4 * (x & 3) + (x >> 2), col = g * (D / 4) * TT::BYTES;     // keys: see exact_tiles
+    const int kx = 4 * (x & 3) + (x >> 2), col = g * (D / 4) * TT::BYTES;     // keys: see exact_tile
     uint32_t qw[NWORDS];
     double qd[2 * NWORDS];
     load_words<NWORDS>(qb + (size_t)min(qt * TILE + x, P - 1) * tok + col, qw);
@@ -797,7 +786,7 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
                                              const double* etab, int g, int x)
 {
     constexpr int NWORDS = D / 8;
-    const int kx = 4 * (x & 3) + (x >> 2), col = g * (D / 4) * TT::BYTES;     // keys: see exact_tiles
+    const int kx = 4 * (x & 3) + (x >> 2), col = g * (D / 4) * TT::BYTES;     // keys: see exact_tile
     uint32_t kw[NWORDS], next[NWORDS];
     double kd[2 * NWORDS], next_l, acc[4] = {0.0, 0.0, 0.0, 0.0};
     load_words<NWORDS>(kb + (size_t)min(kt * TILE + kx, P - 1) * tok + col, kw);
