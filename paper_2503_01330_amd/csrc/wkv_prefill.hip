@@ -214,7 +214,7 @@ template <class TT> struct RowSpan {
 template <class TT> __device__ __forceinline__ int digit_shift(uint32_t top, int& e, bool& bad) {
     const uint32_t one[1] = { top + (__is_same(TT, TF16) ? 8u : 1u) };
     e = (int)(__builtin_bit_cast(uint32_t, frag_elem<TT>(one, 0)) >> 23);
-    bad = e == 255 || (e < 36 && top != 0u);
+    bad = e >= 255 || (e < 36 && top != 0u);             // (beyond 255: the format's last NaNs, which the addition takes into the sign)
     return (top == 0u || bad) ? 0 : INT_BITS - 1 + 127 - e;
 }
 // Whether this lane's elements are no integers at that scale.  fp16 has no bit below 2^-24, so a row that

@@ -604,3 +604,54 @@ def test_digits_at_their_edges(P, units, dtype, d):
         print(f"\n  {parity.compare_prefill(big, got, decode_steps=3)}", flush=True)
     finally:
         got["cache"].close()
+
+
+@pytest.mark.parametrize("code", ["7FFF", "FFFF", "7FF9"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("P,units", [(129, 170), (129, 171), (3073, 256)])
+def test_a_nan_is_a_nan_whatever_its_bits(P, units, dtype, d, code):
+    """NaNs at the top of the code range (memory filled with ones; other makers' conversions), in one element, in whole rows and in a row
+    of zeros, of queries and of keys, in every launch form: what the call leaves is bit for bit what the format's usual NaN leaves, and the rows
+    that are NaN are those that attend to one, or ask with one."""
+    t = torch.float16 if dtype == "fp16" else torch.bfloat16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9700)
+    base = [x.to(t) for x in torch.randn(3, P, 9, d, generator=gen, device="cuda")]
+    usual = torch.tensor([float("nan")], dtype=t).view(torch.int16).item()
+    given = np.array([int(code, 16)], np.uint16).view(np.int16).item()
+    keys, queries = {}, {}                                     # unit: the first key, the queries that are NaN
+
+    def prompt(nan):
+        q, k, v = (x.clone() for x in base)
+        q, k = q.view(torch.int16), k.view(torch.int16)
+        k[37, 1, 5] = nan; keys[1] = 37
+        q[50, 2, 7] = nan; queries[2] = [50]
+        k[37, 3] = nan; keys[3] = 37
+        q[21, 4] = nan; queries[4] = [21]
+        k[:, 5] = nan; keys[5] = 0
+        q[:, 6] = nan; queries[6] = list(range(P))
+        k[100, 7] = 0; k[100, 7, 3] = nan; keys[7] = 100
+        q[16, 8] = 0; q[16, 8, 3] = nan; queries[8] = [16]
+        return [x.view(t)[:, torch.arange(units, device="cuda") % 9].contiguous() for x in (q, k, v)]
+
+    got = []
+    for nan in (usual, given):
+        q, k, v = prompt(nan)
+        out = torch.zeros_like(q)
+        cache = wkv.Cache(1, units, d, 100, 9, synth.DTYPE_CODE[dtype], split=1, log_capacity=1)
+        try:
+            cache.prefill(q, k, v, out)
+            torch.cuda.synchronize()
+            got.append((out.float().cpu().numpy(), *(cache.state(w) for w in (wkv.WKV_SCORE_SUM, wkv.WKV_POS, wkv.WKV_STATUS))))
+        finally:
+            cache.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f")
+    want = np.zeros((P, 9), bool)
+    for u, first in keys.items():
+        want[first:, u] = True
+    for u, rows in queries.items():
+        want[rows, u] = True
+    want = want[:, np.arange(units) % 9, None]
+    assert np.array_equal(np.isnan(got[1][0]), np.broadcast_to(want, got[1][0].shape))
