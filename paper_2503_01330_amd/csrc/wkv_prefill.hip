@@ -133,9 +133,10 @@ template <class TT> __device__ __forceinline__ float4_t mfma16(uint2_t a, uint2_
 // Score sums of 16 units, 77 to 1024 tokens, against 64 bits: 1.6e-16 to 1.4e-15 rms, 9.5e-15 at most (64 entries: 2.2e-15 to 8.8e-15, 5.5e-14; a cubic,
 // which saves 1 % of the prompt's time, 2.0e-15 to 1.1e-14).
 constexpr int EXP_STEPS = 256;
-__device__ __forceinline__ void exp_table_init(double* tab) {
+// unit: a power of two that every result is a multiple of (exactly: it only moves the exponent).
+__device__ __forceinline__ void exp_table_init(double* tab, double unit) {
     static_assert(EXP_STEPS == 256, "one entry a thread of a workgroup");
-    tab[threadIdx.x & 255] = exp2((double)(threadIdx.x & 255) * (1.0 / EXP_STEPS));
+    tab[threadIdx.x & 255] = unit * exp2((double)(threadIdx.x & 255) * (1.0 / EXP_STEPS));
     __syncthreads();
 }
 // ------------------------------------------------------------------ logits from 8-bit digits
@@ -175,7 +176,7 @@ typedef int int4v_t __attribute__((ext_vector_type(4)));
 constexpr double LOGIT_UNIT = 369.3299304675746;                           // 256 / ln 2
 template <int D> __device__ __forceinline__ double logit_scale() { return LOGIT_UNIT / sqrt((double)D); }
 
-// exp(x ln 2 / 256): method above the table.  -inf would give NaN, so where a
+// exp(x ln 2 / 256), times the table's unit: method above the table.  -inf would give NaN, so where a
 // logit may be -inf (a masked one, a row with infinities) the argument goes through no_infinity first.  NaN stays NaN.
 // Finite arguments go far beyond int (logits of fp16 rows reach 1e12 units): the cast, undefined there in C++, is the one
 // instruction v_cvt_i32_f64, which saturates, and with any k that low ldexp gives 0.  (That instruction written out costs 2 % of a
@@ -453,6 +454,7 @@ template <int NW> __device__ __forceinline__ bool mostly_marked(bool own, const 
 // Softmax and output accumulators of N consecutive tiles of 16 queries.
 template <class TT, int D, int N> struct Rows {
     static constexpr double AHEAD = 8.0 * EXP_STEPS;
+    static constexpr double UNIT = __is_same(TT, TBF16) ? 1.0 / 256 : 1.0;     // of the weights: the kernel's table has it
     static constexpr int NE = D / 16;         // output column sets: lane (g, x) owns columns NE*x .. NE*x+NE-1
     double m[N], l[N];                        // reference of query x (same in the 4 lanes x, x+16, ...); this lane's share of the sum
     float4_t o[N][NE];
@@ -470,7 +472,8 @@ template <class TT, int D, int N> struct Rows {
     __device__ __forceinline__ void add(double (&s)[N][4], const uint32_t (&vfrag)[4][NE / 2], bool infinities, bool lone, const double* etab, int g) {
         // Weights are relative to a reference m, the row's maximum when it was last looked for; that is when a logit exceeds it by
         // more than AHEAD units, so weights stay below 2^8 (and one of them is 1 or more: the 16-bit parts that P.V takes lose no more
-        // than with the running maximum itself).  Following the maximum costs a rescaling of the sum and all output
+        // than with the running maximum itself).  bf16 values reach 2^128, where a weight above 1 would take a product out of fp32: there all
+        // weights are times 2^-8 (UNIT), and what is added up is never more than with the running maximum.  Following the maximum costs a rescaling of the sum and all output
         // accumulators in every tile in which any of the wave's rows has a new one, 16 / k of the k-th tiles with random logits:
         // half the tiles of a prompt of 4096 where a wave has 32 rows.
         double tmax[N];
@@ -486,7 +489,7 @@ template <class TT, int D, int N> struct Rows {
                 const double top = pair_max<32>(pair_max<16>(tmax[i]));        // all 16 keys of the tile
                 const double mnew = fmax(m[i], top);          // finite: key 16 kt + 0 <= every query of a later tile,
                                                               // and on the diagonal key x is attended by query x
-                const double resc = exp_units(no_infinity(m[i] - mnew), etab);  // 0 on the first tile (m = -inf), 1 where nothing moved
+                const double resc = exp_units(no_infinity(m[i] - mnew), etab) * (1.0 / UNIT);  // 0 on the first tile (m = -inf), 1 where nothing moved
                 l[i] *= resc;
                 m[i] = mnew;
                 const float rf = (float)resc;                 // the output rows this lane holds (queries 4g + r') by their own factor
@@ -556,7 +559,7 @@ template <class TT, int D, int N> struct Rows {
                 }
             }
             const int tq = q0 + i * TILE + x;
-            if (g == 0 && tq < P) lse[tq] = m[i] + log(sum) * LOGIT_UNIT;
+            if (g == 0 && tq < P) lse[tq] = m[i] + log(sum * (1.0 / UNIT)) * LOGIT_UNIT;
         }
     }
 };
@@ -653,7 +656,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
     const int last = min(qt0 + TPG, ntiles) - 1;
     __shared__ double etab[EXP_STEPS];
     __shared__ SharedRows<D> sh;
-    exp_table_init(etab);
+    exp_table_init(etab, Rows<TT, D, QT>::UNIT);
     const size_t tok = (size_t)units * ROWB;                              // bytes from one token to the next
     const char* qb = reinterpret_cast<const char*>(q_) + (size_t)u * ROWB;
     const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;
@@ -760,7 +763,8 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
             const double m2 = dm[me + w * 64], l2 = dm[PS + me + w * 64];
             if (__all(l2 == 0.0)) continue;                                // uniform: no key of this part (a NaN goes on)
             const double mnew = fmax(rows.m[0], m2);
-            const double f1 = exp_units(no_infinity(rows.m[0] - mnew), etab), f2 = exp_units(no_infinity(m2 - mnew), etab);
+            const double f1 = exp_units(no_infinity(rows.m[0] - mnew), etab) * (1.0 / rows.UNIT);
+            const double f2 = exp_units(no_infinity(m2 - mnew), etab) * (1.0 / rows.UNIT);
             rows.l[0] = rows.l[0] * f1 + l2 * f2;
             rows.m[0] = mnew;
 #pragma unroll
@@ -857,7 +861,7 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     const bool active = kt < ntiles;
     __shared__ double etab[EXP_STEPS];
     __shared__ SharedRows<D> sh;
-    exp_table_init(etab);
+    exp_table_init(etab, 1.0);
     const size_t tok = (size_t)units * ROWB;
     const char* qb = reinterpret_cast<const char*>(q_) + (size_t)u * ROWB;
     const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;

@@ -655,3 +655,36 @@ def test_a_nan_is_a_nan_whatever_its_bits(P, units, dtype, d, code):
         want[rows, u] = True
     want = want[:, np.arange(units) % 9, None]
     assert np.array_equal(np.isnan(got[1][0]), np.broadcast_to(want, got[1][0].shape))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("P,units,marked", [(130, 4, 0), (129, 171, 0), (129, 171, 1), (3073, 256, 0)])
+@pytest.mark.parametrize("largest", [2.0 ** 126, 2.0 ** -110])
+def test_values_at_both_ends_of_bf16(largest, P, units, marked, d):
+    """Logits rise by 7 octaves of the weight after the first tiles, which is less than what moves the softmax reference, and the token they rise
+    for has a value near the format's largest: the output is finite, and so must be all that is added up on the way.  And small values, whose products
+    with the lowest parts of small weights are below the normal fp32 numbers (from 2^-118 on results are rounded to bf16's own subnormal numbers, where the bound below
+    does not hold).  Every launch form; with marked: keys that take the fp64 instruction."""
+    T, m = P + 4, 100
+    g = np.random.default_rng(9800)
+    q, k = (0.05 * g.standard_normal((T, 4, d)).astype(np.float32) for _ in range(2))
+    v = g.uniform(0.5, 1.0, (T, 4, d)).astype(np.float32) * np.float32(largest) * np.where(g.random((T, 4, d)) < 0.5, -1, 1).astype(np.float32)
+    if largest > 1.0:
+        v *= np.float32(2.0 ** -9)
+    q[..., 0] = np.sqrt(d)
+    k[..., 0] = 0.0
+    for u in range(4):
+        t = 40 + 13 * u
+        k[t, u, 0] = 7.0 * np.log(2.0)
+        v[t, u] = g.uniform(0.5, 1.0, d) * largest
+    if marked:
+        k[:, :, 1] = 2.0 ** 10
+        q[:, :, 1] = 0.0
+        k[:, :, 2] = 2.0 ** -22
+    cfg = synth.StreamConfig("pre-ends", 9800, 1, units, d, "bf16", T, m, 9)
+    rep = np.arange(units) % 4
+    got = parity.gpu_prefill(cfg, P, arrays=tuple(np.ascontiguousarray(x[:, rep]) for x in (q, k, v)), units_sel=np.arange(4))
+    try:
+        print(f"\n  {parity.compare_prefill(cfg, got)}", flush=True)
+    finally:
+        got["cache"].close()
