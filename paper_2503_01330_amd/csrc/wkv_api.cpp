@@ -199,6 +199,9 @@ struct Kept {
 
 struct Staging {
     static constexpr size_t SLOTS = 4, CHUNK = 1 << 20, KEPT = SLOTS * (2 << 20);
+    // Coherent, stated and not left to the runtime's default: the host rewrites a slot that an earlier kernel has read, and reads one that
+    // a kernel has written, while later kernels of the call still run.
+    static constexpr unsigned FLAGS = hipHostMallocPortable | hipHostMallocCoherent;
     char* p = nullptr;
     hipEvent_t event[SLOTS] = {};
     size_t units = 0, chunks = 0, slots = 0, stride = 0;       // units of a chunk
@@ -217,7 +220,7 @@ struct Staging {
                 if (g_kept.n < need) {                         // (a larger one than this call needs, for the next)
                     if (g_kept.p) (void)hipHostFree(g_kept.p);
                     g_kept.n = 0;
-                    e = hipHostMalloc((void**)&g_kept.p, KEPT, hipHostMallocPortable);
+                    e = hipHostMalloc((void**)&g_kept.p, KEPT, FLAGS);
                     if (e != hipSuccess) { g_kept.p = nullptr; return e; }
                     g_kept.n = KEPT;
                 }
@@ -225,7 +228,7 @@ struct Staging {
                 g_kept.lent = borrowed = true;
             }
         }
-        if (!borrowed) e = hipHostMalloc((void**)&p, need, hipHostMallocDefault);
+        if (!borrowed) e = hipHostMalloc((void**)&p, need, FLAGS);
         for (size_t i = 0; i < slots && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&event[i], hipEventDisableTiming);
         return e;
     }

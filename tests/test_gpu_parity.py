@@ -493,14 +493,16 @@ def test_checkpoint_and_resume():
             a.close(); b.close()
 
 
-def test_plain_c_caller():
-    """tests/c_abi/check.c drives libwkv from C (hipMalloc'ed buffers, no Python in the loop)."""
+@pytest.mark.parametrize("name,says", [("check", "c_abi ok"), ("pinned", "pinned ok")])
+def test_plain_c_caller(name, says):
+    """tests/c_abi/*.c drive libwkv from C (hipMalloc'ed buffers, no Python in the loop): the whole boundary; the pinned memory
+    of readback and upload."""
     import os
     import subprocess
-    exe = os.path.join(os.path.dirname(os.path.abspath(__file__)), "c_abi", "check")
+    exe = os.path.join(os.path.dirname(os.path.abspath(__file__)), "c_abi", name)
     assert os.path.exists(exe), "build it first: python -c 'import __graft_entry__ as g; g.build()'"
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
-    assert r.returncode == 0 and "c_abi ok" in r.stdout, r.stdout + r.stderr
+    assert r.returncode == 0 and says in r.stdout, r.stdout + r.stderr
 
 
 def _made_up_state(units, m, length, d, dtype, seed):
