@@ -205,9 +205,10 @@ int wkv_prefill_noalloc(wkv_handle* h, const void* q, const void* k, const void*
  * device memory.  For the two eviction logs, n = bytes / (4*units) most recent
  * steps are returned, oldest first; n must not exceed min(tokens, log_capacity).
  * For everything else `bytes` must be at least the size listed above
- * (WKV_ESIZE otherwise; nothing is written then).  Slot arrays travel through pinned host memory: a few
+ * (WKV_ESIZE otherwise; nothing is written then).  Slot arrays travel through pinned host memory: 8
  * megabytes of it are kept from the first such call (or wkv_load) on, until the process's last handle is
- * destroyed; calls on several threads at once are fine.  Like every call that takes a handle, it
+ * destroyed; calls on several threads at once are fine.  Where the system refuses pinned memory they travel, more slowly, through as
+ * much device memory, allocated for the call; WKV_ENOMEM if that is refused too.  Like every call that takes a handle, it
  * must come with the handle's device current (WKV_EINVAL otherwise); wkv_destroy alone does
  * not mind.
  */
@@ -221,7 +222,7 @@ int wkv_state(wkv_handle* h, int what, void* host_dst, size_t bytes);
  *   K, V   : dtype[units,len,d];  score_sum : double[units,len];  pos : int32[units,len],
  *            strictly increasing within a unit, last entry = tokens-1, all < tokens
  * Counts and merge counts follow from pos and are not passed.  Synchronous; waits for
- * enqueued work first.  The eviction log is cleared.  On error the cache is unchanged, except for
+ * enqueued work first.  The eviction log is cleared.   On error the cache is unchanged, except for
  * WKV_EHIP during the upload itself (the message says so).
  */
 int wkv_load(wkv_handle* h, int64_t tokens, int len, const void* K, const void* V,

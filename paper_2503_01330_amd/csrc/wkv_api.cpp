@@ -179,70 +179,92 @@ struct wkv_handle {
 
 namespace {
 
-// Pinned memory through which readbacks and uploads go: a few slots of a chunk of units (about a megabyte, or one unit), and an event each.
-// The memory of the first one is kept for the next (made anew for each, its pages cost 230 us of a 5.7 MB matrix' 400): one
-// block of at most KEPT bytes in the process, lent to one call at a time (another thread's call gets memory of its
-// own meanwhile), freed with the last handle.
+// Memory through which readbacks and uploads go: a few slots of a chunk of units (about a megabyte, or one unit), and an event each.
+// It is pinned, and the memory of the first call is kept for the next (made anew for each, its pages cost 230 us of a 5.7 MB matrix' 400): one
+// block of KEPT bytes in the process, lent to one call at a time (another thread's call gets memory of its
+// own meanwhile), freed with the last handle.  Where the system has no pinned memory to give, the slots are device memory and go to
+// and from the caller's by copies that pageable memory takes.
 struct Kept {
     std::mutex mu;
     char* p = nullptr;
-    size_t n = 0;
     int handles = 0;
     bool lent = false;
     void created() { std::lock_guard<std::mutex> lock(mu); ++handles; }
     void destroyed()
     {
         std::lock_guard<std::mutex> lock(mu);
-        if (--handles == 0 && p && !lent) { (void)hipHostFree(p); p = nullptr; n = 0; }
+        if (--handles == 0 && !lent) release();
     }
+    void release() { if (p) (void)hipHostFree(p); p = nullptr; }
 } g_kept;
 
 struct Staging {
     static constexpr size_t SLOTS = 4, CHUNK = 1 << 20, KEPT = SLOTS * (2 << 20);
+    static_assert((size_t)WKV_MAX_BUDGET * 512 <= KEPT / SLOTS, "a slot holds the largest unit");
     // Coherent, stated and not left to the runtime's default: the host rewrites a slot that an earlier kernel has read, and reads one that
     // a kernel has written, while later kernels of the call still run.
     static constexpr unsigned FLAGS = hipHostMallocPortable | hipHostMallocCoherent;
     char* p = nullptr;
     hipEvent_t event[SLOTS] = {};
-    size_t units = 0, chunks = 0, slots = 0, stride = 0;       // units of a chunk
-    bool borrowed = false;
-    hipError_t open(size_t all, size_t unit_bytes)
+    size_t all = 0, units = 0, chunks = 0, slots = 0, stride = 0;       // units of the cache, of a chunk
+    bool borrowed = false, device = false;
+    // Cuts the cache into chunks for items of unit_bytes a unit; returns the bytes that takes.  Between two items the caller waits.
+    size_t cut(size_t unit_bytes)
     {
         units = std::min(all, std::max<size_t>(1, CHUNK / unit_bytes));
         chunks = (all + units - 1) / units;
         slots = std::min(SLOTS, chunks);
         stride = (units * unit_bytes + 255) / 256 * 256;
-        const size_t need = slots * stride;
+        return slots * stride;
+    }
+    // Everything that can fail for want of memory; items of up to `bytes` (see cut) and most_chunks chunks go through it.
+    hipError_t open(size_t bytes, size_t most_chunks)
+    {
         hipError_t e = hipSuccess;
+        bool lent;
         {
             std::lock_guard<std::mutex> lock(g_kept.mu);
-            if (!g_kept.lent && need <= KEPT) {
-                if (g_kept.n < need) {                         // (a larger one than this call needs, for the next)
-                    if (g_kept.p) (void)hipHostFree(g_kept.p);
-                    g_kept.n = 0;
-                    e = hipHostMalloc((void**)&g_kept.p, KEPT, FLAGS);
-                    if (e != hipSuccess) { g_kept.p = nullptr; return e; }
-                    g_kept.n = KEPT;
-                }
+            lent = g_kept.lent;
+            if (!lent) {
+                if (!g_kept.p) e = hipHostMalloc((void**)&g_kept.p, KEPT, FLAGS);
+                if (e != hipSuccess) g_kept.p = nullptr;
                 p = g_kept.p;
-                g_kept.lent = borrowed = true;
+                g_kept.lent = borrowed = p != nullptr;
             }
         }
-        if (!borrowed) e = hipHostMalloc((void**)&p, need, FLAGS);
-        for (size_t i = 0; i < slots && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&event[i], hipEventDisableTiming);
+        if (lent) e = hipHostMalloc((void**)&p, bytes, FLAGS);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            e = hipMalloc((void**)&p, bytes);
+            device = e == hipSuccess;
+            if (!device) p = nullptr;
+        }
+        for (size_t i = 0; i < std::min(SLOTS, most_chunks) && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&event[i], hipEventDisableTiming);
         return e;
     }
     char* slot(size_t chunk) const { return p + chunk % slots * stride; }
-    size_t count(size_t chunk, size_t all) const { return std::min(units, all - chunk * units); }
+    size_t count(size_t chunk) const { return std::min(units, all - chunk * units); }
+    // From a slot to the caller's memory, and from there to a slot
+    hipError_t out(void* to, const void* from, size_t n) const { return copy(to, from, n, hipMemcpyDeviceToHost); }
+    hipError_t in(void* to, const void* from, size_t n) const { return copy(to, from, n, hipMemcpyHostToDevice); }
+    hipError_t copy(void* to, const void* from, size_t n, hipMemcpyKind kind) const
+    {
+        if (device) return hipMemcpy(to, from, n, kind);
+        memcpy(to, from, n);
+        return hipSuccess;
+    }
     ~Staging()
     {
         if (p == nullptr) return;
         (void)hipStreamSynchronize(nullptr);                   // (a call that failed half way may have left work behind)
         for (hipEvent_t ev : event) if (ev) (void)hipEventDestroy(ev);
-        if (!borrowed) { (void)hipHostFree(p); return; }
+        if (!borrowed) {
+            (void)(device ? hipFree(p) : hipHostFree(p));
+            return;
+        }
         std::lock_guard<std::mutex> lock(g_kept.mu);
         g_kept.lent = false;
-        if (g_kept.handles == 0) { (void)hipHostFree(g_kept.p); g_kept.p = nullptr; g_kept.n = 0; }
+        if (g_kept.handles == 0) g_kept.release();
     }
 };
 
@@ -577,15 +599,17 @@ static int state_impl(wkv_handle* h, int what, void* dst, size_t bytes)
     // A kernel puts a few units' slots in token order into pinned memory while the previous ones' are copied to the caller
     const size_t unit_bytes = need / units;
     Staging st;
-    e = st.open(units, unit_bytes);
+    st.all = units;
+    const size_t staged = st.cut(unit_bytes);
+    e = st.open(staged, st.chunks);
     for (size_t i = 0; i < st.chunks + st.slots && e == hipSuccess; ++i) {
         if (i >= st.slots) {                            // chunk i - slots has its slot: wait for it, copy it out
             const size_t j = i - st.slots;
             e = hipEventSynchronize(st.event[j % st.slots]);
-            if (e == hipSuccess) memcpy((char*)dst + j * st.units * unit_bytes, st.slot(j), st.count(j, units) * unit_bytes);
+            if (e == hipSuccess) e = st.out((char*)dst + j * st.units * unit_bytes, st.slot(j), st.count(j) * unit_bytes);
         }
         if (i < st.chunks && e == hipSuccess) {
-            e = wkv_launch_gather(c, what, (int)(d * eb), (int)(i * st.units), (int)st.count(i, units), (int)len, T, st.slot(i), nullptr);
+            e = wkv_launch_gather(c, what, (int)(d * eb), (int)(i * st.units), (int)st.count(i), (int)len, T, st.slot(i), nullptr);
             if (e == hipSuccess) e = hipEventRecord(st.event[i % st.slots], nullptr);
         }
     }
@@ -629,18 +653,19 @@ static int load_impl(wkv_handle* h, int64_t tokens, int len, const void* K, cons
         e = wkv_launch_clear(c, nullptr);
         if (e == hipSuccess) e = hipDeviceSynchronize();
     } else {
-        // device layout: slot l of a unit holds the l-th token in token order, links run l -> l+1.  Through pinned memory, a few
-        // units at a time: a kernel places them while the next ones are copied there.
-        const size_t rb = (size_t)h->opt.head_dim * dtype_bytes(h->opt.dtype);
+        // device layout: slot l of a unit holds the l-th token in token order, links run l -> l+1.  A few
+        // units at a time: a kernel places them while the next ones are copied to a slot.
+        const size_t rb = (size_t)h->opt.head_dim * dtype_bytes(h->opt.dtype), row_bytes = len * rb, item_bytes = (size_t)len * 12;
         e = wkv_launch_clear(c, nullptr);
         auto upload = [&](size_t unit_bytes, auto&& fill, auto&& place) {
             Staging st;
-            hipError_t e2 = st.open(units, unit_bytes);
+            st.all = units;
+            const size_t staged = st.cut(unit_bytes);
+            hipError_t e2 = st.open(staged, st.chunks);
             for (size_t i = 0; i < st.chunks && e2 == hipSuccess; ++i) {
                 if (i >= st.slots) e2 = hipEventSynchronize(st.event[i % st.slots]);     // its last contents have been placed
-                if (e2 != hipSuccess) break;
-                fill(st.slot(i), i * st.units, st.count(i, units));
-                e2 = place(st.slot(i), (int)(i * st.units), (int)st.count(i, units));
+                if (e2 == hipSuccess) e2 = fill(st, st.slot(i), i * st.units, st.count(i));
+                if (e2 == hipSuccess) e2 = place(st.slot(i), (int)(i * st.units), (int)st.count(i));
                 if (e2 == hipSuccess) e2 = hipEventRecord(st.event[i % st.slots], nullptr);
             }
             const hipError_t e3 = hipDeviceSynchronize();                                // before the memory goes
@@ -649,14 +674,14 @@ static int load_impl(wkv_handle* h, int64_t tokens, int len, const void* K, cons
         for (int what : { WKV_K, WKV_V }) {
             const char* src = static_cast<const char*>(what == WKV_K ? K : V);
             if (e == hipSuccess)
-                e = upload(len * rb, [&](char* to, size_t u0, size_t n) { memcpy(to, src + u0 * len * rb, n * len * rb); },
+                e = upload(row_bytes, [&](const Staging& st, char* to, size_t u0, size_t n) { return st.in(to, src + u0 * row_bytes, n * row_bytes); },
                            [&](const char* from, int u0, int n) { return wkv_launch_place_rows(c, what, (int)rb, u0, n, len, from, nullptr); });
         }
         // score sums of a chunk's units, then their token indices
         if (e == hipSuccess)
-            e = upload(len * 12, [&](char* to, size_t u0, size_t n) {
-                           memcpy(to, score_sum + u0 * len, n * len * 8);
-                           memcpy(to + n * len * 8, pos + u0 * len, n * len * 4);
+            e = upload(item_bytes, [&](const Staging& st, char* to, size_t u0, size_t n) {
+                           const hipError_t e2 = st.in(to, score_sum + u0 * len, n * len * 8);
+                           return e2 != hipSuccess ? e2 : st.in(to + n * len * 8, pos + u0 * len, n * len * 4);
                        },
                        [&](const char* from, int u0, int n) {
                            return wkv_launch_place_items(c, u0, n, len, (const double*)from, (const int32_t*)(from + (size_t)n * len * 8), nullptr);

@@ -1,8 +1,9 @@
 /*
  * Readback and upload (wkv_state, wkv_load) as a C caller sees them that stands between libwkv and the HIP runtime: this
- * program's own hipHostMalloc and hipEventSynchronize are the ones the library calls (the symbols of an executable come first).
+ * program's own hipHostMalloc, hipMalloc and hipEventSynchronize are the ones the library calls (the symbols of an executable come first).
  *   - All pinned memory is asked for as coherent: the host rewrites a slot, and reads one, while kernels of the same call still run.
  *   - A call that finds the kept memory lent to another thread's call gets memory of its own, of the same kind.
+ *   - Without pinned memory both calls work all the same; without device memory either they say so.
  * Prints "pinned ok" and exits 0 on success.
  */
 #define _GNU_SOURCE
@@ -20,14 +21,22 @@
 #define WKV(x) do { int r_ = (x); if (r_ != WKV_OK) { printf("wkv: %d %s (line %d)\n", r_, wkv_last_error(), __LINE__); exit(3); } } while (0)
 #define CHECK(c) do { if (!(c)) { printf("check failed: %s (line %d)\n", #c, __LINE__); exit(4); } } while (0)
 
-static int host_calls, host_flags_differ;
+static int host_calls, host_flags_differ, refuse_host, refuse_device;
 hipError_t hipHostMalloc(void** p, size_t n, unsigned flags)
 {
     static hipError_t (*next)(void**, size_t, unsigned);
     if (!next) next = (hipError_t (*)(void**, size_t, unsigned))dlsym(RTLD_NEXT, "hipHostMalloc");
     ++host_calls;
+    if (refuse_host) return hipErrorOutOfMemory;
     if (flags != (hipHostMallocPortable | hipHostMallocCoherent)) { ++host_flags_differ; printf("hipHostMalloc with flags 0x%x\n", flags); }
     return next(p, n, flags);
+}
+
+hipError_t hipMalloc(void** p, size_t n)
+{
+    static hipError_t (*next)(void**, size_t);
+    if (!next) next = (hipError_t (*)(void**, size_t))dlsym(RTLD_NEXT, "hipMalloc");
+    return refuse_device ? hipErrorOutOfMemory : next(p, n);
 }
 
 /* A thread that has `held` set stops in its first wait for an event until it is let go. */
@@ -94,6 +103,21 @@ int main(void)
     make(0, 1u);
     make(1, 2u);
     HIP(hipSetDevice(0));
+
+    /* no pinned memory: nothing is kept from these calls */
+    refuse_host = 1;
+    WKV(wkv_create(&h, 1, UNITS, D, M, 9, WKV_FP32));
+    WKV(wkv_load(h, TOKENS, M, K[0], V[0], A[0], P[0]));
+    expect(h, 0);
+    CHECK(host_calls > 0);
+    refuse_device = 1;
+    CHECK(wkv_state(h, WKV_K, back[0], sizeof back[0]) == WKV_ENOMEM);
+    refuse_host = refuse_device = 0;
+    host_calls = 0;
+    expect(h, 0);
+    WKV(wkv_destroy(h));
+    host_calls = 0;
+
     WKV(wkv_create(&h, 1, UNITS, D, M, 9, WKV_FP32));
     WKV(wkv_create(&other, 1, UNITS, D, M, 9, WKV_FP32));
     WKV(wkv_load(h, TOKENS, M, K[0], V[0], A[0], P[0]));
