@@ -222,8 +222,8 @@ int wkv_state(wkv_handle* h, int what, void* host_dst, size_t bytes);
  *   K, V   : dtype[units,len,d];  score_sum : double[units,len];  pos : int32[units,len],
  *            strictly increasing within a unit, last entry = tokens-1, all < tokens
  * Counts and merge counts follow from pos and are not passed.  Synchronous; waits for
- * enqueued work first.  The eviction log is cleared.   On error the cache is unchanged, except for
- * WKV_EHIP during the upload itself (the message says so).
+ * enqueued work first.  The eviction log is cleared.  Memory for the way there as for wkv_state.  On error the cache is
+ * unchanged (WKV_ENOMEM among them), except for WKV_EHIP during the upload itself (the message says so).
  */
 int wkv_load(wkv_handle* h, int64_t tokens, int len, const void* K, const void* V,
              const double* score_sum, const int32_t* pos);

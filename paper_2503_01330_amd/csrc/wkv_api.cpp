@@ -654,32 +654,39 @@ static int load_impl(wkv_handle* h, int64_t tokens, int len, const void* K, cons
         if (e == hipSuccess) e = hipDeviceSynchronize();
     } else {
         // device layout: slot l of a unit holds the l-th token in token order, links run l -> l+1.  A few
-        // units at a time: a kernel places them while the next ones are copied to a slot.
+        // units at a time: a kernel places them while the next ones are copied to a slot.  Whatever may find no memory comes before the first
+        // change of the cache.
         const size_t rb = (size_t)h->opt.head_dim * dtype_bytes(h->opt.dtype), row_bytes = len * rb, item_bytes = (size_t)len * 12;
+        Staging st;
+        st.all = units;
+        const size_t staged = std::max(st.cut(item_bytes), st.cut(row_bytes));           // (rows come in at least as many chunks)
+        e = st.open(staged, st.chunks);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(e == hipErrorOutOfMemory ? WKV_ENOMEM : WKV_EHIP, "memory for the upload: %s (the cache is unchanged)", hipGetErrorString(e));
+        }
         e = wkv_launch_clear(c, nullptr);
         auto upload = [&](size_t unit_bytes, auto&& fill, auto&& place) {
-            Staging st;
-            st.all = units;
-            const size_t staged = st.cut(unit_bytes);
-            hipError_t e2 = st.open(staged, st.chunks);
+            st.cut(unit_bytes);
+            hipError_t e2 = hipSuccess;
             for (size_t i = 0; i < st.chunks && e2 == hipSuccess; ++i) {
                 if (i >= st.slots) e2 = hipEventSynchronize(st.event[i % st.slots]);     // its last contents have been placed
-                if (e2 == hipSuccess) e2 = fill(st, st.slot(i), i * st.units, st.count(i));
+                if (e2 == hipSuccess) e2 = fill(st.slot(i), i * st.units, st.count(i));
                 if (e2 == hipSuccess) e2 = place(st.slot(i), (int)(i * st.units), (int)st.count(i));
                 if (e2 == hipSuccess) e2 = hipEventRecord(st.event[i % st.slots], nullptr);
             }
-            const hipError_t e3 = hipDeviceSynchronize();                                // before the memory goes
+            const hipError_t e3 = hipDeviceSynchronize();                                // before the next item takes the slots
             return e2 != hipSuccess ? e2 : e3;
         };
         for (int what : { WKV_K, WKV_V }) {
             const char* src = static_cast<const char*>(what == WKV_K ? K : V);
             if (e == hipSuccess)
-                e = upload(row_bytes, [&](const Staging& st, char* to, size_t u0, size_t n) { return st.in(to, src + u0 * row_bytes, n * row_bytes); },
+                e = upload(row_bytes, [&](char* to, size_t u0, size_t n) { return st.in(to, src + u0 * row_bytes, n * row_bytes); },
                            [&](const char* from, int u0, int n) { return wkv_launch_place_rows(c, what, (int)rb, u0, n, len, from, nullptr); });
         }
         // score sums of a chunk's units, then their token indices
         if (e == hipSuccess)
-            e = upload(item_bytes, [&](const Staging& st, char* to, size_t u0, size_t n) {
+            e = upload(item_bytes, [&](char* to, size_t u0, size_t n) {
                            const hipError_t e2 = st.in(to, score_sum + u0 * len, n * len * 8);
                            return e2 != hipSuccess ? e2 : st.in(to + n * len * 8, pos + u0 * len, n * len * 4);
                        },
@@ -693,7 +700,7 @@ static int load_impl(wkv_handle* h, int64_t tokens, int len, const void* K, cons
     }
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        return fail(e == hipErrorOutOfMemory ? WKV_ENOMEM : WKV_EHIP, "uploading the state: %s (the cache may be partly overwritten)", hipGetErrorString(e));
+        return fail(WKV_EHIP, "uploading the state: %s (the cache may be partly overwritten)", hipGetErrorString(e));
     }
     h->t = tokens;
     h->log_from = tokens;

@@ -3,7 +3,7 @@
  * program's own hipHostMalloc, hipMalloc and hipEventSynchronize are the ones the library calls (the symbols of an executable come first).
  *   - All pinned memory is asked for as coherent: the host rewrites a slot, and reads one, while kernels of the same call still run.
  *   - A call that finds the kept memory lent to another thread's call gets memory of its own, of the same kind.
- *   - Without pinned memory both calls work all the same; without device memory either they say so.
+ *   - Without pinned memory both calls work all the same; without device memory either they say so, and the cache is what it was.
  * Prints "pinned ok" and exits 0 on success.
  */
 #define _GNU_SOURCE
@@ -111,6 +111,7 @@ int main(void)
     expect(h, 0);
     CHECK(host_calls > 0);
     refuse_device = 1;
+    CHECK(wkv_load(h, TOKENS, M, K[1], V[1], A[1], P[1]) == WKV_ENOMEM);
     CHECK(wkv_state(h, WKV_K, back[0], sizeof back[0]) == WKV_ENOMEM);
     refuse_host = refuse_device = 0;
     host_calls = 0;
