@@ -75,6 +75,17 @@ constexpr int XCDS = 8;
 __device__ __forceinline__ int xcd_unit(unsigned b, int groups) { return (int)((b >> 3) / groups) * XCDS + (int)(b & 7); }
 inline int xcd_grid(int units, int groups) { return (units + XCDS - 1) / XCDS * XCDS * groups; }
 
+// Units of a launch.  A grid of 2^32 threads and more is not refused: the count wraps, without an error (2796203 units x 3 workgroups of
+// 512 threads: one ran).  So a launch has at most 2^31, in whole rounds of the partitions.
+constexpr int units_of_a_launch(int workgroups, int threads) { return (int)((1ll << 31) / threads / workgroups) / XCDS * XCDS; }
+static_assert(units_of_a_launch(1, 1024) == 1 << 21 && units_of_a_launch(256, 1024) >= XCDS && units_of_a_launch(3, 512) * 3ll * 512 <= 1ll << 31,
+              "every kernel of a prompt has launches of some units");
+// launch(u0, n) for the units u0 .. u0 + n - 1, until all have been launched
+template <class F> inline void launches(int units, int workgroups, int threads, F&& launch) {
+    const int most = units_of_a_launch(workgroups, threads);
+    for (int u0 = 0; u0 < units; u0 += most) launch(u0, units - u0 < most ? units - u0 : most);
+}
+
 // Four softmax weights p >= 0, each as a sum of 16-bit numbers of the cache format, packed as MFMA
 // operands, so that P.V can run on the 16-bit matrix instruction without costing accuracy against
 // an fp32 P.V.  Every part but the last is the running remainder cut to the format's significand
@@ -639,7 +650,7 @@ __device__ __attribute__((noinline)) void exact_rows_apart(const char* qb, const
 template <class TT, int D, int NW, int QT, int SPLIT>
 __global__ __launch_bounds__(64 * NW, D == 128 && SPLIT == 1 && QT == 1 ? 3 : 2)
 void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, const void* __restrict__ v_,
-                      void* __restrict__ out_, double* __restrict__ lse, int P, int units)
+                      void* __restrict__ out_, double* __restrict__ lse, int P, int units, int unit0)
 {
     constexpr int ROWB = D * TT::BYTES;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -647,7 +658,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
     const int ntiles = (P + TILE - 1) / TILE;
     constexpr int TPG = NW / SPLIT * QT;                                         // tiles of a workgroup
     const int groups = (ntiles + TPG - 1) / TPG;
-    const int u = xcd_unit(blockIdx.x, groups);
+    const int u = unit0 + xcd_unit(blockIdx.x, groups);
     const int qt0 = (groups - 1 - (int)((blockIdx.x >> 3) % groups)) * TPG;      // long rows are scheduled first
     if (u >= units) return;                                                      // the whole workgroup
     const int qt = qt0 + wid / SPLIT * QT, part = wid % SPLIT;                   // first tile of the wave; its share of the keys
@@ -846,7 +857,7 @@ __device__ __attribute__((noinline)) void exact_scores_apart(const char* qb, con
 template <class TT, int D, int NW, int SPLIT>
 __global__ __launch_bounds__(64 * NW, D == 128 && SPLIT == 1 ? 4 : 2)
 void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_, const double* __restrict__ lse,
-                        double* __restrict__ a, int P, int units)
+                        double* __restrict__ a, int P, int units, int unit0)
 {
     constexpr int ROWB = D * TT::BYTES;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -854,7 +865,7 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     const int ntiles = (P + TILE - 1) / TILE;
     constexpr int TPG = NW / SPLIT;                                       // tiles of a workgroup
     const int groups = (ntiles + TPG - 1) / TPG;
-    const int u = xcd_unit(blockIdx.x, groups);
+    const int u = unit0 + xcd_unit(blockIdx.x, groups);
     const int kt0 = (int)((blockIdx.x >> 3) % groups) * TPG;              // low key tiles have the most rows: first
     if (u >= units) return;                                               // the whole workgroup
     const int kt = kt0 + wid / SPLIT, part = wid % SPLIT;
@@ -971,10 +982,10 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
 //      own coefficient | slot[P] | wcnt[NT] (one per wave is used) | rk[P] rank (16 bit) | par[P] parent (16 bit) |
 //      ptr[P] list successor (16 bit) | bmax[64]; gmax[512] takes wcnt's place.  The sort keys borrow ae[], a0[] and slot[].
 __global__ __launch_bounds__(1024)
-void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __restrict__ weight, int P)
+void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __restrict__ weight, int P, int unit0)
 {
     const int tid = threadIdx.x, NT = blockDim.x, lane = tid & 63, wid = tid >> 6, NW = NT >> 6;
-    const int u = blockIdx.x, m = c.m;
+    const int u = unit0 + blockIdx.x, m = c.m;
     double*  au = c.a + (size_t)u * m;
     int32_t* pu = c.pos + (size_t)u * m;
     int32_t* nu = c.nxt + (size_t)u * m;
@@ -1392,9 +1403,13 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
     const long long tiles = (long long)c.units * ntiles;
     auto contract = [&](auto tiles_c, auto split_c) {
         constexpr int T = decltype(tiles_c)::value, S = decltype(split_c)::value, TPG = NW / S * T, NS = 4 * T, TPS = NS / S;
-        const int grid = xcd_grid(c.units, (ntiles + TPG - 1) / TPG), grids = xcd_grid(c.units, (ntiles + TPS - 1) / TPS);
-        hipLaunchKernelGGL((wkv_prefill_rows<TT, D, NW, T, S>), dim3(grid), dim3(64 * NW), 0, stream, q, k, v, out, lse, P, c.units);
-        hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NS, S>), dim3(grids), dim3(64 * NS), 0, stream, q, k, lse, a, P, c.units);
+        const int groups = (ntiles + TPG - 1) / TPG, groups_s = (ntiles + TPS - 1) / TPS;
+        launches(c.units, groups, 64 * NW, [&](int u0, int n) {
+            hipLaunchKernelGGL((wkv_prefill_rows<TT, D, NW, T, S>), dim3(xcd_grid(n, groups)), dim3(64 * NW), 0, stream, q, k, v, out, lse, P, c.units, u0);
+        });
+        launches(c.units, groups_s, 64 * NS, [&](int u0, int n) {
+            hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NS, S>), dim3(xcd_grid(n, groups_s)), dim3(64 * NS), 0, stream, q, k, lse, a, P, c.units, u0);
+        });
     };
     using std::integral_constant;
     if (two_waves_a_tile(tiles, P)) {
@@ -1412,17 +1427,15 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
         if (e != hipSuccess) return e;
         const size_t lds = wkv_prefill_lds_bytes(P);
         // the row log-sum-exps have been used: their place takes the weights of the tokens
-        hipLaunchKernelGGL(wkv_prefill_compress, dim3(c.units), dim3(1024), lds, stream, c, a, lse, P);
+        launches(c.units, 1, 1024, [&](int u0, int n) {
+            hipLaunchKernelGGL(wkv_prefill_compress, dim3(n), dim3(1024), lds, stream, c, a, lse, P, u0);
+        });
     }
     const int blocks = ((P < c.m ? P : c.m) + FOLD_ROWS - 1) / FOLD_ROWS;
     const int merging = c.merge_mode == 0 && P > c.m;
-    // units x blocks workgroups may come to 2^32 threads and more, which a launch does not hold: the count wraps, without an
-    // error (2796203 units x 33 survivors: one workgroup ran).  One launch for every 2^22 workgroups.
-    const int most = (1 << 22) / blocks;                      // units of a launch; blocks <= 256
-    for (int u0 = 0; u0 < c.units; u0 += most) {
-        const int n = c.units - u0 < most ? c.units - u0 : most;
+    launches(c.units, blocks, 64 * FOLD_WAVES, [&](int u0, int n) {
         hipLaunchKernelGGL((wkv_prefill_fold<TT, D>), dim3(n * blocks), dim3(64 * FOLD_WAVES), 0, stream, c, k, v, lse, a, P, u0, blocks, merging);
-    }
+    });
     return hipGetLastError();
 }
 

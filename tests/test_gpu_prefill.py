@@ -688,3 +688,35 @@ def test_values_at_both_ends_of_bf16(largest, P, units, marked, d):
         print(f"\n  {parity.compare_prefill(cfg, got)}", flush=True)
     finally:
         got["cache"].close()
+
+
+@pytest.mark.parametrize("units", [(1 << 22) + 3, (1 << 24) - 1])
+def test_prompts_of_more_units_than_a_launch_has_threads_for(units):
+    """2^22 units and more are 2^32 threads in the kernel that ranks a unit's tokens, 2^24 - 1 (rounded up to whole partitions) in the two contractions
+    as well.  Two tokens into one slot; five units' inputs, repeated: the step after the prompt gives every unit what the
+    same unit gets in a smaller handle of the same launch form, bit for bit."""
+    P, d = 2, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9900)
+    base = torch.randn(P + 1, 5, d, generator=gen, device="cuda").half()
+
+    def next_out(units):
+        x = base[:, torch.arange(units, device="cuda") % 5].contiguous().view(P + 1, units, 1, d)
+        cache = wkv.Cache(units, 1, d, 1, 1, wkv.WKV_FP16, split=1, threads=256, streaming=wkv.WKV_LOADS_CACHED, log_capacity=1)
+        try:
+            out = torch.empty_like(x[P])
+            cache.prefill(x[:P], x[:P], x[:P], None)
+            cache.step(x[P], x[P], x[P], out)
+            torch.cuda.synchronize()
+            return out.view(units, d)
+        finally:
+            cache.close()
+
+    try:
+        few, many = next_out(30000), next_out(units)
+        assert torch.equal(few, few[:5].repeat(6000, 1))
+        whole = units // 5 * 5
+        assert torch.equal(many[:whole].view(-1, 5, d), few[:5].expand(units // 5, 5, d))
+        assert torch.equal(many[whole:], few[:units - whole])
+    finally:
+        torch.cuda.empty_cache()
