@@ -79,7 +79,8 @@ typedef struct wkv_handle wkv_handle;
 /* Every field is plain int so the struct can be filled from any language.
  * Zero in an optional field means "default". */
 typedef struct wkv_options {
-    int batch, heads, head_dim;  /* units = batch*heads; head_dim in {64,128,256} (fp32: {64,128}) */
+    int batch, heads, head_dim;  /* units = batch*heads; head_dim in {64,128,256} (fp32: {64,128});  */
+                                 /*   units x workgroups per unit x threads stay below 2^32 (WKV_ESIZE) */
     int budget;                  /* m, 1..WKV_MAX_BUDGET: slots kept after every step             */
     int recent_window;           /* R, 1..budget: newest R tokens are never evicted               */
     int dtype;                   /* WKV_FP32 / WKV_FP16 / WKV_BF16                                */
@@ -259,7 +260,7 @@ int wkv_launch_shape(const wkv_options* opt, int* workgroups, int* threads);
  * otherwise zero buffer sees that the word was read.  Asynchronous on `stream`.  The benchmark times it
  * with the grid and byte count of a wkv_step launch: what that launch shape can pull out of
  * memory when it does nothing else.  `bytes` must be a positive multiple of 16*workgroups
- * (WKV_EINVAL otherwise); the caller owns src and keeps it valid.
+ * (WKV_EINVAL otherwise), workgroups x threads below 2^32 (WKV_ESIZE); the caller owns src and keeps it valid.
  */
 int wkv_probe_read(const void* src, size_t bytes, int workgroups, int threads, int nontemporal,
                    void* sink, void* stream);

@@ -104,6 +104,8 @@ int validate(const wkv_options& o, int* threads, int* split)
                                   : wkv_step_lds_bytes(o.budget, o.dtype, o.head_dim, n);
         return lds <= LDS_LIMIT && o.budget + 1 <= wkv_step_max_entries(n);
     };
+    // a launch of 2^32 threads and more is not refused by the runtime: the count wraps
+    auto too_many = [&](int n) { return (long long)units * sp * n >= 1ll << 32; };
     if (th == 0) {
         // up to one unit per compute unit (256): large workgroups, so that one unit's rows are spread
         // over many waves (a compute unit holds only one workgroup of 1024 threads: 384 units take
@@ -129,10 +131,13 @@ int validate(const wkv_options& o, int* threads, int* split)
             wkv_step_padded_rows(o.budget, o.dtype, o.head_dim, 512, units) * 19)
             th = 256;
         while (th < 1024 && !fits(th)) th *= 2;
+        while (th > 256 && too_many(th) && fits(th / 2)) th /= 2;
     }
     if (th != 256 && th != 512 && th != 1024) return fail(WKV_EINVAL, "threads must be 256, 512 or 1024");
     if (!fits(th))
         return fail(WKV_ESIZE, "a score row of %d entries does not fit a workgroup of %d threads", o.budget + 1, th);
+    if (too_many(th))
+        return fail(WKV_ESIZE, "%d units x %d workgroups of %d threads: a launch holds fewer than 2^32 threads", units, sp, th);
     *threads = th;
     *split = sp;
     return WKV_OK;
@@ -724,6 +729,7 @@ int wkv_probe_read(const void* src, size_t bytes, int workgroups, int threads, i
     if (((uintptr_t)src & 15) != 0) return fail(WKV_EINVAL, "src must be 16-byte aligned");
     if (workgroups < 1 || threads < 64 || threads > 1024 || threads % 64 != 0)
         return fail(WKV_EINVAL, "workgroups must be positive, threads a multiple of 64 in 64..1024");
+    if ((long long)workgroups * threads >= 1ll << 32) return fail(WKV_ESIZE, "workgroups x threads must be below 2^32");
     if (bytes == 0 || bytes % (16 * (size_t)workgroups) != 0)
         return fail(WKV_EINVAL, "bytes must be a positive multiple of 16*workgroups");
     const hipError_t e = wkv_launch_probe_read(src, bytes, workgroups, threads, nontemporal != 0, sink, (hipStream_t)stream);

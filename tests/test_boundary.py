@@ -101,6 +101,20 @@ def test_launch_shape_follows_the_unit_count():
         shape(8, 32, 410, threads=300)
 
 
+def test_launches_stay_below_the_threads_a_grid_holds():
+    """Host-only: a grid of 2^32 threads and more wraps without an error.  The default takes smaller workgroups there; what does not fit is refused."""
+    def shape(units, d=128, **kw):
+        return wkv.wkv_launch_shape(wkv.make_options(1, units, d, 2, 1, wkv.WKV_FP16, **kw))
+    assert shape((1 << 23) - 1) == ((1 << 23) - 1, 512) and shape(1 << 23) == (1 << 23, 256)
+    assert shape((1 << 24) - 1, d=64) == ((1 << 24) - 1, 256)
+    assert shape(1 << 18, split=16)[0] == 1 << 22
+    for units, kw in ((1 << 24, {}), (1 << 23, dict(threads=512)), (1 << 22, dict(threads=1024)), (1 << 20, dict(threads=256, split=16))):
+        with pytest.raises(wkv.WkvError) as e:
+            shape(units, **kw)
+        assert e.value.code == wkv.WKV_ESIZE
+    assert wkv._lib.wkv_probe_read(1 << 20, 16 << 22, 1 << 22, 1024, 0, None, None) == wkv.WKV_ESIZE
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py measures exactly one GPU: a larger --gpus exits with a message before anything is imported."""
     import subprocess
