@@ -53,7 +53,7 @@ int wkv_step_padded_rows(int m, int dtype, int head_dim, int threads, int units)
 // Bytes of dynamic LDS wkv_launch_step needs for this shape.
 size_t wkv_step_lds_bytes(int m, int dtype, int head_dim, int threads);
 
-// Raises the kernel's dynamic-LDS limit to `lds` bytes (needed above 64 KiB).
+// Raises the kernels' dynamic-LDS limit if `lds` bytes need it (above 64 KiB): to the largest budget's, as it is one limit for all handles.
 hipError_t wkv_step_prepare(int dtype, int head_dim, size_t lds);
 
 // Largest number of attended entries (m + 1) a workgroup of this size handles.

@@ -26,6 +26,7 @@
 // Results are those of wkv_step.hip up to summation order: the same fp64 score path (so the
 // same eviction decisions), the same write-back; o_t is assembled from S partial sums with
 // their own maxima instead of one sum with the global maximum.
+#include "../../include/wkv.h"
 #include "wkv_internal.h"
 #include "wkv_device.h"
 
@@ -468,6 +469,8 @@ size_t wkv_split_lds_bytes(int m, int dtype, int head_dim, int threads)
 
 hipError_t wkv_split_prepare(int dtype, int head_dim, size_t lds)
 {
+    if (lds <= 64 * 1024) return hipSuccess;      // every kernel's limit as it is
+    lds = wkv_split_lds_bytes(WKV_MAX_BUDGET, dtype, head_dim, 1024);    // of every handle: none lowers another's
 #define WKV_CASE(DT, TT, DD) if (dtype == DT && head_dim == DD) { \
         hipError_t e = prepare<TT, DD, 1024>(lds); return e != hipSuccess ? e : prepare<TT, DD, 512>(lds); }
     WKV_CASE(0, TF32, 64)  WKV_CASE(0, TF32, 128)

@@ -39,6 +39,7 @@
 // per-wave results are combined by one DPP row reduction per wave, and the two
 // V rows of the merge are requested the moment a bookkeeping wave knows its
 // candidate, well ahead of the barrier after which they are needed.
+#include "../../include/wkv.h"
 #include "wkv_internal.h"
 #include <type_traits>
 
@@ -913,6 +914,7 @@ hipError_t wkv_launch_set_clock(const WkvCache& c, int64_t tokens, hipStream_t s
 hipError_t wkv_step_prepare(int dtype, int head_dim, size_t lds)
 {
     if (lds <= 64 * 1024) return hipSuccess;      // every kernel's limit as it is (two dozen calls, 10 us of a handle's creation)
+    lds = wkv_step_lds_bytes(WKV_MAX_BUDGET, dtype, head_dim, 1024);     // of every handle: none lowers another's
 #define WKV_CASE(DT, TT, DD) if (dtype == DT && head_dim == DD) { \
         hipError_t e = prepare<TT, DD, 1024>(lds); return e != hipSuccess ? e : prepare<TT, DD, 512>(lds); }
     WKV_CASE(0, TF32, 64)  WKV_CASE(0, TF32, 128)

@@ -493,10 +493,10 @@ def test_checkpoint_and_resume():
             a.close(); b.close()
 
 
-@pytest.mark.parametrize("name,says", [("check", "c_abi ok"), ("pinned", "pinned ok")])
+@pytest.mark.parametrize("name,says", [("check", "c_abi ok"), ("pinned", "pinned ok"), ("limits", "limits ok")])
 def test_plain_c_caller(name, says):
     """tests/c_abi/*.c drive libwkv from C (hipMalloc'ed buffers, no Python in the loop): the whole boundary; the pinned memory
-    of readback and upload."""
+    of readback and upload; the kernels' limits."""
     import os
     import subprocess
     exe = os.path.join(os.path.dirname(os.path.abspath(__file__)), "c_abi", name)
