@@ -449,7 +449,7 @@ __device__ __attribute__((noinline)) double4_t exact_tile(const char* shared, co
 // shared chunk are marked (at that rate two tiles in three hold one; a row or two at a prompt's beginning say nothing about the rest).  (Uniform over the workgroup; the chunk is visible afterwards.)  Tile by tile, with the digits made beside it and
 // nothing requested ahead, a prompt of marked rows only is slower than the fp64 instruction alone was before there were digits; in
 // loops of its own it is not.  Rows + scores, every key marked, tile by tile | in loops of its own | before: 256 units x 4096, d 128,
-// fp16 16.4 + 14.1 | 13.6 + 12.8 | 13.0 + 10.5 ms; 128 x 2048 2.51 + 2.07 | 1.93 + 1.77 | 1.85 + 1.48 ms.
+// fp16 16.4 + 14.1 | 13.6 + 10.2 | 13.0 + 10.5 ms; 128 x 2048 2.51 + 2.07 | 1.93 + 1.77 | 1.85 + 1.48 ms.
 // Without marked rows the test costs nothing that shows (11.32 | 11.32 ms, 1.91 | 1.92 ms for the whole prompts); with __syncthreads_and
 // instead of one barrier and two ballots 11.40 ms.
 template <int NW> __device__ __forceinline__ bool mostly_marked(bool own, const int (&flags)[CHUNK]) {
@@ -793,10 +793,10 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
 
 // ------------------------------------------------------------------ 2. scores
 // The tile of keys kt against all its queries with the fp64 matrix instruction, for workgroups of marked rows: the next tile of
-// queries is requested before this one is used.  The keys are converted anew each round, which keeps the kernel within 128 registers (four waves;
-// d 64, 256 units x 4096, every key marked: the prompt 15.5 -> 13.9 ms, 14.7 before there were digits; d 128, where they could stay in fp64
-// with two waves a SIMD: scores 10.9 -> 12.8 ms for a prompt of nothing but marked rows, 4.15 -> 3.85 for one without).
-template <class TT, int D>
+// queries is requested before this one is used.  LEAN: the keys are converted anew each round, which keeps the kernel within 128 registers (four waves;
+// d 64, 256 units x 4096, every key marked: the prompt 15.5 -> 13.9 ms, 14.7 before there were digits).  With d 128 and long loops they
+// stay in fp64 (see wkv_prefill_scores_marked).
+template <class TT, int D, bool LEAN>
 __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, const double* lse, double* a, int kt, int ntiles, int P, size_t tok,
                                              const double* etab, int g, int x)
 {
@@ -815,15 +815,22 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
         next_l = lse[t];
     };
     request(kt);
+    if constexpr (!LEAN) {
+        convert();
+#pragma unroll
+        for (int e = 0; e < 2 * NWORDS; ++e) asm volatile("" : "+v"(kd[e]));      // (held, and not converted in the loop all the same)
+    }
     for (int qt = kt; qt < ntiles; ++qt) {
         uint32_t w[NWORDS];
 #pragma unroll
         for (int i = 0; i < NWORDS; ++i) w[i] = next[i];
         const double l = next_l;
         request(qt + 1);
+        if constexpr (LEAN) {
 #pragma unroll
-        for (int i = 0; i < NWORDS; ++i) asm volatile("" : "+v"(kw[i]));
-        convert();                                            // anew each round: see above
+            for (int i = 0; i < NWORDS; ++i) asm volatile("" : "+v"(kw[i]));
+            convert();
+        }
         double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int e = 0; e < 2 * NWORDS; e += 2) {
@@ -849,8 +856,9 @@ template <class TT, int D>
 __device__ __attribute__((noinline)) void exact_scores_apart(const char* qb, const char* kb, const double* lse, double* a, int kt, int ntiles, int P, size_t tok,
                                              const double* etab, int g, int x)
 {
-    exact_scores<TT, D>(qb, kb, lse, a, kt, ntiles, P, tok, etab, g, x);
+    exact_scores<TT, D, true>(qb, kb, lse, a, kt, ntiles, P, tok, etab, g, x);
 }
+constexpr double LATER = -1.0;        // in place of a tile's first column sum, which is never negative: left to wkv_prefill_scores_marked
 
 // a[u][i] = sum over rows t >= i of exp(s_ti - lse_t).  A wave has one tile of keys, or shares it with SPLIT - 1 others; NW waves, a workgroup,
 // share the sliced queries.
@@ -891,8 +899,9 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     if constexpr (SPLIT == 1) {
         if (mostly_marked<NW>(kmarked || !active, sh.flags[0])) {
             if (active) {
-                if constexpr (D == 128) exact_scores_apart<TT, D>(qb, kb, lseu, a + (size_t)u * P, kt, ntiles, P, tok, etab, g, x);
-                else exact_scores<TT, D>(qb, kb, lseu, a + (size_t)u * P, kt, ntiles, P, tok, etab, g, x);
+                if constexpr (NW == 8) { if (lane == 0) a[(size_t)u * P + kt * TILE] = LATER; }
+                else if constexpr (D == 128) exact_scores_apart<TT, D>(qb, kb, lseu, a + (size_t)u * P, kt, ntiles, P, tok, etab, g, x);
+                else exact_scores<TT, D, true>(qb, kb, lseu, a + (size_t)u * P, kt, ntiles, P, tok, etab, g, x);
             }
             return;
         }
@@ -954,6 +963,36 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
         const int key = kt * TILE + 4 * g + r;
         if (x == 0 && key < P) a[(size_t)u * P + key] = c;
     }
+}
+
+// The tiles of keys that the launch before left out, as its workgroups had marked rows.  A kernel of its own, where the keys stay in fp64: the registers
+// for that would cost the kernel above two of its four waves a SIMD.  Only after launches with eight waves a workgroup, which take milliseconds: where nothing is
+// marked all it does is look, 12 us.  A wave has a long tile and a short one, so that all have the same work: half as many workgroups look (a tile each
+// 19.5 us), and the chip empties at once.  256 units x 4096, every key marked, fp16: scores 12.8 -> 10.2 ms (a tile a wave 10.4; two or four next to each
+// other 11.8, 13.6; the same tile of four units 11.8), the prompt 26.4 -> 23.9.
+constexpr int MARKED_WAVES = 4;
+template <class TT, int D>
+__global__ __launch_bounds__(64 * MARKED_WAVES, 2)
+void wkv_prefill_scores_marked(const void* __restrict__ q_, const void* __restrict__ k_, const double* __restrict__ lse,
+                               double* __restrict__ a, int P, int units, int unit0)
+{
+    constexpr int ROWB = D * TT::BYTES;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int ntiles = (P + TILE - 1) / TILE, pairs = (ntiles + 1) / 2, groups = (pairs + MARKED_WAVES - 1) / MARKED_WAVES;
+    const int u = unit0 + xcd_unit(blockIdx.x, groups);
+    const int kt = (int)((blockIdx.x >> 3) % groups) * MARKED_WAVES + wid, other = ntiles - 1 - kt;   // a wave's tiles (the middle one alone)
+    if (u >= units) return;                                               // the whole workgroup
+    double* au = a + (size_t)u * P;
+    const bool left = kt < pairs && (lane == 0 || (lane == 1 && other != kt)) && au[(lane == 0 ? kt : other) * TILE] == LATER;
+    if (!__syncthreads_or(left)) return;
+    __shared__ double etab[EXP_STEPS];
+    exp_table_init(etab, 1.0);
+    const char* qb = reinterpret_cast<const char*>(q_) + (size_t)u * ROWB;
+    const char* kb = reinterpret_cast<const char*>(k_) + (size_t)u * ROWB;
+    unsigned long long todo = __ballot(left);                             // uniform over the wave
+#pragma unroll 1
+    for (; todo != 0; todo &= todo - 1)
+        exact_scores<TT, D, false>(qb, kb, lse + (size_t)u * P, au, (todo & 1) ? kt : other, ntiles, P, (size_t)units * ROWB, etab, lane >> 4, lane & 15);
 }
 
 // ------------------------------------------------------------------ 3. compress
@@ -1410,6 +1449,13 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
         launches(c.units, groups_s, 64 * NS, [&](int u0, int n) {
             hipLaunchKernelGGL((wkv_prefill_scores<TT, D, NS, S>), dim3(xcd_grid(n, groups_s)), dim3(64 * NS), 0, stream, q, k, lse, a, P, c.units, u0);
         });
+        if constexpr (NS == 8) {
+            const int groups_m = ((ntiles + 1) / 2 + MARKED_WAVES - 1) / MARKED_WAVES;
+            launches(c.units, groups_m, 64 * MARKED_WAVES, [&](int u0, int n) {
+                hipLaunchKernelGGL((wkv_prefill_scores_marked<TT, D>), dim3(xcd_grid(n, groups_m)), dim3(64 * MARKED_WAVES), 0, stream, q, k, lse, a, P,
+                                   c.units, u0);
+            });
+        }
     };
     using std::integral_constant;
     if (two_waves_a_tile(tiles, P)) {
