@@ -1430,8 +1430,14 @@ inline bool two_tiles_a_wave(long long tiles, int P) { return P >= 3072 && tiles
 //   64 x 384 (1536) 126 | 120; 129 | 123; 106 | 98; -                    128 x 384 (3072) 145 | 170; 156 | 177; 119 | 136; -
 //   24 x 1024 (1536) 270 | 214; 274 | 218; 205 | 183; 204 | 184          48 x 1024 (3072) 331 | 301; 339 | 302; 250 | 219; 250 | 226
 //   96 x 512 (3072) 196 | 198; 198 | 205; 153 | 149; -                   32 x 2048 (4096) 649 | 586; 655 | 607; 486 | 426; 547 | 450
-//   8 x 4096 (2048) 810 | 646; 1063 | 709; 584 | 452; 584 | 463          16 x 4096 (4096) 1097 | 1063; 1097 | 1151; 807 | 790; 872 | 816
-inline bool two_waves_a_tile(long long tiles, int P) { return tiles <= (P < 512 ? 1536 : 4096); }
+//   8 x 4096 (2048) 810 | 646; 1063 | 709; 584 | 452; 584 | 463          16 x 4096 (4096) 1039 | 1026; 1062 | 1105; 759 | 744; 827 | 772
+// (bf16 d 128 at 16 x 4096 with one key channel at 20: 1218 | 1191, 12 x 4096 1056 | 1036, 9 x 4096 1126 | 1044, so the line stays for all.)
+// From 3072 tokens on one unit more for some partitions is felt, so units count in rounds of all eight: fp16 d 128, d 64 17 x 3800 (3 a partition, as 24)
+// 1175 | 1307, -; 18 x 3500 981 | 1102; 697 | 749; 20 x 3200 850 | 948; 625 | 647; bf16 927 | 961; 628 | 672; fp16 9 x 4096 (as 16) 1017 | 1000.
+inline bool two_waves_a_tile(int units, int ntiles, int P) {
+    const long long counted = P >= 3072 ? (units + XCDS - 1) / XCDS * (long long)XCDS : units;
+    return counted * ntiles <= (P < 512 ? 1536 : 4096);
+}
 
 template <class TT, int D>
 hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, void* out,
@@ -1458,7 +1464,7 @@ hipError_t run(const WkvCache& c, const void* q, const void* k, const void* v, v
         }
     };
     using std::integral_constant;
-    if (two_waves_a_tile(tiles, P)) {
+    if (two_waves_a_tile(c.units, ntiles, P)) {
         contract(integral_constant<int, 1>{}, integral_constant<int, 2>{});
     } else if (D == 64 || !two_tiles_a_wave(tiles, P)) {
         contract(integral_constant<int, 1>{}, integral_constant<int, 1>{});

@@ -290,9 +290,10 @@ def test_sort_and_runs_at_their_edges(P, d):
 
 
 @pytest.mark.parametrize("dtype,d,P,units", [("fp16", 128, 129, 170), ("bf16", 64, 129, 170), ("fp16", 64, 129, 171), ("bf16", 128, 129, 171),
-                                             ("bf16", 64, 1025, 63), ("fp16", 128, 1025, 64), ("bf16", 64, 1025, 1017)])
+                                             ("bf16", 64, 1025, 63), ("fp16", 128, 1025, 64), ("bf16", 64, 1025, 1017),
+                                             ("fp16", 128, 3073, 16), ("bf16", 64, 3073, 17)])
 def test_prompts_of_many_units(dtype, d, P, units):
-    """Up to 1536 tiles of 16 tokens a launch (4096 from 512 tokens on) two waves share a tile (most prompts of these tests), then a
+    """Up to 1536 tiles of 16 tokens a launch (4096 from 512 tokens on, where from 3072 on units count in rounds of eight) two waves share a tile (most prompts of these tests), then a
     wave has one: launches on either side.  An odd number of tiles, one row in the last tile, units that are no
     multiple of eight and a row that takes the fp64 instruction (one element far above the others).  Five units' inputs,
     repeated."""
