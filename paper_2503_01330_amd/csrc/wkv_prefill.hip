@@ -169,7 +169,7 @@ __device__ __forceinline__ void exp_table_init(double* tab, double unit) {
 // What bounds both kernels: the instructions of a SIMD in turn.  A vector instruction takes 4 cycles, one of these matrix instructions 8 of its 16 (alone and beside each
 // other, measured in loops of both); waves on one SIMD overlap the rest, two of them badly (rows with two tiles a wave: 1640 cycles a tile
 // where the instructions add up to 1010), four well (scores: 1050 of 860).  So scores keeps to 128 registers, rows to 168 (three waves) where a wave has one tile, and
-// the paths for marked rows, which would take more, are functions of their own (128 units x 2048, bf16: rows 1.03 -> 0.94 ms, scores 0.71 -> 0.62).
+// the fp64 tile among others is a function of its own (128 units x 2048, bf16: rows 1.03 -> 0.94 ms, scores 0.71 -> 0.62).
 // The 32x32 matrix instructions would need half the issue cycles and were slower: the chip lowers its clock (2.2 -> 1.95 GHz).
 // A row whose elements are not all integers at its scale (an element more than 2^-23 below the
 // largest that uses its last bits; possible for bf16, and for fp16 rows that reach 128) or that holds
@@ -192,15 +192,18 @@ template <int D> __device__ __forceinline__ double logit_scale() { return LOGIT_
 // Finite arguments go far beyond int (logits of fp16 rows reach 1e12 units): the cast, undefined there in C++, is the one
 // instruction v_cvt_i32_f64, which saturates, and with any k that low ldexp gives 0.  (That instruction written out costs 2 % of a
 // 128 x 2048 prompt, a clamp before it more; a test with logits of 3e10 units holds the result.)
-__device__ __forceinline__ double exp_units(double x, const double* tab) {
+// COLD: in a seldom path; its constants are not held in registers across the loop.
+template <bool COLD = false> __device__ __forceinline__ double exp_units(double x, const double* tab) {
     const double kd = __builtin_rint(x);
     const double r = x - kd;
     const int k = (int)kd;
     const double tj = tab[k & 255];
     // ln2/256 = c: c, c^2/2, c^3/6, c^4/24
-    double p = fma(r, 2.239395190875157e-12, 3.308302680541371e-09);
-    p = fma(p, r, 3.665565596910106e-06);
-    p = fma(p, r, 0.0027076061740622863);
+    double c1 = 0.0027076061740622863, c2 = 3.665565596910106e-06, c3 = 3.308302680541371e-09;
+    if constexpr (COLD) asm volatile("" : "+s"(c1), "+s"(c2), "+s"(c3));
+    double p = fma(r, 2.239395190875157e-12, c3);
+    p = fma(p, r, c2);
+    p = fma(p, r, c1);
     p = fma(p, r, 1.0);
     return ldexp(tj * p, k >> 8);
 }
@@ -369,7 +372,8 @@ template <class TT, int D, int NT> struct ChunkLoad {
         const unsigned long long fm = __ballot(bad), fl = __ballot(lowest != 0);
         if (j == 0) {
             constexpr unsigned long long mask = (1ull << TPR) - 1;
-            const int lane = threadIdx.x & 63;
+            int lane = threadIdx.x & 63;
+            if constexpr (D == 128) asm volatile("" : "+v"(lane));    // (not a 64-bit mask held across the loop)
             sh.scale[buf][row] = ldexp(unit, -s);
             bool mark = ((fm >> lane) & mask) != 0;
             if (with_lse) {
@@ -383,10 +387,10 @@ template <class TT, int D, int NT> struct ChunkLoad {
 
 // Products of a tile in units of 2^16, unscaled (rows = keys, columns = queries): register r of lane (g, x) = key 4g + r, query x.
 // SHARED_KEYS: the shared rows are the keys and the own rows the queries, or the other way round.  low (uniform): whether any of the rows
-// uses the lowest digit.
-template <class TT, int D, bool SHARED_KEYS>
+// uses the lowest digit.  parked: the lane's own lowest digits, where they are kept in LDS and not in own.
+template <class TT, int D, bool SHARED_KEYS, bool PARKED = false>
 __device__ __forceinline__ void digit_tile(const unsigned char* pl, const int4v_t (&own)[D / 64][DIGITS], bool low,
-                                           int g, int x, double (&s)[4])
+                                           int g, int x, double (&s)[4], const int4v_t* parked = nullptr)
 {
     auto mm = [](int4v_t a, int4v_t o, int4v_t c) __attribute__((always_inline)) {
         return SHARED_KEYS ? __builtin_amdgcn_mfma_i32_16x16x64_i8(a, o, c, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(o, a, c, 0, 0, 0);
@@ -407,7 +411,7 @@ __device__ __forceinline__ void digit_tile(const unsigned char* pl, const int4v_
             for (int i = from; i < DIGITS; ++i) {
                 const int4v_t a = plane(c, i);
 #pragma unroll
-                for (int j = from; j < DIGITS; ++j) S[i + j] = mm(a, own[c][j], S[i + j]);
+                for (int j = from; j < DIGITS; ++j) S[i + j] = mm(a, PARKED && j == 0 ? parked[c * 64] : own[c][j], S[i + j]);
             }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -424,7 +428,9 @@ __device__ __forceinline__ void digit_tile(const unsigned char* pl, const int4v_
 // A tile that touches a marked row, scaled, with the fp64 matrix instruction.  Its result register r of lane (g, x) is row g + 4r: row i is given key 4 (i % 4) + i / 4, so that the layout is digit_tile's.
 // All words are requested ahead of the first product: these tiles wait for memory, not for the instruction (256 units x 4096,
 // d 128, fp16, every key marked, two requests a tile against one: 34.3 against 30.9 ms).
-// A function of its own (not inlined): its registers are then not the kernel's, which saves what it needs of its own only around the call.
+// A function of its own (not inlined): its registers are then not the kernel's, which saves what it needs of its own only around the call.  It needs
+// no stack, and neither does any kernel here: the runtime gives every queue stack memory for the whole chip when a kernel first wants some (396 bytes a lane:
+// 200 MB a queue), behind the back of a caller who was promised that nothing is allocated.
 template <class TT, int D, bool SHARED_KEYS>
 __device__ __attribute__((noinline)) double4_t exact_tile(const char* shared, const char* own, int shared0, int own0, int P, size_t tok, int lane)
 {
@@ -500,13 +506,15 @@ template <class TT, int D, int N> struct Rows {
                 const double top = pair_max<32>(pair_max<16>(tmax[i]));        // all 16 keys of the tile
                 const double mnew = fmax(m[i], top);          // finite: key 16 kt + 0 <= every query of a later tile,
                                                               // and on the diagonal key x is attended by query x
-                const double resc = exp_units(no_infinity(m[i] - mnew), etab) * (1.0 / UNIT);  // 0 on the first tile (m = -inf), 1 where nothing moved
+                const double resc = exp_units<D == 128>(no_infinity(m[i] - mnew), etab) * (1.0 / UNIT);  // 0 on the first tile (m = -inf), 1 where nothing moved
                 l[i] *= resc;
                 m[i] = mnew;
                 const float rf = (float)resc;                 // the output rows this lane holds (queries 4g + r') by their own factor
+                int row = 4 * g;
+                if constexpr (D == 128) asm volatile("" : "+v"(row));     // (not four lane numbers held across the loop)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float f = __shfl(rf, 4 * g + r);
+                    const float f = __shfl(rf, row + r);
 #pragma unroll
                     for (int e = 0; e < NE; ++e) o[i][e][r] *= f;
                 }
@@ -544,10 +552,8 @@ template <class TT, int D, int N> struct Rows {
                                       __builtin_amdgcn_perm(vfrag[3][e >> 1], vfrag[2][e >> 1], sel) };
 #pragma unroll
                 for (int i = decltype(first)::value; i < N; ++i)
-{
 #pragma unroll
                     for (int w = 0; w < weight_parts<TT>(); ++w) o[i][e] = mfma16<TT>(pa[i][w], vb2, o[i][e]);
-                }
             }
         };
         if (lone) values(std::integral_constant<int, N - 1>{});
@@ -577,7 +583,8 @@ template <class TT, int D, int N> struct Rows {
 
 // The tile of queries qt against all its keys with the fp64 matrix instruction, for workgroups of marked rows: the queries stay in
 // fp64, the next tile's keys and values are requested before this one's are used (two sets of registers take turns).  LEAN: the queries
-// are converted anew for every tile, for kernels that have no registers to hold them.
+// are converted anew for every tile and nothing is requested ahead, for a kernel that has no registers for more (and three waves a SIMD to wait with:
+// 128 units x 2048, every key marked, the prompt 3.86 -> 3.74 ms, against a call of a function with the other form and a stack).
 template <class TT, int D, bool LEAN>
 __device__ __forceinline__ void exact_rows(const char* qb, const char* kb, const char* vb, char* ob, double* lse, int qt, int P, size_t tok,
                                            const double* etab, int g, int x)
@@ -619,24 +626,25 @@ __device__ __forceinline__ void exact_rows(const char* qb, const char* kb, const
         }
         rows.add(s, vf, true, false, etab, g);
     };
-    uint32_t kf0[NWORDS], vf0[4][NE / 2], kf1[NWORDS], vf1[4][NE / 2];
-    request(0, kf0, vf0);
-    for (int kt = 0; kt <= qt; kt += 2) {
-        request(min(kt + 1, qt), kf1, vf1);                   // past the last tile: a repeat, unused
-        tile(kt, kf0, vf0);
-        if (kt + 1 > qt) break;
-        request(min(kt + 2, qt), kf0, vf0);
-        tile(kt + 1, kf1, vf1);
+    uint32_t kf0[NWORDS], vf0[4][NE / 2];
+    if constexpr (LEAN) {
+#pragma unroll 1
+        for (int kt = 0; kt <= qt; ++kt) {
+            request(kt, kf0, vf0);
+            tile(kt, kf0, vf0);
+        }
+    } else {
+        uint32_t kf1[NWORDS], vf1[4][NE / 2];
+        request(0, kf0, vf0);
+        for (int kt = 0; kt <= qt; kt += 2) {
+            request(min(kt + 1, qt), kf1, vf1);               // past the last tile: a repeat, unused
+            tile(kt, kf0, vf0);
+            if (kt + 1 > qt) break;
+            request(min(kt + 2, qt), kf0, vf0);
+            tile(kt + 1, kf1, vf1);
+        }
     }
     rows.finish(qt * TILE, P, ob, tok, lse, g, x);
-}
-// The same as a function of its own, so that its registers are not the kernel's: inline, they would cost the kernel with one tile a wave and d 128 its
-// third wave a SIMD (128 units x 2048, fp16, no marked row: rows 0.95 | 0.91 ms).
-template <class TT, int D>
-__device__ __attribute__((noinline)) void exact_rows_apart(const char* qb, const char* kb, const char* vb, char* ob, double* lse, int qt, int P, size_t tok,
-                                           const double* etab, int g, int x)
-{
-    exact_rows<TT, D, true>(qb, kb, vb, ob, lse, qt, P, tok, etab, g, x);
 }
 
 // q, k, v, out: [P][units][D] (token-major, as a decode step sees them one token at a time).
@@ -644,8 +652,10 @@ __device__ __attribute__((noinline)) void exact_rows_apart(const char* qb, const
 // the keys are sliced into digits once per workgroup and read by every wave from LDS.  What bounds
 // this kernel and the next is vector instructions (slicing, recombining the digit sums, the
 // exponentials), so a wave takes two tiles where that pays: slicing, value loads and their
-// permutes are then paid once for both (d 128: all 256 registers of two waves a SIMD, a dozen spilled outside the loop over tiles or in
-// its seldom paths).  One tile, d 128: three waves a SIMD.
+// permutes are then paid once for both (d 128: 250 registers of two waves a SIMD).  One tile, d 128: three waves a SIMD, 167 registers.
+// To that end (rows of 128 bytes have no need) a lane's own lowest digits, which are seldom used, wait in LDS, the base of a tile of values is kept scalar (the compiler
+// makes a 64-bit address a lane of each of its rows otherwise, 16 registers for a chunk), and what only seldom paths need is made there.
+// Before, 23 and 11 registers were spilled: 128 units x 2048 1.82 -> 1.76 ms (fp16), 1.77 -> 1.67 (bf16), 256 x 4096 10.2 -> 9.9, 10.1 -> 9.7.
 // In small launches SPLIT waves share a tile instead, each taking every SPLIT-th tile of keys.
 template <class TT, int D, int NW, int QT, int SPLIT>
 __global__ __launch_bounds__(64 * NW, D == 128 && SPLIT == 1 && QT == 1 ? 3 : 2)
@@ -682,15 +692,21 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
 #pragma unroll
     for (int i = 0; i < QT; ++i) qmarked |= own_digits<TT, D>(qb, (qt + i) * TILE, P, tok, g, x, qdg[i], qscale[i], 1.0, qlow[i]);
     next.store(sh, 0, false, logit_scale<D>());
+    constexpr bool PARK = D == 128 && SPLIT == 1;
+    __shared__ int4v_t parked[PARK ? NW * QT * (D / 64) * 64 : 1];
+    int4v_t* park = parked + (PARK ? wid * QT * (D / 64) * 64 + lane : 0);
+    if constexpr (PARK)
+#pragma unroll
+        for (int i = 0; i < QT; ++i)
+#pragma unroll
+            for (int c = 0; c < D / 64; ++c) park[(i * (D / 64) + c) * 64] = qdg[i][c][0];         // (read by the same lane)
 
     if constexpr (SPLIT == 1) {
         if (mostly_marked<NW>(qmarked || !active, sh.flags[0])) {
             if (active)
 #pragma unroll 1
-                for (int t = qt; t <= mine; ++t) {
-                    if constexpr (D == 128 && QT == 1) exact_rows_apart<TT, D>(qb, kb, vb, ob, lse + (size_t)u * P, t, P, tok, etab, g, x);
-                    else exact_rows<TT, D, false>(qb, kb, vb, ob, lse + (size_t)u * P, t, P, tok, etab, g, x);
-                }
+                for (int t = qt; t <= mine; ++t)
+                    exact_rows<TT, D, D == 128 && QT == 1>(qb, kb, vb, ob, lse + (size_t)u * P, t, P, tok, etab, g, x);
             return;
         }
     }
@@ -705,6 +721,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
         uint32_t vfrag[4][NE / 2];
         if (kt * TILE + TILE <= P) {                          // uniform
             const char* vt = vb + (size_t)(kt * TILE) * tok;
+            if constexpr (PARK) asm volatile("" : "+s"(vt));      // (see above; with parts, kt is not known to be scalar)
 #pragma unroll
             for (int r = 0; r < 4; ++r) load_words<NE / 2>(vt + r * tok + voff, vfrag[r]);
         } else {
@@ -727,7 +744,7 @@ void wkv_prefill_rows(const void* __restrict__ q_, const void* __restrict__ k_, 
 #pragma unroll
             for (int i = 0; i < QT; ++i) {
                 if (QT > 1) __builtin_amdgcn_sched_barrier(0);       // one tile's sums at a time: the registers do not hold two
-                digit_tile<TT, D, true>(&sh.dg[buf][t * TILE * 16], qdg[i], low || qlow[i], g, x, s[i]);
+                digit_tile<TT, D, true, PARK>(&sh.dg[buf][t * TILE * 16], qdg[i], low || qlow[i], g, x, s[i], park + i * (D / 64) * 64);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s[i][r] *= sh.scale[buf][t * TILE + 4 * g + r] * qscale[i];
             }
@@ -812,7 +829,7 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
     auto request = [&](int qt) __attribute__((always_inline)) {
         const int t = min(min(qt, ntiles - 1) * TILE + x, P - 1);          // past the last tile: a repeat, unused
         load_words<NWORDS>(qb + (size_t)t * tok + col, next);
-        next_l = lse[t];
+        next_l = *reinterpret_cast<const double*>(reinterpret_cast<const char*>(lse) + (unsigned)t * 8u);     // (t < 4096: a 32-bit offset)
     };
     request(kt);
     if constexpr (!LEAN) {
@@ -826,7 +843,8 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
         for (int i = 0; i < NWORDS; ++i) w[i] = next[i];
         const double l = next_l;
         request(qt + 1);
-        if constexpr (LEAN) {
+        constexpr bool TIED = LEAN && D == 128;               // converted four words at a time, when the products before are done
+        if constexpr (LEAN && !TIED) {
 #pragma unroll
             for (int i = 0; i < NWORDS; ++i) asm volatile("" : "+v"(kw[i]));
             convert();
@@ -834,6 +852,12 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
         double4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int e = 0; e < 2 * NWORDS; e += 2) {
+            if constexpr (TIED) {
+                asm volatile("" : "+v"(kw[e >> 1]), "+v"(w[e >> 1]));
+                if (e % 8 == 0) asm volatile("" : "+v"(s0));
+                kd[e] = (double)frag_elem<TT>(kw, e);
+                kd[e + 1] = (double)frag_elem<TT>(kw, e + 1);
+            }
             s0 = __builtin_amdgcn_mfma_f64_16x16x4f64(kd[e], (double)frag_elem<TT>(w, e), s0, 0, 0, 0);
             s1 = __builtin_amdgcn_mfma_f64_16x16x4f64(kd[e + 1], (double)frag_elem<TT>(w, e + 1), s1, 0, 0, 0);
         }
@@ -841,7 +865,7 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const bool on = tq < P && kt * TILE + 4 * g + r <= tq;         // causal, and inside the prompt
-            acc[r] += exp_units(no_infinity(on ? (s0[r] + s1[r]) * logit_scale<D>() - l : -INFINITY), etab);
+            acc[r] += exp_units<LEAN && D == 128>(no_infinity(on ? (s0[r] + s1[r]) * logit_scale<D>() - l : -INFINITY), etab);
         }
     }
 #pragma unroll
@@ -850,13 +874,6 @@ __device__ __forceinline__ void exact_scores(const char* qb, const char* kb, con
         const int key = kt * TILE + 4 * g + r;
         if (x == 0 && key < P) a[key] = c;
     }
-}
-// The same as a function of its own (see exact_rows_apart).
-template <class TT, int D>
-__device__ __attribute__((noinline)) void exact_scores_apart(const char* qb, const char* kb, const double* lse, double* a, int kt, int ntiles, int P, size_t tok,
-                                             const double* etab, int g, int x)
-{
-    exact_scores<TT, D, true>(qb, kb, lse, a, kt, ntiles, P, tok, etab, g, x);
 }
 constexpr double LATER = -1.0;        // in place of a tile's first column sum, which is never negative: left to wkv_prefill_scores_marked
 
@@ -899,9 +916,13 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
     if constexpr (SPLIT == 1) {
         if (mostly_marked<NW>(kmarked || !active, sh.flags[0])) {
             if (active) {
-                if constexpr (NW == 8) { if (lane == 0) a[(size_t)u * P + kt * TILE] = LATER; }
-                else if constexpr (D == 128) exact_scores_apart<TT, D>(qb, kb, lseu, a + (size_t)u * P, kt, ntiles, P, tok, etab, g, x);
-                else exact_scores<TT, D, true>(qb, kb, lseu, a + (size_t)u * P, kt, ntiles, P, tok, etab, g, x);
+                if constexpr (NW == 8) {
+                    if (lane == 0) a[(size_t)u * P + kt * TILE] = LATER;
+                } else {
+                    int tid = threadIdx.x;
+                    asm volatile("" : "+v"(tid));                         // (what the two paths share would be held, or spilled, across the other one)
+                    exact_scores<TT, D, true>(qb, kb, lseu, a + (size_t)u * P, kt, ntiles, P, tok, etab, tid >> 4 & 3, tid & 15);
+                }
             }
             return;
         }
@@ -957,11 +978,13 @@ void wkv_prefill_scores(const void* __restrict__ q_, const void* __restrict__ k_
             for (int r = 0; r < 4; ++r) acc[r] += ps[r * NW * 64 + me + w * 64];
     }
     if (!active) return;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                                         // (as above)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const double c = row_allsum(acc[r]);                               // over the 16 queries x
-        const int key = kt * TILE + 4 * g + r;
-        if (x == 0 && key < P) a[(size_t)u * P + key] = c;
+        const int key = kt * TILE + 4 * (tid >> 4 & 3) + r;
+        if ((tid & 15) == 0 && key < P) a[(size_t)u * P + key] = c;
     }
 }
 

@@ -115,6 +115,20 @@ def test_launches_stay_below_the_threads_a_grid_holds():
     assert wkv._lib.wkv_probe_read(1 << 20, 16 << 22, 1 << 22, 1024, 0, None, None) == wkv.WKV_ESIZE
 
 
+def test_kernels_of_a_prompt_need_no_stack():
+    """Host-only: the runtime gives every queue stack memory for the whole chip when a kernel first wants some, hundreds of megabytes of device memory that
+    wkv_prefill_noalloc promises not to take and wkv_workspace_bytes does not count.  The library's kernel descriptions say how much a lane wants."""
+    data = open(wkv.LIB_PATH, "rb").read()
+    found = {}
+    for key in re.finditer(rb"\.private_segment_fixed_size([\x00-\x7f]|\xcc.|\xcd..|\xce....)", data, re.S):
+        name = data[data.rindex(b".name", 0, key.start()):key.start()]                 # (keys of a kernel's description are sorted)
+        value = key.group(1) if len(key.group(1)) == 1 else key.group(1)[1:]
+        found[re.search(rb"\w*wkv_\w+", name).group().decode()] = int.from_bytes(value, "big")
+    prompt = {n: v for n, v in found.items() if "wkv_prefill_" in n}
+    assert len(prompt) > 20 and len(found) > len(prompt), "no descriptions found: has their format changed?"
+    assert {n: v for n, v in prompt.items() if v} == {}
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py measures exactly one GPU: a larger --gpus exits with a message before anything is imported."""
     import subprocess
