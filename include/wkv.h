@@ -235,7 +235,8 @@ int wkv_destroy(wkv_handle* h);
 /* Message of the last failing call on this thread ("" if none).  Never NULL. */
 const char* wkv_last_error(void);
 
-/* Device bytes a handle with these options allocates (0 if the options are invalid).
+/* Device bytes the arrays of a handle with these options take (0 if the options are invalid).  In the one
+ * block they share, each starts at a multiple of 256 bytes: less than 4 KB more in all.
  * Host-only arithmetic: usable without a GPU. */
 size_t wkv_workspace_bytes(const wkv_options* opt);
 

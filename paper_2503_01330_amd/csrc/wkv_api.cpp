@@ -118,7 +118,8 @@ int validate(const wkv_options& o, int* threads, int* split)
         // fp16 d 64: m 64 5.75 | 7.09 (5.89 | 7.25), 127 6.68 | 7.35 (7.13 | 7.69), 200 7.06 | 8.03 (7.84 | 8.39), 255 7.96 | 8.12 (8.73 | 8.67),
         // 256 8.38 | 8.05 (9.13 | 8.41); bf16 d 128: 64 6.10 | 7.30 (6.24 | 7.50), 200 7.74 | 8.48 (8.86 | 9.22), 255 8.73 | 8.58 (9.87 | 9.67);
         // fp16 d 256: 200 8.91 | 9.47 (10.3 | 10.7), 255 10.2 | 10.3 (12.4 | 12.1); fp32 d 128: 200 8.32 | 8.87 (10.6 | 12.2).  From about 250 slots
-        // on the two are level or 1024 threads ahead (8 x 300: 1-3 % behind for rows of 256 bytes and less, 200 x 300 ahead).
+        // on the two are level or 1024 threads ahead (8 x 300: 1-3 % behind for rows of 256 bytes and less, 200 x 300 ahead).  All formats and widths, 1, 64,
+        // 160 and 256 units, 8 to 224 slots: 512 threads ahead by 2 to 25 %, but for bf16 d 256 with 160 units and more at 224 (10.1 | 10.0, 12.5 | 12.4).
         constexpr int FEW_ENTRIES = 224;
         th = sp > 1 ? 512 : units >= 1024 ? (row_bytes < 256 ? 256 : 512) : units > 256 || o.budget <= FEW_ENTRIES ? 512 : 1024;
         // from 768 to about 1200 units, 256 threads where m + 1 sits clearly closer above a multiple

@@ -233,7 +233,7 @@ template <class TT> __device__ __forceinline__ int digit_shift(uint32_t top, int
     return (top == 0u || bad) ? 0 : INT_BITS - 1 + 127 - e;
 }
 // Whether this lane's elements are no integers at that scale.  fp16 has no bit below 2^-24, so a row that
-// stays below 8 (s >= 24) fits; beyond, the elements are looked at.  bf16: 8 significant bits,
+// stays below 128 (s >= 24) fits; beyond, the elements are looked at.  bf16: 8 significant bits,
 // the last one 7 below the exponent.
 template <class TT, int NWORDS> __device__ __forceinline__ bool no_integers(const uint32_t (&w)[NWORDS], const RowSpan<TT>& span, int e, float mul) {
     if constexpr (__is_same(TT, TF16)) {
@@ -1176,7 +1176,7 @@ void wkv_prefill_compress(WkvCache c, const double* __restrict__ a, double* __re
         // Parent of a removed token: the nearest token to its right that outranks it (survivors
         // outrank everything: rank 0xFFFF); also the nearest one to its LEFT that outranks it.  Both by
         // a search that skips whole groups of 8 and blocks of 64 tokens whose highest rank is too low: each look waits for LDS, and a
-        // wave for the lane with the most of them, so a token looks at no more than 100 entries however long the runs are.
+        // wave for the lane with the most of them, so each of a token's two searches looks at no more than 100 entries however long the runs are.
         constexpr int NIL = 0xFFFF;
         const int nblk = (P + 63) >> 6;
         uint16_t* gmax = reinterpret_cast<uint16_t*>(wcnt);   // [512] highest rank in a group of 8 (the counts have been used)

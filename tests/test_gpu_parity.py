@@ -584,21 +584,26 @@ def test_numbers_of_a_long_unit_do_not_wait_for_its_length():
 
 
 def test_two_threads_read_and_load_at_once():
-    """The pinned memory of one readback is kept for the next: a second thread's calls, at the same time, get memory of their own."""
+    """The pinned memory of one readback is kept for the next: a second thread's calls, at the same time, get memory of their own.  8 chunks a matrix, twice
+    as many as there are slots; both threads start each round together.  (That a call does find the block lent, and what it
+    gets then, is the C caller's: tests/c_abi/pinned.c.)"""
     import threading
-    made = [_made_up_state(6, 300, 300, 128, "fp16", 8400 + i) for i in range(2)]
-    caches = [wkv.Cache(1, 6, 128, 300, 9, wkv.WKV_FP16) for _ in made]
+    made = [_made_up_state(100, 300, 300, 128, "fp16", 8400 + i) for i in range(2)]
+    caches = [wkv.Cache(1, 100, 128, 300, 9, wkv.WKV_FP16) for _ in made]
     failed = []
+    together = threading.Barrier(2)
 
     def work(i):
         try:
             tokens, K, V, a, pos = made[i]
-            for _ in range(30):
+            for _ in range(12):
+                together.wait(timeout=60)
                 caches[i].load(tokens, K, V, a, pos)
                 for w, x in ((wkv.WKV_K, K), (wkv.WKV_V, V), (wkv.WKV_SCORE_SUM, a), (wkv.WKV_POS, pos)):
                     assert np.array_equal(caches[i].state(w), x)
         except Exception as exc:                                    # noqa: BLE001
             failed.append(exc)
+            together.abort()
 
     threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
     for t in threads:

@@ -251,7 +251,7 @@ def test_llama_shaped_prompt_sampled_units():
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("where", ["queries", "keys", "one row"])
 def test_rows_that_span_more_than_the_digits(dtype, d, where):
-    """Logits are formed from 8-bit digits of rows brought to integers below 2^30; a row with elements
+    """Logits are formed from 8-bit digits of rows brought to integers below 2^31; a row with elements
     that are no integers at its scale must take the fp64 instruction.  Such a row here: one large
     element (times zero on the other side) and small ones below the last digit, which meet large
     elements, so that dropping what does not fit would move a logit by more than 1e-5 (score sums are held to
@@ -492,7 +492,7 @@ def test_marked_rows_in_every_launch_form(P, units, d, dtype):
 
     def mark(x, rows, unit, big):
         n = x[rows, unit, 1].shape
-        x[rows, unit, big] = 2.0 ** 11                      # the digits end at 2^-18
+        x[rows, unit, big] = 2.0 ** 11                      # the digits end at 2^-19
         x[rows, unit, 1] = 2.0 ** -20 * (1 + 2 * g.integers(0, 4, n))
 
     for unit, keys, queries in ((1, 37, None), (2, None, 5), (3, None, 21), (4, 37, 21), (5, everything, None), (6, None, everything),
@@ -553,7 +553,7 @@ def test_an_infinite_value_stays_out_of_the_tiles_before_it(P, units, dtype, d):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 def test_logits_far_beyond_the_exponential(dtype, d):
-    """Logits at least 3e5 apart and up to 7e7 (7e9 in the units the kernels count in, where a 32-bit integer ends at 2e9): every row
+    """Logits at least 3e5 apart and up to 7e7 (3e10 in the units the kernels count in, where a 32-bit integer ends at 2e9): every row
     attends to one token, all other weights are 0 exactly.  Elements are chosen so that logits are exact."""
     P, U, m = 129, 3, 100
     g = np.random.default_rng(9500)
@@ -595,7 +595,8 @@ def test_digits_at_their_edges(P, units, dtype, d):
             x[70:86, u, 4] = tiny * (1 + ulp) / 4                                   # every row of a tile, and its neighbours' some
             other[:, u, 3:5] *= 8.0                                                 # what they meet is large
         if u >= 2:
-            k[90, u, 0], k[90, u, 5], q[:, u, 0] = 2.0 ** 6, 2.0 ** -16 if dtype == "fp16" else 2.0 ** -17, 0.0
+            # last bit 2^-24: the format's last one in fp16; in bf16 the last of integers whose largest is 2^6 and has 31 bits
+            k[90, u, 0], k[90, u, 5], q[:, u, 0] = 2.0 ** 6, (2.0 ** -14 if dtype == "fp16" else 2.0 ** -17) * (1 + ulp), 0.0
             k[91, u, 0], k[91, u, 5] = 2.0 ** 11, 2.0 ** -14 * (1 + ulp)            # beyond: marked
     cfg = synth.StreamConfig("pre-digit", 9600, 1, 4, d, dtype, T, 60, 9)
     rep = np.arange(units) % 4
