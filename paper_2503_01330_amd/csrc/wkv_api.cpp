@@ -436,6 +436,9 @@ int wkv_create_ex(wkv_handle** hp, const wkv_options* opt)
     e = hipMalloc(&h->block, filled[0] + filled[1]);
     if (e == hipSuccess) e = hipMemset(h->block, 0, filled[0]);
     if (e == hipSuccess) e = hipMemset((char*)h->block + filled[0], 0xFF, filled[1]);
+    // The fills are only enqueued by then, on the default stream (8 GiB: back after 4 us, done after 1.4 ms); a first step may come on a
+    // stream that does not wait for that one.
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
         rc = fail(e == hipErrorOutOfMemory ? WKV_ENOMEM : WKV_EHIP, "device allocation of %zu bytes: %s", filled[0] + filled[1], hipGetErrorString(e));
         (void)hipGetLastError();

@@ -505,6 +505,34 @@ def test_plain_c_caller(name, says):
     assert r.returncode == 0 and says in r.stdout, r.stdout + r.stderr
 
 
+@pytest.mark.parametrize("split", [1, 4])
+def test_first_steps_on_a_stream_that_does_not_wait_for_the_default_one(split):
+    """A handle's memory (4 GiB here, a millisecond to fill) is filled when creating it returns: steps that follow at once on a non-blocking stream, where nothing
+    orders them behind the fills, find an empty cache, and what they write stays.  Outputs and state are those of a handle used on the default stream."""
+    units, m, d, steps = 2048, 2048, 256, 3
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8600)
+    x = torch.randn(steps, 3, units, d, generator=gen, device="cuda").half()
+    side = torch.cuda.Stream()
+    got = []
+    for stream in (torch.cuda.current_stream(), side):
+        torch.cuda.synchronize()
+        out = torch.zeros_like(x[:, 0])
+        torch.cuda.synchronize()
+        cache = wkv.Cache(1, units, d, m, 1, wkv.WKV_FP16, split=split, log_capacity=4)
+        try:
+            with torch.cuda.stream(stream):
+                for t in range(steps):
+                    cache.step(x[t, 0], x[t, 1], x[t, 2], out[t])
+            torch.cuda.synchronize()
+            got.append([out.cpu().numpy()] + [cache.state(w) for w in (wkv.WKV_K, wkv.WKV_V, wkv.WKV_SCORE_SUM, wkv.WKV_POS, wkv.WKV_STATUS)])
+        finally:
+            cache.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+    assert (got[1][4] == np.arange(steps)).all() and np.array_equal(got[1][1], x[:, 1].cpu().numpy().transpose(1, 0, 2))
+
+
 def _made_up_state(units, m, length, d, dtype, seed):
     g = np.random.default_rng(seed)
     def rows():
