@@ -336,7 +336,7 @@ def main():
             "value": round(cfg.batch * P / (ms * 1e-3), 1), "unit": "prompt tokens/s per layer", "ms": round(ms, 3),
             "roofline": {"bound": "mfma", "achieved": round(2 * half / (ms * 1e-3) / 1e12, 2), "peak": HALF_MFMA_TFLOPS,
                          "unit": "TFLOP/s", "frac": round(algo_ms / ms, 4), "traffic": None,
-                         "kernel": "wkv_prefill_rows + _scores + _compress + _fold (one wkv_prefill call)",
+                         "kernel": "wkv_prefill_rows + _scores + _scores_marked + _compress + _fold (one wkv_prefill call)",
                          "flops_per_contraction": half,
                          "algorithmic_ms": round(algo_ms, 3), "executed_flops_ms_at_peak": round(exec_ms, 3),
                          "frac_of_executed": round(exec_ms / ms, 4),

@@ -9,7 +9,7 @@
 // by token; beyond that it is a different function (streamed tokens attend to an already
 // compressed cache).
 //
-// Four kernels (three for a prompt that fits the cache):
+// Four kernels (three for a prompt that fits the cache, one more behind the second in large launches of rows of 256 bytes):
 //   1. wkv_prefill_rows: causal attention in tiles of 16 queries x 16 keys.  A wave takes one tile of queries, two in large launches of
 //      long prompts, or shares one with another wave in small launches (the rules stand at run()).
 //      The logits are a dense contraction of 16-bit numbers, formed exactly: every row becomes 8-bit
@@ -22,7 +22,7 @@
 //   2. wkv_prefill_scores: the column sums a_i = sum_{t >= i} exp(s_ti - lse_t): tiles of 16 keys, one a wave or
 //      shared by two in small launches, looping over the query tiles below the diagonal, the same contraction
 //      again (recomputing the logits costs less than storing P^2/2 of them);
-//      sums stay in registers, no atomics.  The order of a sum is fixed for a launch form, so a result is the same from call to
+//      sums stay in registers, no atomics.  Large launches leave keys of rows that digits do not hold to wkv_prefill_scores_marked.  The order of a sum is fixed for a launch form, so a result is the same from call to
 //      call, and from one number of units to another as long as the form is.
 //   3. wkv_prefill_compress (prompts longer than the budget): one workgroup per unit: rank of every candidate by (score, token),
 //      the P - m lowest are removed; survivors get slots in token order; the weight with which every raw row
@@ -167,7 +167,7 @@ __device__ __forceinline__ void exp_table_init(double* tab, double unit) {
 // normal numbers in three (fp16) or seven in eight (bf16).  256 units x 4096, d 128: scores 4.15 -> 3.85 ms in fp16, 4.57 -> 3.54 in bf16 (with the launch form
 // below); where every tile uses it (keys with one channel at 20, fp16) what is left is the test for it.
 // What bounds both kernels: the instructions of a SIMD in turn.  A vector instruction takes 4 cycles, one of these matrix instructions 8 of its 16 (alone and beside each
-// other, measured in loops of both); waves on one SIMD overlap the rest, two of them badly (rows with two tiles a wave: 1640 cycles a tile
+// other, measured in loops of both); waves on one SIMD overlap the rest, two of them badly (rows with two tiles a wave: 1560 cycles a tile
 // where the instructions add up to 1010), four well (scores: 1050 of 860).  So scores keeps to 128 registers, rows to 168 (three waves) where a wave has one tile, and
 // the fp64 tile among others is a function of its own (128 units x 2048, bf16: rows 1.03 -> 0.94 ms, scores 0.71 -> 0.62).
 // The 32x32 matrix instructions would need half the issue cycles and were slower: the chip lowers its clock (2.2 -> 1.95 GHz).
@@ -1444,7 +1444,7 @@ void wkv_prefill_fold(WkvCache c, const void* __restrict__ k_, const void* __res
 // 10.55 | 9.98, 384 x 3072 9.15 | 8.98, 512 x 2048 5.58 | 5.67.  Rows of 128 bytes: fp16 256 x 4096 7.75 | 7.64, 384 x 3072 6.76 | 6.87,
 // bf16 384 x 4096 11.88 | 12.04 (before the lowest digit was left out), so never.
 // In those launches a workgroup of scores has eight waves instead of four, which halves the slicing: 256 x 4096 fp16 4.08 | 4.05 ms, bf16 3.84 | 3.60, but 128 x 2048
-// 0.612 | 0.629 and 96 x 1024 0.152 | 0.170.
+// 0.612 | 0.629 and 96 x 1024 0.152 | 0.170.  (All of these with a stack in both forms; without it 128 x 2048 5 % and 256 x 4096 3 % less, for both.)
 inline bool two_tiles_a_wave(long long tiles, int P) { return P >= 3072 && tiles >= 49152; }
 // Whether two waves share a tile, each taking every other tile of its loop.  Small launches last as long as their longest loop;
 // but every part slices all the rows it shares with fewer waves, which pays until the chip is full: for short prompts early.
